@@ -48,7 +48,7 @@ struct OpA {
     __device__ OpA at(int c) const {
         OpA o = *this;
         if (cs) {
-            const long long off = (long long)(c / cpi) * cs;
+            const long long off = (long long)__builtin_amdgcn_readfirstlane(c / cpi) * cs;  // c is uniform
             o.wE += off;
             o.wN += off;
             o.dinv += off;
@@ -226,7 +226,7 @@ struct OpKARef {
     int cpi = 0;  // 0: one instance
     __device__ OpKARef at(int c) const {
         OpKARef o = *this;
-        if (cpi) o.rows += 9 * (c / cpi);
+        if (cpi) o.rows += 9 * __builtin_amdgcn_readfirstlane(c / cpi);  // c is uniform
         return o;
     }
     __device__ bool is_free(int, int) const { return true; }

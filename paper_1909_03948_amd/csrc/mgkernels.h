@@ -26,16 +26,12 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Tile sides: large tiles (less halo work) for batches, small tiles (more
-// workgroups) when few columns make the V-cycle latency bound.
-constexpr int kTCBig = 16, kTFBig = 32;      // coarse / fine nodes per tile side
-constexpr int kTCSmall = 8, kTFSmall = 16;
-constexpr int kTCWide = 9, kTFWide = 18;     // finest level of small-tile cycles with many workgroups
+constexpr int kTFSmall = 16, kTFWide = 18;  // tile sides of the r^T z partials of few columns
 constexpr int kTPair = 4;      // k_down2: level-C tile side
 constexpr int kPairMaxN = 256;  // k_down2 pairs levels whose finer one has N_l <= this
 constexpr int kTFChain = 16;   // k_up_chain: level-0 tile side
 constexpr int kChainLen = 4;   // k_up_chain: levels a launch (measured: 4 > 2 at N = 1024)
-constexpr int kSmallTileCols = 8;            // batches below this use the small tiles
+constexpr int kFewCols = 8;    // calls below this many columns are latency bound
 constexpr int kBottomN = 32;   // levels with N_l <= kBottomN run in the bottom kernel
 constexpr int kBottomLevels = 4;  // at most (N_l = 64, 32, 16, 8 when kBottomN = 64)
 
@@ -81,13 +77,10 @@ __device__ inline double partial_share(const double* part, int col, int stride, 
     return s;
 }
 
-// Index i clamped into the mesh [0, N]: tile loads read a valid node for
-// every slot and drop the off-mesh ones afterwards.  Used on tiles of at
-// most kFlatLoads elements a thread (the few-column cycles, latency bound);
-// larger tiles keep branched loads and fewer registers.
+// Index i clamped into the mesh [0, N]: loads are issued without a branch, at a
+// valid node for every slot, and the off-mesh ones dropped afterwards (a load
+// inside a branch makes the wave wait for it there).
 __device__ inline int clamp_node(int i, int N) { return min(max(i, 0), N); }
-template <int E>
-constexpr bool kFlatLoads = E <= 3;
 
 // Waves of the workgroup as a uniform value (read once, outside the
 // single-thread code that sums the per-wave slots).
@@ -110,8 +103,43 @@ __device__ inline double share_total(double s) {
     return tot;
 }
 
-__device__ inline double partial_total(const double* part, int col, int stride, int nblk) {
-    return share_total(partial_share(part, col, stride, nblk));
+// Workgroup total of the partials in the order in which a workgroup of bd
+// threads (a multiple of 64, at most 1024) would take it (partial_share,
+// then share_total), whatever the size of this one: the shares of bd virtual
+// threads, summed wave by wave.  vt_first issues this thread's first loads.
+constexpr int kVtMax = 4;  // virtual threads a thread of a 256-thread workgroup stands for
+struct VtShare {
+    double v[kVtMax];
+};
+__device__ inline VtShare vt_first(const double* part, int col, int stride, int nblk, int bd) {
+    const double* p = part + (size_t)col * stride;
+    VtShare s;
+#pragma unroll
+    for (int k = 0; k < kVtMax; ++k) s.v[k] = p[min((int)(threadIdx.x + k * blockDim.x), nblk - 1)];
+    return s;
+}
+__device__ inline double vt_total(VtShare s, const double* part, int col, int stride, int nblk, int bd) {
+    __shared__ double ps[16];
+    __shared__ double tot;
+    const double* p = part + (size_t)col * stride;
+#pragma unroll
+    for (int k = 0; k < kVtMax; ++k) {
+        const int vt = threadIdx.x + k * blockDim.x;
+        if (k * (int)blockDim.x >= bd) break;  // uniform
+        double t = vt < nblk && vt < bd ? s.v[k] : 0.0;
+        if (vt < bd)
+            for (int b = vt + bd; b < nblk; b += bd) t += p[b];
+        t = wave_sum(t);
+        if ((threadIdx.x & 63) == 0) ps[vt >> 6] = t;
+    }
+    lds_barrier();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < (bd >> 6); ++w) t += ps[w];
+        tot = t;
+    }
+    lds_barrier();
+    return tot;
 }
 
 // Partial-sum buffers of the PCG inner products ([ncols][stride] each).
@@ -120,13 +148,14 @@ struct PcgRed {
     double* pq;
     double* rr;
     int stride;
-    int nrz;  // number of partials of r^T z (workgroups of the last V-cycle kernel)
-    int nvec; // number of partials of p^T q and r^T r (workgroups of the PCG vector kernels)
-    int per;  // node blocks of 256 per workgroup: sets the PCG vector kernels' threads
-    int chunk;  // consecutive nodes per workgroup in the PCG vector kernels (<= kVecNodes threads)
+    int nrz;  // number of partials of r^T z (workgroups, or tiles, of the last V-cycle kernel)
+    int npq;  // number of partials of p^T q (workgroups of the apply kernel)
+    int nrr;  // number of partials of r^T r (workgroups of the kernel that updates r)
+    int per;  // node blocks of 256 per workgroup: sets the threads of the linear vector kernels
+    int chunk;  // consecutive nodes per workgroup of the linear vector kernels (<= kVecNodes threads)
 };
 
-// Threads per workgroup of the PCG vector kernels: 256 per node block up to
+// Threads per workgroup of the linear PCG vector kernels: 256 per node block up to
 // 1024, so a workgroup covers its 256 per nodes in at most kVecNodes passes.
 __host__ __device__ inline int vec_threads(int per) { return per >= 4 ? 1024 : 256 * per; }
 constexpr int kVecNodes = 4;
@@ -142,6 +171,20 @@ __device__ inline double group_sum(double v) {
     if (threadIdx.x == 0)
         for (int w = 0; w < nw; ++w) r += part[w];
     return r;
+}
+
+// alpha of a column from its r^T z and p^T q (0 on breakdown); the lead
+// workgroup records the iteration and stops a column that broke down.
+__device__ inline double pcg_alpha(double rz, double pq, ColState* st, int* act, bool lead) {
+    const double alpha = pq > 0.0 ? rz / pq : 0.0;
+    if (lead && threadIdx.x == 0) {
+        st->rz = rz;
+        st->pq = pq;
+        st->alpha = alpha;
+        st->its += 1.0;
+        if (!(pq > 0.0)) *act = 0;
+    }
+    return alpha;
 }
 
 // Convergence test at the start of a V-cycle: r^T r of the PCG update that
@@ -169,306 +212,26 @@ __device__ inline bool column_done_share(double share, const PcgRed& red, int co
 // then the column block), so left/right and most upper/lower halos come from
 // its own L2.  The last T - 8 P workgroups keep the plain order.  A
 // bijection of [0, T); returns the logical (x, y, z) of this workgroup.
+// A value the same in every lane of the wave, moved to a scalar register:
+// integer division runs on the vector unit, and its result would otherwise
+// keep the addresses formed from it in vector registers.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 __device__ inline int3 xcd_tile() {
     const int X = gridDim.x, Y = gridDim.y;
     const int T = X * Y * gridDim.z;
     const int h = blockIdx.x + X * (blockIdx.y + Y * blockIdx.z);
     const int P = T >> 3;
     const int L = h < 8 * P ? (h & 7) * P + (h >> 3) : h;
-    const int z = L / (X * Y), r = L - z * X * Y;
-    return make_int3(r % X, r / X, z);
+    const int z = uniform(L / (X * Y)), r = L - z * X * Y, y = uniform(r / X);
+    return make_int3(r - y * X, y, z);
 }
 
-// --------------------------------------------------------------- k_down ---
-// Grid: (tiles over coarse x, tiles over coarse y, column blocks).  Coarse
-// tile [I0, I0+kTC) x [J0, J0+kTC) needs the fine residual on
-// [2 I0 - 1, 2 I1 + 1], hence x2 one node further out and b two nodes further
-// out.  The operator rows of the tile are staged once per problem instance;
-// the workgroup then sweeps cb consecutive columns.
-// b may be of a wider type TB than the level's vectors (the finest level of a
-// V-cycle in FP32 preconditioning an FP64 PCG reads the FP64 residual).
-template <typename T, class Op, int kTC, typename TB = T, int WPE = 1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void k_down(Op op_, const TB* __restrict__ b, T* __restrict__ x,
-                                              int ld, T* __restrict__ bc, int ldc, int dirichlet,
-                                              int* __restrict__ act, ChebCoef cc, PcgRed red,
-                                              ColState* __restrict__ st, int check, int nc, int cb) {
-    constexpr int TW = 2 * kTC + 5, NN = TW * TW;
-    // the prior operator (7 points, constant coefficients) on large tiles
-    // reads its class table: a third of the LDS, more workgroups per compute
-    // unit, for the batched solves that are bound by LDS traffic (measured:
-    // a 220-column prior solve at N = 1024 9% faster; on the small tiles of
-    // single-column cycles the staged rows stay faster, except on tiles of
-    // interior nodes only, which apply row 0 of the table throughout (HYB)
-    constexpr bool NE = kNorthEast<Op>;
-    constexpr bool KA = NE && kTC == kTCBig;
-    constexpr bool HYB = NE && !KA;
-    __shared__ T sb[NN], sx[NN], sr[NN];
-    __shared__ T tc[NE && !KA ? NN : 1], te[KA ? 1 : NN], tn[KA ? 1 : NN], tdv[KA ? 1 : NN], tg[NE && !KA ? NN : 1];
-    __shared__ KARow<T> krows[KA ? 9 : 1];
-    const TileStencil<T> ts{tc, te, tn, tg, tdv};
-    const int N = op_.N, N1 = N + 1, Nc = N / 2, Nc1 = Nc + 1;
-    const int3 tb = xcd_tile();
-    const int I0 = tb.x * kTC, J0 = tb.y * kTC;
-    const int I1 = min(I0 + kTC - 1, Nc), J1 = min(J0 + kTC - 1, Nc);
-    const int ox = 2 * I0 - 3, oy = 2 * J0 - 3;  // global coordinates of local (0, 0)
-    const TileKA<T, TW> tk{krows, ox, oy, N, ox >= 1 && oy >= 1 && ox + TW - 1 <= N - 1 && oy + TW - 1 <= N - 1};
-    const bool inner = HYB && tk.interior;  // uniform in the workgroup
-    KARow<T> r0{};  // inner tiles: row 0 of the instance's class table (uniform: scalar registers)
-    auto tapply = [&](int l, const T* v) -> T {
-        if constexpr (KA) return tk.apply(l, v);
-        else if constexpr (HYB) return inner ? row_apply(r0, TW, l, v) : tile_apply<NE>(ts, TW, l, v);
-        else return tile_apply<NE>(ts, TW, l, v);
-    };
-    auto tdinv = [&](int l) -> T {
-        if constexpr (KA) return tk.dinv(l);
-        else if constexpr (HYB) return inner ? r0.dinv : tdv[l];
-        else return tdv[l];
-    };
-    const T inv_theta = (T)cc.inv_theta, cA = (T)cc.cA, cB = (T)cc.cB;
-    const int own_i1 = min(2 * I1 + 1, N), own_j1 = min(2 * J1 + 1, N);
-    constexpr int E = (NN + 255) / 256;  // tile elements per thread
-    const void* staged = nullptr;  // the staged rows belong to this instance
-    const int c_end = min(nc, (tb.z + 1) * cb);
-    for (int col = tb.z * cb; col < c_end; ++col) {
-        // with the convergence test on, the lead workgroup clears act[col]
-        // (column_done_share below) while other workgroups of this launch read it:
-        // one decision for the whole workgroup, or its waves could see
-        // different values and meet different barriers (without the test no
-        // kernel of the launch writes act)
-        if (act && !(check ? __syncthreads_or(act[col]) : act[col])) continue;
-        const auto& op = op_.at(col);  // operator of the instance owning this column
-        const TB* bcol = b + (size_t)col * ld;
-        T* xcol = x + (size_t)col * ld;
-        // loads first: b, the convergence test's partials, then the operator
-        // rows, so that their latencies overlap.  On small tiles of the prior
-        // operator b is read at a clamped node without a branch (a load
-        // converted inside its branch waits there for its data) and the
-        // off-mesh entries are dropped at the LDS store.  Large tiles (many
-        // workgroups a compute unit) keep the branch and their registers, and
-        // so does the state operator, whose row loads from global memory
-        // cover the latency of b (measured: the branch-free form no faster)
-        constexpr bool kFlat = kFlatLoads<E> && NE;
-        T vb[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int t = threadIdx.x + 256 * e;
-            const int i = ox + t % TW, j = oy + t / TW;
-            if constexpr (kFlat)
-                vb[e] = (T)bcol[clamp_node(j, N) * N1 + clamp_node(i, N)];
-            else
-                vb[e] = (t < NN && i >= 0 && i <= N && j >= 0 && j <= N) ? (T)bcol[j * N1 + i] : (T)0;
-        }
-        const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nvec) : 0.0;
-        lds_barrier();  // the previous column's LDS reads are done
-        if (instance_key(op) != staged) {
-            if constexpr (KA) {
-                if (threadIdx.x < 9) krows[threadIdx.x] = op.rows[threadIdx.x];
-            } else if constexpr (HYB) {
-                if (inner)
-                    r0 = op.rows[0];
-                else
-                    stage_stencil<TW, 256>(op, ts, ox, oy);
-            } else {
-                stage_stencil<TW, 256>(op, ts, ox, oy);
-            }
-            staged = instance_key(op);
-        }
-        if (check && column_done_share(rr_share, red, col, st, act, tb.x == 0 && tb.y == 0)) continue;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int t = threadIdx.x + 256 * e;
-            const int i = ox + t % TW, j = oy + t / TW;
-            if (t < NN) sb[t] = !kFlat || (i >= 0 && i <= N && j >= 0 && j <= N) ? vb[e] : (T)0;
-        }
-        lds_barrier();
-        // d0 = D^-1 b / theta on the whole tile (zero off the free nodes)
-        for (int t = threadIdx.x; t < NN; t += blockDim.x) sr[t] = tdinv(t) * sb[t] * inv_theta;
-        lds_barrier();
-        // x2 = cA d0 + cB D^-1 (b - A d0) on local [1, TW-1)^2; owned nodes to global
-        {
-            constexpr int W = TW - 2;
-            for (int t = threadIdx.x; t < W * W; t += blockDim.x) {
-                const int il = 1 + t % W, jl = 1 + t / W, l = jl * TW + il;
-                const T v = cA * sr[l] + cB * tdinv(l) * (sb[l] - tapply(l, sr));
-                sx[l] = v;
-                const int i = ox + il, j = oy + jl;
-                if (i >= 2 * I0 && i <= own_i1 && j >= 2 * J0 && j <= own_j1) xcol[j * N1 + i] = v;
-            }
-        }
-        lds_barrier();
-        // residual b - A x2 on the free nodes of local [2, TW-2)^2
-        {
-            constexpr int W = TW - 4;
-            for (int t = threadIdx.x; t < W * W; t += blockDim.x) {
-                const int l = (2 + t / W) * TW + 2 + t % W;
-                const T v = sb[l] - tapply(l, sx);
-                sr[l] = tdinv(l) != (T)0 ? v : (T)0;
-            }
-        }
-        lds_barrier();
-        // restriction P^T onto the coarse tile
-        T* bccol = bc + (size_t)col * ldc;
-        const int cw = I1 - I0 + 1, ch = J1 - J0 + 1;
-        auto res = [&](int i, int j) { return sr[(j - oy) * TW + (i - ox)]; };
-        for (int t = threadIdx.x; t < cw * ch; t += blockDim.x) {
-            const int I = I0 + t % cw, J = J0 + t / cw;
-            T v = 0;
-            if (!(dirichlet && (J == 0 || J == Nc))) {
-                const int i = 2 * I, j = 2 * J;
-                T sm = 0;
-                if (i > 0) sm += res(i - 1, j);
-                if (i < N) sm += res(i + 1, j);
-                if (j > 0) sm += res(i, j - 1);
-                if (j < N) sm += res(i, j + 1);
-                if (i < N && j < N) sm += res(i + 1, j + 1);
-                if (i > 0 && j > 0) sm += res(i - 1, j - 1);
-                v = res(i, j) + (T)0.5 * sm;
-            }
-            bccol[J * Nc1 + I] = v;
-        }
-    }
-}
+}  // namespace hinv
 
-// ----------------------------------------------------------------- k_up ---
-// Grid: (tiles over fine x, tiles over fine y, column blocks).  Fine tile O of
-// kTF x kTF nodes; x = x2 + P x_coarse is formed two nodes around O (x2 is
-// read from its own buffer: neighbouring workgroups write the output), b and
-// the first Chebyshev correction d0 one node around O.  Optionally writes the
-// workgroup's part of sum_k rv_k x_k (the PCG inner product r^T z).
-// b and rv may be of a wider type TB and the output x of a wider type TX than
-// the level's vectors (see k_down).
-template <typename T, class Op, int kTF, typename TB = T, typename TX = T, int WPE = 1>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void k_up(Op op_, const TB* __restrict__ b, const T* __restrict__ x2,
-                                            TX* __restrict__ x, int ld, const T* __restrict__ xc,
-                                            int ldc, int dirichlet,
-                                            const int* __restrict__ act, ChebCoef cc,
-                                            const TB* __restrict__ rv, PcgRed red, int nc, int cb) {
-    constexpr int TW = kTF + 4, NN = TW * TW;
-    constexpr bool NE = kNorthEast<Op>;
-    constexpr bool KA = NE && kTF == kTFBig;  // class table for the prior operator (see k_down)
-    constexpr bool HYB = NE && !KA;           // row 0 on interior small tiles (see k_down)
-    __shared__ T sx[NN], sd[NN], sb[NN];
-    __shared__ T tc[NE && !KA ? NN : 1], te[KA ? 1 : NN], tn[KA ? 1 : NN], tdv[KA ? 1 : NN], tg[NE && !KA ? NN : 1];
-    __shared__ KARow<T> krows[KA ? 9 : 1];
-    const TileStencil<T> ts{tc, te, tn, tg, tdv};
-    const int N = op_.N, N1 = N + 1, Nc1 = N / 2 + 1;
-    const int3 tb = xcd_tile();
-    const int i0 = tb.x * kTF, j0 = tb.y * kTF;
-    const int i1 = min(i0 + kTF - 1, N), j1 = min(j0 + kTF - 1, N);
-    const int ox = i0 - 2, oy = j0 - 2;
-    const TileKA<T, TW> tk{krows, ox, oy, N, ox >= 1 && oy >= 1 && ox + TW - 1 <= N - 1 && oy + TW - 1 <= N - 1};
-    const bool inner = HYB && tk.interior;  // uniform in the workgroup
-    KARow<T> r0{};  // inner tiles: row 0 of the instance's class table (uniform: scalar registers)
-    auto tapply = [&](int l, const T* v) -> T {
-        if constexpr (KA) return tk.apply(l, v);
-        else if constexpr (HYB) return inner ? row_apply(r0, TW, l, v) : tile_apply<NE>(ts, TW, l, v);
-        else return tile_apply<NE>(ts, TW, l, v);
-    };
-    auto tdinv = [&](int l) -> T {
-        if constexpr (KA) return tk.dinv(l);
-        else if constexpr (HYB) return inner ? r0.dinv : tdv[l];
-        else return tdv[l];
-    };
-    auto tcen = [&](int l) -> T {
-        if constexpr (KA) return tk.center(l);
-        else if constexpr (HYB) return inner ? r0.c : tile_center<NE>(ts, TW, l);
-        else return tile_center<NE>(ts, TW, l);
-    };
-    const T inv_theta = (T)cc.inv_theta, theta = (T)cc.theta, cB = (T)cc.cB, c1 = (T)cc.c1;
-    constexpr int E = (NN + 255) / 256;  // tile elements per thread
-    const void* staged = nullptr;
-    const int c_end = min(nc, (tb.z + 1) * cb);
-    for (int col = tb.z * cb; col < c_end; ++col) {
-        if (act && !act[col]) continue;
-        const auto& op = op_.at(col);  // operator of the instance owning this column
-        const TB* bcol = b + (size_t)col * ld;
-        const T* x2col = x2 + (size_t)col * ld;
-        TX* xcol = x + (size_t)col * ld;
-        const T* ccol = xc + (size_t)col * ldc;
-        // loads first (b, x2 and the two coarse values of the prolongation,
-        // then the operator rows) so that their latencies overlap.  P x_c at
-        // (i, j): the coarse node (i/2, j/2) when both are even, else the mean
-        // of the two coarse ends of the fine edge through (i, j).
-        TB vb[E];  // small tiles: read at a clamped node without a branch (see k_down)
-        T vx[E], pc0[E], pc1[E];
-        bool even[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int t = threadIdx.x + 256 * e;
-            const int i = ox + t % TW, j = oy + t / TW;
-            const bool in = t < NN && i >= 0 && i <= N && j >= 0 && j <= N;
-            const bool fr = in && !(dirichlet && (j == 0 || j == N));
-            const int I = i >> 1, J = j >> 1;
-            const int a0 = J * Nc1 + I, a1 = (J + (j & 1)) * Nc1 + I + (i & 1);
-            if constexpr (kFlatLoads<E>)
-                vb[e] = bcol[clamp_node(j, N) * N1 + clamp_node(i, N)];  // dropped at its store when !in
-            else
-                vb[e] = in ? bcol[j * N1 + i] : (TB)0;
-            vx[e] = fr ? x2col[j * N1 + i] : (T)0;
-            pc0[e] = fr ? ccol[a0] : (T)0;
-            pc1[e] = fr ? ccol[a1] : (T)0;
-            even[e] = !((i | j) & 1);
-        }
-        // small tiles (one output node a thread, the few-column cycles): rv at
-        // the thread's output node is loaded with the tile; large tiles read it
-        // at use (prefetching four values costs them occupancy)
-        const int w = i1 - i0 + 1, h = j1 - j0 + 1;
-        constexpr bool kPre = kTF * kTF <= 256;
-        TB rv0 = 0;
-        if constexpr (kPre) {
-            const int t = threadIdx.x;
-            if (rv && t < w * h) rv0 = rv[(size_t)col * ld + (j0 + t / w) * N1 + (i0 + t % w)];
-        }
-        lds_barrier();  // the previous column's LDS reads are done
-        if (instance_key(op) != staged) {
-            if constexpr (KA) {
-                if (threadIdx.x < 9) krows[threadIdx.x] = op.rows[threadIdx.x];
-            } else if constexpr (HYB) {
-                if (inner)
-                    r0 = op.rows[0];
-                else
-                    stage_stencil<TW, 256>(op, ts, ox, oy);
-            } else {
-                stage_stencil<TW, 256>(op, ts, ox, oy);
-            }
-            staged = instance_key(op);
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int t = threadIdx.x + 256 * e;
-            if (t < NN) {
-                const int i = ox + t % TW, j = oy + t / TW;
-                sx[t] = vx[e] + (even[e] ? pc0[e] : (T)0.5 * (pc0[e] + pc1[e]));
-                sb[t] = (i >= 0 && i <= N && j >= 0 && j <= N) ? (T)vb[e] : (T)0;
-            }
-        }
-        lds_barrier();
-        // d0 = D^-1 (b - A x) / theta on local [1, TW-1)^2 (zero off the free nodes)
-        {
-            constexpr int W = TW - 2;
-            for (int t = threadIdx.x; t < W * W; t += blockDim.x) {
-                const int l = (1 + t / W) * TW + 1 + t % W;
-                sd[l] = tdinv(l) * (sb[l] - tapply(l, sx)) * inv_theta;
-            }
-        }
-        lds_barrier();
-        // x += (1 + c1) d0 + cB D^-1 r1 on O with r1 = r0 - A d0 = theta D d0 - A d0
-        double dot = 0.0;
-        for (int t = threadIdx.x; t < w * h; t += blockDim.x) {
-            const int i = i0 + t % w, j = j0 + t / w;
-            const int l = (j - oy) * TW + (i - ox), k = j * N1 + i;
-            const T dk = sd[l];
-            const T r1 = theta * dk * tcen(l) - tapply(l, sd);
-            const T v = sx[l] + ((T)1 + c1) * dk + cB * tdinv(l) * r1;
-            xcol[k] = (TX)v;
-            if (rv) dot += (double)v * (double)(kPre ? rv0 : rv[(size_t)col * ld + k]);
-        }
-        if (rv) {
-            const double sm = group_sum(dot);
-            if (threadIdx.x == 0) red.rz[(size_t)col * red.stride + tb.y * gridDim.x + tb.x] = sm;
-        }
-    }
-}
+#include "waverow.h"
+
+namespace hinv {
 
 // ------------------------------------------------- two levels a launch ---
 // Few columns make the coarse levels latency bound: a launch there costs
@@ -489,7 +252,8 @@ template <typename T, class Op, int kT, int NT>
 __global__ __launch_bounds__(NT) void k_down2(Op opF_, Op opM_, const T* __restrict__ bF, T* __restrict__ xF,
                                                int ldF, T* __restrict__ bM, T* __restrict__ xM, int ldM,
                                                T* __restrict__ bC, int ldC, int dirichlet,
-                                               const int* __restrict__ act, ChebCoef cc, int nc, int cb) {
+                                               int* __restrict__ act, ChebCoef cc, PcgRed red,
+                                               ColState* __restrict__ st, int check, int nc, int cb) {
     constexpr int MW = 2 * kT + 5, FW = 2 * MW + 5, NM = MW * MW, NF = FW * FW;
     constexpr bool NE = kNorthEast<Op>;
     __shared__ T fb[NF], fx[NF], fr[NF];
@@ -511,8 +275,9 @@ __global__ __launch_bounds__(NT) void k_down2(Op opF_, Op opM_, const T* __restr
     const void* staged = nullptr;
     const int c_end = min(nc, (tb.z + 1) * cb);
     for (int col = tb.z * cb; col < c_end; ++col) {
-        // no kernel of the launch writes act (the convergence test runs on the finest level)
-        if (act && !act[col]) continue;
+        // one decision for the workgroup where the launch writes act (see k_down)
+        if (act && !(check ? __syncthreads_or(act[col]) : act[col])) continue;
+        const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
         const auto& opF = opF_.at(col);
         const auto& opM = opM_.at(col);
         const T* bcol = bF + (size_t)col * ldF;
@@ -529,6 +294,7 @@ __global__ __launch_bounds__(NT) void k_down2(Op opF_, Op opM_, const T* __restr
             stage_stencil<MW, NT>(opM, tsM, mox, moy);
             staged = instance_key(opF);
         }
+        if (check && column_done_share(rr_share, red, col, st, act, tb.x == 0 && tb.y == 0)) continue;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int t = threadIdx.x + NT * e;
@@ -837,7 +603,7 @@ __global__ __launch_bounds__(NT) void k_up_chain(ChainArgs<T, Op> a, int dirichl
     const void* staged = nullptr;
     const int c_end = min(nc, (tb.z + 1) * cb);
     for (int col = tb.z * cb; col < c_end; ++col) {
-        // no kernel of the launch writes act (the convergence test runs on the finest level)
+        // no kernel of the launch writes act (the convergence test runs on the way down)
         if (act && !act[col]) continue;
         const void* key = instance_key(a.op[0].at(col));
         lds_barrier();  // the previous column's LDS reads are done
@@ -920,7 +686,7 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
     if (act && !act[col]) return;
     // the convergence test's partials load together with the level data
     // below; the test itself follows the loads
-    const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nvec) : 0.0;
+    const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
     __shared__ float sb[PN], sx[PN], sw[PN];  // right-hand side, iterate, work vector
     __shared__ float te[PRIOR ? 1 : PN], tn[PRIOR ? 1 : PN], tdv[PRIOR ? 1 : PN];  // -wE, -wN, 1/diag
     __shared__ KARow<float> rows[PRIOR ? LV * 9 : 1];
@@ -1186,11 +952,14 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
 }
 
 // ------------------------------------------------------------------ PCG ---
-// Workgroup blockIdx.x covers nodes [chunk x, chunk (x + 1)) of column
+// The linear kernels (few columns, and hierarchies of bottom levels only):
+// workgroup blockIdx.x covers nodes [chunk x, chunk (x + 1)) of column
 // blockIdx.y with vec_threads(per) threads, at most kVecNodes nodes a thread.
 
 // p_new = z + beta p_old with beta = (r^T z) / rz_old (p_new = z on the first
-// iteration, FIRST), q = A p_new = A z + beta A p_old, partials of p_new^T q.
+// iteration, FIRST), q = A p_new = A z + beta A p_old, partials of p_new^T q;
+// and x += alpha p_old, the step of the iteration before (p_old is read here
+// anyway; the refinement step adds the last iteration's).
 // The loads of the r^T z partials and of the thread's nodes (z and p_old at
 // the stencil points, the operator rows) are issued before any of them is
 // used, so their latencies overlap: all at once where the registers allow,
@@ -1224,10 +993,10 @@ constexpr int apply_window() {
 }
 
 template <typename T, class Op, bool FIRST>
-__global__ __launch_bounds__(1024) void k_pcg_apply(Op op_, const T* __restrict__ z, const T* __restrict__ p_old,
-                                                    T* __restrict__ p_new, T* __restrict__ q, int ld,
-                                                    const int* __restrict__ act, ColState* __restrict__ st,
-                                                    PcgRed red) {
+__global__ __launch_bounds__(1024) void k_pcg_apply_few(Op op_, const T* __restrict__ z, const T* __restrict__ p_old,
+                                                        T* __restrict__ p_new, T* __restrict__ q, T* __restrict__ x,
+                                                        int ld, const int* __restrict__ act,
+                                                        ColState* __restrict__ st, PcgRed red) {
     // node blocks in XCD-aware order: the rows above and below a block's
     // nodes belong to blocks on the same XCD
     const int3 tb = xcd_tile();
@@ -1238,6 +1007,7 @@ __global__ __launch_bounds__(1024) void k_pcg_apply(Op op_, const T* __restrict_
     const bool need_rz = !FIRST || bx == 0;  // uniform in the workgroup
     double srz = need_rz ? partial_first(red.rz, col, red.stride, red.nrz) : 0.0;
     const double rz_old = FIRST ? 1.0 : st[col].rz;
+    const T alpha = FIRST ? (T)0 : (T)st[col].alpha;
     const T* zc = z + (size_t)col * ld;
     const T* pc = p_old + (size_t)col * ld;
     const int k0 = bx * red.chunk, k1 = min(n, k0 + red.chunk);
@@ -1300,6 +1070,14 @@ __global__ __launch_bounds__(1024) void k_pcg_apply(Op op_, const T* __restrict_
     if (need_rz) srz = partial_rest(srz, red.rz, col, red.stride, red.nrz);
 #pragma unroll
     for (int e = kVecNodes - W; e < kVecNodes; ++e) combine(e);
+    // the iterate's loads overlap the sum of r^T z
+    T xk[kVecNodes];
+    if constexpr (!FIRST)
+#pragma unroll
+        for (int e = 0; e < kVecNodes; ++e) {
+            const int k = k0 + e * (int)blockDim.x + (int)threadIdx.x;
+            xk[e] = k < k1 ? x[(size_t)col * ld + k] : (T)0;
+        }
     T beta = 0;
     if (need_rz) {
         const double rz = share_total(srz);
@@ -1315,6 +1093,7 @@ __global__ __launch_bounds__(1024) void k_pcg_apply(Op op_, const T* __restrict_
             const T v = FIRST ? az[e] : az[e] + beta * ap[e];
             p_new[(size_t)col * ld + k] = pn;
             q[(size_t)col * ld + k] = v;
+            if constexpr (!FIRST) x[(size_t)col * ld + k] = xk[e] + alpha * pk[e];
             dot += (double)pn * (double)v;
         }
     }
@@ -1322,58 +1101,44 @@ __global__ __launch_bounds__(1024) void k_pcg_apply(Op op_, const T* __restrict_
     if (threadIdx.x == 0) red.pq[(size_t)col * red.stride + bx] = sm;
 }
 
-// alpha = (r^T z) / (p^T q); x += alpha p, r -= alpha q; partials of r^T r.
-// Workgroup 0 records rz (the next beta's denominator) and alpha; a column
-// with p^T q <= 0 (breakdown) stops.
-// Eight waves a SIMD: two 1024-thread workgroups a compute unit, so the ~500
-// workgroups of a one-column update at N = 1024 run in one round instead of
-// two (the FP64 form then spills four registers; measured 2% faster solves).
+// alpha = (r^T z) / (p^T q), r <- r - alpha q into r_new; partials of r^T r.
+// For hierarchies whose levels all run in the bottom kernel; larger ones do
+// this in k_down.  Workgroup 0 records rz (the next beta's denominator) and
+// alpha, with which the next apply kernel (or the refinement step) advances
+// x; a column with p^T q <= 0 (breakdown) stops.
 template <typename T>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_pcg_update(T* __restrict__ x, T* __restrict__ r,
-                                                     const T* __restrict__ p, const T* __restrict__ q,
-                                                     int ld, int n, int* __restrict__ act,
+__global__ __launch_bounds__(1024) void k_pcg_update(const T* __restrict__ r, T* __restrict__ r_new,
+                                                     const T* __restrict__ q, int ld, int n, int* __restrict__ act,
                                                      ColState* __restrict__ st, PcgRed red) {
     const int col = blockIdx.y;
     // workgroup 0 clears act[col] on breakdown while the others read it: one
     // decision per workgroup (see k_down)
     if (!__syncthreads_or(act[col])) return;
-    double spq = partial_first(red.pq, col, red.stride, red.nvec);
+    double spq = partial_first(red.pq, col, red.stride, red.npq);
     const double rz = st[col].rz_new;
     const int k0 = blockIdx.x * red.chunk, k1 = min(n, k0 + red.chunk);
-    T xk[kVecNodes], rk[kVecNodes], pk[kVecNodes], qk[kVecNodes];
+    T rk[kVecNodes], qk[kVecNodes];
 #pragma unroll
     for (int e = 0; e < kVecNodes; ++e) {
         const int k = k0 + e * blockDim.x + threadIdx.x;
         const size_t o = (size_t)col * ld + k;
-        xk[e] = rk[e] = pk[e] = qk[e] = 0;
+        rk[e] = qk[e] = 0;
         if (k < k1) {
-            xk[e] = x[o];
             rk[e] = r[o];
-            pk[e] = p[o];
             qk[e] = q[o];
         }
     }
-    spq = partial_rest(spq, red.pq, col, red.stride, red.nvec);
+    spq = partial_rest(spq, red.pq, col, red.stride, red.npq);
     const double pq = share_total(spq);
-    const double alpha = pq > 0.0 ? rz / pq : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ColState& c = st[col];
-        c.rz = rz;
-        c.pq = pq;
-        c.alpha = alpha;
-        c.its += 1.0;
-        if (!(pq > 0.0)) act[col] = 0;
-    }
+    const double alpha = pcg_alpha(rz, pq, st + col, act + col, blockIdx.x == 0);
     double rr = 0.0;
     const T a = (T)alpha;
 #pragma unroll
     for (int e = 0; e < kVecNodes; ++e) {
         const int k = k0 + e * blockDim.x + threadIdx.x;
         if (k < k1) {
-            const size_t o = (size_t)col * ld + k;
-            x[o] = xk[e] + a * pk[e];
             const T rv = rk[e] - a * qk[e];
-            r[o] = rv;
+            r_new[(size_t)col * ld + k] = rv;
             rr += (double)rv * (double)rv;
         }
     }

@@ -45,7 +45,7 @@ struct SolveStats {
 template <typename T>
 struct PcgWork {
     int cap = 0;  // columns
-    DBuf<T> x, r, z, p, p2, q;
+    DBuf<T> x, r, r2, z, p, p2, q;
     std::vector<std::unique_ptr<DBuf<T>>> lb, lx, lt;  // per level b, x, t
 };
 
@@ -110,41 +110,43 @@ class Hierarchy {
     hipGraphExec_t capture(int nc, bool prologue, int reps);
     void drop_graphs();
     template <typename T>
-    void vcycle(int nc, int check);
+    void vcycle(int nc, int rcur, bool upd);
     template <typename T, typename TI>
-    void vcycle_impl(int nc, int check);
+    void vcycle_impl(int nc, int rcur, bool upd);
     struct PcgRed pcg_red(int nc) const;
     template <typename T>
     PcgWork<T>& work();
     void ensure_cols(int nc);
     void set_columns(int nc);
-    // Launch shape of the batched kernels: V-cycle tiles (small: 8 / 16 nodes
-    // per coarse / fine side, else 16 / 32), columns per V-cycle workgroup
-    // (the coefficient tile is staged once for them) and node blocks per
-    // workgroup of the PCG vector kernels.  Chosen by timing on the first call of each
-    // (column count, precision); HINV_AUTOTUNE=0 uses the fixed rule instead.
+    // Launch shape of the batched kernels, chosen by timing on the first call
+    // of each (column count, precision); HINV_AUTOTUNE=0 uses the fixed rule
+    // instead.
     struct LaunchShape {
-        bool small;         // small tiles on every level
-        int small_max = 0;  // otherwise small tiles on the levels with N_l <= small_max
-        int per;
-        int cb;  // columns per workgroup of the V-cycle kernels
+        bool small;  // latency bound: short segments, several coarse levels a launch
+        int len;     // otherwise: coarse rows per segment of the wave-row kernels
+        int per;     // node blocks per workgroup of the PCG vector kernels
+        int cb;      // columns that share one reading of the operator in the V-cycle kernels
         // nodes per workgroup of the PCG vector kernels; 0: 256 per.  A
         // balanced chunk spreads a column over a whole number of workgroups
         // per compute unit instead of whole 256-node blocks.
         int chunk = 0;
     };
-    bool small_tiles(int l) const { return shape_.small || lev_[l]->N <= shape_.small_max; }
-    // Cycles with small tiles everywhere (few columns: the coarse launches are
-    // latency bound) run two coarse levels a launch; one instance only
+    enum { kMarchDown, kMarchUp, kMarchApply };
+    struct March march(int l, int nc, int kind) const;
+    int up_tile(int nc) const;
+    // Latency-bound cycles (few columns) run several coarse levels a launch; one
+    // instance only
     // (HINV_NO_PAIRS: one level a launch throughout).
     bool pair_levels() const { return shape_.small && ninst_ == 1 && !no_pairs_; }
     bool no_pairs_ = std::getenv("HINV_NO_PAIRS") != nullptr;
     int cus_ = 0;  // compute units of the device
-    bool finest_wide(int nc) const;
     LaunchShape default_shape(int nc) const;
     int min_per() const;
     template <typename T>
-    void tune_shape(int nc);
+    void tune_shape(int nc, bool in_pass);
+    // the inner right-hand side, zero iterate and column states of a refinement pass
+    template <typename T>
+    void start_pass(int nc);
     void build_coarse(int inst);
     // calls fn with the operator of level l in precision T (all instances)
     template <typename T, class F>
@@ -157,7 +159,7 @@ class Hierarchy {
     bool ready_ = false;
     int ninst_ = 1;
     int cpi_ = 1;  // columns per instance of the current call
-    LaunchShape shape_{true, 1, 1};  // launch shape of the current call
+    LaunchShape shape_{true, 1, 1, 1};  // launch shape of the current call
     std::vector<std::pair<long long, LaunchShape>> tuned_;  // (nc * 2 + fp32, shape)
     std::vector<std::pair<long long, int>> last_iters_;    // (nc * 2 + fp32, PCG iterations)
     std::vector<PriorParams> inst_pp_;

@@ -315,6 +315,7 @@ __global__ void k_ir_scale(const double* __restrict__ r64, T* __restrict__ r, T*
         act[c] = oact[c];
         st[c].bb = 1.0;
         st[c].its = 0.0;
+        st[c].alpha = 0.0;
         tdone[c] = 0;
     }
     if (!oact[c]) return;
@@ -325,14 +326,23 @@ __global__ void k_ir_scale(const double* __restrict__ r64, T* __restrict__ r, T*
     col(x, ld)[k] = 0;
 }
 
+// x64 += |r| d with d = x + alpha p the inner solution: the PCG leaves its last
+// step to this kernel (p of iteration it is in buffer it mod 2).
 template <typename T>
-__global__ void k_ir_update(double* __restrict__ x64, const T* __restrict__ d, int ld, int n,
-                            const int* __restrict__ oact, const double* __restrict__ colnorm,
-                            const int* __restrict__ inner, const int* __restrict__ tdone) {
+__global__ void k_ir_update(double* __restrict__ x64, const T* __restrict__ x, const T* __restrict__ p0,
+                            const T* __restrict__ p1, int ld, int n, const int* __restrict__ oact,
+                            const double* __restrict__ colnorm, const int* __restrict__ inner,
+                            const int* __restrict__ tdone, const ColState* __restrict__ st) {
     if (!ir_step_on(blockIdx.y, oact, inner, tdone)) return;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
-    col(x64, ld)[k] += colnorm[blockIdx.y] * (double)col(d, ld)[k];
+    const ColState& c = st[blockIdx.y];
+    T d = col(x, ld)[k];
+    if (c.its > 0.0) {
+        const T a = (T)c.alpha;
+        d = d + a * col(((int)c.its & 1) ? p1 : p0, ld)[k];
+    }
+    col(x64, ld)[k] += colnorm[blockIdx.y] * (double)d;
 }
 
 __global__ void k_copy_cols(const double* __restrict__ a, int lda, double* __restrict__ b, int ldb,
@@ -568,9 +578,10 @@ void Hierarchy::ensure_cols(int nc) {
     x64_.ensure(n * nc);
     r64_.ensure(n * nc);
     // one partial per workgroup: vector kernels use ceil(n / kBlock) workgroups,
-    // the fine-level V-cycle kernel one per tile (the small tiles give the most)
+    // the finest V-cycle kernels one per kMarchWaves segments or per tile
     const int tiles = ceil_div(N_ + 1, kTFSmall) * ceil_div(N_ + 1, kTFSmall);
-    red_stride_ = std::max(ceil_div(n, kBlock), tiles);
+    red_stride_ = std::max({ceil_div(n, kBlock), tiles,
+                            ceil_div(ceil_div(N_ / 2 + 1, kDownOwn) * (N_ / 2 + 1), kMarchWaves)});
     partial_.ensure((size_t)red_stride_ * nc);
     pcg_part_.ensure((size_t)red_stride_ * nc * 3);
     if (nc > 4096) fail(HINV_EINVAL, "more than 4096 right-hand sides in one call");
@@ -594,6 +605,7 @@ static void ensure_work(PcgWork<T>& w, const std::vector<std::unique_ptr<Level>>
     const size_t n = lev[0]->n;
     w.x.ensure(n * nc);
     w.r.ensure(n * nc);
+    w.r2.ensure(n * nc);
     w.z.ensure(n * nc);
     w.p.ensure(n * nc);
     w.p2.ensure(n * nc);
@@ -615,16 +627,35 @@ static void ensure_work(PcgWork<T>& w, const std::vector<std::unique_ptr<Level>>
     w.cap = nc;
 }
 
-// The finest level of a small-tile cycle takes 9 x 9 coarse / 18 x 18 fine
-// tiles at eight waves a SIMD when its 8 x 8 / 16 x 16 tiles (seven
-// workgroups a compute unit) would need more than two rounds of workgroups:
-// at N = 1024, 4 225 workgroups in three rounds against 3 249 in two, 20%
-// more halo work each (measured: one-column actions 3% faster there, 2%
-// slower at N = 256, where one round holds the smaller tiles).
-bool Hierarchy::finest_wide(int nc) const {
-    if (!shape_.small || lev_.size() < 2 || lev_[0]->N <= kBottomN) return false;
-    const long long t = ceil_div(lev_[1]->N + 1, kTCSmall);
-    return t * t * ceil_div(nc, shape_.cb) > 2LL * 7 * cus_;
+// Segments of the wave-row kernels of level l (down: coarse rows a wave; up and
+// PCG apply: fine rows).  Calls of few columns are latency bound: segments as short as
+// it takes to give every SIMD a wave or two, at most kLatencyRows coarse rows
+// (both row chunks of a wave are then in flight from the start).  Batches take
+// the tuned length: longer segments repeat fewer halo rows.
+March Hierarchy::march(int l, int nc, int kind) const {
+    const Level& L = *lev_[l];
+    const int Nc = L.N / 2;
+    March m;
+    m.cpi = ninst_ == 1 ? nc : cpi_;
+    int len = shape_.len;
+    if (nc < kFewCols) {
+        const long long waves = (long long)ceil_div(Nc + 1, kDownOwn) * (Nc + 1) * nc;
+        len = (int)std::min<long long>(kLatencyRows, std::max<long long>(1, waves / (kLatencyWaves * (long long)cus_)));
+    }
+    m.len = kind == kMarchDown ? len : 2 * len + 2;
+    m.strips = kind == kMarchDown ? ceil_div(Nc + 1, kDownOwn) : ceil_div(L.N + 1, kind == kMarchUp ? kUpOwn : kApplyOwn);
+    m.segs = ceil_div(kind == kMarchDown ? Nc + 1 : L.N + 1, m.len);
+    return m;
+}
+
+// Tile side of the r^T z partials of few columns (k_up_few): 18 instead of 16
+// above two rounds of seven 16 x 16 tiles a compute unit (the partials are
+// summed by every workgroup of the apply kernel: N = 1024, 3 249 instead of
+// 4 225).  The order of the sum, hence the last bit of FP64 results, follows
+// from it.
+int Hierarchy::up_tile(int nc) const {
+    const long long t = ceil_div(lev_[1]->N + 1, kTFSmall / 2);
+    return t * t * nc > 2LL * 7 * cus_ ? kTFWide : kTFSmall;
 }
 
 static ChebCoef cheb_coef() {
@@ -649,25 +680,53 @@ PcgRed Hierarchy::pcg_red(int nc) const {
     r.rr = r.pq + (size_t)red_stride_ * cap_;
     int Lb = 0;
     while (lev_[Lb]->N > kBottomN) ++Lb;
-    const int tf = finest_wide(nc) ? kTFWide : small_tiles(0) ? kTFSmall : kTFBig;
-    r.nrz = Lb == 0 ? 1 : ceil_div(lev_[0]->N + 1, tf) * ceil_div(lev_[0]->N + 1, tf);
+    r.nrz = 1;
+    if (Lb > 0 && nc < kFewCols) {
+        const int tiles = ceil_div(N_ + 1, up_tile(nc));
+        r.nrz = tiles * tiles;
+    } else if (Lb > 0) {
+        const March m = march(0, nc, kMarchUp);
+        r.nrz = ceil_div(m.strips * m.segs, kMarchWaves);
+    }
     r.per = shape_.per;
     r.chunk = shape_.chunk > 0 ? shape_.chunk : kBlock * r.per;
-    r.nvec = ceil_div(n_, r.chunk);
+    const int nvec = ceil_div(n_, r.chunk);
+    r.npq = r.nrr = nvec;
+    if (Lb > 0) {
+        const March d = march(0, nc, kMarchDown);
+        r.nrr = ceil_div(d.strips * d.segs, kMarchWaves);
+        if (nc >= kFewCols) {
+            const March a = march(0, nc, kMarchApply);
+            r.npq = ceil_div(a.strips * a.segs, kMarchWaves);
+        }
+    }
     return r;
 }
 
-// Fixed rule: small tiles below kSmallTileCols columns (more workgroups when
-// few columns make the V-cycle latency bound); batched calls give each
-// workgroup of the PCG vector kernels several node blocks, since every
-// workgroup sums all partials of its column.
+// Fixed rule: short segments and several coarse levels a launch below kFewCols
+// columns (latency bound); batched calls give each workgroup of the PCG vector
+// kernels several node blocks, since every workgroup sums all partials of its
+// column.
 Hierarchy::LaunchShape Hierarchy::default_shape(int nc) const {
     const int nb = ceil_div(n_, kBlock);
     LaunchShape sh;
-    sh.small = nc < kSmallTileCols;
-    sh.per = nc < kSmallTileCols ? 1 : std::min(16, std::max(1, ceil_div(nb, 64)));
+    sh.small = nc < kFewCols;
+    sh.per = nc < kFewCols ? 1 : std::min(16, std::max(1, ceil_div(nb, 64)));
     sh.per = std::max(sh.per, min_per());
     sh.cb = 1;
+    sh.len = kBatchRows[0];
+    if (nc < kFewCols && min_per() > 1) {
+        // too many node blocks for one a workgroup: the column split into one or
+        // two workgroups of 1024 threads per compute unit (a partial last round
+        // of workgroups costs as much as a full one)
+        for (int w : {1, 2}) {
+            const int chunk = ceil_div(ceil_div(n_, w * cus_), 64) * 64;
+            if (chunk > kVecNodes * 1024 || ceil_div(n_, chunk) > kMaxVecPartials) continue;
+            sh.per = 16;
+            sh.chunk = chunk;
+            break;
+        }
+    }
     return sh;
 }
 
@@ -691,12 +750,12 @@ int Hierarchy::min_per() const {
 // unit count, operator kind, mesh size, stacked instances, columns, solve
 // precision, and the version of the kernels' launch-shape rules.
 namespace {
-constexpr int kTuneVersion = 3;
+constexpr int kTuneVersion = 4;
 std::mutex g_tune_mu;
 bool g_tune_loaded = false;
 struct TuneRec {
     std::string arch;
-    int kind, N, ninst, nc, fp32, small, small_max, per, cb, chunk;
+    int kind, N, ninst, nc, fp32, small, len, per, cb, chunk;
 };
 std::vector<TuneRec> g_tune;
 long g_tune_timed = 0, g_tune_cached = 0;
@@ -721,10 +780,10 @@ void tune_load_locked() {
         if (std::sscanf(line,
                         "{\"version\": %d, \"device\": \"%127[^\"]\", \"kind\": %d, \"N\": %d, "
                         "\"instances\": %d, \"columns\": %d, \"fp32\": %d, \"small\": %d, "
-                        "\"small_max\": %d, \"per\": %d, \"cb\": %d, \"chunk\": %d}",
-                        &ver, arch, &r.kind, &r.N, &r.ninst, &r.nc, &r.fp32, &r.small, &r.small_max, &r.per,
+                        "\"rows\": %d, \"per\": %d, \"cb\": %d, \"chunk\": %d}",
+                        &ver, arch, &r.kind, &r.N, &r.ninst, &r.nc, &r.fp32, &r.small, &r.len, &r.per,
                         &r.cb, &r.chunk) == 12 &&
-            ver == kTuneVersion && r.per >= 1 && r.per <= 16 && r.cb >= 1 && r.cb <= 64 && r.chunk >= 0 &&
+            ver == kTuneVersion && r.len >= 1 && r.len <= 4096 && r.per >= 1 && r.per <= 16 && r.cb >= 1 && r.cb <= 64 && r.chunk >= 0 &&
             r.chunk % 64 == 0 && r.chunk <= kVecNodes * vec_threads(r.per)) {
             r.arch = arch;
             g_tune.push_back(r);
@@ -740,13 +799,20 @@ void tuner_counts(long* timed, long* cached) {
     *cached = g_tune_cached;
 }
 
-// Times the candidate shapes on the call's own right-hand sides (w.r is set):
-// the V-cycle with each tile choice, then the PCG apply kernel in its general
-// form (beta from the r^T z partials) with 1, 4, 8 and 16 node blocks per
-// workgroup.  Neither touches the solve's state: the apply kernel's outputs
-// (p_new, q, the recorded r^T z) are rewritten by the first real iteration.
+// Times the candidate shapes on the call's own right-hand sides: in a
+// refinement pass the start of the pass and three PCG iterations, restarted
+// for each trial and once more at the end; else (w.r is set) the V-cycle
+// alone, which leaves no trace.
 template <typename T>
-void Hierarchy::tune_shape(int nc) {
+void Hierarchy::start_pass(int nc) {
+    PcgWork<T>& w = work<T>();
+    k_ir_scale<T><<<grid2(n_, nc), kBlock, 0, ctx_->stream>>>(r64_.get(), w.r.get(), w.x.get(), n_, n_, oact_.get(),
+                                                             colnorm_.get(), act_.get(), st_.get(), tdone_.get());
+    HINV_LAUNCH_CHECK();
+}
+
+template <typename T>
+void Hierarchy::tune_shape(int nc, bool in_pass) {
     const long long key = 2LL * nc + (sizeof(T) == 4);
     for (const auto& kv : tuned_)
         if (kv.first == key) {
@@ -759,7 +825,6 @@ void Hierarchy::tune_shape(int nc) {
         // HINV_SHAPE=<s|l><per>[c<cb>][k<chunk>]
         if ((f[0] == 's' || f[0] == 'l') && std::atoi(f + 1) >= 1) {
             shape_.small = f[0] == 's';
-            shape_.small_max = 0;
             shape_.per = std::min(16, std::atoi(f + 1));
             const char* c = std::strchr(f, 'c');
             shape_.cb = c ? std::max(1, std::min(64, std::atoi(c + 1))) : 1;
@@ -782,7 +847,7 @@ void Hierarchy::tune_shape(int nc) {
             if (it->arch == arch && it->kind == (int)kind_ && it->N == N_ && it->ninst == ninst_ && it->nc == nc &&
                 it->fp32 == fp32 && it->per >= min_per()) {
                 shape_.small = it->small != 0;
-                shape_.small_max = it->small_max;
+                shape_.len = it->len;
                 shape_.per = it->per;
                 shape_.cb = it->cb;
                 shape_.chunk = it->chunk;
@@ -801,7 +866,7 @@ void Hierarchy::tune_shape(int nc) {
     auto timed = [&](auto fn) {
         fn();  // warm
         float best = 1e30f;
-        for (int rep = 0; rep < 3; ++rep) {
+        for (int rep = 0; rep < 2; ++rep) {
             HINV_HIP(hipEventRecord(e0, s));
             fn();
             HINV_HIP(hipEventRecord(e1, s));
@@ -814,71 +879,36 @@ void Hierarchy::tune_shape(int nc) {
     };
     LaunchShape best = shape_;
     float best_ms = 1e30f;
-    // tiles: small on every level, or large above N_l = small_max (0: every
-    // level large; 128, 256: the coarser levels keep the shorter workgroups)
-    // Below kSmallTileCols columns every level keeps small tiles: timed back
-    // to back, the V-cycle's vectors stay in cache and favour large tiles
-    // (less halo), while inside PCG iterations they do not.
-    const int N0 = lev_[0]->N;
-    // cb: the RHS-block width, columns one workgroup of the V-cycle kernels sweeps
-    for (int small_max : {-1, 0, 128, 256})
-        for (int cb : {1, 2, 4, 8, 16}) {
-            if (nc < kSmallTileCols && (cb > 1 || small_max >= 0)) continue;
-            if (small_max > 0 && small_max >= N0) continue;
-            shape_.small = small_max < 0;
-            shape_.small_max = std::max(0, small_max);
-            shape_.cb = cb;
-            const float ms = timed([&] { vcycle<T>(nc, 0); });
-            if (ms < best_ms) {
-                best_ms = ms;
-                best.small = shape_.small;
-                best.small_max = shape_.small_max;
-                best.cb = cb;
-            }
-        }
-    shape_.small = best.small;
-    shape_.small_max = best.small_max;
-    shape_.cb = best.cb;
-    PcgWork<T>& w = work<T>();
-    const int n = n_;
-    best_ms = 1e30f;
-    // Few columns whose node blocks fit the partial cap one per workgroup keep
-    // one block per workgroup: measured fastest inside the solves, while timing
-    // the apply kernel alone has picked 4 in some runs (3% slower solves).
-    const bool fixed_per = nc < kSmallTileCols && min_per() == 1;
-    if (fixed_per) best.per = 1;
-    // candidates (per, chunk): whole 256-node blocks, and for few columns the
-    // column split into one or two workgroups of 1024 threads per compute unit
-    // (a partial last round of workgroups costs as much as a full one)
-    std::vector<std::pair<int, int>> cand;
-    for (int per : {1, 4, 8, 16})
-        if (!fixed_per && per >= min_per()) cand.push_back({per, 0});
-    if (!fixed_per && nc < kSmallTileCols) {
-        hipDeviceProp_t prop;
-        HINV_HIP(hipGetDeviceProperties(&prop, ctx_->device));
-        for (int w : {1, 2}) {
-            const int want = prop.multiProcessorCount * w;
-            const int chunk = ceil_div(ceil_div(n, want), 64) * 64;
-            if (chunk <= kVecNodes * 1024 && ceil_div(n, chunk) <= kMaxVecPartials) cand.push_back({16, chunk});
-        }
-    }
-    best.chunk = 0;
-    for (const auto& pc : cand) {
-        shape_.per = pc.first;
-        shape_.chunk = pc.second;
-        const PcgRed red = pcg_red(nc);
-        const float ms = timed([&] {
-            with_op<T>(0, [&](auto op) {
-                k_pcg_apply<T, decltype(op), false><<<dim3(red.nvec, nc), vec_threads(red.per), 0, s>>>(
-                    op, w.z.get(), w.p.get(), w.p2.get(), w.q.get(), n, act_.get(), st_.get(), red);
-            });
-            HINV_LAUNCH_CHECK();
-        });
-        if (ms < best_ms) {
-            best_ms = ms;
-            best.per = pc.first;
-            best.chunk = pc.second;
-        }
+    // Below kFewCols columns the V-cycle's shape is fixed (latency bound).
+    // Batches: coarse levels one or several a launch, the segment length of
+    // the wave-row kernels, and the RHS-block width: the columns that share one
+    // reading of the operator (a wave of the wave-row kernels, a workgroup of
+    // the multi-level ones).
+    if (nc >= kFewCols) {
+        for (int small : {0, 1})
+            for (int len : kBatchRows)
+                for (int cb : {1, 2}) {
+                    if (small && (len != kBatchRows[0] || cb > 1)) continue;
+                    shape_.small = small != 0;
+                    shape_.len = len;
+                    shape_.cb = cb;
+                    const float ms = timed([&] {
+                        if (in_pass) start_pass<T>(nc);
+                        vcycle<T>(nc, 0, false);
+                        if (!in_pass) return;
+                        pcg_iteration<T>(nc, 0, 1);
+                        pcg_iteration<T>(nc, 1, 0);
+                        pcg_iteration<T>(nc, 0, 0);
+                    });
+                    if (ms < best_ms) {
+                        best_ms = ms;
+                        best.small = shape_.small;
+                        best.len = len;
+                        best.cb = cb;
+                    }
+                }
+        shape_ = best;
+        if (in_pass) start_pass<T>(nc);
     }
     ctx_->timer.paused = timer_was;
     (void)hipEventDestroy(e0);
@@ -888,7 +918,7 @@ void Hierarchy::tune_shape(int nc) {
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         ++g_tune_timed;
-        TuneRec r{arch, (int)kind_, N_, ninst_, nc, fp32, best.small ? 1 : 0, best.small_max, best.per, best.cb,
+        TuneRec r{arch, (int)kind_, N_, ninst_, nc, fp32, best.small ? 1 : 0, best.len, best.per, best.cb,
                   best.chunk};
         g_tune.push_back(r);
         const char* path = std::getenv("HINV_TUNE_CACHE");
@@ -896,18 +926,18 @@ void Hierarchy::tune_shape(int nc) {
             if (std::FILE* f = std::fopen(path, "a")) {
                 std::fprintf(f,
                              "{\"version\": %d, \"device\": \"%s\", \"kind\": %d, \"N\": %d, \"instances\": %d, "
-                             "\"columns\": %d, \"fp32\": %d, \"small\": %d, \"small_max\": %d, \"per\": %d, "
+                             "\"columns\": %d, \"fp32\": %d, \"small\": %d, \"rows\": %d, \"per\": %d, "
                              "\"cb\": %d, \"chunk\": %d}\n",
-                             kTuneVersion, r.arch.c_str(), r.kind, r.N, r.ninst, r.nc, r.fp32, r.small, r.small_max,
+                             kTuneVersion, r.arch.c_str(), r.kind, r.N, r.ninst, r.nc, r.fp32, r.small, r.len,
                              r.per, r.cb, r.chunk);
                 std::fclose(f);
             }
     }
     if (std::getenv("HINV_TRACE_SHAPES"))
-        std::fprintf(stderr, "[hinv] launch shape N=%d nc=%d %s: %s tiles, %d columns per V-cycle workgroup, "
-                     "%d node blocks per workgroup, chunk %d\n", N_, nc, sizeof(T) == 8 ? "fp64" : "fp32",
-                     best.small ? "small" : (best.small_max ? "large above N=256/128, small" : "large"), best.cb,
-                     best.per, best.chunk);
+        std::fprintf(stderr, "[hinv] launch shape N=%d nc=%d %s: %s coarse levels a launch, segments of %d coarse rows, "
+                     "%d columns a block, %d node blocks per workgroup, chunk %d\n", N_, nc,
+                     sizeof(T) == 8 ? "fp64" : "fp32", best.small ? "several" : "one", best.small ? 0 : best.len,
+                     best.cb, best.per, best.chunk);
 }
 
 // z = V-cycle(r) for the PCG of precision T.  An FP64 PCG runs its V-cycle
@@ -915,9 +945,12 @@ void Hierarchy::tune_shape(int nc) {
 // solve's result, which the PCG and the refinement test hold to their
 // tolerance in FP64): the finest-level kernels read r and write z in FP64,
 // every other vector of the cycle is FP32.
+// The residual is R[rcur] of the two residual buffers; upd: the finest kernel
+// down first takes the PCG step, R[rcur] -> R[1 - rcur], which is then the
+// cycle's residual, and the next kernel tests the columns' convergence.
 template <typename T>
-void Hierarchy::vcycle(int nc, int check) {
-    vcycle_impl<T, float>(nc, check);
+void Hierarchy::vcycle(int nc, int rcur, bool upd) {
+    vcycle_impl<T, float>(nc, rcur, upd);
 }
 
 // k_up_chain for NL levels with nt threads per workgroup (template dispatch).
@@ -945,9 +978,12 @@ static void launch_chain(int NL, int nt, dim3 g, hipStream_t s, const ChainArgs<
 }
 
 template <typename T, typename TI>
-void Hierarchy::vcycle_impl(int nc, int check) {
+void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
     hipStream_t s = launch_stream_;
     PcgWork<T>& wt = work<T>();
+    T* const R[2] = {wt.r.get(), wt.r2.get()};
+    const T* const rin = R[rcur];
+    T* const rv = upd ? R[1 - rcur] : R[rcur];  // the cycle's residual
     PcgWork<TI>& wi = work<TI>();
     const int nlev = (int)lev_.size();
     int Lb = 0;
@@ -986,8 +1022,8 @@ void Hierarchy::vcycle_impl(int nc, int check) {
                         auto go = [&](auto kern, int nt) {
                             timed_launch(ctx_, -1, 0.0, kern, dim3(tc, tc, gz), dim3(nt), s, opF, opM,
                                          (const TI*)wi.lb[l]->get(), wi.lt[l]->get(), L.n, wi.lb[l + 1]->get(),
-                                         wi.lt[l + 1]->get(), C.n, wi.lb[l + 2]->get(), Cc.n, dir,
-                                         (const int*)act, cc, nc, shape_.cb);
+                                         wi.lt[l + 1]->get(), C.n, wi.lb[l + 2]->get(), Cc.n, dir, act, cc, red,
+                                         st_.get(), l == 1 && upd ? 1 : 0, nc, shape_.cb);
                         };
                         if (threads_for(tc * tc) == 512)
                             go(k_down2<TI, Op, kTPair, 512>, 512);
@@ -1000,35 +1036,40 @@ void Hierarchy::vcycle_impl(int nc, int check) {
             ++l;
             continue;
         }
-        // algorithmic bytes: read b, write x2 and b_coarse per column; the state
-        // operator's three coefficient arrays once per launch and instance
-        const double bytes_down = nc * ((l == 0 ? st : si) * L.n + si * (L.n + C.n)) + (dir ? si * 3.0 * L.n * ninst_ : 0.0);
+        // algorithmic bytes: read b (with the PCG step: r and q, and write r),
+        // write x2 and b_coarse per column; the state operator's three
+        // coefficient arrays once per launch and instance
+        const double bytes_down = nc * ((l == 0 ? (upd ? 3.0 * st : st) : si) * L.n + si * (L.n + C.n)) +
+                                  (dir ? si * 3.0 * L.n * ninst_ : 0.0);
         const int kcls = l == 0 ? kclass_for(kKDown, nc) : -1;
         with_op<TI>(l, [&](auto op) {
             using Op = decltype(op);
-            const int chk = l == 0 ? check : 0;
-            const int cb = shape_.cb, gz = ceil_div(nc, cb);
+            const int chk = l == 1 && upd ? 1 : 0;
             TI* xl = wi.lt[l]->get();
             TI* bcl = wi.lb[l + 1]->get();
             ColState* stp = st_.get();
-            auto launch = [&](auto kern, int tcs, const auto* bl) {
-                const int tc = ceil_div(C.N + 1, tcs);
-                timed_launch(ctx_, kcls, bytes_down, kern, dim3(tc, tc, gz), dim3(256), s, op, bl, xl, L.n, bcl, C.n,
-                             dir, act, cc, red, stp, chk, nc, cb);
+            const March m = march(l, nc, kMarchDown);
+            auto launch = [&](auto kern, int nb, const auto* bl, const auto* ql, auto* rn) {
+                const dim3 g(ceil_div(m.strips * m.segs, kMarchWaves), 1, ninst_ * ceil_div(m.cpi, nb));
+                timed_launch(ctx_, kcls, bytes_down, kern, g, dim3(64 * kMarchWaves), s, op, bl, ql, rn, xl, L.n, bcl,
+                             C.n, dir, act, cc, red, stp, chk, m);
             };
-            if (l == 0) {
-                if (finest_wide(nc))
-                    launch(k_down<TI, Op, kTCWide, T, 8>, kTCWide, (const T*)wt.r.get());
-                else if (small_tiles(l))
-                    launch(k_down<TI, Op, kTCSmall, T>, kTCSmall, (const T*)wt.r.get());
+            auto shaped = [&](auto step, const auto* bl, const auto* ql, auto* rn) {
+                using TB = std::remove_pointer_t<decltype(rn)>;
+                constexpr bool U = decltype(step)::value;
+                if (nc < kFewCols)
+                    launch(k_down<TI, Op, TB, kLatencyChunk, 1, U>, 1, bl, ql, rn);
+                else if (shape_.cb >= 2)
+                    launch(k_down<TI, Op, TB, kBatchChunk, 2, U>, 2, bl, ql, rn);
                 else
-                    launch(k_down<TI, Op, kTCBig, T>, kTCBig, (const T*)wt.r.get());
-            } else {
-                if (small_tiles(l))
-                    launch(k_down<TI, Op, kTCSmall>, kTCSmall, (const TI*)wi.lb[l]->get());
-                else
-                    launch(k_down<TI, Op, kTCBig>, kTCBig, (const TI*)wi.lb[l]->get());
-            }
+                    launch(k_down<TI, Op, TB, kBatchChunk, 1, U>, 1, bl, ql, rn);
+            };
+            if (l > 0)
+                shaped(std::false_type{}, (const TI*)wi.lb[l]->get(), (const TI*)nullptr, (TI*)nullptr);
+            else if (upd)
+                shaped(std::true_type{}, rin, (const T*)wt.q.get(), rv);
+            else
+                shaped(std::false_type{}, rin, (const T*)nullptr, (T*)nullptr);
         });
         HINV_LAUNCH_CHECK();
     }
@@ -1063,7 +1104,7 @@ void Hierarchy::vcycle_impl(int nc, int check) {
                 a.karows[l] = karow32_.get() ? karow32_.get() + off : nullptr;
             }
         }
-        const int chk = Lb == 0 ? check : 0;
+        const int chk = Lb <= 1 && upd ? 1 : 0;
         // per column: read b (and r for r^T z), write x; once per launch: the
         // state coefficients of every bottom level and the dense coarse inverse
         const double nb = (double)(lev_[Lb]->n);
@@ -1078,7 +1119,7 @@ void Hierarchy::vcycle_impl(int nc, int check) {
         };
         if (Lb == 0) {
             // the whole hierarchy: r in, z out, and the r^T z partial
-            const T* r = wt.r.get();
+            const T* r = rv;
             if (kind_ == kOpState)
                 launch(k_bottom<T, kOpState, kBottomN>, r, wt.z.get(), r, st);
             else
@@ -1125,44 +1166,51 @@ void Hierarchy::vcycle_impl(int nc, int check) {
             l = lo;  // the loop's decrement continues below the chain
             continue;
         }
-        // read b, x2, x_coarse (and r for r^T z), write x; coefficients once per instance
-        const double bytes_up = nc * ((l == 0 ? 3.0 * st : 2.0 * si) * L.n + si * (L.n + C.n)) +
+        // read b, x2, x_coarse, write x; coefficients once per instance
+        const double bytes_up = nc * ((l == 0 ? 2.0 * st : 2.0 * si) * L.n + si * (L.n + C.n)) +
                                 (dir ? si * 3.0 * L.n * ninst_ : 0.0);
         const int kcls = l == 0 ? kclass_for(kKUp, nc) : -1;
         with_op<TI>(l, [&](auto op) {
             using Op = decltype(op);
-            const int cb = shape_.cb, gz = ceil_div(nc, cb);
             const TI* x2l = wi.lt[l]->get();
             const TI* xcl = wi.lx[l + 1]->get();
             const int* actc = act;
-            auto launch = [&](auto kern, int tfs, const auto* bl, auto* xl, const auto* rv) {
-                const int tf = ceil_div(L.N + 1, tfs);
-                timed_launch(ctx_, kcls, bytes_up, kern, dim3(tf, tf, gz), dim3(256), s, op, bl, x2l, xl, L.n, xcl,
-                             C.n, dir, actc, cc, rv, red, nc, cb);
+            const March m = march(l, nc, kMarchUp);
+            auto launch = [&](auto kern, int nb, const auto* bl, auto* xl, int rz) {
+                const dim3 g(ceil_div(m.strips * m.segs, kMarchWaves), 1, ninst_ * ceil_div(m.cpi, nb));
+                timed_launch(ctx_, kcls, bytes_up, kern, g, dim3(64 * kMarchWaves), s, op, bl, x2l, xl, L.n, xcl, C.n,
+                             dir, actc, cc, rz, red, m);
             };
-            if (l == 0) {
-                const T* r = wt.r.get();
-                if (finest_wide(nc))
-                    launch(k_up<TI, Op, kTFWide, T, T, 8>, kTFWide, r, wt.z.get(), r);
-                else if (small_tiles(l))
-                    launch(k_up<TI, Op, kTFSmall, T, T>, kTFSmall, r, wt.z.get(), r);
+            auto shaped = [&](const auto* bl, auto* xl, int rz) {
+                using TB = std::remove_cv_t<std::remove_pointer_t<decltype(bl)>>;
+                using TX = std::remove_pointer_t<decltype(xl)>;
+                if (nc < kFewCols)
+                    launch(k_up<TI, Op, TB, TX, kLatencyChunk, 1>, 1, bl, xl, rz);
+                else if (shape_.cb >= 2)
+                    launch(k_up<TI, Op, TB, TX, kBatchChunk, 2>, 2, bl, xl, rz);
                 else
-                    launch(k_up<TI, Op, kTFBig, T, T>, kTFBig, r, wt.z.get(), r);
-            } else {
-                const TI* bl = wi.lb[l]->get();
-                const TI* none = nullptr;
-                if (small_tiles(l))
-                    launch(k_up<TI, Op, kTFSmall>, kTFSmall, bl, wi.lx[l]->get(), none);
-                else
-                    launch(k_up<TI, Op, kTFBig>, kTFBig, bl, wi.lx[l]->get(), none);
-            }
+                    launch(k_up<TI, Op, TB, TX, kBatchChunk, 1>, 1, bl, xl, rz);
+            };
+            auto few = [&](auto kern, int tf) {
+                const int t = ceil_div(L.N + 1, tf);
+                timed_launch(ctx_, kcls, bytes_up, kern, dim3(ceil_div(t, kUpTiles), t, nc), dim3(64 * kMarchWaves), s,
+                             op, (const T*)rv, x2l, wt.z.get(), L.n, xcl, C.n, dir, actc, cc, red);
+            };
+            if (l > 0)
+                shaped((const TI*)wi.lb[l]->get(), wi.lx[l]->get(), 0);
+            else if (nc >= kFewCols)
+                shaped((const T*)rv, wt.z.get(), 1);
+            else if (up_tile(nc) == kTFWide)
+                few(k_up_few<TI, Op, T, T, kTFWide>, kTFWide);
+            else
+                few(k_up_few<TI, Op, T, T, kTFSmall>, kTFSmall);
         });
         HINV_LAUNCH_CHECK();
     }
 }
 
-// One PCG iteration (apply, update, V-cycle) on launch_stream_: p moves from
-// P[cur] to P[1 - cur].
+// One PCG iteration (apply, then the V-cycle with the step of the residual) on
+// launch_stream_: p and r move from buffer cur to buffer 1 - cur.
 template <typename T>
 void Hierarchy::pcg_iteration(int nc, int cur, int first) {
     hipStream_t s = launch_stream_;
@@ -1171,33 +1219,51 @@ void Hierarchy::pcg_iteration(int nc, int cur, int first) {
     const int n = L.n, ld = n;
     int* act = act_.get();
     const PcgRed red = pcg_red(nc);
-    const dim3 g(red.nvec, nc);
+    const bool linear = nc < kFewCols || L.N <= kBottomN;
+    const int nvec = ceil_div(n, red.chunk);
     T* P[2] = {w.p.get(), w.p2.get()};
     {
-        // read z, p_old, write p_new, q; state coefficients once per instance
+        // read z, p_old, x, write p_new, q, x; state coefficients once per instance
         const double bytes_apply =
-            sizeof(T) * ((double)nc * 4.0 * n + (kind_ == kOpState ? 2.0 * n * ninst_ : 0.0));
+            sizeof(T) * ((double)nc * (first ? 3.0 : 6.0) * n + (kind_ == kOpState ? 2.0 * n * ninst_ : 0.0));
         with_op<T>(0, [&](auto op) {
             using Op = decltype(op);
             const T* zc = w.z.get();
             const T* pold = P[cur];
+            T* pnew = P[1 - cur];
             const int* actc = act;
             ColState* stc = st_.get();
-            timed_launch(ctx_, kclass_for(kKPcgApply, nc), bytes_apply, first ? k_pcg_apply<T, Op, true> : k_pcg_apply<T, Op, false>, g,
-                         dim3(vec_threads(red.per)), s, op, zc, pold, P[1 - cur], w.q.get(), ld, actc, stc, red);
+            const int kcls = kclass_for(kKPcgApply, nc);
+            if (linear) {
+                timed_launch(ctx_, kcls, bytes_apply, first ? k_pcg_apply_few<T, Op, true> : k_pcg_apply_few<T, Op, false>,
+                             dim3(nvec, nc), dim3(vec_threads(red.per)), s, op, zc, pold, pnew, w.q.get(), w.x.get(),
+                             ld, actc, stc, red);
+                return;
+            }
+            const March m = march(0, nc, kMarchApply);
+            auto launch = [&](auto kern, int nb) {
+                const dim3 g(ceil_div(m.strips * m.segs, kMarchWaves), 1, ninst_ * ceil_div(m.cpi, nb));
+                timed_launch(ctx_, kcls, bytes_apply, kern, g, dim3(64 * kMarchWaves), s, op, zc, pold, pnew,
+                             w.q.get(), w.x.get(), ld, actc, stc, red, m);
+            };
+            if (first)
+                launch(k_pcg_apply<T, Op, true, kBatchChunk, 1>, 1);
+            else if (shape_.cb >= 2)
+                launch(k_pcg_apply<T, Op, false, kBatchChunk, 2>, 2);
+            else
+                launch(k_pcg_apply<T, Op, false, kBatchChunk, 1>, 1);
         });
         HINV_LAUNCH_CHECK();
     }
-    {
-        // x, r in/out, p, q in
-        const T* pn = P[1 - cur];
+    if (L.N <= kBottomN) {
+        T* R[2] = {w.r.get(), w.r2.get()};
+        const T* rc = R[cur];
         const T* qc = w.q.get();
-        timed_launch(ctx_, kclass_for(kKPcgUpdate, nc), sizeof(T) * (double)nc * 6.0 * n, k_pcg_update<T>, g,
-                     dim3(vec_threads(red.per)), s,
-                     w.x.get(), w.r.get(), pn, qc, ld, n, act, st_.get(), red);
+        timed_launch(ctx_, kclass_for(kKPcgUpdate, nc), sizeof(T) * (double)nc * 3.0 * n, k_pcg_update<T>,
+                     dim3(nvec, nc), dim3(vec_threads(red.per)), s, rc, R[1 - cur], qc, ld, n, act, st_.get(), red);
         HINV_LAUNCH_CHECK();
     }
-    vcycle<T>(nc, 1);
+    vcycle<T>(nc, cur, true);
 }
 
 // Graph of 2 reps PCG iterations starting from P[1], or of the prologue
@@ -1211,7 +1277,7 @@ hipGraphExec_t Hierarchy::capture(int nc, bool prologue, int reps) {
     ctx_->timer.paused = true;
     try {
         if (prologue) {
-            vcycle<T>(nc, 0);
+            vcycle<T>(nc, 0, false);
             pcg_iteration<T>(nc, 0, 1);
         }
         for (int r = 0; r < reps; ++r) {
@@ -1296,7 +1362,7 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
     hipStream_t s = ctx_->stream;
     launch_stream_ = s;
     int* act = act_.get();
-    tune_shape<T>(nc);
+    tune_shape<T>(nc, true);
     const bool graphs = !std::getenv("HINV_NO_GRAPHS");
     // The prologue (V-cycle of the initial residual, first iteration) is a
     // graph too.  While the kernel timer runs, every 16th solve of few columns
@@ -1307,7 +1373,7 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
     // their eager launches cost nothing measurable, and sampling each batched
     // solve keeps the mix of operators in the class averages fixed.)
     int it = 0;
-    bool sampled = ctx_->timer.any_on() && (nc >= kSmallTileCols || solves_++ % 16 == 0);
+    bool sampled = ctx_->timer.any_on() && (nc >= kFewCols || solves_++ % 16 == 0);
     // Iterations before the first completion check follow the iteration count of
     // the last solve of this shape: the columns count their own iterations in
     // the column state, so the estimate is the slowest column's count, not the
@@ -1327,9 +1393,9 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
         HINV_HIP(hipGraphLaunch(prologue_graph<T>(nc, pre), s));
         it = 1 + 2 * pre;
         for (int k : {kclass_for(kKDown, nc), kclass_for(kKUp, nc), (int)kKBottom}) ctx_->timer.count_only(k, 2 + 2 * pre);
-        for (int k : {kclass_for(kKPcgApply, nc), kclass_for(kKPcgUpdate, nc)}) ctx_->timer.count_only(k, 1 + 2 * pre);
+        ctx_->timer.count_only(kclass_for(kKPcgApply, nc), 1 + 2 * pre);
     } else {
-        vcycle<T>(nc, 0);
+        vcycle<T>(nc, 0, false);
         if (max_iter > 0) {
             pcg_iteration<T>(nc, 0, 1);
             it = 1;
@@ -1357,7 +1423,7 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
                     HINV_HIP(hipGraphLaunch(pcg_graph<T>(nc, reps - 1), s));
                     it += 2 * (reps - 1);
                     for (int k : {kclass_for(kKDown, nc), kclass_for(kKUp, nc), (int)kKBottom,
-                                  kclass_for(kKPcgApply, nc), kclass_for(kKPcgUpdate, nc)})
+                                  kclass_for(kKPcgApply, nc)})
                         ctx_->timer.count_only(k, 2 * (reps - 1));
                 }
             } else if (graphs && reps > 0) {
@@ -1429,8 +1495,8 @@ void Hierarchy::precondition(int nc, const double* r, int ldr, double* z, int ld
     k_fill_int<<<ceil_div(nc, 64), 64, 0, s>>>(nc, 1, act_.get());
     HINV_LAUNCH_CHECK();
     launch_stream_ = s;
-    tune_shape<double>(nc);
-    vcycle<double>(nc, 0);
+    tune_shape<double>(nc, false);
+    vcycle<double>(nc, 0, false);
     with_op<double>(0, [&](auto op) {
         k_masked_copy<<<g, kBlock, 0, s>>>(op, w64_.z.get(), n_, z, ldz);
     });
@@ -1564,9 +1630,9 @@ void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int 
         // refinement step x64 += |r| x_inner, r64 = b - A x64, outer bookkeeping;
         // with inner flags given, only for the columns whose PCG has finished
         // (and once per pass)
-        auto step = [&](auto* xin, const int* inner) {
-            using TI = std::remove_pointer_t<decltype(xin)>;
-            k_ir_update<TI><<<g, kBlock, 0, s>>>(xw, xin, ld, n, oact_.get(), colnorm_.get(), inner, tdone_.get());
+        auto step = [&](auto& wk, const int* inner) {
+            k_ir_update<<<g, kBlock, 0, s>>>(xw, wk.x.get(), wk.p.get(), wk.p2.get(), ld, n, oact_.get(),
+                                             colnorm_.get(), inner, tdone_.get(), st_.get());
             HINV_LAUNCH_CHECK();
             with_op<double>(0, [&](auto op) {
                 k_ir_residual<<<g, kBlock, 0, s>>>(op, b, ldb, xw, r64_.get(), ld, oact_.get(), inner, tdone_.get(),
@@ -1578,22 +1644,18 @@ void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int 
             HINV_LAUNCH_CHECK();
         };
         if (use32) {
-            k_ir_scale<float><<<g, kBlock, 0, s>>>(r64_.get(), w32_.r.get(), w32_.x.get(), ld, n, oact_.get(),
-                                                   colnorm_.get(), act_.get(), st_.get(), tdone_.get());
-            HINV_LAUNCH_CHECK();
+            start_pass<float>(nc);
             pcg<float>(nc, max_iter - iters, &iters);
-            step(w32_.x.get(), nullptr);
+            step(w32_, nullptr);
             last64 = false;
         } else {
-            k_ir_scale<double><<<g, kBlock, 0, s>>>(r64_.get(), w64_.r.get(), w64_.x.get(), ld, n, oact_.get(),
-                                                    colnorm_.get(), act_.get(), st_.get(), tdone_.get());
-            HINV_LAUNCH_CHECK();
+            start_pass<double>(nc);
             // the step is enqueued before each completion check of the PCG, so
             // that one read-back serves both checks when the PCG has finished
-            const std::function<void()> tail = [&] { step(w64_.x.get(), act_.get()); };
+            const std::function<void()> tail = [&] { step(w64_, act_.get()); };
             have_state = pcg<double>(nc, max_iter - iters, &iters, &tail);
             // stopped at the iteration limit: unfinished columns take the step they have
-            if (!have_state) step(w64_.x.get(), nullptr);
+            if (!have_state) step(w64_, nullptr);
             last64 = true;
         }
         ++outer;

@@ -38,7 +38,7 @@ import json
 import os
 import sys
 
-CLASSES = (("hinv::k_down<", "mg_down"), ("hinv::k_up<", "mg_up"), ("hinv::k_bottom<", "mg_bottom"),
+CLASSES = (("hinv::k_down<", "mg_down"), ("hinv::k_up<", "mg_up"), ("hinv::k_up_few<", "mg_up"), ("hinv::k_bottom<", "mg_bottom"),
            ("hinv::k_pcg_apply<", "pcg_apply"), ("hinv::k_pcg_update<", "pcg_update"),
            ("k_gram_bf16", "gram"), ("k_gram_f64", "gram"), ("k_gram_wide", "gram"))
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
@@ -140,7 +140,7 @@ def kernel_source_hash(root):
     """Hash of the V-cycle and PCG kernel sources (the traffic is valid while they are unchanged)."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("mgkernels.h", "grid.h"):
+    for f in ("mgkernels.h", "waverow.h", "grid.h"):
         h.update(open(os.path.join(root, "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
