@@ -7,8 +7,39 @@
 namespace hinv {
 
 // ------------------------------------------------------------ reductions ---
+// Butterfly sum over the wave (lanes 32, 16, 8, 4, 2, 1 apart), every lane.
+// On the vector unit: lanes 32 and 16 apart through the lane swaps, the
+// others by rotations within 16 lanes (after the step 8 apart the values
+// repeat every 8 lanes, so rotating by 4 meets the lane 4 apart, and so on).
+// A shuffle through the LDS unit takes several times as long a step, and the
+// reductions sit in the dependency chain of every latency-bound kernel.
+template <int CTRL>
+__device__ inline double dpp_d(double v) {
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
 __device__ inline double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    auto join = [](unsigned lo, unsigned hi) {
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    };
+    {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+        v = join(l[0], h[0]) + join(l[1], h[1]);
+    }
+    {
+        const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+        v = join(l[0], h[0]) + join(l[1], h[1]);
+    }
+    v += dpp_d<0x128>(v);  // row_ror:8
+    v += dpp_d<0x124>(v);  // row_ror:4
+    v += dpp_d<0x122>(v);  // row_ror:2
+    v += dpp_d<0x121>(v);  // row_ror:1
     return v;
 }
 

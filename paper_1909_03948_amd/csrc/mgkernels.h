@@ -62,7 +62,7 @@ __device__ inline double partial_rest(double s, const double* part, int col, int
 // are in flight together with the caller's other loads (a loop waits for
 // each load it accumulates); more partials than kShareLoads per thread
 // follow in a loop.  Summed in index order, as partial_rest does.
-constexpr int kShareLoads = 3;
+constexpr int kShareLoads = 4;
 __device__ inline double partial_share(const double* part, int col, int stride, int nblk) {
     const double* p = part + (size_t)col * stride;
     const int t = threadIdx.x, nt = blockDim.x;
@@ -82,25 +82,36 @@ __device__ inline double partial_share(const double* part, int col, int stride, 
 // inside a branch makes the wave wait for it there).
 __device__ inline int clamp_node(int i, int N) { return min(max(i, 0), N); }
 
+// A value the same in every lane of the wave, moved to a scalar register:
+// integer division runs on the vector unit, and its result would otherwise
+// keep the addresses formed from it in vector registers.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Waves of the workgroup as a uniform value (read once, outside the
 // single-thread code that sums the per-wave slots).
 __device__ inline int group_waves() { return __builtin_amdgcn_readfirstlane((int)(blockDim.x >> 6)); }
 
-// Second phase: the workgroup total of the shares, returned to every thread.
+// Sum of the first nw of 16 wave slots in LDS, in index order (all reads are
+// issued together).
+__device__ inline double slot_sum(const double* ps, int nw) {
+    double q[16];
+#pragma unroll
+    for (int w = 0; w < 16; ++w) q[w] = ps[w];
+    double t = q[0];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) t = w < nw ? t + q[w] : t;
+    return t;
+}
+
+// Second phase: the workgroup total of the shares, returned to every thread
+// (each sums the wave slots itself: one barrier).  The slots of a call stay
+// in use until the workgroup's next barrier.
 __device__ inline double share_total(double s) {
-    __shared__ double ps[16];
-    __shared__ double tot;
-    const int nw = group_waves();
+    __shared__ __attribute__((aligned(16))) double ps[16];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) ps[threadIdx.x >> 6] = s;
     lds_barrier();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < nw; ++w) t += ps[w];
-        tot = t;
-    }
-    lds_barrier();
-    return tot;
+    return slot_sum(ps, group_waves());
 }
 
 // Workgroup total of the partials in the order in which a workgroup of bd
@@ -118,9 +129,12 @@ __device__ inline VtShare vt_first(const double* part, int col, int stride, int 
     for (int k = 0; k < kVtMax; ++k) s.v[k] = p[min((int)(threadIdx.x + k * blockDim.x), nblk - 1)];
     return s;
 }
-__device__ inline double vt_total(VtShare s, const double* part, int col, int stride, int nblk, int bd) {
-    __shared__ double ps[16];
-    __shared__ double tot;
+// on: thread 0's reading of the column's flag, returned to every thread (one
+// decision for the workgroup where the launch may clear the flag).
+__device__ inline double vt_total(VtShare s, const double* part, int col, int stride, int nblk, int bd, int& on) {
+    __shared__ __attribute__((aligned(16))) double ps[16];
+    __shared__ int flag;
+    if (threadIdx.x == 0) flag = on;
     const double* p = part + (size_t)col * stride;
 #pragma unroll
     for (int k = 0; k < kVtMax; ++k) {
@@ -133,13 +147,8 @@ __device__ inline double vt_total(VtShare s, const double* part, int col, int st
         if ((threadIdx.x & 63) == 0) ps[vt >> 6] = t;
     }
     lds_barrier();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < (bd >> 6); ++w) t += ps[w];
-        tot = t;
-    }
-    lds_barrier();
-    return tot;
+    on = uniform(flag);
+    return slot_sum(ps, bd >> 6);
 }
 
 // Partial-sum buffers of the PCG inner products ([ncols][stride] each).
@@ -162,15 +171,11 @@ constexpr int kVecNodes = 4;
 
 // Workgroup sum with its own LDS slot; result valid in thread 0.
 __device__ inline double group_sum(double v) {
-    __shared__ double part[16];
-    const int nw = group_waves();
+    __shared__ __attribute__((aligned(16))) double part[16];
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
     lds_barrier();
-    double r = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < nw; ++w) r += part[w];
-    return r;
+    return threadIdx.x < 64 ? slot_sum(part, group_waves()) : 0.0;
 }
 
 // alpha of a column from its r^T z and p^T q (0 on breakdown); the lead
@@ -187,20 +192,26 @@ __device__ inline double pcg_alpha(double rz, double pq, ColState* st, int* act,
     return alpha;
 }
 
-// Convergence test at the start of a V-cycle: r^T r of the PCG update that
-// precedes it is summed from its partials (share: this thread's part of
-// them, loaded ahead by the caller); a column at its tolerance stops (every
-// workgroup reaches the same decision; workgroup 0 records it).
-__device__ inline bool column_done_share(double share, const PcgRed& red, int col, ColState* st, int* act,
+// Convergence test in the first kernel after the PCG step: r^T r is summed
+// from its partials (share: this thread's part of them, loaded ahead by the
+// caller); a column at its tolerance stops (every workgroup reaches the same
+// decision; the lead workgroup records it).  The launch does not read act: a
+// column that had stopped before still has the r^T r it stopped with, and one
+// that never ran (or broke down) costs a cycle on vectors nothing reads.
+__device__ inline bool column_done_share(double share, const PcgRed& red, int col, const ColState* st, int* act,
                                          bool lead) {
     const double rr = share_total(share);
     const ColState& c = st[col];
     const bool done = rr <= c.tol2 * c.bb;
-    if (lead && threadIdx.x == 0) {
-        st[col].rr = rr;
-        if (done) act[col] = 0;
-    }
+    if (lead && threadIdx.x == 0 && done) act[col] = 0;
     return done;
+}
+
+// Flag of a column through the scalar cache, for launches that do not write
+// the flags (a scalar load is not queued behind the vector loads).
+__device__ inline int column_on(const int* act, int col) {
+    if (!act) return 1;
+    return *reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(act + col));
 }
 
 // XCD-aware tile order.  The hardware hands consecutive workgroups to the
@@ -212,19 +223,24 @@ __device__ inline bool column_done_share(double share, const PcgRed& red, int co
 // then the column block), so left/right and most upper/lower halos come from
 // its own L2.  The last T - 8 P workgroups keep the plain order.  A
 // bijection of [0, T); returns the logical (x, y, z) of this workgroup.
-// A value the same in every lane of the wave, moved to a scalar register:
-// integer division runs on the vector unit, and its result would otherwise
-// keep the addresses formed from it in vector registers.
-__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// The grid's extents with the reciprocals of the two divisions (an integer
+// division costs ~40 instructions of a latency-bound kernel's start):
+// (n + 1/2) / d lies at least 1 / (2 d) from an integer and the product errs by
+// far less, so the truncation is exact.
+struct TileMap {
+    int X, XY, T;
+    double inv_x, inv_xy;
+    __host__ explicit TileMap(dim3 g)
+        : X(g.x), XY(g.x * g.y), T(g.x * g.y * g.z), inv_x(1.0 / g.x), inv_xy(1.0 / ((double)g.x * g.y)) {}
+};
+__device__ inline int fast_div(int n, double inv) { return uniform((int)(((double)n + 0.5) * inv)); }
 
-__device__ inline int3 xcd_tile() {
-    const int X = gridDim.x, Y = gridDim.y;
-    const int T = X * Y * gridDim.z;
-    const int h = blockIdx.x + X * (blockIdx.y + Y * blockIdx.z);
-    const int P = T >> 3;
+__device__ inline int3 xcd_tile(const TileMap& g) {
+    const int h = blockIdx.x + g.X * blockIdx.y + g.XY * blockIdx.z;
+    const int P = g.T >> 3;
     const int L = h < 8 * P ? (h & 7) * P + (h >> 3) : h;
-    const int z = uniform(L / (X * Y)), r = L - z * X * Y, y = uniform(r / X);
-    return make_int3(r - y * X, y, z);
+    const int z = fast_div(L, g.inv_xy), r = L - z * g.XY, y = fast_div(r, g.inv_x);
+    return make_int3(r - y * g.X, y, z);
 }
 
 }  // namespace hinv
@@ -253,7 +269,7 @@ __global__ __launch_bounds__(NT) void k_down2(Op opF_, Op opM_, const T* __restr
                                                int ldF, T* __restrict__ bM, T* __restrict__ xM, int ldM,
                                                T* __restrict__ bC, int ldC, int dirichlet,
                                                int* __restrict__ act, ChebCoef cc, PcgRed red,
-                                               ColState* __restrict__ st, int check, int nc, int cb) {
+                                               ColState* __restrict__ st, int check, int nc, int cb, TileMap tm) {
     constexpr int MW = 2 * kT + 5, FW = 2 * MW + 5, NM = MW * MW, NF = FW * FW;
     constexpr bool NE = kNorthEast<Op>;
     __shared__ T fb[NF], fx[NF], fr[NF];
@@ -262,7 +278,7 @@ __global__ __launch_bounds__(NT) void k_down2(Op opF_, Op opM_, const T* __restr
     __shared__ T mc[NE ? NM : 1], me[NM], mn[NM], mdv[NM], mg[NE ? NM : 1];
     const TileStencil<T> tsF{fc, fe, fn, fg, fdv}, tsM{mc, me, mn, mg, mdv};
     const int Nf = opF_.N, Nf1 = Nf + 1, Nm = Nf / 2, Nm1 = Nm + 1, Nc = Nm / 2, Nc1 = Nc + 1;
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     const int K0 = tb.x * kT, L0 = tb.y * kT;
     const int K1 = min(K0 + kT - 1, Nc), L1 = min(L0 + kT - 1, Nc);
     const int mox = 2 * K0 - 3, moy = 2 * L0 - 3;  // level-M coordinates of local (0, 0)
@@ -275,8 +291,7 @@ __global__ __launch_bounds__(NT) void k_down2(Op opF_, Op opM_, const T* __restr
     const void* staged = nullptr;
     const int c_end = min(nc, (tb.z + 1) * cb);
     for (int col = tb.z * cb; col < c_end; ++col) {
-        // one decision for the workgroup where the launch writes act (see k_down)
-        if (act && !(check ? __syncthreads_or(act[col]) : act[col])) continue;
+        if (!check && !column_on(act, col)) continue;
         const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
         const auto& opF = opF_.at(col);
         const auto& opM = opM_.at(col);
@@ -582,14 +597,14 @@ __device__ inline void chain_load(const ChainArgs<T, Op>& a, const int* ox, cons
 
 template <typename T, class Op, int kTF, int NL, int NT>
 __global__ __launch_bounds__(NT) void k_up_chain(ChainArgs<T, Op> a, int dirichlet, const int* __restrict__ act,
-                                                 ChebCoef cc, int nc, int cb) {
+                                                 ChebCoef cc, int nc, int cb, TileMap tm) {
     static_assert(kTF % 2 == 0 && NL >= 2 && NL <= kChainMax, "chain shape");
     constexpr int NA = chain_offset<kTF>(NL);  // nodes of all the chain's tiles
     constexpr bool NE = kNorthEast<Op>;
     __shared__ T sx[NA], sd[NA], sb[NA];
     __shared__ T tc[NE ? NA : 1], te[NA], tn[NA], tdv[NA], tg[NE ? NA : 1];
     const TileStencil<T> ts{tc, te, tn, tg, tdv};
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     const int i0 = tb.x * kTF, j0 = tb.y * kTF;
     const int i1 = min(i0 + kTF - 1, a.op[0].N), j1 = min(j0 + kTF - 1, a.op[0].N);
     int ox[NL], oy[NL];
@@ -603,8 +618,7 @@ __global__ __launch_bounds__(NT) void k_up_chain(ChainArgs<T, Op> a, int dirichl
     const void* staged = nullptr;
     const int c_end = min(nc, (tb.z + 1) * cb);
     for (int col = tb.z * cb; col < c_end; ++col) {
-        // no kernel of the launch writes act (the convergence test runs on the way down)
-        if (act && !act[col]) continue;
+        if (!column_on(act, col)) continue;
         const void* key = instance_key(a.op[0].at(col));
         lds_barrier();  // the previous column's LDS reads are done
         chain_load<T, Op, kTF, NL, NT, 0>(a, ox, oy, dirichlet, col, key != staged, sx, sb, ts);
@@ -683,7 +697,7 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
     constexpr bool PRIOR = KIND == kOpPrior;
     constexpr int PN = bottom_padded<TOP>(), NT = 1024, LV = kBottomLevels, MS = bottom_slots<TOP>(0);
     const int col = blockIdx.x;
-    if (act && !act[col]) return;
+    if (!check && !column_on(act, col)) return;
     // the convergence test's partials load together with the level data
     // below; the test itself follows the loads
     const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
@@ -996,16 +1010,16 @@ template <typename T, class Op, bool FIRST>
 __global__ __launch_bounds__(1024) void k_pcg_apply_few(Op op_, const T* __restrict__ z, const T* __restrict__ p_old,
                                                         T* __restrict__ p_new, T* __restrict__ q, T* __restrict__ x,
                                                         int ld, const int* __restrict__ act,
-                                                        ColState* __restrict__ st, PcgRed red) {
+                                                        ColState* __restrict__ st, PcgRed red, TileMap tm) {
     // node blocks in XCD-aware order: the rows above and below a block's
     // nodes belong to blocks on the same XCD
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     const int col = tb.y, bx = tb.x;
     const auto& op = op_.at(col);  // operator of the instance owning this column
-    if (!act[col]) return;
+    if (!column_on(act, col)) return;
     const int N = op.N, N1 = N + 1, n = N1 * N1;
     const bool need_rz = !FIRST || bx == 0;  // uniform in the workgroup
-    double srz = need_rz ? partial_first(red.rz, col, red.stride, red.nrz) : 0.0;
+    const double srz = need_rz ? partial_share(red.rz, col, red.stride, red.nrz) : 0.0;
     const double rz_old = FIRST ? 1.0 : st[col].rz;
     const T alpha = FIRST ? (T)0 : (T)st[col].alpha;
     const T* zc = z + (size_t)col * ld;
@@ -1067,7 +1081,6 @@ __global__ __launch_bounds__(1024) void k_pcg_apply_few(Op op_, const T* __restr
         __builtin_amdgcn_sched_barrier(0);  // keeps the window: no later load moves above
         load(e);
     }
-    if (need_rz) srz = partial_rest(srz, red.rz, col, red.stride, red.nrz);
 #pragma unroll
     for (int e = kVecNodes - W; e < kVecNodes; ++e) combine(e);
     // the iterate's loads overlap the sum of r^T z

@@ -645,6 +645,8 @@ March Hierarchy::march(int l, int nc, int kind) const {
     m.len = kind == kMarchDown ? len : 2 * len + 2;
     m.strips = kind == kMarchDown ? ceil_div(Nc + 1, kDownOwn) : ceil_div(L.N + 1, kind == kMarchUp ? kUpOwn : kApplyOwn);
     m.segs = ceil_div(kind == kMarchDown ? Nc + 1 : L.N + 1, m.len);
+    m.many = ninst_ > 1;
+    m.inv_strips = 1.0 / m.strips;
     return m;
 }
 
@@ -957,7 +959,7 @@ void Hierarchy::vcycle(int nc, int rcur, bool upd) {
 template <typename T, class Op, int NL, int NT>
 static void launch_chain1(dim3 g, hipStream_t s, const ChainArgs<T, Op>& ca, int dir, const int* act,
                           const ChebCoef& cc, int nc, int cb) {
-    hipLaunchKernelGGL((k_up_chain<T, Op, kTFChain, NL, NT>), g, dim3(NT), 0, s, ca, dir, act, cc, nc, cb);
+    hipLaunchKernelGGL((k_up_chain<T, Op, kTFChain, NL, NT>), g, dim3(NT), 0, s, ca, dir, act, cc, nc, cb, TileMap(g));
 }
 template <typename T, class Op, int NL>
 static void launch_chain_nt(int nt, dim3 g, hipStream_t s, const ChainArgs<T, Op>& ca, int dir, const int* act,
@@ -1023,7 +1025,7 @@ void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
                             timed_launch(ctx_, -1, 0.0, kern, dim3(tc, tc, gz), dim3(nt), s, opF, opM,
                                          (const TI*)wi.lb[l]->get(), wi.lt[l]->get(), L.n, wi.lb[l + 1]->get(),
                                          wi.lt[l + 1]->get(), C.n, wi.lb[l + 2]->get(), Cc.n, dir, act, cc, red,
-                                         st_.get(), l == 1 && upd ? 1 : 0, nc, shape_.cb);
+                                         st_.get(), l == 1 && upd ? 1 : 0, nc, shape_.cb, TileMap(dim3(tc, tc, gz)));
                         };
                         if (threads_for(tc * tc) == 512)
                             go(k_down2<TI, Op, kTPair, 512>, 512);
@@ -1052,7 +1054,7 @@ void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
             auto launch = [&](auto kern, int nb, const auto* bl, const auto* ql, auto* rn) {
                 const dim3 g(ceil_div(m.strips * m.segs, kMarchWaves), 1, ninst_ * ceil_div(m.cpi, nb));
                 timed_launch(ctx_, kcls, bytes_down, kern, g, dim3(64 * kMarchWaves), s, op, bl, ql, rn, xl, L.n, bcl,
-                             C.n, dir, act, cc, red, stp, chk, m);
+                             C.n, dir, act, cc, red, stp, chk, m, TileMap(g));
             };
             auto shaped = [&](auto step, const auto* bl, const auto* ql, auto* rn) {
                 using TB = std::remove_pointer_t<decltype(rn)>;
@@ -1179,7 +1181,7 @@ void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
             auto launch = [&](auto kern, int nb, const auto* bl, auto* xl, int rz) {
                 const dim3 g(ceil_div(m.strips * m.segs, kMarchWaves), 1, ninst_ * ceil_div(m.cpi, nb));
                 timed_launch(ctx_, kcls, bytes_up, kern, g, dim3(64 * kMarchWaves), s, op, bl, x2l, xl, L.n, xcl, C.n,
-                             dir, actc, cc, rz, red, m);
+                             dir, actc, cc, rz, red, m, TileMap(g));
             };
             auto shaped = [&](const auto* bl, auto* xl, int rz) {
                 using TB = std::remove_cv_t<std::remove_pointer_t<decltype(bl)>>;
@@ -1193,8 +1195,9 @@ void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
             };
             auto few = [&](auto kern, int tf) {
                 const int t = ceil_div(L.N + 1, tf);
-                timed_launch(ctx_, kcls, bytes_up, kern, dim3(ceil_div(t, kUpTiles), t, nc), dim3(64 * kMarchWaves), s,
-                             op, (const T*)rv, x2l, wt.z.get(), L.n, xcl, C.n, dir, actc, cc, red);
+                const dim3 g(ceil_div(t, kUpTiles), t, nc);
+                timed_launch(ctx_, kcls, bytes_up, kern, g, dim3(64 * kMarchWaves), s, op, (const T*)rv, x2l,
+                             wt.z.get(), L.n, xcl, C.n, dir, actc, cc, red, TileMap(g));
             };
             if (l > 0)
                 shaped((const TI*)wi.lb[l]->get(), wi.lx[l]->get(), 0);
@@ -1237,14 +1240,14 @@ void Hierarchy::pcg_iteration(int nc, int cur, int first) {
             if (linear) {
                 timed_launch(ctx_, kcls, bytes_apply, first ? k_pcg_apply_few<T, Op, true> : k_pcg_apply_few<T, Op, false>,
                              dim3(nvec, nc), dim3(vec_threads(red.per)), s, op, zc, pold, pnew, w.q.get(), w.x.get(),
-                             ld, actc, stc, red);
+                             ld, actc, stc, red, TileMap(dim3(nvec, nc)));
                 return;
             }
             const March m = march(0, nc, kMarchApply);
             auto launch = [&](auto kern, int nb) {
                 const dim3 g(ceil_div(m.strips * m.segs, kMarchWaves), 1, ninst_ * ceil_div(m.cpi, nb));
                 timed_launch(ctx_, kcls, bytes_apply, kern, g, dim3(64 * kMarchWaves), s, op, zc, pold, pnew,
-                             w.q.get(), w.x.get(), ld, actc, stc, red, m);
+                             w.q.get(), w.x.get(), ld, actc, stc, red, m, TileMap(g));
             };
             if (first)
                 launch(k_pcg_apply<T, Op, true, kBatchChunk, 1>, 1);

@@ -36,7 +36,9 @@ constexpr int kBatchRows[] = {13, 29, 5};
 // 2 len + 5 rows, one of len fine rows of the up step len + 4.
 struct March {
     int strips, segs, len;
-    int cpi;  // columns per instance
+    int cpi;   // columns per instance
+    int many;  // several instances
+    double inv_strips;
 };
 
 // Value of the lane's east / west neighbour (0 beyond the wave).
@@ -606,7 +608,7 @@ __device__ inline void stage_rows(const Op& op, KARow<T>* tab) {
 // Columns of column block z: blocks of C columns within an instance.
 template <int C>
 __device__ inline int block_columns(const March& m, int z, int& col0) {
-    const int bpi = (m.cpi + C - 1) / C, inst = uniform(z / bpi), k = z - inst * bpi;
+    const int bpi = (m.cpi + C - 1) / C, inst = m.many ? uniform(z / bpi) : 0, k = z - inst * bpi;
     col0 = inst * m.cpi + k * C;
     return min(C, m.cpi - k * C);
 }
@@ -625,45 +627,44 @@ __global__ __launch_bounds__(64 * kMarchWaves) void k_down(Op op_, const TB* __r
                                                            TB* __restrict__ rn, T* __restrict__ x, int ld,
                                                            T* __restrict__ bc, int ldc, int dirichlet,
                                                            int* __restrict__ act, ChebCoef cc, PcgRed red,
-                                                           ColState* __restrict__ st, int check, March m) {
+                                                           ColState* __restrict__ st, int check, March m,
+                                                           TileMap tm) {
     __shared__ KARow<T> tab[kNorthEast<Op> ? 10 : 1];
     __shared__ double part[C][kMarchWaves];
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     int col0;
     const int cnt = block_columns<C>(m, tb.z, col0);
     const auto& op = op_.at(col0);
     // waves past the last segment take part in the barriers alone
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), item = tb.x * kMarchWaves + wave;
-    const int it = min(item, m.strips * m.segs - 1), seg = uniform(it / m.strips), strip = it - seg * m.strips;
+    const int it = min(item, m.strips * m.segs - 1), seg = fast_div(it, m.inv_strips), strip = it - seg * m.strips;
     DownMarch<T, std::decay_t<decltype(op)>, TB, CH, C, UPD> w(op, b, q, ld, strip, seg, m.len);
     w.bind(col0, cnt);
-    // few columns: the first rows are loaded ahead of the flags that say
-    // whether the column still runs (one memory latency less)
+    // the partials and the first rows are in flight together (few columns:
+    // also with the flags that say whether the column still runs)
     constexpr bool kAhead = CH == kLatencyChunk;
+    double share[C]{}, rz[C]{};
+    VtShare vt[C];
+    int live[C]{};
+    const int bd = kAhead ? vec_threads(red.per) : (int)blockDim.x;
     if constexpr (kAhead) w.load(w.A, 0);
-    // where the lead workgroup may clear act[col] while other workgroups of
-    // this launch read it (a column converged, or broke down): one decision
-    // for the workgroup
     bool any = false;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        w.cb.on[c] = c < cnt && (!act || (check || UPD ? __syncthreads_or(act[col0 + c]) : act[col0 + c]));
+        // UPD: the lead workgroup clears act[col] on a breakdown while others
+        // read it, so thread 0 reads it for the workgroup (vt_total)
+        w.cb.on[c] = c < cnt && (UPD || check || column_on(act, col0 + c));
+        if constexpr (UPD && !kAhead) w.cb.on[c] = w.cb.on[c] && __syncthreads_or(act[col0 + c]);
         any = any || w.cb.on[c];
+        if (!w.cb.on[c]) continue;
+        if (check) share[c] = partial_share(red.rr, col0 + c, red.stride, red.nrr);
+        if constexpr (UPD) {
+            live[c] = act[col0 + c];
+            vt[c] = vt_first(red.pq, col0 + c, red.stride, red.npq, bd);
+            rz[c] = st[col0 + c].rz_new;
+        }
     }
     if (!any) return;
-    // the partials and the first rows are in flight together
-    double share[C]{}, rz[C]{};
-    VtShare vt[C];
-    const int bd = CH == kLatencyChunk ? vec_threads(red.per) : (int)blockDim.x;
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-        if (w.cb.on[c]) {
-            if (check) share[c] = partial_share(red.rr, col0 + c, red.stride, red.nrr);
-            if constexpr (UPD) {
-                vt[c] = vt_first(red.pq, col0 + c, red.stride, red.npq, bd);
-                rz[c] = st[col0 + c].rz_new;
-            }
-        }
     if constexpr (!kAhead) w.load(w.A, 0);
     stage_rows(op, tab);
     TB alpha[C]{};
@@ -673,9 +674,13 @@ __global__ __launch_bounds__(64 * kMarchWaves) void k_down(Op op_, const TB* __r
         for (int c = 0; c < C; ++c)
             if (w.cb.on[c]) {
                 if constexpr (UPD) {
-                    const double pq = vt_total(vt[c], red.pq, col0 + c, red.stride, red.npq, bd);
-                    alpha[c] = (TB)pcg_alpha(rz[c], pq, st + col0 + c, act + col0 + c, tb.x == 0);
-                    if (!(pq > 0.0)) w.cb.on[c] = false;
+                    const double pq = vt_total(vt[c], red.pq, col0 + c, red.stride, red.npq, bd, live[c]);
+                    if (live[c]) {
+                        alpha[c] = (TB)pcg_alpha(rz[c], pq, st + col0 + c, act + col0 + c, tb.x == 0);
+                        if (!(pq > 0.0)) w.cb.on[c] = false;
+                    } else {
+                        w.cb.on[c] = false;
+                    }
                 } else if (column_done_share(share[c], red, col0 + c, st, act, tb.x == 0)) {
                     w.cb.on[c] = false;
                 }
@@ -719,15 +724,15 @@ template <typename T, class Op, typename TB, typename TX, int CH, int C>
 __global__ __launch_bounds__(64 * kMarchWaves) void k_up(Op op_, const TB* __restrict__ b, const T* __restrict__ x2,
                                                          TX* __restrict__ x, int ld, const T* __restrict__ xc, int ldc,
                                                          int dirichlet, const int* __restrict__ act, ChebCoef cc,
-                                                         int rz, PcgRed red, March m) {
+                                                         int rz, PcgRed red, March m, TileMap tm) {
     __shared__ KARow<T> tab[kNorthEast<Op> ? 10 : 1];
     __shared__ double part[C][kMarchWaves];
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     int col0;
     const int cnt = block_columns<C>(m, tb.z, col0);
     const auto& op = op_.at(col0);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), item = tb.x * kMarchWaves + wave;
-    const int it = min(item, m.strips * m.segs - 1), seg = uniform(it / m.strips), strip = it - seg * m.strips;
+    const int it = min(item, m.strips * m.segs - 1), seg = fast_div(it, m.inv_strips), strip = it - seg * m.strips;
     UpMarch<T, std::decay_t<decltype(op)>, TB, TX, CH, C> w(op, b, x2, xc, ld, ldc, strip * kUpOwn, seg * m.len, m.len);
     constexpr bool kAhead = CH == kLatencyChunk;  // see k_down
     bool any = false;
@@ -735,7 +740,7 @@ __global__ __launch_bounds__(64 * kMarchWaves) void k_up(Op op_, const TB* __res
     if constexpr (kAhead) w.load(w.A, 0);
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        w.cb.on[c] = c < cnt && (!act || act[col0 + c]);  // no kernel of the launch writes act
+        w.cb.on[c] = c < cnt && column_on(act, col0 + c);
         any = any || w.cb.on[c];
     }
     if (!any) return;
@@ -790,7 +795,7 @@ template <typename T, class Op, typename TB, typename TX, int TF>
 __global__ __launch_bounds__(64 * kMarchWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_up_few(Op op_, const TB* __restrict__ b, const T* __restrict__ x2,
                                                              TX* __restrict__ x, int ld, const T* __restrict__ xc,
                                                              int ldc, int dirichlet, const int* __restrict__ act,
-                                                             ChebCoef cc, PcgRed red) {
+                                                             ChebCoef cc, PcgRed red, TileMap tm) {
     constexpr int OW = kUpTiles * TF, NT = 64 * kMarchWaves;
     constexpr int R1 = TF / kMarchWaves / 2 * 2, R0 = TF - (kMarchWaves - 1) * R1;  // rows of wave 0, of the others
     static_assert(OW + 4 <= 64 && R0 + 4 <= kUpFewChunk && TF % 2 == 0, "tile shape");
@@ -798,7 +803,7 @@ __global__ __launch_bounds__(64 * kMarchWaves) __attribute__((amdgpu_waves_per_e
     __shared__ T xs[TF][OW];
     __shared__ TB bs[TF][OW];
     __shared__ double part[kUpTiles][NT / 64];
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     const int col = tb.z;
     const auto& op = op_.at(col);
     const int N = op.N, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -808,7 +813,7 @@ __global__ __launch_bounds__(64 * kMarchWaves) __attribute__((amdgpu_waves_per_e
     w.bind(col, 1);
     w.cb.on[0] = true;
     w.load(w.A, 0);
-    if (act && !act[col]) return;  // no kernel of the launch writes act
+    if (!column_on(act, col)) return;
     if constexpr (kNorthEast<Op>) {
         stage_rows(op, tab);
         lds_barrier();
@@ -863,20 +868,20 @@ __global__ __launch_bounds__(64 * kMarchWaves) void k_pcg_apply(Op op_, const T*
                                                                 const T* __restrict__ p_old, T* __restrict__ p_new,
                                                                 T* __restrict__ q, T* __restrict__ x, int ld,
                                                                 const int* __restrict__ act, ColState* __restrict__ st,
-                                                                PcgRed red, March m) {
+                                                                PcgRed red, March m, TileMap tm) {
     __shared__ KARow<T> tab[kNorthEast<Op> ? 10 : 1];
     __shared__ double part[C][kMarchWaves];
-    const int3 tb = xcd_tile();
+    const int3 tb = xcd_tile(tm);
     int col0;
     const int cnt = block_columns<C>(m, tb.z, col0);
     const auto& op = op_.at(col0);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), item = tb.x * kMarchWaves + wave;
-    const int it = min(item, m.strips * m.segs - 1), seg = uniform(it / m.strips), strip = it - seg * m.strips;
+    const int it = min(item, m.strips * m.segs - 1), seg = fast_div(it, m.inv_strips), strip = it - seg * m.strips;
     ApplyMarch<T, std::decay_t<decltype(op)>, CH, C, FIRST> w(op, strip, seg, m.len);
     bool any = false;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-        w.cb.on[c] = c < cnt && act[col0 + c];  // no kernel of the launch writes act
+        w.cb.on[c] = c < cnt && column_on(act, col0 + c);
         any = any || w.cb.on[c];
     }
     if (!any) return;
