@@ -33,7 +33,7 @@ constexpr int kTFChain = 16;   // k_up_chain: level-0 tile side
 constexpr int kChainLen = 4;   // k_up_chain: levels a launch (measured: 4 > 2 at N = 1024)
 constexpr int kFewCols = 8;    // calls below this many columns are latency bound
 constexpr int kBottomN = 32;   // levels with N_l <= kBottomN run in the bottom kernel
-constexpr int kBottomLevels = 4;  // at most (N_l = 64, 32, 16, 8 when kBottomN = 64)
+constexpr int kBottomLevels = 3;  // at most (N_l = 32, 16, 8)
 
 // Chebyshev degree-2 coefficients passed to the smoothing kernels.
 struct ChebCoef {
@@ -629,14 +629,16 @@ __global__ __launch_bounds__(NT) void k_up_chain(ChainArgs<T, Op> a, int dirichl
 }
 
 // -------------------------------------------------------------- bottom ---
-// All levels with N_l <= kBottomN (up to four: 64, 32, 16, 8) for one column in
+// All levels with N_l <= kBottomN (at most three: 32, 16, 8) for one column in
 // one workgroup of 1024 threads.  The bottom computes in FP32 whatever the
 // solve's precision: it is the coarse correction of a preconditioner, so its
 // rounding changes the preconditioner slightly but no result (the PCG and the
-// refinement test residuals of the solve's own precision), and FP32 halves the
-// LDS a level takes, so that the level-64 sweeps run here instead of in two
-// more launches per V-cycle.  b and x are global level-Lb vectors of the
-// solve's precision TV.
+// refinement test residuals of the solve's own precision).  b and x are global
+// level-Lb vectors of the solve's precision TV.
+// One workgroup does ~18 short phases between barriers, so what counts is the
+// instructions and LDS reads of a phase: a thread owns the same nodes of each
+// level throughout and keeps their operator rows, right-hand sides and
+// positions in registers; LDS holds the two vectors that neighbours read.
 struct BottomArgs {
     int nlev;                           // levels handled here (the last is the coarsest)
     int N[kBottomLevels];
@@ -656,29 +658,6 @@ struct BottomArgs {
     const KARow<float>* karows[kBottomLevels];
 };
 
-// Bottom levels in LDS with a ring of zeros around each level (padded width
-// P_l = N_l + 3): the stencil applies without boundary branches (an absent
-// neighbour has a zero coupling and a zero value), and Dirichlet rows are
-// masked by their zero inverse diagonal.  Sizes for a top level of at most
-// TOP (a power of two, at least 8).
-template <int TOP>
-constexpr int bottom_padded() {
-    int s = 0;
-    for (int n = TOP; n >= 8; n /= 2) s += (n + 3) * (n + 3);
-    return s;
-}
-template <int TOP>
-constexpr int bottom_nodes() {
-    int s = 0;
-    for (int n = TOP; n >= 8; n /= 2) s += (n + 1) * (n + 1);
-    return s;
-}
-// node slots of a thread on level l (a level of N has (N + 1)^2 nodes)
-template <int TOP>
-constexpr int bottom_slots(int l) {
-    return l < kBottomLevels && (TOP >> l) >= 8 ? (((TOP >> l) + 1) * ((TOP >> l) + 1) + 1023) / 1024 : 0;
-}
-
 // q / d for 0 <= q < 2^22 and d >= 1 by a float reciprocal: (q + 1/2) / d lies
 // at least 1 / (2 d) from an integer and the float product errs by less than
 // 2^-23 (q / d) < 1 / (2 d), so the truncation is exact (integer division is a
@@ -687,75 +666,80 @@ __device__ inline int small_div(int q, float inv_d) { return (int)(((float)q + 0
 
 // x_top = V-cycle(b_top) for every column (blockIdx.x = column).  When rv is
 // given (the bottom is the whole hierarchy), sum_k rv_k x_k is written as the
-// single partial of r^T z.  Thread t holds the nodes q = t + 1024 s of each
-// level (padded position and (i, j) per slot).
-template <typename TV, int KIND, int TOP>
+// single partial of r^T z.  Each level lies in LDS with a ring of zeros (padded
+// width N_l + 3), so the stencil applies without boundary branches; Dirichlet
+// rows are masked by their zero inverse diagonal.  Node slots of a thread:
+// nodes t and t + 1024 of level 0, node t of levels 1 and 2.
+template <typename TV, int KIND>
 __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restrict__ bg, TV* __restrict__ xg,
                                                  int ld, int* __restrict__ act, ChebCoef cc,
                                                  const TV* __restrict__ rv, PcgRed red,
                                                  ColState* __restrict__ st, int check) {
     constexpr bool PRIOR = KIND == kOpPrior;
-    constexpr int PN = bottom_padded<TOP>(), NT = 1024, LV = kBottomLevels, MS = bottom_slots<TOP>(0);
+    constexpr int NT = 1024, LV = kBottomLevels, NS = LV + 1;
+    constexpr int PN = (kBottomN + 3) * (kBottomN + 3) + (kBottomN / 2 + 3) * (kBottomN / 2 + 3) + 11 * 11;
+    static_assert(kBottomN == 32 && LV == 3 && (kBottomN + 1) * (kBottomN + 1) <= 2 * NT, "node slots");
     const int col = blockIdx.x;
     if (!check && !column_on(act, col)) return;
     // the convergence test's partials load together with the level data
     // below; the test itself follows the loads
     const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
-    __shared__ float sb[PN], sx[PN], sw[PN];  // right-hand side, iterate, work vector
-    __shared__ float te[PRIOR ? 1 : PN], tn[PRIOR ? 1 : PN], tdv[PRIOR ? 1 : PN];  // -wE, -wN, 1/diag
-    __shared__ KARow<float> rows[PRIOR ? LV * 9 : 1];
-    const int inst = a.cpi ? col / a.cpi : 0;
+    __shared__ float sx[PN], sw[PN], sbc[81], tmp[NT];
+    const int inst = a.cpi ? uniform(col / a.cpi) : 0;
     const int nlev = a.nlev, L = nlev - 1;  // L: the coarsest level, solved with its dense inverse
-    int Nl[LV], Pl[LV], po[LV], uo[LV + 1];
-    float inv_n1[LV];
+    int Nl[LV], Pl[LV], po[LV];
     {
-        int p = 0, u = 0;
+        int p = 0;
 #pragma unroll
         for (int l = 0; l < LV; ++l) {
-            const int n = l < nlev ? a.N[l] : 0;
-            Nl[l] = n;
-            Pl[l] = n + 3;
+            Nl[l] = l < nlev ? a.N[l] : 0;
+            Pl[l] = Nl[l] + 3;
             po[l] = p;
-            uo[l] = u;
-            inv_n1[l] = 1.0f / (float)(n + 1);
-            if (l < nlev) {
-                p += (n + 3) * (n + 3);
-                u += (n + 1) * (n + 1);
-            }
+            p += Pl[l] * Pl[l];
         }
-        uo[LV] = u;
     }
-    const int n0 = uo[1];
-    // ---- loads: b, the state coefficients (unpadded concatenation of the
-    // levels), this thread's part of the dense coarse inverse
-    constexpr int EB = (bottom_nodes<TOP>() + NT - 1) / NT, S = 12, kCU = 8;
-    float vb[EB], vE[EB], vN[EB], vD[EB];
-    int vp[EB], vl[EB], vij[EB];
+    // ---- this thread's nodes: padded position (-1 past the level), (i, j),
+    // operator row, right-hand side; every global load issued here
+    struct Row {
+        float c, e, w, n, s, ne, sw, dv;
+    };
+    auto level = [](int s) { return s < 2 ? 0 : s - 1; };
+    int sp[NS], si[NS], sj[NS];
+    Row rw[NS];
+    float bl[NS];
 #pragma unroll
-    for (int e = 0; e < EB; ++e) {
-        const int t = threadIdx.x + NT * e;
-        const int l = (t >= uo[1]) + (t >= uo[2]) + (t >= uo[3]);
-        const bool in = t < uo[LV];
-        const int q = t - (l == 0 ? 0 : (l == 1 ? uo[1] : (l == 2 ? uo[2] : uo[3])));
-        const int N1 = (l == 0 ? Nl[0] : (l == 1 ? Nl[1] : (l == 2 ? Nl[2] : Nl[3]))) + 1;
-        const int j = small_div(q, l == 0 ? inv_n1[0] : (l == 1 ? inv_n1[1] : (l == 2 ? inv_n1[2] : inv_n1[3])));
-        const int P = N1 + 2, i = q - j * N1;
-        vl[e] = l;
-        vij[e] = i | (j << 16);
-        vp[e] = in ? (l == 0 ? po[0] : (l == 1 ? po[1] : (l == 2 ? po[2] : po[3]))) + (j + 1) * P + i + 1 : -1;
-        vb[e] = t < n0 ? (float)bg[(size_t)col * ld + t] : 0.0f;
-        vE[e] = vN[e] = vD[e] = 0.0f;
-        if constexpr (!PRIOR) {
-            const long long cs = l == 0 ? a.cs[0] : (l == 1 ? a.cs[1] : (l == 2 ? a.cs[2] : a.cs[3]));
-            const long long at = (a.cpi ? inst * cs : 0) + q;
-            const float* pE = l == 0 ? a.wE[0] : (l == 1 ? a.wE[1] : (l == 2 ? a.wE[2] : a.wE[3]));
-            const float* pN = l == 0 ? a.wN[0] : (l == 1 ? a.wN[1] : (l == 2 ? a.wN[2] : a.wN[3]));
-            const float* pD = l == 0 ? a.dinv[0] : (l == 1 ? a.dinv[1] : (l == 2 ? a.dinv[2] : a.dinv[3]));
-            vE[e] = in ? pE[at] : 0.0f;
-            vN[e] = in ? pN[at] : 0.0f;
-            vD[e] = in ? pD[at] : 0.0f;
+    for (int s = 0; s < NS; ++s) {
+        const int l = level(s), q = threadIdx.x + (s == 1 ? NT : 0), N = Nl[l], N1 = N + 1;
+        const bool in = l < nlev && q < N1 * N1;
+        const int jq = small_div(q, 1.0f / (float)N1);
+        const int i = in ? q - jq * N1 : 0, j = in ? jq : 0;
+        si[s] = i;
+        sj[s] = j;
+        sp[s] = in ? po[l] + (j + 1) * Pl[l] + i + 1 : -1;
+        bl[s] = 0.0f;
+        rw[s] = Row{};
+        if (!in) continue;
+        if constexpr (PRIOR) {
+            const int c = ka_class(i, j, N);
+            const KARow<float> r = a.cpi ? a.karows[l][9 * inst + c] : a.ka[l][c];
+            rw[s] = Row{r.c, r.e, r.w, r.n, r.s, r.ne, r.sw, r.dinv};
+        } else {
+            const long long at = a.cpi ? inst * a.cs[l] : 0;
+            const float* pE = a.wE[l] + at;
+            const float* pN = a.wN[l] + at;
+            const float vE = pE[q], vW = pE[i > 0 ? q - 1 : q], vN = pN[q], vS = pN[j > 0 ? q - N1 : q];
+            Row& r = rw[s];
+            r.e = -vE;
+            r.w = i > 0 ? -vW : 0.0f;
+            r.n = -vN;
+            r.s = j > 0 ? -vS : 0.0f;
+            r.c = -(r.e + r.w + r.n + r.s);
+            r.dv = (a.dinv[l] + at)[q];
         }
+        if (l == 0) bl[s] = (float)bg[(size_t)col * ld + q];
     }
+    // the thread's part of the dense coarse inverse
+    constexpr int S = 12, kCU = 8;
     const float* ci = a.cinv + (a.cpi ? inst * a.cinv_stride : 0);
     const int cr = threadIdx.x / S, cpart = threadIdx.x % S;
     float cv[kCU];
@@ -764,162 +748,103 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
         const int c = cpart + u * S;
         cv[u] = (cr < a.nc && c < a.nc) ? ci[cr * a.nc + c] : 0.0f;
     }
-    if (check && column_done_share(rr_share, red, col, st, act, true)) return;
-    // ---- per-thread slots: padded position (-1 past the level) and (i, j)
-    int sp[LV][MS], sij[LV][MS];
-#pragma unroll
-    for (int l = 0; l < LV; ++l)
-#pragma unroll
-        for (int s = 0; s < MS; ++s) {
-            if (s >= bottom_slots<TOP>(l)) break;
-            const int q = threadIdx.x + NT * s;
-            const int N1 = Nl[l] + 1;
-            const bool in = l < nlev && q < N1 * N1;
-            const int jq = small_div(q, inv_n1[l]);
-            const int i = in ? q - jq * N1 : 0, j = in ? jq : 0;
-            sp[l][s] = in ? po[l] + (j + 1) * Pl[l] + i + 1 : -1;
-            sij[l][s] = i | (j << 16);
-        }
-    // ---- LDS: zeros everywhere (the rings stay zero), then the interiors
-    if constexpr (PRIOR)
-        for (int t = threadIdx.x; t < nlev * 9; t += NT)
-            rows[t] = a.cpi ? a.karows[t / 9][9 * inst + t % 9] : a.ka[t / 9][t % 9];
-    for (int q = threadIdx.x; q < PN; q += NT) {
-        sb[q] = sx[q] = sw[q] = 0.0f;
-        if constexpr (!PRIOR) te[q] = tn[q] = tdv[q] = 0.0f;
+    // ---- LDS: zeros everywhere (the rings stay zero)
+    for (int q = threadIdx.x; q < PN; q += NT) sx[q] = sw[q] = 0.0f;
+    if (check) {
+        if (column_done_share(rr_share, red, col, st, act, true)) return;  // its barrier follows the zeros
+    } else {
+        lds_barrier();
     }
-    lds_barrier();
     const float inv_theta = (float)cc.inv_theta, theta = (float)cc.theta, cA = (float)cc.cA, cB = (float)cc.cB,
                 c1 = (float)cc.c1;
+    // d0 of the first smoothing step (or the right-hand side of the dense solve)
 #pragma unroll
-    for (int e = 0; e < EB; ++e) {
-        const int p = vp[e];
-        if (p < 0) continue;
-        if constexpr (!PRIOR) {
-            te[p] = -vE[e];
-            tn[p] = -vN[e];
-            tdv[p] = vD[e];
-        } else {
-            const int l = vl[e];
-            const int N = l == 0 ? Nl[0] : (l == 1 ? Nl[1] : (l == 2 ? Nl[2] : Nl[3]));
-            vD[e] = rows[9 * l + ka_class(vij[e] & 0xffff, vij[e] >> 16, N)].dinv;
+    for (int s = 0; s < 2; ++s)
+        if (sp[s] >= 0) {
+            sw[sp[s]] = rw[s].dv * bl[s] * inv_theta;
+            if (L == 0 && s == 0) sbc[threadIdx.x] = bl[s];
         }
-        if (threadIdx.x + NT * e < n0) {
-            sb[p] = vb[e];
-            sw[p] = vD[e] * vb[e] * inv_theta;  // d0 of the first smoothing step
-        }
-    }
     lds_barrier();
-    // (A x)_p at padded position p of level l (node ij), with the diagonal and
-    // 1/diagonal of the row
-    auto apply = [&](int l, int p, int ij, const float* x, float& diag, float& dv) -> float {
-        const int P = Pl[l];
-        if constexpr (!PRIOR) {
-            const float e0 = te[p], e1 = te[p - 1], m0 = tn[p], m1 = tn[p - P];
-            diag = -(e0 + e1 + m0 + m1);
-            dv = tdv[p];
-            return diag * x[p] + e0 * x[p + 1] + e1 * x[p - 1] + m0 * x[p + P] + m1 * x[p - P];
-        } else {
-            const KARow<float>& r = rows[9 * l + ka_class(ij & 0xffff, ij >> 16, Nl[l])];
-            diag = r.c;
-            dv = r.dinv;
+    // (A x)_p at padded position p of level l
+    auto apply = [&](const Row& r, int P, int p, const float* x) -> float {
+        if constexpr (PRIOR)
             return r.c * x[p] + r.e * x[p + 1] + r.w * x[p - 1] + r.n * x[p + P] + r.s * x[p - P] +
                    r.ne * x[p + P + 1] + r.sw * x[p - P - 1];
-        }
-    };
-    auto inv_diag = [&](int l, int p, int ij) -> float {
-        if constexpr (!PRIOR)
-            return tdv[p];
-        else
-            return rows[9 * l + ka_class(ij & 0xffff, ij >> 16, Nl[l])].dinv;
+        else  // the diagonal's product is the rounded one of the sum
+            return __builtin_fmaf(r.e, x[p + 1], r.c * x[p]) + r.w * x[p - 1] + r.n * x[p + P] + r.s * x[p - P];
     };
     // ---- down
 #pragma unroll
     for (int l = 0; l < LV - 1; ++l) {
         if (l >= L) break;
         const int P = Pl[l];
+        const int s0 = l == 0 ? 0 : l + 1, s1 = l + 2;
         // x2 = cA d0 + cB D^-1 (b - A d0), d0 in sw
 #pragma unroll
-        for (int s = 0; s < bottom_slots<TOP>(l); ++s) {
-            const int p = sp[l][s];
+        for (int s = s0; s < s1; ++s) {
+            const int p = sp[s];
             if (p < 0) continue;
-            float dg, dv;
-            const float ad = apply(l, p, sij[l][s], sw, dg, dv);
-            sx[p] = cA * sw[p] + cB * dv * (sb[p] - ad);
+            const float ad = apply(rw[s], P, p, sw);
+            sx[p] = cA * sw[p] + cB * rw[s].dv * (bl[s] - ad);
         }
         lds_barrier();
         // residual b - A x2 on the free nodes, into sw
 #pragma unroll
-        for (int s = 0; s < bottom_slots<TOP>(l); ++s) {
-            const int p = sp[l][s];
+        for (int s = s0; s < s1; ++s) {
+            const int p = sp[s];
             if (p < 0) continue;
-            float dg, dv;
-            const float v = sb[p] - apply(l, p, sij[l][s], sx, dg, dv);
-            sw[p] = dv != 0.0f ? v : 0.0f;
+            const float v = bl[s] - apply(rw[s], P, p, sx);
+            sw[p] = rw[s].dv != 0.0f ? v : 0.0f;
         }
         lds_barrier();
         // restriction P^T to level l + 1, and its first smoothing correction d0
-#pragma unroll
-        for (int s = 0; s < bottom_slots<TOP>(l + 1); ++s) {
-            const int pc = sp[l + 1][s];
-            if (pc < 0) continue;
-            const int I = sij[l + 1][s] & 0xffff, J = sij[l + 1][s] >> 16;
-            const int f = po[l] + (2 * J + 1) * P + 2 * I + 1;
-            const float dvc = inv_diag(l + 1, pc, sij[l + 1][s]);
-            float v = 0.0f;
-            if (dvc != 0.0f)
-                v = sw[f] + 0.5f * (sw[f - 1] + sw[f + 1] + sw[f - P] + sw[f + P] + sw[f + P + 1] + sw[f - P - 1]);
-            sb[pc] = v;
-            sw[pc] = dvc * v * inv_theta;
+        {
+            const int sc = l + 2, pc = sp[sc];
+            if (pc >= 0) {
+                const int f = po[l] + (2 * sj[sc] + 1) * P + 2 * si[sc] + 1;
+                const float dvc = rw[sc].dv;
+                float v = 0.0f;
+                if (dvc != 0.0f)
+                    v = sw[f] + 0.5f * (sw[f - 1] + sw[f + 1] + sw[f - P] + sw[f + P] + sw[f + P + 1] + sw[f - P - 1]);
+                bl[sc] = v;
+                sw[pc] = dvc * v * inv_theta;
+                if (l + 1 == L) sbc[threadIdx.x] = v;
+            }
         }
         lds_barrier();
     }
     // ---- coarsest: dense inverse, S threads per row (entries prefetched in cv)
-    {
-        const int N1 = (L == 0 ? Nl[0] : (L == 1 ? Nl[1] : (L == 2 ? Nl[2] : Nl[3]))) + 1;
-        const int P = N1 + 2, o = L == 0 ? po[0] : (L == 1 ? po[1] : (L == 2 ? po[2] : po[3]));
-        // the work vector is free here (the dense solve reads b only; the ring
-        // entries it overwrites meet zero couplings only): 12 * 81 <= PN
-        float* tmp = sw;
-        const float inv_c = 1.0f / (float)N1;
-        if (cr < a.nc) {
-            float s = 0.0f;
-            // entry c = cpart + u S at (c mod N1, c / N1), stepped without dividing
-            int jc = small_div(cpart, inv_c), ic = cpart - jc * N1;
+    if (cr < a.nc) {
+        float s = 0.0f;
 #pragma unroll
-            for (int u = 0; u < kCU; ++u) {
-                const int c = cpart + u * S;
-                if (c < a.nc) s += cv[u] * sb[o + (jc + 1) * P + ic + 1];
-                ic += S;
-                while (ic >= N1) {
-                    ic -= N1;
-                    ++jc;
-                }
-            }
-            tmp[threadIdx.x] = s;
+        for (int u = 0; u < kCU; ++u) {
+            const int c = cpart + u * S;
+            if (c < a.nc) s += cv[u] * sbc[c];
         }
-        lds_barrier();
-        for (int r = threadIdx.x; r < a.nc; r += NT) {
-            float s = 0.0f;
-            for (int part = 0; part < S; ++part) s += tmp[r * S + part];
-            const int jr = small_div(r, inv_c);
-            sx[o + (jr + 1) * P + r - jr * N1 + 1] = s;
-        }
-        lds_barrier();
+        tmp[threadIdx.x] = s;
     }
+    lds_barrier();
+    {
+        const int sl = L == 0 ? 0 : L + 1, p = L == 0 ? sp[0] : (L == 1 ? sp[2] : sp[3]);
+        if ((int)threadIdx.x < a.nc) {
+            float s = 0.0f;
+            for (int part = 0; part < S; ++part) s += tmp[threadIdx.x * S + part];
+            sx[p] = s;
+        }
+    }
+    lds_barrier();
     // ---- up
 #pragma unroll
     for (int l = LV - 2; l >= 0; --l) {
         if (l >= L) continue;
-        const int Pc = Pl[l + 1];
+        const int P = Pl[l], Pc = Pl[l + 1];
+        const int s0 = l == 0 ? 0 : l + 1, s1 = l + 2;
         // x += P x_coarse on the free nodes
 #pragma unroll
-        for (int s = 0; s < bottom_slots<TOP>(l); ++s) {
-            const int p = sp[l][s];
-            if (p < 0) continue;
-            const int ij = sij[l][s], i = ij & 0xffff, j = ij >> 16;
-            if (inv_diag(l, p, ij) == 0.0f) continue;
-            const int I = i >> 1, J = j >> 1;
+        for (int s = s0; s < s1; ++s) {
+            const int p = sp[s];
+            if (p < 0 || rw[s].dv == 0.0f) continue;
+            const int i = si[s], j = sj[s], I = i >> 1, J = j >> 1;
             const int ca0 = po[l + 1] + (J + 1) * Pc + I + 1;
             const int ca1 = po[l + 1] + (J + 1 + (j & 1)) * Pc + I + 1 + (i & 1);
             sx[p] += ((i | j) & 1) ? 0.5f * (sx[ca0] + sx[ca1]) : sx[ca0];
@@ -927,34 +852,31 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
         lds_barrier();
         // d0 = D^-1 (b - A x) / theta
 #pragma unroll
-        for (int s = 0; s < bottom_slots<TOP>(l); ++s) {
-            const int p = sp[l][s];
+        for (int s = s0; s < s1; ++s) {
+            const int p = sp[s];
             if (p < 0) continue;
-            float dg, dv;
-            const float ax = apply(l, p, sij[l][s], sx, dg, dv);
-            sw[p] = dv * (sb[p] - ax) * inv_theta;
+            const float ax = apply(rw[s], P, p, sx);
+            sw[p] = rw[s].dv * (bl[s] - ax) * inv_theta;
         }
         lds_barrier();
         // x += (1 + c1) d0 + cB D^-1 r1 with r1 = theta D d0 - A d0
 #pragma unroll
-        for (int s = 0; s < bottom_slots<TOP>(l); ++s) {
-            const int p = sp[l][s];
+        for (int s = s0; s < s1; ++s) {
+            const int p = sp[s];
             if (p < 0) continue;
-            float dg, dv;
-            const float ad = apply(l, p, sij[l][s], sw, dg, dv);
+            const float ad = apply(rw[s], P, p, sw);
             const float dk = sw[p];
-            const float r1 = theta * dk * dg - ad;
-            sx[p] += (1.0f + c1) * dk + cB * dv * r1;
+            const float r1 = theta * dk * rw[s].c - ad;
+            sx[p] += (1.0f + c1) * dk + cB * rw[s].dv * r1;
         }
-        lds_barrier();
+        if (l > 0) lds_barrier();  // level 0 is read back by its own threads
     }
     double dot = 0.0;
 #pragma unroll
-    for (int s = 0; s < bottom_slots<TOP>(0); ++s) {
+    for (int s = 0; s < 2; ++s) {
         const int q = threadIdx.x + NT * s;
-        const int p = sp[0][s];
-        if (p >= 0) {
-            const TV v = (TV)sx[p];
+        if (sp[s] >= 0) {
+            const TV v = (TV)sx[sp[s]];
             xg[(size_t)col * ld + q] = v;
             if (rv) dot += (double)v * (double)rv[(size_t)col * ld + q];
         }

@@ -1123,15 +1123,15 @@ void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
             // the whole hierarchy: r in, z out, and the r^T z partial
             const T* r = rv;
             if (kind_ == kOpState)
-                launch(k_bottom<T, kOpState, kBottomN>, r, wt.z.get(), r, st);
+                launch(k_bottom<T, kOpState>, r, wt.z.get(), r, st);
             else
-                launch(k_bottom<T, kOpPrior, kBottomN>, r, wt.z.get(), r, st);
+                launch(k_bottom<T, kOpPrior>, r, wt.z.get(), r, st);
         } else {
             const TI* none = nullptr;
             if (kind_ == kOpState)
-                launch(k_bottom<TI, kOpState, kBottomN>, (const TI*)wi.lb[Lb]->get(), wi.lx[Lb]->get(), none, si);
+                launch(k_bottom<TI, kOpState>, (const TI*)wi.lb[Lb]->get(), wi.lx[Lb]->get(), none, si);
             else
-                launch(k_bottom<TI, kOpPrior, kBottomN>, (const TI*)wi.lb[Lb]->get(), wi.lx[Lb]->get(), none, si);
+                launch(k_bottom<TI, kOpPrior>, (const TI*)wi.lb[Lb]->get(), wi.lx[Lb]->get(), none, si);
         }
         HINV_LAUNCH_CHECK();
     }
