@@ -178,6 +178,43 @@ __device__ inline double group_sum(double v) {
     return threadIdx.x < 64 ? slot_sum(part, group_waves()) : 0.0;
 }
 
+// The same with the first kShareLoads partials of each of V virtual threads a
+// thread loaded ahead (more of them follow in a loop).
+template <int V>
+struct VtRest {
+    double v[V][kShareLoads];
+};
+template <int V>
+__device__ inline VtRest<V> vt_rest(const double* part, int col, int stride, int nblk, int bd) {
+    const double* p = part + (size_t)col * stride;
+    VtRest<V> s;
+#pragma unroll
+    for (int h = 0; h < V; ++h)
+#pragma unroll
+        for (int k = 0; k < kShareLoads; ++k)
+            s.v[h][k] = p[min((int)(threadIdx.x + h * blockDim.x) + k * bd, nblk - 1)];
+    return s;
+}
+template <int V>
+__device__ inline double vt_rest_total(const VtRest<V>& s, const double* part, int col, int stride, int nblk, int bd) {
+    __shared__ __attribute__((aligned(16))) double ps[16];
+    const double* p = part + (size_t)col * stride;
+#pragma unroll
+    for (int h = 0; h < V; ++h) {
+        if (h * (int)blockDim.x >= bd) break;  // uniform
+        const int vt = threadIdx.x + h * blockDim.x;
+        double t = vt < nblk ? s.v[h][0] : 0.0;
+#pragma unroll
+        for (int k = 1; k < kShareLoads; ++k)
+            if (vt + k * bd < nblk) t += s.v[h][k];
+        for (int b = vt + kShareLoads * bd; b < nblk; b += bd) t += p[b];
+        t = wave_sum(t);
+        if ((threadIdx.x & 63) == 0) ps[vt >> 6] = t;
+    }
+    lds_barrier();
+    return slot_sum(ps, bd >> 6);
+}
+
 // alpha of a column from its r^T z and p^T q (0 on breakdown); the lead
 // workgroup records the iteration and stops a column that broke down.
 __device__ inline double pcg_alpha(double rz, double pq, ColState* st, int* act, bool lead) {
@@ -925,14 +962,20 @@ struct ApplyForm<OpKARef<T>> {
 template <class OpT>
 constexpr int apply_window() {
     constexpr size_t b = sizeof(typename OpT::Row) + 2 * sizeof(typename OpT::Nb);  // loaded bytes per node
-    return b <= 96 ? kVecNodes : (b <= 128 ? 3 : 2);
+    return b <= 64 ? 4 : (b <= 112 ? 3 : 2);
 }
 
-template <typename T, class Op, bool FIRST>
-__global__ __launch_bounds__(1024) void k_pcg_apply_few(Op op_, const T* __restrict__ z, const T* __restrict__ p_old,
-                                                        T* __restrict__ p_new, T* __restrict__ q, T* __restrict__ x,
-                                                        int ld, const int* __restrict__ act,
-                                                        ColState* __restrict__ st, PcgRed red, TileMap tm) {
+// A workgroup of NT threads does the work of bd = vec_threads(per) of them:
+// thread t stands for the virtual threads t and t + NT (bd = 2 NT; or one, bd =
+// NT), and the sums are taken in the order of the bd.  Half of the waves with
+// twice the nodes each: at N = 1024 a column's ~500 workgroups fit the
+// registers of the 256 compute units in one round instead of two.
+template <typename T, class Op, bool FIRST, int NT>
+__global__ __launch_bounds__(NT, 4) void k_pcg_apply_few(Op op_, const T* __restrict__ z, const T* __restrict__ p_old,
+                                                      T* __restrict__ p_new, T* __restrict__ q, T* __restrict__ x,
+                                                      int ld, const int* __restrict__ act, ColState* __restrict__ st,
+                                                      PcgRed red, TileMap tm) {
+    constexpr int kHalves = 2, SL = kHalves * kVecNodes;  // node slots of a thread
     // node blocks in XCD-aware order: the rows above and below a block's
     // nodes belong to blocks on the same XCD
     const int3 tb = xcd_tile(tm);
@@ -940,100 +983,104 @@ __global__ __launch_bounds__(1024) void k_pcg_apply_few(Op op_, const T* __restr
     const auto& op = op_.at(col);  // operator of the instance owning this column
     if (!column_on(act, col)) return;
     const int N = op.N, N1 = N + 1, n = N1 * N1;
+    const int bd = vec_threads(red.per), halves = bd / NT;
     const bool need_rz = !FIRST || bx == 0;  // uniform in the workgroup
-    const double srz = need_rz ? partial_share(red.rz, col, red.stride, red.nrz) : 0.0;
+    VtRest<kHalves> srz;
+    if (need_rz) srz = vt_rest<kHalves>(red.rz, col, red.stride, red.nrz, bd);
     const double rz_old = FIRST ? 1.0 : st[col].rz;
     const T alpha = FIRST ? (T)0 : (T)st[col].alpha;
     const T* zc = z + (size_t)col * ld;
     const T* pc = p_old + (size_t)col * ld;
+    const T* xc = x + (size_t)col * ld;
     const int k0 = bx * red.chunk, k1 = min(n, k0 + red.chunk);
     const double inv_n1 = 1.0 / N1;
     using Form = ApplyForm<std::decay_t<decltype(op)>>;
     using OpT = typename Form::type;
     __shared__ KARow<T> krows[Form::kTable ? 9 : 1];
+    __shared__ __attribute__((aligned(16))) double slots[16];
     OpT sop;
     if constexpr (Form::kTable)
         sop = OpT{N, krows};
     else
         sop = op;
-    typename OpT::Row rw[kVecNodes];
-    typename OpT::Nb vz[kVecNodes], vp[kVecNodes];
-    T zk[kVecNodes], pk[kVecNodes], az[kVecNodes], ap[kVecNodes];
-    auto node = [&](int e, int& i, int& j) {
-        const int k = k0 + e * (int)blockDim.x + (int)threadIdx.x;
+    constexpr int W = apply_window<OpT>();
+    typename OpT::Row rw[W];
+    typename OpT::Nb vz[W], vp[W];
+    T xk[W];
+    // slot s: node of virtual thread t + NT (s mod halves), pass s / halves
+    auto node = [&](int s, int& i, int& j) {
+        const int e = halves == 2 ? s >> 1 : s, h = halves == 2 ? s & 1 : 0;
+        const int k = k0 + e * bd + h * NT + (int)threadIdx.x;
         j = (int)(((double)k + 0.5) * inv_n1);
         i = k - j * N1;
         return k;
     };
-    auto load = [&](int e) {
+    auto used = [&](int s) {  // uniform: some thread's node lies in the chunk
+        const int e = halves == 2 ? s >> 1 : s, h = halves == 2 ? s & 1 : 0;
+        return e < kVecNodes && k0 + e * bd + h * NT < k1;
+    };
+    auto load = [&](int s) {
+        if (!used(s)) return;
         int i, j;
-        const int k = node(e, i, j);
-        if (k < k1) {
-            rw[e] = sop.row(i, j, k);
-            vz[e] = sop.gather(i, j, k, zc);
-            if constexpr (!FIRST) vp[e] = sop.gather(i, j, k, pc);
+        const int k = min(node(s, i, j), k1 - 1);
+        j = (int)(((double)k + 0.5) * inv_n1);
+        i = k - j * N1;
+        rw[s % W] = sop.row(i, j, k);
+        vz[s % W] = sop.gather(i, j, k, zc);
+        if constexpr (!FIRST) {
+            vp[s % W] = sop.gather(i, j, k, pc);
+            xk[s % W] = xc[k];
         }
     };
-    auto combine = [&](int e) {
-        int i, j;
-        const int k = node(e, i, j);
-        zk[e] = pk[e] = az[e] = ap[e] = 0;
-        if (k < k1) {
-            const bool fr = sop.is_free(i, j);
-            zk[e] = vz[e].c;
-            if (fr) az[e] = sop.combine(i, j, rw[e], vz[e]);
-            if constexpr (!FIRST) {
-                pk[e] = vp[e].c;
-                if (fr) ap[e] = sop.combine(i, j, rw[e], vp[e]);
-            }
-        }
-    };
-    constexpr int W = apply_window<OpT>();
 #pragma unroll
-    for (int e = 0; e < W; ++e) load(e);
+    for (int s = 0; s < W; ++s) load(s);
     if constexpr (Form::kTable) {
         // rows staged after the node loads are issued (waiting for them then
         // waits for nothing those loads would not)
         if (threadIdx.x < 9) krows[threadIdx.x] = ka_row(op, threadIdx.x);
-        lds_barrier();
     }
-#pragma unroll
-    for (int e = W; e < kVecNodes; ++e) {
-        combine(e - W);
-        __builtin_amdgcn_sched_barrier(0);  // keeps the window: no later load moves above
-        load(e);
-    }
-#pragma unroll
-    for (int e = kVecNodes - W; e < kVecNodes; ++e) combine(e);
-    // the iterate's loads overlap the sum of r^T z
-    T xk[kVecNodes];
-    if constexpr (!FIRST)
-#pragma unroll
-        for (int e = 0; e < kVecNodes; ++e) {
-            const int k = k0 + e * (int)blockDim.x + (int)threadIdx.x;
-            xk[e] = k < k1 ? x[(size_t)col * ld + k] : (T)0;
-        }
     T beta = 0;
     if (need_rz) {
-        const double rz = share_total(srz);
+        const double rz = vt_rest_total<kHalves>(srz, red.rz, col, red.stride, red.nrz, bd);
         if (!FIRST) beta = (T)(rz / rz_old);
         if (bx == 0 && threadIdx.x == 0) st[col].rz_new = rz;
+    } else if constexpr (Form::kTable) {
+        lds_barrier();
     }
-    double dot = 0.0;
+    double dot[kHalves] = {0.0, 0.0};
 #pragma unroll
-    for (int e = 0; e < kVecNodes; ++e) {
-        const int k = k0 + e * (int)blockDim.x + (int)threadIdx.x;
+    for (int s = 0; s < SL; ++s) {
+        if (!used(s)) continue;
+        int i, j;
+        const int k = node(s, i, j);
         if (k < k1) {
-            const T pn = FIRST ? zk[e] : zk[e] + beta * pk[e];
-            const T v = FIRST ? az[e] : az[e] + beta * ap[e];
-            p_new[(size_t)col * ld + k] = pn;
-            q[(size_t)col * ld + k] = v;
-            if constexpr (!FIRST) x[(size_t)col * ld + k] = xk[e] + alpha * pk[e];
-            dot += (double)pn * (double)v;
+            const bool fr = sop.is_free(i, j);
+            const T zk = vz[s % W].c;
+            T az = fr ? sop.combine(i, j, rw[s % W], vz[s % W]) : (T)0;
+            T pn = zk, v = az;
+            const size_t o = (size_t)col * ld + k;
+            if constexpr (!FIRST) {
+                const T pk = vp[s % W].c;
+                const T ap = fr ? sop.combine(i, j, rw[s % W], vp[s % W]) : (T)0;
+                pn = zk + beta * pk;
+                v = az + beta * ap;
+                x[o] = xk[s % W] + alpha * pk;
+            }
+            p_new[o] = pn;
+            q[o] = v;
+            dot[halves == 2 ? s & 1 : 0] += (double)pn * (double)v;
         }
+        __builtin_amdgcn_sched_barrier(0);  // keeps the window: no later load moves above
+        if (s + W < SL) load(s + W);
     }
-    const double sm = group_sum(dot);
-    if (threadIdx.x == 0) red.pq[(size_t)col * red.stride + bx] = sm;
+#pragma unroll
+    for (int h = 0; h < kHalves; ++h) {
+        if (h >= halves) break;
+        const double sm = wave_sum(dot[h]);
+        if ((threadIdx.x & 63) == 0) slots[(h * NT + (int)threadIdx.x) >> 6] = sm;
+    }
+    lds_barrier();
+    if (threadIdx.x == 0) red.pq[(size_t)col * red.stride + bx] = slot_sum(slots, bd >> 6);
 }
 
 // alpha = (r^T z) / (p^T q), r <- r - alpha q into r_new; partials of r^T r.

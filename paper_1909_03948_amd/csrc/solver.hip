@@ -1238,9 +1238,18 @@ void Hierarchy::pcg_iteration(int nc, int cur, int first) {
             ColState* stc = st_.get();
             const int kcls = kclass_for(kKPcgApply, nc);
             if (linear) {
-                timed_launch(ctx_, kcls, bytes_apply, first ? k_pcg_apply_few<T, Op, true> : k_pcg_apply_few<T, Op, false>,
-                             dim3(nvec, nc), dim3(vec_threads(red.per)), s, op, zc, pold, pnew, w.q.get(), w.x.get(),
-                             ld, actc, stc, red, TileMap(dim3(nvec, nc)));
+                const dim3 g(nvec, nc);
+                auto few = [&](auto kern, int nt) {
+                    timed_launch(ctx_, kcls, bytes_apply, kern, g, dim3(nt), s, op, zc, pold, pnew, w.q.get(),
+                                 w.x.get(), ld, actc, stc, red, TileMap(g));
+                };
+                const int bd = vec_threads(red.per);
+                if (bd == 768)
+                    few(first ? k_pcg_apply_few<T, Op, true, 384> : k_pcg_apply_few<T, Op, false, 384>, 384);
+                else if (bd == 1024)
+                    few(first ? k_pcg_apply_few<T, Op, true, 512> : k_pcg_apply_few<T, Op, false, 512>, 512);
+                else
+                    few(first ? k_pcg_apply_few<T, Op, true, 256> : k_pcg_apply_few<T, Op, false, 256>, 256);
                 return;
             }
             const March m = march(0, nc, kMarchApply);
