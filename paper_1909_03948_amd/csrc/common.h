@@ -179,7 +179,7 @@ struct DenseWork {
     DBuf<double> part;
     DBuf<double> shift;  // per-matrix diagonal shifts
     DBuf<double> tmp;    // block products of the blocked triangular inverse
-    DBuf<double> rot;    // recorded Jacobi rotations (large s)
+    DBuf<double> rot;    // Jacobi block rotations and norms (large s)
     DBuf<int> flag;
 };
 

@@ -32,8 +32,8 @@ void tri_inverse_upper(Ctx* ctx, DenseWork& w, int nb, int s, const double* R, i
                        int ldi, size_t si);
 
 // Symmetric eigendecompositions T_b = S_b diag(lam_b) S_b^T by parallel
-// cyclic Jacobi; T_b is symmetrized and overwritten; eigenpairs sorted by
-// decreasing eigenvalue.
+// Jacobi of the symmetric part of T_b, which may be overwritten; eigenpairs
+// sorted by decreasing eigenvalue (synchronizes the stream for large s).
 void sym_eig(Ctx* ctx, DenseWork& w, int nb, int s, double* T, int ldt, size_t st, double* S, int lds, size_t ss,
              double* lam, size_t sl);
 
@@ -41,7 +41,7 @@ void sym_eig(Ctx* ctx, DenseWork& w, int nb, int s, double* T, int ldt, size_t s
 void scaled_trace(Ctx* ctx, int nb, int s, const double* A, int lda, size_t sa, double factor, double* out);
 
 // C (m x n) = alpha op(A) op(B) + beta C, op(X) = X^T when its flag is set
-// (kk inner dimension; small matrices, one thread per entry of C).
+// (kk inner dimension; small matrices).
 void small_gemm(Ctx* ctx, bool ta, bool tb, int m, int n, int kk, double alpha, const double* A, int lda,
                 const double* B, int ldb, double beta, double* C, int ldc);
 
