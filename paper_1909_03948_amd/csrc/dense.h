@@ -17,8 +17,8 @@ void gram(Ctx* ctx, DenseWork& w, int n, int s1, int s2, const double* X, int ld
 void gemm_tall(Ctx* ctx, int n, int s, int t, double alpha, const double* X, int ldx,
                const double* B, int ldb, double beta, double* C, int ldc);
 
-// The small s x s routines below treat nb independent matrices at once, one
-// workgroup each: matrix b starts at base + b * stride (strides in elements).
+// The small s x s routines below treat nb independent matrices at once: matrix
+// b starts at base + b * stride (strides in elements).
 
 // Upper Cholesky factors in place: A_b (s x s, lda) = R^T R, R upper, lower
 // part zeroed, after adding shift[b] (device array, or null for none) to the

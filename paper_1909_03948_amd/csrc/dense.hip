@@ -1,6 +1,6 @@
 // Dense kernels: matrix-core tall-skinny products and s x s factorizations
-// (s = k + oversampling <= 512), one workgroup per matrix in LDS while it
-// fits, blocked or in global memory beyond.
+// (s = k + oversampling <= 512), blocked over the compute units; the
+// eigenproblems of small s in one workgroup's LDS.
 //
 // Matrix-core operand layouts (wave64), checked on the device:
 //   f64 16x16x4:   A (16 x 4): lane l holds A[l % 16][l / 16]
@@ -413,124 +413,242 @@ __global__ __launch_bounds__(512) void k_gemm_tall(int n, int s, int t, double a
     }
 }
 
-// The one-workgroup factorizations below run on matrices addressed through a
-// pointer and a leading dimension, either in place in global memory or, for
-// small s, on copies staged in LDS (the _lds kernels: dynamic LDS, ld = s).
-// A launch factors nb independent matrices, one workgroup each: workgroup b
-// takes the matrices at base + b * stride (strides in elements).
+// The factorizations below treat nb matrices of a launch at once: matrix b's
+// at base + b * stride (strides in elements); A(a, c) = A[a + c lda].
 
-// Upper Cholesky in place, one workgroup; A(a, c) = A[a + c lda].  Step j
-// reads the pivot A(j, j), final since the previous step, in every thread,
-// updates the trailing upper triangle by the outer product of row j scaled by
-// 1 / sqrt(pivot), and scales row j - 1, which that update does not read:
-// one barrier per step.
-// With U > 1, U items of the trailing update per thread are loaded before
-// they are stored; item indices advance by the workgroup size without
-// dividing.  (Measured: U = 8 gains nothing in global memory, where the
-// single-CU bandwidth bounds the update.)
-template <int U>
-__device__ __forceinline__ void cholesky_body(int s, double* A, int lda, double shift, int* __restrict__ flag) {
-    for (int i = threadIdx.x; i < s; i += blockDim.x) A[i + (size_t)i * lda] += shift;
-    __syncthreads();
-    int bad = 0;
-    double rprev = 1.0;  // sqrt of the previous pivot
-    for (int j = 0; j <= s; ++j) {
-        if (j > 0)  // row j - 1 by its pivot root
-            for (int c = j - 1 + threadIdx.x; c < s; c += blockDim.x)
-                A[j - 1 + (size_t)c * lda] = c == j - 1 ? rprev : A[j - 1 + (size_t)c * lda] / rprev;
-        if (j == s) break;
-        const double piv = A[j + (size_t)j * lda];
-        if (!(piv > 0.0)) {
-            bad = 1;
-            break;
+// 1 / sqrt(x) for normal x > 0, to about one ulp: the hardware's estimate, a
+// third-order and a second-order step.
+__device__ __forceinline__ double rsqrt_full(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    double e = __builtin_fma(-x * y, y, 1.0);
+    y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+    e = __builtin_fma(-x * y, y, 1.0);
+    return __builtin_fma(y * e, 0.5, y);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {  // lane: uniform
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+constexpr int kFacB = 32;           // block of the Cholesky factor and its inverse
+constexpr int kFacLd = kFacB + 1;   // LDS column stride: a lane a column, no bank conflicts
+
+// Block row j of the upper Cholesky factor R, left-looking: workgroup x forms
+// tile (j, j + x) of A - R(0..j-1, j)^T R(0..j-1, j + x) and, again in each
+// workgroup, the diagonal tile, on the matrix cores (one quadrant of both a
+// wave); then wave 0 eliminates with a column of [diagonal | tile] in the
+// registers of each lane, pivot row entries broadcast by lane reads: the
+// diagonal's factor and the tile's triangular solve in one pass without LDS
+// or barriers.  shift: per-matrix diagonal shifts (device) or null.
+// All workgroups of a launch read the diagonal tile of A, so its factor goes
+// to dbuf (two slots by the parity of j) and is copied into A by the next
+// launch, whose workgroups do not read it; the last one's goes to A itself.
+// Bound by that chain, ~10-16 us a block row; one workgroup updating the whole
+// trailing matrix for each of the s pivots took 0.09 / 0.30 / 3.9 / 19 ms at
+// s = 64 / 139 / 300 / 512 (whole factor with the flag's read-back), this
+// 0.04 / 0.08 / 0.20 / 0.50 ms.
+__global__ __launch_bounds__(256) void k_cholesky_row(int s, int j, double* __restrict__ A, int lda, size_t sa,
+                                                      const double* __restrict__ shift, double* __restrict__ dbuf,
+                                                      int* __restrict__ flag) {
+    __shared__ double sm[2 * kFacB * kFacLd];
+    A += blockIdx.y * sa;
+    dbuf += (size_t)blockIdx.y * 2 * kFacB * kFacB;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lm = lane & 15, lk = lane >> 4;
+    const int m0 = (wave & 1) * 16, n0 = (wave >> 1) * 16;
+    const int oj = j * kFacB, ok = (j + blockIdx.x) * kFacB;
+    const bool tile = blockIdx.x > 0, last = oj + kFacB >= s;
+    const double sh = shift ? shift[blockIdx.y] : 0.0;
+    if (j > 0 && !tile) {  // the previous diagonal factor, lower part zero
+        const double* d = dbuf + ((j - 1) & 1) * kFacB * kFacB;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int id = threadIdx.x + 256 * u, r = id & 31, c = id >> 5;
+            A[oj - kFacB + r + (size_t)(oj - kFacB + c) * lda] = d[id];
         }
-        const double rj = sqrt(piv), irj = 1.0 / rj;
-        const int m = s - j - 1, bd = blockDim.x;
-        if (m > 0) {
-            const int da = bd % m, dc = bd / m;
-            int a = threadIdx.x % m, c = threadIdx.x / m;  // trailing block offsets, a fastest
-            for (int id = threadIdx.x; id < m * m; id += U * bd) {
-                double x[U], ya[U], yc[U];
-                int as[U], cs[U];
+    }
+    auto col = [&](int c) { return A + (size_t)min(c, s - 1) * lda; };  // columns past the end are not stored
+    const double *ca = col(oj + m0 + lm), *cd = col(oj + n0 + lm), *ct = col(ok + n0 + lm);
+    double av[2][8], dv[2][8], tv[2][8];
+    auto load = [&](int k0, int b) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    as[u] = a;
-                    cs[u] = c;
-                    x[u] = ya[u] = yc[u] = 0.0;
-                    if (id + u * bd < m * m && a <= c) {
-                        ya[u] = A[j + (size_t)(j + 1 + a) * lda];
-                        yc[u] = A[j + (size_t)(j + 1 + c) * lda];
-                        x[u] = A[j + 1 + a + (size_t)(j + 1 + c) * lda];
-                    }
-                    a += da;
-                    c += dc;
-                    if (a >= m) {
-                        a -= m;
-                        ++c;
-                    }
-                }
+        for (int u = 0; u < 8; ++u) {
+            const int k = k0 + 4 * u + lk;
+            av[b][u] = ca[k];
+            dv[b][u] = cd[k];
+            tv[b][u] = ct[k];  // workgroup 0 does its tile twice
+        }
+    };
+    d4_t ad = {0.0, 0.0, 0.0, 0.0}, at = ad, od, ot;
+    if (j > 0) load(0, 0);
+    // this lane's entries of A itself
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (id + u * bd < m * m && as[u] <= cs[u])
-                        A[j + 1 + as[u] + (size_t)(j + 1 + cs[u]) * lda] = x[u] - (ya[u] * irj) * (yc[u] * irj);
+    for (int v = 0; v < 4; ++v) {
+        const int r = min(oj + m0 + 4 * v + lk, s - 1);
+        od[v] = cd[r];
+        ot[v] = ct[r];
+    }
+    for (int k0 = 0; k0 < oj; k0 += 2 * kFacB) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int k = k0 + b * kFacB;
+            if (k >= oj) break;
+            if (k + kFacB < oj) load(k + kFacB, 1 - b);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                ad = __builtin_amdgcn_mfma_f64_16x16x4f64(av[b][u], dv[b][u], ad, 0, 0, 0);
+                at = __builtin_amdgcn_mfma_f64_16x16x4f64(av[b][u], tv[b][u], at, 0, 0, 0);
             }
         }
-        rprev = rj;
-        __syncthreads();
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int r = m0 + 4 * v + lk, c = n0 + lm;
+        const bool in = oj + r < s && oj + c < s;  // beyond: the identity
+        const double dd = od[v] + (r == c ? sh : 0.0) - ad[v];
+        sm[r + c * kFacLd] = in ? dd : (r == c ? 1.0 : 0.0);
+        sm[r + (kFacB + c) * kFacLd] = tile ? ot[v] - at[v] : 0.0;
     }
     __syncthreads();
-    for (int id = threadIdx.x; id < s * s; id += blockDim.x) {
-        const int a = id % s, c = id / s;
-        if (a > c) A[a + (size_t)c * lda] = 0.0;
-    }
-    if (threadIdx.x == 0) *flag = bad;
-}
-
-// shift: per-matrix diagonal shifts (device) or null
-__global__ __launch_bounds__(1024) void k_cholesky(int s, double* __restrict__ A, int lda, size_t sa, const double* __restrict__ shift,
-                           int* __restrict__ flag) {
-    cholesky_body<1>(s, A + blockIdx.x * sa, lda, shift ? shift[blockIdx.x] : 0.0, flag + blockIdx.x);
-}
-
-__global__ __launch_bounds__(1024) void k_cholesky_lds(int s, double* __restrict__ A, int lda, size_t sa, const double* __restrict__ shift,
-                               int* __restrict__ flag) {
-    extern __shared__ double sm[];
-    A += blockIdx.x * sa;
-    for (int id = threadIdx.x; id < s * s; id += blockDim.x) sm[id] = A[id % s + (size_t)(id / s) * lda];
-    __syncthreads();
-    cholesky_body<1>(s, sm, s, shift ? shift[blockIdx.x] : 0.0, flag + blockIdx.x);
-    __syncthreads();
-    for (int id = threadIdx.x; id < s * s; id += blockDim.x) A[id % s + (size_t)(id / s) * lda] = sm[id];
-}
-
-// Rinv = R^-1 (upper), one workgroup: thread j solves R x = e_j for column j
-// by back substitution (no barriers; the longest chain is s^2 / 2 products,
-// which LDS keeps short for small s).
-__device__ __forceinline__ void tri_inverse_body(int s, const double* R, int ldr, double* Ri, int ldi) {
-    for (int j = threadIdx.x; j < s; j += blockDim.x) {
-        double* x = Ri + (size_t)j * ldi;
-        for (int i = j + 1; i < s; ++i) x[i] = 0.0;
-        for (int i = j; i >= 0; --i) {
-            double acc = i == j ? 1.0 : 0.0;
-#pragma unroll 4
-            for (int k = i + 1; k <= j; ++k) acc -= R[i + (size_t)k * ldr] * x[k];
-            x[i] = acc / R[i + (size_t)i * ldr];
+    if (wave == 0) {
+        double x[kFacB];
+#pragma unroll
+        for (int r = 0; r < kFacB; ++r) x[r] = sm[r + lane * kFacLd];
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < kFacB; ++i) {
+            const double piv = lane_value(x[i], i);
+            bad |= !(piv > 0.0);
+            x[i] *= rsqrt_full(piv);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = i + 1; r < kFacB; ++r) {
+                x[r] = __builtin_fma(-lane_value(x[i], r), x[i], x[r]);
+                if ((r & 7) == 7) __builtin_amdgcn_sched_barrier(0);  // few broadcast entries live at once
+            }
         }
+#pragma unroll
+        for (int r = 0; r < kFacB; ++r) sm[r + lane * kFacLd] = lane >= kFacB || r <= lane ? x[r] : 0.0;
+        if (!tile && lane == 0) flag[blockIdx.y] = (j > 0 ? flag[blockIdx.y] : 0) | (bad ? 1 : 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int id = threadIdx.x + 256 * u, r = id & 31, c = id >> 5;
+        if (!tile) {
+            if (!last)
+                dbuf[(j & 1) * kFacB * kFacB + id] = sm[r + c * kFacLd];
+            else if (oj + r < s && oj + c < s)
+                A[oj + r + (size_t)(oj + c) * lda] = sm[r + c * kFacLd];
+        } else if (ok + c < s) {
+            A[oj + r + (size_t)(ok + c) * lda] = sm[r + (kFacB + c) * kFacLd];
+        }
+        if (tile && ok + r < s) A[ok + r + (size_t)(oj + c) * lda] = 0.0;  // the tile below the diagonal
     }
 }
 
-__global__ void k_tri_inverse_lds(int s, const double* __restrict__ R, int ldr, size_t sr,
-                                  double* __restrict__ Ri, int ldi, size_t si) {
-    extern __shared__ double sm[];
-    R += blockIdx.x * sr;
-    Ri += blockIdx.x * si;
-    double* lr = sm;
-    double* li = sm + (size_t)s * s;
-    for (int id = threadIdx.x; id < s * s; id += blockDim.x) lr[id] = R[id % s + (size_t)(id / s) * ldr];
+// Diagonal blocks of Ri = R^-1: one wave a block, a column of R and one of the
+// inverse in the registers of each lane, back substitution with lane reads.
+__global__ __launch_bounds__(64) void k_tri_inverse_diag(int s, const double* __restrict__ R, int ldr, size_t sr,
+                                                         double* __restrict__ Ri, int ldi, size_t si) {
+    __shared__ double sm[kFacB * kFacLd];
+    R += blockIdx.y * sr;
+    Ri += blockIdx.y * si;
+    const int lane = threadIdx.x, o = blockIdx.x * kFacB;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int id = lane + 64 * u, r = id & 31, c = id >> 5;
+        double v = r == c ? 1.0 : 0.0;  // beyond the matrix: the identity
+        if (o + c < s && r <= c) v = R[o + r + (size_t)(o + c) * ldr];
+        sm[r + c * kFacLd] = v;
+    }
     __syncthreads();
-    tri_inverse_body(s, lr, s, li, s);
+    const int c = lane & 31;
+    double x[kFacB], y[kFacB];
+#pragma unroll
+    for (int r = 0; r < kFacB; ++r) {
+        x[r] = sm[r + c * kFacLd];
+        y[r] = r == c ? 1.0 : 0.0;
+    }
+    const double inv = 1.0 / sm[c + c * kFacLd];
+#pragma unroll
+    for (int i = kFacB - 1; i >= 0; --i) {
+        y[i] *= lane_value(inv, i);
+#pragma unroll
+        for (int r = 0; r < i; ++r) y[r] = __builtin_fma(-lane_value(x[r], i), y[i], y[r]);
+    }
     __syncthreads();
-    for (int id = threadIdx.x; id < s * s; id += blockDim.x) Ri[id % s + (size_t)(id / s) * ldi] = li[id];
+#pragma unroll
+    for (int r = 0; r < kFacB; ++r) sm[r + c * kFacLd] = y[r];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const int id = lane + 64 * u, r = id & 31, cc = id >> 5;
+        if (o + r < s && o + cc < s) Ri[o + r + (size_t)(o + cc) * ldi] = sm[r + cc * kFacLd];
+    }
+}
+
+// Block column J of Ri off the diagonal, given its diagonal blocks: upwards,
+// Ri(I, J) = -Ri(I, I) sum_{K = I+1..J} R(I, K) Ri(K, J), the column kept in
+// dynamic LDS (ld: its rows, padded), one quadrant of the tile a wave.  The
+// columns are independent, so one launch does them all: 0.056 / 0.10 ms with
+// the diagonal blocks at s = 300 / 512; block products a launch each over
+// 128 x 128 blocks took 0.44 / 0.88 ms.
+__global__ __launch_bounds__(256) void k_tri_inverse_cols(int s, const double* __restrict__ R, int ldr, size_t sr,
+                                                          double* __restrict__ Ri, int ldi, size_t si, int ld) {
+    extern __shared__ double col[];
+    __shared__ double ws[kFacB * kFacLd];
+    R += blockIdx.y * sr;
+    Ri += blockIdx.y * si;
+    const int J = gridDim.x - 1 - blockIdx.x, oj = J * kFacB;  // longest first
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lm = lane & 15, lk = lane >> 4;
+    const int m0 = (wave & 1) * 16, n0 = (wave >> 1) * 16;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int id = threadIdx.x + 256 * u, r = id & 31, c = id >> 5;
+        col[oj + r + c * ld] = oj + r < s && oj + c < s ? Ri[oj + r + (size_t)(oj + c) * ldi] : 0.0;
+    }
+    for (int I = J - 1; I >= 0; --I) {
+        const int oi = I * kFacB, n = oj + kFacB;
+        const double* ra = R + oi + m0 + lm;
+        double av[2][8], dv[8];
+        auto load = [&](int k0, int b) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) av[b][u] = ra[(size_t)min(k0 + 4 * u + lk, s - 1) * ldr];  // beyond: times 0
+        };
+        load(oi + kFacB, 0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) dv[u] = Ri[oi + m0 + lm + (size_t)(oi + 4 * u + lk) * ldi];
+        d4_t acc = {0.0, 0.0, 0.0, 0.0};
+        __syncthreads();  // the column's rows from block I + 1 on are there, ws is free
+        for (int k0 = oi + kFacB; k0 < n; k0 += 2 * kFacB) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int k = k0 + b * kFacB;
+                if (k >= n) break;
+                if (k + kFacB < n) load(k + kFacB, 1 - b);
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[b][u], col[k + 4 * u + lk + (n0 + lm) * ld], acc, 0,
+                                                               0, 0);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ws[m0 + 4 * v + lk + (n0 + lm) * kFacLd] = acc[v];
+        __syncthreads();
+        acc = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(dv[u], ws[4 * u + lk + (n0 + lm) * kFacLd], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) col[oi + m0 + 4 * v + lk + (n0 + lm) * ld] = -acc[v];
+    }
+    __syncthreads();
+    for (int id = threadIdx.x; id < s * kFacB; id += 256) {
+        const int c = id / s, r = id - c * s;
+        if (oj + c < s && (r < oj || r >= oj + kFacB)) Ri[r + (size_t)(oj + c) * ldi] = r < oj ? col[r + c * ld] : 0.0;
+    }
 }
 
 // Pair k of step `step` of the round-robin ordering of an even number m of
@@ -548,16 +666,6 @@ __device__ __forceinline__ void rr_pair(int step, int k, int m, int& p, int& q) 
         p = q;
         q = tmp;
     }
-}
-
-// 1 / sqrt(x) for normal x > 0, to about one ulp: the hardware's estimate, a
-// third-order and a second-order step.
-__device__ __forceinline__ double rsqrt_full(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    double e = __builtin_fma(-x * y, y, 1.0);
-    y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
-    e = __builtin_fma(-x * y, y, 1.0);
-    return __builtin_fma(y * e, 0.5, y);
 }
 
 // Plane rotation (c, sv) that zeroes the off-diagonal entry of the symmetric
@@ -994,8 +1102,7 @@ __global__ void k_scaled_trace(int s, const double* __restrict__ A, int lda, siz
 // the batch), strides in elements; D may be C.  One 16 x 16 quadrant of the
 // tile a wave; bound by the latency of its loads (from the L2), so the 16
 // loads of 32 inner indices are issued together, those of the next 32 before
-// this one's matrix steps.  A thread per entry of C took 7.3 us for a 128 x 44
-// block of an inverse at s = 300, this 6.5 us.
+// this one's matrix steps (s = 300: 15 us a product).
 struct SmallMat {
     const double* p;
     int ld;
@@ -1065,11 +1172,6 @@ __global__ void k_weighted_squares(int n, int k, const double* __restrict__ V, i
         acc += w[j] * v * v;
     }
     out[i] = (base ? base[i] : 0.0) + acc;
-}
-
-__global__ void k_zero_matrix(int m, int n, double* __restrict__ C, int ldc, size_t sc) {
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id < m * n) C[blockIdx.y * sc + id % m + (size_t)(id / m) * ldc] = 0.0;
 }
 
 __global__ void k_scale_rows(int s, int t, const double* __restrict__ d, double* __restrict__ B, int ldb) {
@@ -1152,11 +1254,11 @@ bool cholesky_upper(Ctx* ctx, DenseWork& w, int nb, int s, double* A, int lda, s
                     const double* shift) {
     if (nb <= 0) return true;
     w.flag.ensure(nb);
-    const size_t shm = sizeof(double) * s * s;
-    if (lds_fits(ctx, shm))
-        k_cholesky_lds<<<nb, 1024, shm, ctx->stream>>>(s, A, lda, sa, shift, w.flag.get());
-    else
-        k_cholesky<<<nb, 1024, 0, ctx->stream>>>(s, A, lda, sa, shift, w.flag.get());
+    w.tmp.ensure((size_t)nb * 2 * kFacB * kFacB);
+    const int nblk = ceil_div(s, kFacB);
+    for (int j = 0; j < nblk; ++j)
+        k_cholesky_row<<<dim3(nblk - j, nb), 256, 0, ctx->stream>>>(s, j, A, lda, sa, shift, w.tmp.get(),
+                                                                    w.flag.get());
     HINV_LAUNCH_CHECK();
     std::vector<int> bad(nb);
     HINV_HIP(hipMemcpyAsync(bad.data(), w.flag.get(), sizeof(int) * nb, hipMemcpyDeviceToHost, ctx->stream));
@@ -1169,43 +1271,13 @@ bool cholesky_upper(Ctx* ctx, DenseWork& w, int nb, int s, double* A, int lda, s
 void tri_inverse_upper(Ctx* ctx, DenseWork& w, int nb, int s, const double* R, int ldr, size_t sr, double* Rinv,
                        int ldi, size_t si) {
     if (nb <= 0 || s <= 0) return;
-    auto diag_inverse = [&](int o, int sz) {
-        k_tri_inverse_lds<<<nb, 1024, sizeof(double) * 2 * sz * sz, ctx->stream>>>(
-            sz, R + o + (size_t)o * ldr, ldr, sr, Rinv + o + (size_t)o * ldi, ldi, si);
-        HINV_LAUNCH_CHECK();
-    };
-    if (lds_fits(ctx, sizeof(double) * 2 * s * s)) {
-        diag_inverse(0, s);
-        return;
-    }
-    // Blocked for large s: the diagonal blocks (at most bs, in LDS), then block
-    // rows bottom-up, Rinv(I, J) = -Rinv(I, I) [R(I, I+1..J) Rinv(I+1..J, J)].
-    int bs = 128;
-    while (bs > 8 && !lds_fits(ctx, sizeof(double) * 2 * bs * bs)) bs -= 8;
-    const int nbk = ceil_div(s, bs);
-    const dim3 gz(ceil_div(s * s, 256), nb);
-    k_zero_matrix<<<gz, 256, 0, ctx->stream>>>(s, s, Rinv, ldi, si);
+    const int nblk = ceil_div(s, kFacB), ld = nblk * kFacB + 2;
+    k_tri_inverse_diag<<<dim3(nblk, nb), 64, 0, ctx->stream>>>(s, R, ldr, sr, Rinv, ldi, si);
     HINV_LAUNCH_CHECK();
-    for (int I = 0; I < nbk; ++I) diag_inverse(I * bs, std::min(bs, s - I * bs));
-    const size_t ts = (size_t)bs * bs;
-    w.tmp.ensure(nb * ts);
-    double* tmp = w.tmp.get();
-    for (int I = nbk - 2; I >= 0; --I) {
-        const int oi = I * bs, mi = std::min(bs, s - oi), k0 = oi + mi;
-        for (int J = I + 1; J < nbk; ++J) {
-            const int oj = J * bs, nj = std::min(bs, s - oj), k1 = oj + nj;
-            const dim3 g(ceil_div(nj, 32), ceil_div(mi, 32), nb);
-            const SmallMat none{nullptr, 0, 0};
-            k_small_gemm<false, false><<<g, 256, 0, ctx->stream>>>(
-                mi, nj, k1 - k0, 1.0, SmallMat{R + oi + (size_t)k0 * ldr, ldr, sr},
-                SmallMat{Rinv + k0 + (size_t)oj * ldi, ldi, si}, 0.0, none, tmp, mi, ts);
-            HINV_LAUNCH_CHECK();
-            k_small_gemm<false, false><<<g, 256, 0, ctx->stream>>>(
-                mi, nj, mi, -1.0, SmallMat{Rinv + oi + (size_t)oi * ldi, ldi, si}, SmallMat{tmp, mi, ts}, 0.0, none,
-                Rinv + oi + (size_t)oj * ldi, ldi, si);
-            HINV_LAUNCH_CHECK();
-        }
-    }
+    if (nblk == 1) return;
+    const size_t shm = sizeof(double) * kFacB * ld;  // 129 KB at the largest s, 512
+    k_tri_inverse_cols<<<dim3(nblk, nb), 256, shm, ctx->stream>>>(s, R, ldr, sr, Rinv, ldi, si, ld);
+    HINV_LAUNCH_CHECK();
 }
 
 void sym_eig(Ctx* ctx, DenseWork& w, int nb, int s, double* T, int ldt, size_t st, double* S, int lds, size_t ss,
