@@ -24,9 +24,22 @@ struct P2Elem {
     double K[2][6][6];
 };
 
+// State of a right-hand side of the solver: |b|^2, |r|^2, r^T z (by the parity
+// of the iteration), iterations taken, and whether it is still iterating.
+struct P2Col {
+    double bb, rr, rz[2];
+    int its, live;
+};
+
+constexpr int kP2Tile = 8;  // P1 vertices a side of a workgroup's tile
+// Every workgroup sums a column's partials itself while they are few (a launch
+// of its own costs ~4 us); N >= 184 has more than this many.
+constexpr int kP2MaxParts = 512;
+
 class P2Space {
   public:
     P2Space(Ctx* ctx, int N);
+    ~P2Space();
     int N, side, ns;
 
     // per-triangle coefficient (owned by the P1 state hierarchy) and the
@@ -70,14 +83,16 @@ class P2Space {
     int q_ = 0, n_touch_ = 0;
     DBuf<int> obs_node_, t_node_, t_ptr_, t_ent_;
     DBuf<double> obs_w_;
-    // solver workspaces (ns x cap columns each) and per-column scalars
+    // solver workspaces (ns x cap columns each), partial sums, column states
+    // and their pinned copy
     int cap_ = 0;
-    DBuf<double> r_, z_, p_, q_v_, t1_, t2_, t3_, part_, scal_;
-    DBuf<double> rc_, ec_;  // P1 restriction / coarse correction
-    DBuf<int> act_;
+    DBuf<double> r_, r2_, z_, z2_, p_, p2_, q_v_, part_;
+    DBuf<P2Col> st_;
+    P2Col* hst_ = nullptr;
+    int last_its_ = 8;  // iterations of the last solve
     void ensure(int nc);
-    void precondition(int nc, const double* r, int ldr, double* z, int ldz, Hierarchy& coarse);
-    void dots(int nc, const double* a, int lda, const double* b, int ldb, double* out);
+    void run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hierarchy& coarse, double rtol,
+                   int max_iter);
 };
 
 // The element matrices from the basis gradients at the edge midpoints (the

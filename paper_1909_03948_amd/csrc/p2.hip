@@ -55,43 +55,84 @@ __device__ inline void p2_for_triangles(int N, int I, int J, F f) {
             }
 }
 
+// Partial sums (n.. per column: one a workgroup, or one when they are summed
+// in a launch of their own) and the smoother's coefficients.
+struct P2Red {
+    double *pq, *rr, *rz;
+    int npq, nrr, nrz;
+};
+struct P2Cheb {
+    double inv_theta, c1, c2;
+};
+
 template <typename T>
 __device__ inline T* colp(T* p, int ld) {
     return p + (size_t)blockIdx.y * ld;
 }
 
-// Per-triangle coefficient: c_T, or the sensitivity s_T = (c_T/3) sum mhat.
-__device__ inline double tri_coef(int N, const double* cT, const double* mh, int ci, int cj, int s) {
-    const double c = cT[2 * (cj * N + ci) + s];
-    if (!mh) return c;
-    int ka, kr, kb;
-    tri_nodes(N, ci, cj, s, ka, kr, kb);
-    return c * (1.0 / 3.0) * (mh[ka] + mh[kr] + mh[kb]);
+// Row (I, J) of A_2 on the values x(dx, dy) at the node's offsets and the
+// triangle coefficients c(s, di, dj) of the cells (I/2 + di, J/2 + dj).  On
+// legs 1 the quadratic element couples a vertex to the other vertex (1/6) and
+// the midpoint (-2/3) of each leg it lies on, a leg's midpoint to itself (8/3),
+// the leg's ends (-2/3) and the diagonal's midpoint (-4/3), and nothing else:
+// 9 points for a vertex row, 5 for the others.
+template <class X, class C>
+__device__ __forceinline__ double p2_row(int I, int J, X x, C c) {
+    constexpr double k13 = 1.0 / 3.0, k23 = 2.0 / 3.0, k43 = 4.0 / 3.0, k83 = 8.0 / 3.0;
+    const double x0 = x(0, 0);
+    if (I & 1) {
+        const double xs = x(0, -1), xn = x(0, 1), xw = x(-1, 0), xe = x(1, 0), cl = c(0, 0, 0);
+        if (J & 1) return cl * (k83 * x0 - k43 * (xs + xe)) + c(1, 0, 0) * (k83 * x0 - k43 * (xw + xn));
+        const double t = k83 * x0 - k23 * (xw + xe);
+        return cl * (t - k43 * xn) + c(1, 0, -1) * (t - k43 * xs);
+    }
+    const double cu = c(1, 0, 0), cw = c(0, -1, 0);
+    const double xw = x(-1, 0), xe = x(1, 0), xs = x(0, -1), xn = x(0, 1);
+    if (J & 1) {
+        const double t = k83 * x0 - k23 * (xs + xn);
+        return cu * (t - k43 * xe) + cw * (t - k43 * xw);
+    }
+    const double cd = c(1, 0, -1);
+    const double e = c(0, 0, 0) + cd, w = cw + c(1, -1, -1), n = cu + cw, so = cd + c(0, -1, -1);
+    return 0.5 * (e * (x0 + k13 * x(2, 0) - k43 * xe) + w * (x0 + k13 * x(-2, 0) - k43 * xw) +
+                  n * (x0 + k13 * x(0, 2) - k43 * xn) + so * (x0 + k13 * x(0, -2) - k43 * xs));
 }
 
-// y = scale K[coef] x (or y = b - K[coef] x when b is given) on the free rows,
-// 0 on the Dirichlet rows.  mhat != null: coefficient s_T(mhat) per column.
-// ldx = 0: the same x for every column.  act: columns to skip (may be null).
-__global__ void k_p2_apply(int N, P2Elem el, const double* __restrict__ cT, const double* __restrict__ mhat,
-                           int ldm, const double* __restrict__ x, int ldx, const double* __restrict__ b,
-                           int ldb, double scale, double* __restrict__ y, int ldy,
-                           const int* __restrict__ act) {
+// Coefficient of triangle s of cell (ci, cj), 0 outside the mesh.
+__device__ __forceinline__ double p2_coef(int N, const double* __restrict__ cT, int ci, int cj, int s) {
+    const bool in = ci >= 0 && cj >= 0 && ci < N && cj < N;
+    return in ? cT[2 * (cj * N + ci) + s] : 0.0;
+}
+
+// y = scale K[coef] x on the free rows, 0 on the Dirichlet rows.  mhat: the
+// coefficient is s_T = (c_T/3) sum mhat over the triangle's vertices, per
+// column.  ldx = 0: the same x for every column.
+template <bool SENS>
+__global__ void k_p2_apply(int N, const double* __restrict__ cT, const double* __restrict__ mhat, int ldm,
+                           const double* __restrict__ x, int ldx, double scale, double* __restrict__ y, int ldy) {
     const int side = 2 * N + 1, ns = side * side;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ns || (act && !act[blockIdx.y])) return;
+    if (k >= ns) return;
     const int J = k / side, I = k - J * side;
     double v = 0.0;
     if (J > 0 && J < 2 * N) {
         const double* xc = x + (size_t)blockIdx.y * ldx;
-        const double* mh = mhat ? colp(mhat, ldm) : nullptr;
-        double acc = 0.0;
-        p2_for_triangles(N, I, J, [&](int ci, int cj, int s, int loc) {
-            double t = 0.0;
-#pragma unroll
-            for (int j = 0; j < 6; ++j) t += el.K[s][loc][j] * xc[p2_dof(side, ci, cj, s, j)];
-            acc += tri_coef(N, cT, mh, ci, cj, s) * t;
-        });
-        v = b ? colp(b, ldb)[k] - acc : scale * acc;
+        const double* mh = SENS ? colp(mhat, ldm) : nullptr;
+        // neighbours outside the mesh meet a zero coefficient
+        auto xv = [&](int dx, int dy) { return xc[min(max(J + dy, 0), 2 * N) * side + min(max(I + dx, 0), 2 * N)]; };
+        auto cv = [&](int s, int di, int dj) {
+            const int ci = (I >> 1) + di, cj = (J >> 1) + dj;
+            double c = p2_coef(N, cT, ci, cj, s);
+            if constexpr (SENS) {
+                if (ci >= 0 && ci < N && cj >= 0 && cj < N) {
+                    int ka, kr, kb;
+                    tri_nodes(N, ci, cj, s, ka, kr, kb);
+                    c = c * (1.0 / 3.0) * (mh[ka] + mh[kr] + mh[kb]);
+                }
+            }
+            return c;
+        };
+        v = scale * p2_row(I, J, xv, cv);
     }
     colp(y, ldy)[k] = v;
 }
@@ -115,117 +156,314 @@ __global__ void k_p2_top(int N, double* __restrict__ u) {
     if (I < side) u[(size_t)(2 * N) * side + I] = 1.0;
 }
 
-// rc = P^T r (P1 vertex v: its own value plus half of the midpoints of the
-// edges at v: horizontal, vertical and the SW-NE diagonal), 0 on the P1
-// Dirichlet rows.
-__global__ void k_p2_restrict(int N, const double* __restrict__ r, int ldr, double* __restrict__ rc, int ldc,
-                              const int* __restrict__ act) {
-    const int N1 = N + 1, side = 2 * N + 1;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N1 * N1 || (act && !act[blockIdx.y])) return;
-    const int j = k / N1, i = k - j * N1;
-    double v = 0.0;
-    if (j > 0 && j < N) {
-        const double* rr = colp(r, ldr);
-        const int I = 2 * i, J = 2 * j, c = J * side + I;
-        double h = 0.0;
-        if (I > 0) h += rr[c - 1];
-        if (I < 2 * N) h += rr[c + 1];
-        h += rr[c - side] + rr[c + side];
-        if (I < 2 * N) h += rr[c + side + 1];
-        if (I > 0) h += rr[c - side - 1];
-        v = rr[c] + 0.5 * h;
+// ---- the solver's three kernels -------------------------------------------
+// A workgroup owns V x V P1 vertices with four nodes each: (2i, 2j) and the
+// ones right, above and diagonally above.  What the stages of a kernel need of
+// the neighbours' nodes is computed again in LDS (the stencil reaches two
+// nodes), so a PCG iteration is three launches around the P1 V-cycle where one
+// launch a vector operation took twenty: a 129 x 129 grid is all latency.
+// Measured at 64^2, one column: 2.98 -> 0.85 ms a full Hessian
+// action; tiles of 16 x 16 vertices were slower or equal at every size up
+// to 1024^2 x 1 and 64^2 x 50 (50 columns: 1.64 against 1.96 ms).
+struct P2Tile {
+    static constexpr int V = kP2Tile;
+    static constexpr int D = 2 * V + 7;      // nodes 2 i0 - 4 .. 2 (i0 + V) + 2
+    static constexpr int Z = 2 * V + 3;      // nodes 2 i0 - 2 .. 2 (i0 + V)
+    static constexpr int C = V + 3;          // cells i0 - 2 .. i0 + V
+    static constexpr int SD = (D * D + 255) / 256, SZ = (Z * Z + 255) / 256, SO = (4 * V * V + 255) / 256;
+    int N, i0, j0;
+    __device__ P2Tile(int N_) : N(N_), i0(blockIdx.x * V), j0(blockIdx.y * V) {}
+    __device__ bool free_node(int I, int J) const { return I >= 0 && I <= 2 * N && J > 0 && J < 2 * N; }
+    __device__ bool owned(int I, int J) const {
+        return I >= 2 * i0 && I < 2 * (i0 + V) && I <= 2 * N && J >= 2 * j0 && J < 2 * (j0 + V) && J <= 2 * N;
     }
-    colp(rc, ldc)[k] = v;
-}
+    // node of item id of a square of side w around the tile
+    __device__ void node(int id, int w, int& I, int& J) const {
+        const int h = (w - 2 * V + 1) / 2, jj = id / w;  // D: 4, Z: 2, 2 V + 1: 1, 2 V: 0
+        I = 2 * i0 - h + id - jj * w;
+        J = 2 * j0 - h + jj;
+    }
+    __device__ int at(int I, int J) const { return (J - 2 * j0 + 4) * D + I - 2 * i0 + 4; }
+    __device__ void load_coef(const double* __restrict__ cT, double* cs) const {
+        for (int id = threadIdx.x; id < 2 * C * C; id += 256) {
+            const int s = id & 1, t = id >> 1, cj = t / C, ci = t - cj * C;
+            cs[id] = p2_coef(N, cT, i0 - 2 + ci, j0 - 2 + cj, s);
+        }
+    }
+    // row (I, J) on the values a (indexed by at) and the coefficients cs
+    __device__ double row(int I, int J, const double* a, const double* cs) const {
+        const double* ap = a + at(I, J);
+        const double* cp = cs + 2 * (((J >> 1) - j0 + 2) * C + (I >> 1) - i0 + 2);
+        return p2_row(
+            I, J, [&](int dx, int dy) { return ap[dy * D + dx]; },
+            [&](int s, int di, int dj) { return cp[2 * (dj * C + di) + s]; });
+    }
+};
 
-// x += P e on the free rows (the P1 function e evaluated at the P2 nodes).
-__global__ void k_p2_prolong_add(int N, const double* __restrict__ e, int lde, double* __restrict__ x, int ldx,
-                                 const int* __restrict__ act) {
-    const int N1 = N + 1, side = 2 * N + 1, ns = side * side;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ns || (act && !act[blockIdx.y])) return;
-    const int J = k / side, I = k - J * side;
-    if (J == 0 || J == 2 * N) return;
-    const double* ec = colp(e, lde);
-    const int i0 = I >> 1, j0 = J >> 1, i1 = (I + 1) >> 1, j1 = (J + 1) >> 1;
-    // even coordinates give i0 == i1; odd ones the two ends of the edge
-    const double v = (I & 1) || (J & 1) ? 0.5 * (ec[j0 * N1 + i0] + ec[j1 * N1 + i1]) : ec[j0 * N1 + i0];
-    colp(x, ldx)[k] += v;
-}
-
-// First Chebyshev step: d = dinv r / theta; x = d (from_zero) or x += d.
-__global__ void k_p2_cheb_init(int ns, const double* __restrict__ dinv, const double* __restrict__ r, int ld,
-                               double inv_theta, double* __restrict__ d, double* __restrict__ x, int ldx,
-                               int from_zero, const int* __restrict__ act) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ns || (act && !act[blockIdx.y])) return;
-    const size_t o = (size_t)blockIdx.y * ld + k;
-    const double v = dinv[k] * r[o] * inv_theta;
-    d[o] = v;
-    double* xp = x + (size_t)blockIdx.y * ldx + k;
-    *xp = from_zero ? v : *xp + v;
-}
-
-// Next Chebyshev step after q = A d: r -= q; d = c1 d + c2 dinv r; x += d.
-__global__ void k_p2_cheb_step(int ns, const double* __restrict__ dinv, const double* __restrict__ q,
-                               double* __restrict__ r, double* __restrict__ d, int ld, double* __restrict__ x,
-                               int ldx, double c1, double c2, const int* __restrict__ act) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ns || (act && !act[blockIdx.y])) return;
-    const size_t o = (size_t)blockIdx.y * ld + k;
-    const double rv = r[o] - q[o];
-    const double dv = c1 * d[o] + c2 * dinv[k] * rv;
-    r[o] = rv;
-    d[o] = dv;
-    x[(size_t)blockIdx.y * ldx + k] += dv;
-}
-
-__global__ void k_p2_masked_copy(int N, const double* __restrict__ a, int lda, double* __restrict__ b, int ldb) {
-    const int side = 2 * N + 1, ns = side * side;
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= ns) return;
-    const int J = k / side;
-    colp(b, ldb)[k] = (J > 0 && J < 2 * N) ? colp(a, lda)[k] : 0.0;
-}
-
-__global__ void k_p2_dot_partial(int n, const double* __restrict__ a, int lda, const double* __restrict__ b,
-                                 int ldb, double* __restrict__ part) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const double v = k < n ? colp(a, lda)[k] * colp(b, ldb)[k] : 0.0;
-    const double s = block_sum(v);
-    if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
-}
-
-__global__ void k_p2_dot_finish(const double* __restrict__ part, int nblk, double* __restrict__ out) {
+// Sum of n partials in a fixed order, in every thread (256 threads).
+__device__ __forceinline__ double p2_total(const double* __restrict__ part, int n) {
+    __shared__ double ws[4];
     double v = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += part[(size_t)blockIdx.x * nblk + b];
+    for (int b = threadIdx.x; b < n; b += 256) v += part[b];
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = (ws[0] + ws[1]) + (ws[2] + ws[3]);
+    __syncthreads();
+    return v;
+}
+
+__device__ __forceinline__ void p2_partial(double v, double* part) {
     const double s = block_sum(v);
-    if (threadIdx.x == 0) out[blockIdx.x] = s;
+    if (threadIdx.x == 0) part[(size_t)blockIdx.z * gridDim.x * gridDim.y + blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
-// alpha = rz / pq; x += alpha p; r -= alpha q (pq <= 0: no step)
-__global__ void k_p2_pcg_step(int ns, const double* __restrict__ rz, const double* __restrict__ pq,
-                              double* __restrict__ x, double* __restrict__ r, const double* __restrict__ p,
-                              const double* __restrict__ q, int ld, int ldx, const int* __restrict__ act) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (k >= ns || !act[c]) return;
-    const double a = pq[c] > 0.0 ? rz[c] / pq[c] : 0.0;
-    const size_t o = (size_t)c * ld + k;
-    x[(size_t)c * ldx + k] += a * p[o];
-    r[o] -= a * q[o];
+// The PCG step x += alpha p, r <- r - alpha q (r_in -> r_out; alpha = rz / pq,
+// no step for pq <= 0) with its r^T r, then the cycle's way down: z = two
+// Chebyshev-Jacobi steps from zero, rc = P^T (r - A z) (P1 vertex: its own
+// value plus half of the midpoints of the edges at it), 0 on the P1 Dirichlet
+// rows.  FIRST: r = b on the free rows, x = 0.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_p2_down(int N, const double* __restrict__ cT,
+                                                 const double* __restrict__ dinv, const double* __restrict__ r_in,
+                                                 int ldr, double* __restrict__ r_out, const double* __restrict__ p,
+                                                 const double* __restrict__ q, double* __restrict__ x, int ldx,
+                                                 double* __restrict__ z, double* __restrict__ rc, int ldc,
+                                                 P2Red red, P2Cheb ch, const P2Col* __restrict__ st, int cur,
+                                                 const int* __restrict__ act) {
+    using T = P2Tile;
+    constexpr int V = T::V;
+    const int col = blockIdx.z;
+    if (!FIRST && !act[col]) return;
+    const T t(N);
+    const int side = 2 * N + 1, ns = side * side;
+    __shared__ double cs[2 * T::C * T::C], sr[T::D * T::D], sd[T::D * T::D], sa[T::D * T::D], sz[T::D * T::D];
+    const double* rin = r_in + (size_t)col * ldr;
+    const size_t o = (size_t)col * ns;
+    double rv[T::SD], qv[T::SD], dv[T::SD], pv[T::SD], xv[T::SD];
+#pragma unroll
+    for (int u = 0; u < T::SD; ++u) {
+        const int id = min((int)threadIdx.x + 256 * u, T::D * T::D - 1);
+        int I, J;
+        t.node(id, T::D, I, J);
+        const bool fr = t.free_node(I, J);
+        const int k = fr ? J * side + I : side;
+        rv[u] = rin[k];
+        dv[u] = fr ? dinv[k] : 0.0;
+        if (!FIRST) {
+            qv[u] = q[o + k];
+            pv[u] = xv[u] = 0.0;
+            if (t.owned(I, J)) {
+                pv[u] = p[o + k];
+                xv[u] = x[(size_t)col * ldx + k];
+            }
+        }
+    }
+    t.load_coef(cT, cs);
+    double alpha = 0.0;
+    if (!FIRST) {
+        const double pq = p2_total(red.pq + (size_t)col * red.npq, red.npq);
+        alpha = pq > 0.0 ? st[col].rz[cur] / pq : 0.0;
+    }
+    double rr = 0.0;
+#pragma unroll
+    for (int u = 0; u < T::SD; ++u) {
+        const int id = threadIdx.x + 256 * u;
+        if (id >= T::D * T::D) break;
+        int I, J;
+        t.node(id, T::D, I, J);
+        const bool fr = t.free_node(I, J);
+        double v = fr ? rv[u] : 0.0;
+        if (!FIRST && fr) v -= alpha * qv[u];
+        if (t.owned(I, J)) {
+            const int k = J * side + I;
+            r_out[o + k] = v;
+            if (FIRST)
+                x[(size_t)col * ldx + k] = 0.0;
+            else if (fr)
+                x[(size_t)col * ldx + k] = xv[u] + alpha * pv[u];
+            rr += v * v;
+        }
+        sr[id] = v;
+        sd[id] = dv[u];
+        sa[id] = dv[u] * v * ch.inv_theta;
+    }
+    __syncthreads();
+    for (int id = threadIdx.x; id < T::Z * T::Z; id += 256) {
+        int I, J;
+        t.node(id, T::Z, I, J);
+        const int a = t.at(I, J);
+        double v = 0.0;
+        if (t.free_node(I, J)) v = sa[a] + (ch.c1 * sa[a] + ch.c2 * sd[a] * (sr[a] - t.row(I, J, sa, cs)));
+        sz[a] = v;
+        if (t.owned(I, J)) z[o + J * side + I] = v;
+    }
+    __syncthreads();
+    constexpr int R = 2 * V + 1;
+    for (int id = threadIdx.x; id < R * R; id += 256) {
+        int I, J;
+        t.node(id, R, I, J);
+        const int a = t.at(I, J);
+        sa[a] = t.free_node(I, J) ? sr[a] - t.row(I, J, sz, cs) : 0.0;
+    }
+    __syncthreads();
+    for (int id = threadIdx.x; id < V * V; id += 256) {
+        const int i = t.i0 + id % V, j = t.j0 + id / V;
+        if (i > N || j > N) continue;
+        const double* a = sa + t.at(2 * i, 2 * j);
+        constexpr int D = T::D;
+        const double v = a[0] + 0.5 * (((a[-1] + a[1]) + (a[-D] + a[D])) + (a[D + 1] + a[-D - 1]));
+        rc[(size_t)col * ldc + j * (N + 1) + i] = j > 0 && j < N ? v : 0.0;
+    }
+    p2_partial(rr, red.rr);
 }
 
-// p = z + beta p with beta = rz_new / rz_old (first: p = z)
-__global__ void k_p2_pcg_dir(int ns, const double* __restrict__ rzn, const double* __restrict__ rzo,
-                             const double* __restrict__ z, double* __restrict__ p, int ld, int first,
-                             const int* __restrict__ act) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (k >= ns || !act[c]) return;
-    const size_t o = (size_t)c * ld + k;
-    p[o] = first ? z[o] : z[o] + (rzn[c] / rzo[c]) * p[o];
+// The convergence test, then the cycle's way up: z + P e, and two
+// Chebyshev-Jacobi steps from it on the residual; z_out with its r^T z.
+__global__ __launch_bounds__(256) void k_p2_up(int N, const double* __restrict__ cT, const double* __restrict__ dinv,
+                                               const double* __restrict__ r, const double* __restrict__ z,
+                                               const double* __restrict__ e, int lde, double* __restrict__ z_out,
+                                               P2Red red, P2Cheb ch, P2Col* __restrict__ st, double tol2, int first,
+                                               int* __restrict__ act) {
+    using T = P2Tile;
+    constexpr int V = T::V;
+    const int col = blockIdx.z;
+    if (!act[col]) return;
+    const T t(N);
+    const int side = 2 * N + 1, ns = side * side, N1 = N + 1;
+    __shared__ double cs[2 * T::C * T::C], sr[T::D * T::D], sd[T::D * T::D], sa[T::D * T::D], sz[T::D * T::D];
+    const size_t o = (size_t)col * ns;
+    const double* ec = e + (size_t)col * lde;
+    double rv[T::SD], dv[T::SD], zv[T::SD], e0[T::SD], e1[T::SD];
+#pragma unroll
+    for (int u = 0; u < T::SD; ++u) {
+        const int id = min((int)threadIdx.x + 256 * u, T::D * T::D - 1);
+        int I, J;
+        t.node(id, T::D, I, J);
+        const bool fr = t.free_node(I, J);
+        I = fr ? I : 0;
+        J = fr ? J : 1;
+        const int k = J * side + I;
+        rv[u] = fr ? r[o + k] : 0.0;
+        dv[u] = fr ? dinv[k] : 0.0;
+        // the P1 function at the node: even coordinates give one vertex,
+        // odd ones the two ends of the edge
+        const double a = ec[(J >> 1) * N1 + (I >> 1)], b = ec[((J + 1) >> 1) * N1 + ((I + 1) >> 1)];
+        zv[u] = fr ? z[o + k] : 0.0;
+        e0[u] = fr ? a : 0.0;
+        e1[u] = fr ? b : 0.0;
+    }
+    t.load_coef(cT, cs);
+    // column state: the first pass sets |b|^2; a column ends when |r| <= tol |b|
+    // or is not a number.  Every workgroup decides alike from the same sum.
+    const double rr = p2_total(red.rr + (size_t)col * red.nrr, red.nrr);
+    const double bb = first ? rr : st[col].bb;
+    const bool done = first ? !(rr > 0.0 && rr < INFINITY) : !(rr > tol2 * bb);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        st[col].rr = rr;
+        if (first) st[col].bb = rr;
+        st[col].its += first ? 0 : 1;
+        if (done) act[col] = st[col].live = 0;
+    }
+    if (done) return;
+#pragma unroll
+    for (int u = 0; u < T::SD; ++u) {
+        const int id = threadIdx.x + 256 * u;
+        if (id >= T::D * T::D) break;
+        sr[id] = rv[u];
+        sd[id] = dv[u];
+        sz[id] = zv[u] + 0.5 * (e0[u] + e1[u]);
+    }
+    __syncthreads();
+    double rs[T::SZ];
+#pragma unroll
+    for (int u = 0; u < T::SZ; ++u) {
+        const int id = threadIdx.x + 256 * u;
+        if (id >= T::Z * T::Z) break;
+        int I, J;
+        t.node(id, T::Z, I, J);
+        const int a = t.at(I, J);
+        rs[u] = t.free_node(I, J) ? sr[a] - t.row(I, J, sz, cs) : 0.0;
+        sa[a] = sd[a] * rs[u] * ch.inv_theta;
+    }
+    __syncthreads();
+    double rz = 0.0;
+#pragma unroll
+    for (int u = 0; u < T::SZ; ++u) {
+        const int id = threadIdx.x + 256 * u;
+        if (id >= T::Z * T::Z) break;
+        int I, J;
+        t.node(id, T::Z, I, J);
+        if (!t.owned(I, J)) continue;
+        const int a = t.at(I, J);
+        double v = 0.0;
+        if (t.free_node(I, J))
+            v = sz[a] + sa[a] + (ch.c1 * sa[a] + ch.c2 * sd[a] * (rs[u] - t.row(I, J, sa, cs)));
+        z_out[o + J * side + I] = v;
+        rz += sr[a] * v;
+    }
+    p2_partial(rz, red.rz);
+}
+
+// p = z + beta p_old, beta = rz / rz_old (first: p = z), q = A p, p^T q.
+__global__ __launch_bounds__(256) void k_p2_dir(int N, const double* __restrict__ cT, const double* __restrict__ z,
+                                                const double* __restrict__ p_old, double* __restrict__ p,
+                                                double* __restrict__ q, P2Red red, P2Col* __restrict__ st, int cur,
+                                                int first, const int* __restrict__ act) {
+    using T = P2Tile;
+    constexpr int V = T::V;
+    const int col = blockIdx.z;
+    if (!act[col]) return;
+    const T t(N);
+    const int side = 2 * N + 1, ns = side * side;
+    __shared__ double cs[2 * T::C * T::C], sp[T::D * T::D];
+    const size_t o = (size_t)col * ns;
+    double zv[T::SZ], pv[T::SZ];
+#pragma unroll
+    for (int u = 0; u < T::SZ; ++u) {
+        const int id = min((int)threadIdx.x + 256 * u, T::Z * T::Z - 1);
+        int I, J;
+        t.node(id, T::Z, I, J);
+        const bool fr = t.free_node(I, J);
+        const int k = fr ? J * side + I : side;
+        zv[u] = fr ? z[o + k] : 0.0;
+        pv[u] = fr && !first ? p_old[o + k] : 0.0;
+    }
+    t.load_coef(cT, cs);
+    const double rz = p2_total(red.rz + (size_t)col * red.nrz, red.nrz);
+    const double beta = first ? 0.0 : rz / st[col].rz[1 - cur];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st[col].rz[cur] = rz;
+#pragma unroll
+    for (int u = 0; u < T::SZ; ++u) {
+        const int id = threadIdx.x + 256 * u;
+        if (id >= T::Z * T::Z) break;
+        int I, J;
+        t.node(id, T::Z, I, J);
+        const double v = first ? zv[u] : zv[u] + beta * pv[u];
+        sp[t.at(I, J)] = v;
+        if (t.owned(I, J)) p[o + J * side + I] = v;
+    }
+    __syncthreads();
+    double pq = 0.0;
+    for (int id = threadIdx.x; id < 4 * V * V; id += 256) {
+        int I, J;
+        t.node(id, 2 * V, I, J);
+        if (!t.owned(I, J)) continue;
+        const double v = t.free_node(I, J) ? t.row(I, J, sp, cs) : 0.0;
+        q[o + J * side + I] = v;
+        pq += sp[t.at(I, J)] * v;
+    }
+    p2_partial(pq, red.pq);
+}
+
+__global__ __launch_bounds__(256) void k_p2_finish(const double* __restrict__ part, int n, double* __restrict__ out) {
+    const double v = p2_total(part + (size_t)blockIdx.x * n, n);
+    if (threadIdx.x == 0) out[blockIdx.x] = v;
+}
+
+__global__ void k_p2_start(int nc, P2Col* __restrict__ st) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c < nc) st[c] = P2Col{0.0, 0.0, {0.0, 0.0}, 0, 1};
 }
 
 __global__ void k_p2_zero(int ns, double* __restrict__ x, int ld) {
@@ -419,15 +657,13 @@ void P2Space::set_coefficient(const double* cT) {
 
 void P2Space::apply(int nc, const double* x, int ldx, double* y, int ldy, double scale) {
     if (!cT_) fail(HINV_ESTATE, "P2 operator used before its coefficient was set");
-    k_p2_apply<<<grid2(ns, nc), kBlock, 0, ctx_->stream>>>(N, el_, cT_, nullptr, 0, x, ldx, nullptr, 0, scale,
-                                                           y, ldy, nullptr);
+    k_p2_apply<false><<<grid2(ns, nc), kBlock, 0, ctx_->stream>>>(N, cT_, nullptr, 0, x, ldx, scale, y, ldy);
     HINV_LAUNCH_CHECK();
 }
 
 void P2Space::sens(int nc, const double* mhat, int ldm, const double* w, double scale, double* y, int ldy) {
     if (!cT_) fail(HINV_ESTATE, "P2 operator used before its coefficient was set");
-    k_p2_apply<<<grid2(ns, nc), kBlock, 0, ctx_->stream>>>(N, el_, cT_, mhat, ldm, w, 0, nullptr, 0, scale, y,
-                                                           ldy, nullptr);
+    k_p2_apply<true><<<grid2(ns, nc), kBlock, 0, ctx_->stream>>>(N, cT_, mhat, ldm, w, 0, scale, y, ldy);
     HINV_LAUNCH_CHECK();
 }
 
@@ -438,7 +674,7 @@ void P2Space::set_top(double* u) {
 
 void P2Space::forward_rhs(double* rhs) {
     ensure(1);
-    double* uD = t1_.get();
+    double* uD = z_.get();
     k_p2_zero<<<ceil_div(ns, kBlock), kBlock, 0, ctx_->stream>>>(ns, uD, ns);
     HINV_LAUNCH_CHECK();
     set_top(uD);
@@ -448,66 +684,92 @@ void P2Space::forward_rhs(double* rhs) {
 void P2Space::ensure(int nc) {
     if (nc <= cap_) return;
     const size_t len = (size_t)ns * nc;
-    for (auto* b : {&r_, &z_, &p_, &q_v_, &t1_, &t2_, &t3_}) b->ensure(len);
-    const size_t n1 = (size_t)(N + 1) * (N + 1) * nc;
-    rc_.ensure(n1);
-    ec_.ensure(n1);
-    part_.ensure((size_t)ceil_div(ns, kBlock) * nc);
-    scal_.ensure(6 * (size_t)nc);
-    act_.ensure(nc);
+    for (auto* b : {&r_, &r2_, &z_, &z2_, &p_, &p2_, &q_v_}) b->ensure(len);
+    const int nt = ceil_div(N + 1, kP2Tile);
+    part_.ensure(3 * (size_t)(nt * nt + 1) * nc);
+    st_.ensure(nc);
+    if (hst_) (void)hipHostFree(hst_);
+    hst_ = nullptr;
+    HINV_HIP(hipHostMalloc((void**)&hst_, sizeof(P2Col) * nc, hipHostMallocDefault));
     cap_ = nc;
 }
 
-void P2Space::dots(int nc, const double* a, int lda, const double* b, int ldb, double* out) {
-    const int nblk = ceil_div(ns, kBlock);
-    k_p2_dot_partial<<<grid2(ns, nc), kBlock, 0, ctx_->stream>>>(ns, a, lda, b, ldb, part_.get());
-    HINV_LAUNCH_CHECK();
-    k_p2_dot_finish<<<nc, kBlock, 0, ctx_->stream>>>(part_.get(), nblk, out);
-    HINV_LAUNCH_CHECK();
+P2Space::~P2Space() {
+    if (hst_) (void)hipHostFree(hst_);
 }
 
-// z = two-level cycle applied to r (all in ns-strided columns, act marks the
-// live columns): degree-2 Chebyshev-Jacobi on [lmax / 4, lmax] from zero,
-// P^T of the residual through one V-cycle of the P1 hierarchy, P back, and
-// the same smoother again from the corrected iterate.
-void P2Space::precondition(int nc, const double* r, int ldr, double* z, int ldz, Hierarchy& coarse) {
+// PCG with the two-level cycle: degree-2 Chebyshev-Jacobi on [lmax / 4, lmax]
+// from zero, P^T of the residual through one V-cycle of the P1 hierarchy, P
+// back, and the same smoother again from the corrected iterate.  An iteration
+// is k_p2_dir, k_p2_down, the V-cycle and k_p2_up, which tests the column; the
+// host enqueues as many iterations as the last solve took before it first
+// looks (launches for finished columns return at once).
+void P2Space::run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hierarchy& coarse, double rtol,
+                          int max_iter) {
     hipStream_t s = ctx_->stream;
-    const int* act = act_.get();
     const double hi = lmax_, lo = 0.25 * lmax_;
     const double theta = 0.5 * (hi + lo), dl = 0.5 * (hi - lo), sigma1 = theta / dl;
     const double rho0 = 1.0 / sigma1, rho1 = 1.0 / (2.0 * sigma1 - rho0);
-    const double c1 = rho1 * rho0, c2 = 2.0 * rho1 / dl;
-    const dim3 g = grid2(ns, nc);
-    double* rs = t1_.get();
-    double* d = t2_.get();
-    double* q = t3_.get();
-    const int N1 = N + 1, n1 = N1 * N1;
-    auto smooth = [&](bool from_zero) {
-        // rs = r (from zero) or r - A z; d = D^-1 rs / theta, z = d or z += d
-        if (from_zero)
-            k_p2_masked_copy<<<g, kBlock, 0, s>>>(N, r, ldr, rs, ns);
-        else
-            k_p2_apply<<<g, kBlock, 0, s>>>(N, el_, cT_, nullptr, 0, z, ldz, r, ldr, 1.0, rs, ns, act);
-        HINV_LAUNCH_CHECK();
-        k_p2_cheb_init<<<g, kBlock, 0, s>>>(ns, dinv_.get(), rs, ns, 1.0 / theta, d, z, ldz, from_zero ? 1 : 0,
-                                            act);
-        HINV_LAUNCH_CHECK();
-        // second step: rs -= A d, d = c1 d + c2 D^-1 rs, z += d
-        k_p2_apply<<<g, kBlock, 0, s>>>(N, el_, cT_, nullptr, 0, d, ns, nullptr, 0, 1.0, q, ns, act);
-        HINV_LAUNCH_CHECK();
-        k_p2_cheb_step<<<g, kBlock, 0, s>>>(ns, dinv_.get(), q, rs, d, ns, z, ldz, c1, c2, act);
+    const P2Cheb ch{1.0 / theta, rho1 * rho0, 2.0 * rho1 / dl};
+    const int nt = ceil_div(N + 1, kP2Tile), nblk = nt * nt, n1 = (N + 1) * (N + 1);
+    const dim3 g(nt, nt, nc);
+    const bool fold = nblk > kP2MaxParts;
+    double* part[3];
+    double* tot = part_.get() + 3 * (size_t)nblk * nc;  // folded sums
+    for (int i = 0; i < 3; ++i) part[i] = part_.get() + (size_t)i * nblk * nc;
+    // what the kernels write (one partial a workgroup) and read
+    const P2Red w{part[0], part[1], part[2], nblk, nblk, nblk};
+    const P2Red rd = fold ? P2Red{tot, tot + nc, tot + 2 * nc, 1, 1, 1} : w;
+    auto finish = [&](int i) {
+        if (!fold) return;
+        k_p2_finish<<<nc, 256, 0, s>>>(part[i], nblk, tot + (size_t)i * nc);
         HINV_LAUNCH_CHECK();
     };
-    smooth(true);
-    // coarse correction
-    k_p2_apply<<<g, kBlock, 0, s>>>(N, el_, cT_, nullptr, 0, z, ldz, r, ldr, 1.0, rs, ns, act);
+    // kernels read sums of the earlier ones and write their own
+    const P2Red rdown{rd.pq, w.rr, w.rz, rd.npq, w.nrr, w.nrz}, rup{w.pq, rd.rr, w.rz, w.npq, rd.nrr, w.nrz},
+        rdir{w.pq, w.rr, rd.rz, w.npq, w.nrr, rd.nrz};
+    coarse.cycle_prepare(nc);
+    int* act = coarse.cycle_active();
+    double* rc = coarse.cycle_in();
+    const double* e = coarse.cycle_out();
+    double *R[2] = {r_.get(), r2_.get()}, *P[2] = {p_.get(), p2_.get()};
+    k_p2_start<<<ceil_div(nc, 64), 64, 0, s>>>(nc, st_.get());
     HINV_LAUNCH_CHECK();
-    k_p2_restrict<<<grid2(n1, nc), kBlock, 0, s>>>(N, rs, ns, rc_.get(), n1, act);
+    auto cycle = [&](int it) {
+        finish(1);
+        coarse.cycle(nc);
+        k_p2_up<<<g, 256, 0, s>>>(N, cT_, dinv_.get(), R[it & 1], z_.get(), e, n1, z2_.get(), rup, ch, st_.get(),
+                                     rtol * rtol, it == 0, act);
+        HINV_LAUNCH_CHECK();
+        finish(2);
+    };
+    k_p2_down<true><<<g, 256, 0, s>>>(N, cT_, dinv_.get(), b, ldb, R[0], nullptr, nullptr, x, ldx, z_.get(), rc,
+                                         n1, rdown, ch, st_.get(), 0, act);
     HINV_LAUNCH_CHECK();
-    coarse.precondition(nc, rc_.get(), n1, ec_.get(), n1);
-    k_p2_prolong_add<<<g, kBlock, 0, s>>>(N, ec_.get(), n1, z, ldz, act);
-    HINV_LAUNCH_CHECK();
-    smooth(false);
+    cycle(0);
+    int it = 0;
+    auto run = [&](int to) {
+        for (; it < to; ++it) {
+            const int cur = it & 1;
+            k_p2_dir<<<g, 256, 0, s>>>(N, cT_, z2_.get(), P[1 - cur], P[cur], q_v_.get(), rdir, st_.get(), cur,
+                                          it == 0, act);
+            HINV_LAUNCH_CHECK();
+            finish(0);
+            k_p2_down<false><<<g, 256, 0, s>>>(N, cT_, dinv_.get(), R[cur], ns, R[1 - cur], P[cur], q_v_.get(), x,
+                                                  ldx, z_.get(), rc, n1, rdown, ch, st_.get(), cur, act);
+            HINV_LAUNCH_CHECK();
+            cycle(it + 1);
+        }
+    };
+    run(std::min(max_iter, last_its_));
+    for (;;) {
+        HINV_HIP(hipMemcpyAsync(hst_, st_.get(), sizeof(P2Col) * nc, hipMemcpyDeviceToHost, s));
+        HINV_HIP(hipStreamSynchronize(s));
+        int live = 0;
+        for (int c = 0; c < nc; ++c) live += hst_[c].live;
+        if (!live || it >= max_iter) break;
+        run(std::min(max_iter, it + 2));
+    }
 }
 
 void P2Space::solve(int nc, const double* b, int ldb, double* x, int ldx, Hierarchy& coarse, double rtol,
@@ -515,78 +777,21 @@ void P2Space::solve(int nc, const double* b, int ldb, double* x, int ldx, Hierar
     if (!cT_) fail(HINV_ESTATE, "P2 solve before the coefficient was set");
     if (nc <= 0) return;
     ensure(nc);
-    hipStream_t s = ctx_->stream;
-    const dim3 g = grid2(ns, nc);
-    double* bb = scal_.get();
-    double* rz = bb + nc;
-    double* rzn = rz + nc;
-    double* pq = rzn + nc;
-    double* rr = pq + nc;
-    // r = b on the free rows; x = 0
-    k_p2_masked_copy<<<g, kBlock, 0, s>>>(N, b, ldb, r_.get(), ns);
-    HINV_LAUNCH_CHECK();
-    k_p2_zero<<<g, kBlock, 0, s>>>(ns, x, ldx);
-    HINV_LAUNCH_CHECK();
-    dots(nc, r_.get(), ns, r_.get(), ns, bb);
-    std::vector<double> hbb(nc), hrr(nc);
-    HINV_HIP(hipMemcpyAsync(hbb.data(), bb, sizeof(double) * nc, hipMemcpyDeviceToHost, s));
-    HINV_HIP(hipStreamSynchronize(s));
-    std::vector<int> hact(nc);
-    int live = 0;
-    bool finite = true;
-    for (int c = 0; c < nc; ++c) {
-        hact[c] = hbb[c] > 0.0 && std::isfinite(hbb[c]);
-        if (!std::isfinite(hbb[c])) finite = false;
-        live += hact[c];
-        hrr[c] = hbb[c];
-    }
-    HINV_HIP(hipMemcpyAsync(act_.get(), hact.data(), sizeof(int) * nc, hipMemcpyHostToDevice, s));
-    int its = 0;
-    if (live) {
-        precondition(nc, r_.get(), ns, z_.get(), ns, coarse);
-        dots(nc, r_.get(), ns, z_.get(), ns, rz);
-        k_p2_pcg_dir<<<g, kBlock, 0, s>>>(ns, rz, rz, z_.get(), p_.get(), ns, 1, act_.get());
-        HINV_LAUNCH_CHECK();
-    }
-    while (live && its < max_iter) {
-        k_p2_apply<<<g, kBlock, 0, s>>>(N, el_, cT_, nullptr, 0, p_.get(), ns, nullptr, 0, 1.0, q_v_.get(), ns,
-                                        act_.get());
-        HINV_LAUNCH_CHECK();
-        dots(nc, p_.get(), ns, q_v_.get(), ns, pq);
-        k_p2_pcg_step<<<g, kBlock, 0, s>>>(ns, rz, pq, x, r_.get(), p_.get(), q_v_.get(), ns, ldx, act_.get());
-        HINV_LAUNCH_CHECK();
-        dots(nc, r_.get(), ns, r_.get(), ns, rr);
-        ++its;
-        HINV_HIP(hipMemcpyAsync(hrr.data(), rr, sizeof(double) * nc, hipMemcpyDeviceToHost, s));
-        HINV_HIP(hipStreamSynchronize(s));
-        bool changed = false;
-        for (int c = 0; c < nc; ++c) {
-            if (!hact[c]) continue;
-            const bool done = !(hrr[c] > rtol * rtol * hbb[c]);  // NaN stops the column too
-            if (!std::isfinite(hrr[c])) finite = false;
-            if (done) {
-                hact[c] = 0;
-                --live;
-                changed = true;
-            }
-        }
-        if (changed) HINV_HIP(hipMemcpyAsync(act_.get(), hact.data(), sizeof(int) * nc, hipMemcpyHostToDevice, s));
-        if (!live) break;
-        precondition(nc, r_.get(), ns, z_.get(), ns, coarse);
-        dots(nc, r_.get(), ns, z_.get(), ns, rzn);
-        k_p2_pcg_dir<<<g, kBlock, 0, s>>>(ns, rzn, rz, z_.get(), p_.get(), ns, 0, act_.get());
-        HINV_LAUNCH_CHECK();
-        std::swap(rz, rzn);
-    }
-    // the pinned host copies of act_ are read by the stream: keep them alive
-    HINV_HIP(hipStreamSynchronize(s));
+    run_solve(nc, b, ldb, x, ldx, coarse, rtol, max_iter);
     double worst = 0.0;
+    bool finite = true;
+    int its = 0, live = 0;
     for (int c = 0; c < nc; ++c) {
-        if (!(hbb[c] > 0.0)) continue;
-        const double rel = std::sqrt(hrr[c] / hbb[c]);
+        const P2Col& h = hst_[c];
+        if (!std::isfinite(h.bb) || !std::isfinite(h.rr)) finite = false;
+        its = std::max(its, h.its);
+        live += h.live;
+        if (!(h.bb > 0.0)) continue;
+        const double rel = std::sqrt(h.rr / h.bb);
         if (!std::isfinite(rel)) finite = false;
         else worst = std::max(worst, rel);
     }
+    last_its_ = std::max(1, its);
     if (!finite) worst = std::numeric_limits<double>::quiet_NaN();
     if (st) {
         st->solves += nc;

@@ -79,6 +79,15 @@ class Hierarchy {
     void apply(int nc, const double* x, int ldx, double* y, int ldy);
     // z = one V-cycle (FP64) applied to r, zero on Dirichlet rows.
     void precondition(int nc, const double* r, int ldr, double* z, int ldz);
+    // The same in place, for a caller whose kernels read and write the cycle's
+    // own vectors: cycle_prepare, then cycle(nc) as often as wanted takes
+    // cycle_in() (zero on Dirichlet rows, ld n()) to cycle_out() for the columns
+    // whose flag in cycle_active() is set (cycle_prepare sets them all).
+    void cycle_prepare(int nc);
+    void cycle(int nc);
+    double* cycle_in() { return w64_.r.get(); }
+    const double* cycle_out() { return w64_.z.get(); }
+    int* cycle_active() { return act_.get(); }
     // Level-0 triangle coefficients c_T (state operator only).
     const double* coefficient(int inst = 0) const {
         return lev_[0]->cT.get() + (size_t)inst * 2 * N_ * N_;

@@ -1490,25 +1490,32 @@ void Hierarchy::apply(int nc, const double* x, int ldx, double* y, int ldy) {
     HINV_LAUNCH_CHECK();
 }
 
-void Hierarchy::precondition(int nc, const double* r, int ldr, double* z, int ldz) {
+void Hierarchy::cycle_prepare(int nc) {
     if (!ready_) fail(HINV_ESTATE, "operator used before its coefficient was set");
-    if (nc <= 0) return;
-    hipStream_t s = ctx_->stream;
     set_columns(nc);
     ensure_cols(nc);
     if (w64_.cap < nc || w32_.cap < nc) drop_graphs();
     ensure_work(w64_, lev_, nc);
     ensure_work(w32_, lev_, nc);
+    k_fill_int<<<ceil_div(nc, 64), 64, 0, ctx_->stream>>>(nc, 1, act_.get());
+    HINV_LAUNCH_CHECK();
+    launch_stream_ = ctx_->stream;
+    tune_shape<double>(nc, false);
+}
+
+void Hierarchy::cycle(int nc) { vcycle<double>(nc, 0, false); }
+
+void Hierarchy::precondition(int nc, const double* r, int ldr, double* z, int ldz) {
+    if (!ready_) fail(HINV_ESTATE, "operator used before its coefficient was set");
+    if (nc <= 0) return;
+    hipStream_t s = ctx_->stream;
+    cycle_prepare(nc);
     const dim3 g = grid2(n_, nc);
     with_op<double>(0, [&](auto op) {
         k_masked_copy<<<g, kBlock, 0, s>>>(op, r, ldr, w64_.r.get(), n_);
     });
     HINV_LAUNCH_CHECK();
-    k_fill_int<<<ceil_div(nc, 64), 64, 0, s>>>(nc, 1, act_.get());
-    HINV_LAUNCH_CHECK();
-    launch_stream_ = s;
-    tune_shape<double>(nc, false);
-    vcycle<double>(nc, 0, false);
+    cycle(nc);
     with_op<double>(0, [&](auto op) {
         k_masked_copy<<<g, kBlock, 0, s>>>(op, w64_.z.get(), n_, z, ldz);
     });
