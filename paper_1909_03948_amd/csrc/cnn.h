@@ -41,16 +41,15 @@ class Cnn {
     double train_step(int B, int S, const float* in, const float* target, int tchan, float lr);
 
     // Pre-packed path for the solver: the input buffer (bf16, 16 channels)
-    // for one S x S image, the network run on it, and its FP32 output
-    // (16 channels, channel 0 meaningful).
+    // for one S x S image, the network run on it, and its planar FP32 output.
     short* packed_input(int S);
     void forward_packed(int B, int S);
-    const float* packed_output() const { return z_[kLayers - 1].get(); }
+    const float* packed_output() const { return y_.get(); }
 
   private:
     void ensure(int B, int S);
     void refresh_weights();
-    void run_forward(int B, int S);
+    void run_forward(int B, int S, float* y);
 
     Ctx* ctx_;
     DBuf<float> theta_, grad_, m_, v_;
@@ -58,7 +57,8 @@ class Cnn {
     bool weights_fresh_ = false;
     DBuf<short> wf_[kLayers], wb_[kLayers];  // forward [9][co][ci], backward [9][ci][co] (flipped)
     DBuf<short> in0_, a_[kLayers - 1], dz_[2], gy_;
-    DBuf<float> z_[kLayers], h_[kLayers - 1], gh_[2], part_, loss_;
+    DBuf<float> y_, h_[kLayers - 1], gh_[2], part_, loss_;
+    DBuf<unsigned> mask_[kLayers - 1];  // [z > 0] of each lane's 32 results of a hidden layer
     DBuf<double> lpart_, ratio_, dwtmp_;
     int B_ = 0, S_ = 0, nwg_ = 0;
 };

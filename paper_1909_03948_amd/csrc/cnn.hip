@@ -104,99 +104,154 @@ __global__ void k_pack_input(int B, int S, const float* __restrict__ in, short* 
         o[c] = c < Cnn::kInCh ? bf16_bits(in[(b * Cnn::kInCh + c) * np + p]) : (short)0;
 }
 
-// Channel 0 of a 16-channel FP32 image -> planar [B][S][S].
-__global__ void k_unpack_output(long long npix, const float* __restrict__ y, float* __restrict__ out) {
-    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id < npix) out[id] = y[id * Cnn::kPadIn];
-}
-
 // Convolution with fused epilogue.  Grid: (tiles x, tiles y, images).
 //   EPI_RELU:     z = conv + b; h = relu(z)
 //   EPI_RELU_RES: z = conv + b; h = res + relu(z)
-//   EPI_LINEAR:   z = conv + b
-//   EPI_BWD:      g = conv + res (res optional); out16 = bf16(g * [zmask > 0])
+//   EPI_LINEAR:   z = conv + b, channel 0 only (the one real channel), planar
+//   EPI_BWD:      g = conv + res (res optional); out16 = bf16(g * [z > 0])
+// The weights are operand A and the pixels operand B, so a lane's results are
+// four consecutive channels of one pixel: the epilogue moves 16 bytes a lane.
+// [z > 0] is all the backward pass needs of z: a lane's 32 results give one
+// word, which the backward kernel's lane of the same place reads (mask).
+// Bound by the traffic of h, its BF16 copy and the residual (about 50 MB a layer at
+// 32 images of 64 x 64: ~10 us); the residual is requested before the products,
+// and the LDS pixel stride of 80 bytes keeps 16-byte reads of 16 neighbouring
+// pixels off each other's banks.  Keeping z itself in FP32, with 4-byte
+// accesses, took 25.5 us a layer forward and 29.5 backward there, this 11.7
+// and 11.3.
 template <int CI, int CO, int EPI>
 __global__ __launch_bounds__(256) void k_conv(int S, const short* __restrict__ in, const short* __restrict__ w,
-                                              const float* __restrict__ bias, int co_real,
-                                              const float* __restrict__ res, const float* __restrict__ zmask,
-                                              float* __restrict__ zout, float* __restrict__ out32,
+                                              const float* __restrict__ bias, const float* __restrict__ res,
+                                              unsigned* __restrict__ mask, float* __restrict__ out32,
                                               short* __restrict__ out16) {
-    __shared__ __attribute__((aligned(16))) short sin[kH * kH * CI];
-    __shared__ __attribute__((aligned(16))) short sw[9 * CO * CI];
+    constexpr int PS = CI == 32 ? 40 : CI;  // LDS stride of a pixel / weight row
+    constexpr int CQ = CI / 8;              // 16-byte pieces of it
+    constexpr int NI = kH * kH * CQ, NW = 9 * CO * CQ;
+    __shared__ __attribute__((aligned(16))) short sin[kH * kH * PS];
+    __shared__ __attribute__((aligned(16))) short sw[9 * CO * PS];
     const int tx0 = blockIdx.x * kT, ty0 = blockIdx.y * kT, b = blockIdx.z;
-    for (int e = threadIdx.x; e < 9 * CO * CI / 4; e += blockDim.x)
-        reinterpret_cast<long long*>(sw)[e] = reinterpret_cast<const long long*>(w)[e];
-    for (int e = threadIdx.x; e < kH * kH * (CI / 4); e += blockDim.x) {
-        const int pix = e / (CI / 4), q = e % (CI / 4);
-        const int gy = ty0 + pix / kH - 1, gx = tx0 + pix % kH - 1;
-        long long v = 0;
-        if (gy >= 0 && gy < S && gx >= 0 && gx < S)
-            v = reinterpret_cast<const long long*>(in + (((size_t)b * S + gy) * S + gx) * CI)[q];
-        reinterpret_cast<long long*>(sin)[e] = v;
-    }
-    __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int pi = lane & 15, kq = (lane >> 4) * 4;
     constexpr int NT = CO / 16;
+    {
+        s8_t vi[(NI + 255) / 256], vw[(NW + 255) / 256];
+#pragma unroll
+        for (int u = 0; u < (NI + 255) / 256; ++u) {
+            const int e = threadIdx.x + 256 * u, pix = e / CQ, q = e % CQ;
+            const int gy = ty0 + pix / kH - 1, gx = tx0 + pix % kH - 1;
+            vi[u] = s8_t{0, 0, 0, 0, 0, 0, 0, 0};
+            if (e < NI && gy >= 0 && gy < S && gx >= 0 && gx < S)
+                vi[u] = reinterpret_cast<const s8_t*>(in + (((size_t)b * S + gy) * S + gx) * CI)[q];
+        }
+#pragma unroll
+        for (int u = 0; u < (NW + 255) / 256; ++u)
+            vw[u] = reinterpret_cast<const s8_t*>(w)[min((int)threadIdx.x + 256 * u, NW - 1)];
+#pragma unroll
+        for (int u = 0; u < (NI + 255) / 256; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            if (e < NI) *reinterpret_cast<s8_t*>(sin + e / CQ * PS + e % CQ * 8) = vi[u];
+        }
+#pragma unroll
+        for (int u = 0; u < (NW + 255) / 256; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            if (e < NW) *reinterpret_cast<s8_t*>(sw + e / CQ * PS + e % CQ * 8) = vw[u];
+        }
+    }
+    // this lane's results: pixel (gx, gy0 + r), channels nt * 16 + kq + v
+    const int gx = tx0 + pi, gy0 = ty0 + wave * 4;
+    auto at = [&](int r, int nt) { return (((size_t)b * S + gy0 + r) * S + gx) * CO + nt * 16 + kq; };
+    f4_t rs[4][NT];
+    if constexpr (EPI == EPI_RELU_RES || EPI == EPI_BWD) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                rs[r][nt] = f4_t{0.f, 0.f, 0.f, 0.f};
+                if (res && gx < S && gy0 + r < S) rs[r][nt] = *reinterpret_cast<const f4_t*>(res + at(r, nt));
+            }
+    }
+    const size_t mo = (((size_t)b * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+    unsigned mk = EPI == EPI_BWD ? mask[mo] : 0u;
+    __syncthreads();
     f4_t acc[4][NT];
+#pragma unroll
     for (int r = 0; r < 4; ++r)
+#pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[r][nt] = f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
     for (int t = 0; t < 9; ++t) {
         const int dy = t / 3, dx = t % 3;
-        if constexpr (CI % 32 == 0) {
+        if constexpr (CI == 32) {
             const int k8 = (lane >> 4) * 8;
-            for (int c0 = 0; c0 < CI; c0 += 32) {
-                s8_t bw[NT];
-                for (int nt = 0; nt < NT; ++nt)
-                    bw[nt] = *reinterpret_cast<const s8_t*>(sw + (t * CO + nt * 16 + pi) * CI + c0 + k8);
-                for (int r = 0; r < 4; ++r) {
-                    const int ly = wave * 4 + r + dy, lx = pi + dx;
-                    const s8_t a = *reinterpret_cast<const s8_t*>(sin + (ly * kH + lx) * CI + c0 + k8);
-                    for (int nt = 0; nt < NT; ++nt) acc[r][nt] = mfma_k32(a, bw[nt], acc[r][nt]);
-                }
+            s8_t aw[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                aw[nt] = *reinterpret_cast<const s8_t*>(sw + (t * CO + nt * 16 + pi) * PS + k8);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const s8_t px = *reinterpret_cast<const s8_t*>(sin + ((wave * 4 + r + dy) * kH + pi + dx) * PS + k8);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[r][nt] = mfma_k32(aw[nt], px, acc[r][nt]);
             }
         } else {
-            for (int c0 = 0; c0 < CI; c0 += 16) {
-                s4_t bw[NT];
+            static_assert(CI == 16, "16 or 32 input channels");
+            s4_t aw[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                aw[nt] = *reinterpret_cast<const s4_t*>(sw + (t * CO + nt * 16 + pi) * PS + kq);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const s4_t px = *reinterpret_cast<const s4_t*>(sin + ((wave * 4 + r + dy) * kH + pi + dx) * PS + kq);
+#pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    bw[nt] = *reinterpret_cast<const s4_t*>(sw + (t * CO + nt * 16 + pi) * CI + c0 + kq);
-                for (int r = 0; r < 4; ++r) {
-                    const int ly = wave * 4 + r + dy, lx = pi + dx;
-                    const s4_t a = *reinterpret_cast<const s4_t*>(sin + (ly * kH + lx) * CI + c0 + kq);
-                    for (int nt = 0; nt < NT; ++nt)
-                        acc[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bw[nt], acc[r][nt], 0, 0, 0);
-                }
+                    acc[r][nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(aw[nt], px, acc[r][nt], 0, 0, 0);
             }
         }
     }
+    if constexpr (EPI == EPI_LINEAR) {
+        const float b0 = bias[0];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (kq == 0 && gx < S && gy0 + r < S) out32[((size_t)b * S + gy0 + r) * S + gx] = acc[r][0][0] + b0;
+        return;
+    }
+    float bc[NT][4];
+    if constexpr (EPI == EPI_RELU || EPI == EPI_RELU_RES) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) bc[nt][v] = bias[nt * 16 + kq + v];
+    }
+#pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int gy = ty0 + wave * 4 + r;
-        if (gy >= S) continue;
+#pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            const int co = nt * 16 + pi;
-            const float bco = (EPI != EPI_BWD && co < co_real) ? bias[co] : 0.f;
+            f4_t o32;
+            s4_t o16;
+#pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int gx = tx0 + kq + v;
-                if (gx >= S) continue;
-                const size_t o = (((size_t)b * S + gy) * S + gx) * CO + co;
+                const unsigned bit = 1u << ((r * NT + nt) * 4 + v);
                 const float val = acc[r][nt][v];
-                if constexpr (EPI == EPI_RELU || EPI == EPI_RELU_RES) {
-                    const float z = val + bco;
-                    zout[o] = z;
-                    float h = fmaxf(z, 0.f);
-                    if constexpr (EPI == EPI_RELU_RES) h += res[o];
-                    out32[o] = h;
-                    out16[o] = bf16_bits(h);
-                } else if constexpr (EPI == EPI_LINEAR) {
-                    zout[o] = val + bco;
+                if constexpr (EPI == EPI_BWD) {
+                    const float g = val + rs[r][nt][v];
+                    o32[v] = g;
+                    o16[v] = bf16_bits(mk & bit ? g : 0.f);
                 } else {
-                    const float g = val + (res ? res[o] : 0.f);
-                    out32[o] = g;
-                    out16[o] = bf16_bits(zmask[o] > 0.f ? g : 0.f);
+                    const float z = val + bc[nt][v];
+                    if (z > 0.f) mk |= bit;
+                    float h = fmaxf(z, 0.f);
+                    if constexpr (EPI == EPI_RELU_RES) h += rs[r][nt][v];
+                    o32[v] = h;
+                    o16[v] = bf16_bits(h);
                 }
+            }
+            if (gx < S && gy0 + r < S) {
+                *reinterpret_cast<f4_t*>(out32 + at(r, nt)) = o32;
+                *reinterpret_cast<s4_t*>(out16 + at(r, nt)) = o16;
             }
         }
     }
+    if constexpr (EPI != EPI_BWD) mask[mo] = mk;
 }
 
 // Weight and bias gradients of one layer, per tile: part[wg][t][co][ci] =
@@ -295,7 +350,7 @@ __global__ void k_loss_part(long long np, const float* __restrict__ y, const flo
     const int b = blockIdx.y;
     double num = 0.0, den = 0.0;
     for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < np; p += (long long)gridDim.x * blockDim.x) {
-        const double yv = y[((size_t)b * np + p) * Cnn::kPadIn], tv = tg[(size_t)b * np + p];
+        const double yv = y[(size_t)b * np + p], tv = tg[(size_t)b * np + p];
         num += (yv - tv) * (yv - tv);
         den += tv * tv;
     }
@@ -328,7 +383,7 @@ __global__ void k_loss_grad(int B, long long np, int nchunk, const float* __rest
     if (blockIdx.x == 0 && threadIdx.x == 0) ratio[b] = den > 0 ? num / den : 0.0;
     const long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= np) return;
-    const double yv = y[((size_t)b * np + p) * Cnn::kPadIn], tv = tg[(size_t)b * np + p];
+    const double yv = y[(size_t)b * np + p], tv = tg[(size_t)b * np + p];
     const float g = den > 0 ? (float)(2.0 * (yv - tv) / (den * B)) : 0.f;
     short* o = gy + ((size_t)b * np + p) * Cnn::kPadIn;
     o[0] = bf16_bits(g);
@@ -352,7 +407,7 @@ __device__ inline EnergyPix energy_at(int S, long long b, int row, int col, cons
     const float* mk = in + (b * Cnn::kInCh + 2) * np;
     auto dv = [&](int r, int c) -> double {
         const long long p = (long long)r * S + c;
-        return ((double)y[(b * np + p) * Cnn::kPadIn] - (double)t[p]) * (double)mk[p];
+        return ((double)y[b * np + p] - (double)t[p]) * (double)mk[p];
     };
     auto tv = [&](int r, int c) -> double {
         const long long p = (long long)r * S + c;
@@ -512,12 +567,13 @@ void Cnn::ensure(int B, int S) {
             a_[l].ensure(np * kCh);
             h_[l].ensure(np * kCh);
         }
-        for (int l = 0; l < kLayers; ++l) z_[l].ensure(np * (l == kLayers - 1 ? kPadIn : kCh));
+        y_.ensure(np);
         for (int i = 0; i < 2; ++i) {
             dz_[i].ensure(np * kCh);
             gh_[i].ensure(np * kCh);
         }
         gy_.ensure(np * kPadIn);
+        for (auto& m : mask_) m.ensure((size_t)nwg * 256);
         part_.ensure((size_t)nwg * kWgStride);
         B_ = B;
         S_ = S;
@@ -525,25 +581,23 @@ void Cnn::ensure(int B, int S) {
     }
 }
 
-void Cnn::run_forward(int B, int S) {
+void Cnn::run_forward(int B, int S, float* y) {
     refresh_weights();
     const LayerDesc* L = layers();
     hipStream_t s = ctx_->stream;
-    const int tiles = ceil_div(S, kT);
+    const int tiles = ceil_div(S, kT), top = kLayers - 1;
     const dim3 g(tiles, tiles, B);
     const float* th = theta_.get();
-    k_conv<16, 32, EPI_RELU><<<g, 256, 0, s>>>(S, in0_.get(), wf_[0].get(), th + L[0].boff, L[0].co, nullptr,
-                                                nullptr, z_[0].get(), h_[0].get(), a_[0].get());
+    k_conv<16, 32, EPI_RELU><<<g, 256, 0, s>>>(S, in0_.get(), wf_[0].get(), th + L[0].boff, nullptr, mask_[0].get(),
+                                                h_[0].get(), a_[0].get());
     HINV_LAUNCH_CHECK();
-    for (int l = 1; l < kLayers - 1; ++l) {
-        k_conv<32, 32, EPI_RELU_RES><<<g, 256, 0, s>>>(S, a_[l - 1].get(), wf_[l].get(), th + L[l].boff, L[l].co,
-                                                        h_[l - 1].get(), nullptr, z_[l].get(), h_[l].get(),
-                                                        a_[l].get());
+    for (int l = 1; l < top; ++l) {
+        k_conv<32, 32, EPI_RELU_RES><<<g, 256, 0, s>>>(S, a_[l - 1].get(), wf_[l].get(), th + L[l].boff,
+                                                        h_[l - 1].get(), mask_[l].get(), h_[l].get(), a_[l].get());
         HINV_LAUNCH_CHECK();
     }
-    k_conv<32, 16, EPI_LINEAR><<<g, 256, 0, s>>>(S, a_[kLayers - 2].get(), wf_[kLayers - 1].get(),
-                                                  th + L[kLayers - 1].boff, L[kLayers - 1].co, nullptr, nullptr,
-                                                  z_[kLayers - 1].get(), nullptr, nullptr);
+    k_conv<32, 16, EPI_LINEAR><<<g, 256, 0, s>>>(S, a_[top - 1].get(), wf_[top].get(), th + L[top].boff, nullptr,
+                                                  nullptr, y, nullptr);
     HINV_LAUNCH_CHECK();
 }
 
@@ -553,9 +607,7 @@ void Cnn::forward(int B, int S, const float* in, float* out) {
     k_pack_input<<<(unsigned)ceil_div((int)std::min<long long>(np, 1LL << 30), 256), 256, 0, ctx_->stream>>>(
         B, S, in, in0_.get());
     HINV_LAUNCH_CHECK();
-    run_forward(B, S);
-    k_unpack_output<<<(unsigned)ceil_div((int)np, 256), 256, 0, ctx_->stream>>>(np, z_[kLayers - 1].get(), out);
-    HINV_LAUNCH_CHECK();
+    run_forward(B, S, out);
 }
 
 short* Cnn::packed_input(int S) {
@@ -565,7 +617,7 @@ short* Cnn::packed_input(int S) {
 
 void Cnn::forward_packed(int B, int S) {
     ensure(B, S);
-    run_forward(B, S);
+    run_forward(B, S, y_.get());
 }
 
 double Cnn::gradient(int B, int S, const float* in, const float* target, int tchan, float* grad_host) {
@@ -574,20 +626,20 @@ double Cnn::gradient(int B, int S, const float* in, const float* target, int tch
     const long long np = (long long)S * S;
     k_pack_input<<<(unsigned)ceil_div((int)(np * B), 256), 256, 0, s>>>(B, S, in, in0_.get());
     HINV_LAUNCH_CHECK();
-    run_forward(B, S);
+    run_forward(B, S, y_.get());
     // loss and dL/dy
     const int nchunk = std::min(64, ceil_div((int)np, 256));
     lpart_.ensure((size_t)2 * B * nchunk);
     ratio_.ensure(B);
     if (tchan == 1) {
-        k_loss_part<<<dim3(nchunk, B), 256, 0, s>>>(np, z_[kLayers - 1].get(), target, lpart_.get());
+        k_loss_part<<<dim3(nchunk, B), 256, 0, s>>>(np, y_.get(), target, lpart_.get());
         HINV_LAUNCH_CHECK();
-        k_loss_grad<<<dim3(ceil_div((int)np, 256), B), 256, 0, s>>>(B, np, nchunk, z_[kLayers - 1].get(), target,
+        k_loss_grad<<<dim3(ceil_div((int)np, 256), B), 256, 0, s>>>(B, np, nchunk, y_.get(), target,
                                                                      lpart_.get(), gy_.get(), ratio_.get());
     } else {
-        k_energy_part<<<dim3(nchunk, B), 256, 0, s>>>(S, z_[kLayers - 1].get(), target, in, lpart_.get());
+        k_energy_part<<<dim3(nchunk, B), 256, 0, s>>>(S, y_.get(), target, in, lpart_.get());
         HINV_LAUNCH_CHECK();
-        k_energy_grad<<<dim3(ceil_div((int)np, 256), B), 256, 0, s>>>(B, S, nchunk, z_[kLayers - 1].get(), target,
+        k_energy_grad<<<dim3(ceil_div((int)np, 256), B), 256, 0, s>>>(B, S, nchunk, y_.get(), target,
                                                                        in, lpart_.get(), gy_.get(), ratio_.get());
     }
     HINV_LAUNCH_CHECK();
@@ -611,8 +663,8 @@ double Cnn::gradient(int B, int S, const float* in, const float* target, int tch
     HINV_LAUNCH_CHECK();
     reduce(top);
     // dL/dh4 and dZ4 = dL/dh4 * [z4 > 0]
-    k_conv<16, 32, EPI_BWD><<<g, 256, 0, s>>>(S, gy_.get(), wb_[top].get(), nullptr, 0, nullptr,
-                                               z_[top - 1].get(), nullptr, gh_[0].get(), dz_[0].get());
+    k_conv<16, 32, EPI_BWD><<<g, 256, 0, s>>>(S, gy_.get(), wb_[top].get(), nullptr, nullptr,
+                                               mask_[top - 1].get(), gh_[0].get(), dz_[0].get());
     HINV_LAUNCH_CHECK();
     int cur = 0;
     for (int l = top - 1; l >= 1; --l) {
@@ -620,9 +672,8 @@ double Cnn::gradient(int B, int S, const float* in, const float* target, int tch
         HINV_LAUNCH_CHECK();
         reduce(l);
         // dL/dh_{l-1} = conv^T(dZ_l) + dL/dh_l (identity path), dZ_{l-1}
-        k_conv<32, 32, EPI_BWD><<<g, 256, 0, s>>>(S, dz_[cur].get(), wb_[l].get(), nullptr, 0, gh_[cur].get(),
-                                                   z_[l - 1].get(), nullptr, gh_[1 - cur].get(),
-                                                   dz_[1 - cur].get());
+        k_conv<32, 32, EPI_BWD><<<g, 256, 0, s>>>(S, dz_[cur].get(), wb_[l].get(), nullptr, gh_[cur].get(),
+                                                   mask_[l - 1].get(), gh_[1 - cur].get(), dz_[1 - cur].get());
         HINV_LAUNCH_CHECK();
         cur = 1 - cur;
     }

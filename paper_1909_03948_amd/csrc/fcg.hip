@@ -39,7 +39,7 @@ __global__ void k_fcg_correction(int N, const float* __restrict__ y, double s, d
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= N1 * N1) return;
     const int j = k / N1;
-    cv[k] = (j > 0 && j < N) ? s * (double)y[(size_t)k * Cnn::kPadIn] : 0.0;
+    cv[k] = (j > 0 && j < N) ? s * (double)y[k] : 0.0;
 }
 
 // y = a x + b y on free nodes, 0 on Dirichlet rows (column blockIdx.y).
