@@ -56,7 +56,7 @@ class Cnn {
     int step_ = 0;
     bool weights_fresh_ = false;
     DBuf<short> wf_[kLayers], wb_[kLayers];  // forward [9][co][ci], backward [9][ci][co] (flipped)
-    DBuf<short> in0_, a_[kLayers - 1], dz_[2], gy_;
+    DBuf<short> in0_, a_[kLayers - 1], dz_[kLayers - 1], gy_;
     DBuf<float> y_, h_[kLayers - 1], gh_[2], part_, loss_;
     DBuf<unsigned> mask_[kLayers - 1];  // [z > 0] of each lane's 32 results of a hidden layer
     DBuf<double> lpart_, ratio_, dwtmp_;

@@ -254,93 +254,161 @@ __global__ __launch_bounds__(256) void k_conv(int S, const short* __restrict__ i
     if constexpr (EPI != EPI_BWD) mask[mo] = mk;
 }
 
-// Weight and bias gradients of one layer, per tile: part[wg][t][co][ci] =
-// sum over the tile's pixels p of dz[p][co] in[p + tap t][ci]; part[wg][9 CO CI + co]
-// = sum_p dz[p][co].
-template <int CI, int CO>
-__global__ __launch_bounds__(256) void k_conv_dw(int S, const short* __restrict__ in, const short* __restrict__ dz,
-                                                 float* __restrict__ part) {
-    __shared__ short sin[kH * kH * CI];
-    __shared__ short sdz[kT * kT * CO];
-    const int tx0 = blockIdx.x * kT, ty0 = blockIdx.y * kT, b = blockIdx.z;
-    const size_t wg = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    for (int e = threadIdx.x; e < kH * kH * (CI / 4); e += blockDim.x) {
-        const int pix = e / (CI / 4), q = e % (CI / 4);
-        const int gy = ty0 + pix / kH - 1, gx = tx0 + pix % kH - 1;
-        long long v = 0;
-        if (gy >= 0 && gy < S && gx >= 0 && gx < S)
-            v = reinterpret_cast<const long long*>(in + (((size_t)b * S + gy) * S + gx) * CI)[q];
-        reinterpret_cast<long long*>(sin)[e] = v;
-    }
-    for (int e = threadIdx.x; e < kT * kT * (CO / 4); e += blockDim.x) {
-        const int pix = e / (CO / 4), q = e % (CO / 4);
-        const int gy = ty0 + pix / kT, gx = tx0 + pix % kT;
-        long long v = 0;
-        if (gy < S && gx < S)
-            v = reinterpret_cast<const long long*>(dz + (((size_t)b * S + gy) * S + gx) * CO)[q];
-        reinterpret_cast<long long*>(sdz)[e] = v;
-    }
-    __syncthreads();
-    float* pw = part + wg * kWgStride;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int pi = lane & 15, kq = (lane >> 4) * 4;
-    constexpr int NCO = CO / 16, NCI = CI / 16, NTILE = 9 * NCO * NCI;
-    for (int tile = wave; tile < NTILE; tile += 4) {
-        const int t = tile / (NCO * NCI), cot = (tile / NCI) % NCO, cit = tile % NCI;
-        const int dy = t / 3, dx = t % 3;
-        f4_t acc = {0.f, 0.f, 0.f, 0.f};
-        // K = the tile's pixels, 32 (two rows) per step: pixel 32 st + 8 (l / 16) + e
-        const int k8 = (lane >> 4) * 8;
-        for (int st = 0; st < kT * kT / 32; ++st) {
-            const int p0 = 32 * st + k8, rr = p0 / kT, cc = p0 % kT;
-            s8_t a, bb;
-            for (int e = 0; e < 8; ++e) {
-                a[e] = sdz[(p0 + e) * CO + cot * 16 + pi];
-                bb[e] = sin[((rr + dy) * kH + cc + e + dx) * CI + cit * 16 + pi];
-            }
-            acc = mfma_k32(a, bb, acc);
-        }
-        for (int v = 0; v < 4; ++v) {
-            const int co = cot * 16 + kq + v, ci = cit * 16 + pi;
-            pw[(t * CO + co) * CI + ci] = acc[v];
-        }
-    }
-    for (int co = threadIdx.x; co < CO; co += blockDim.x) {
-        float s = 0.f;
-        for (int p = 0; p < kT * kT; ++p) s += bf16_value(sdz[p * CO + co]);
-        pw[9 * CO * CI + co] = s;
-    }
+// Four BF16 values of a channel for a lane: a transposing LDS read.  Lane j of
+// each 16 gives the address of pixel j / 4 and channels 4 (j % 4) .. + 3, and
+// receives channel j of the four pixels.
+__device__ inline s4_t read_tr(const short* p) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4_t*)p);
 }
 
-// Sum of the per-tile partials (fixed order) into the packed gradient of a layer.
+// Layers of one shape whose gradients one launch takes.
+struct DwArgs {
+    const short* in[4];
+    const short* dz[4];
+};
+
+// Weight and bias gradients per tile: part[layer][wg][t][co][ci] = sum over
+// the tile's pixels p of dz[p][co] in[p + tap t][ci]; then
+// part[layer][wg][9 CO CI + co] = sum_p dz[p][co].  Grid: (tiles x, tiles y,
+// images x layers).  The products run over pixels, which LDS holds as rows of
+// channels, so the operands come through transposing reads (16 LDS reads of
+// two bytes an operand without them); a wave keeps its taps' tiles in
+// registers and shares dz between them, and the bias is a product with ones.
+// Bound by LDS reads (~70 wave reads of 512 bytes a wave) and the partials'
+// 37 KB a tile.  The LDS pixel stride of 96 bytes spreads 8 pixels' 32-byte
+// pieces over all banks.  32 images of 64 x 64, 32 channels: 23.2 us a layer
+// with two-byte reads and a layer a launch, this 35.5 for four.
+template <int CI, int CO>
+__global__ __launch_bounds__(256) void k_conv_dw(int S, int B, DwArgs args, float* __restrict__ part) {
+    constexpr int PI = CI == 32 ? 48 : CI, PO = CO == 32 ? 48 : CO;  // LDS strides of a pixel
+    constexpr int QI = CI / 8, QO = CO / 8;
+    constexpr int NI = kH * kH * QI, NO = kT * kT * QO;
+    __shared__ __attribute__((aligned(16))) short sin[kH * kH * PI];
+    __shared__ __attribute__((aligned(16))) short sdz[kT * kT * PO];
+    const int layer = blockIdx.z / B, b = blockIdx.z - layer * B;
+    const int tx0 = blockIdx.x * kT, ty0 = blockIdx.y * kT;
+    const size_t wg = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const short *in = args.in[layer], *dz = args.dz[layer];
+    {
+        s8_t vi[(NI + 255) / 256], vo[NO / 256];
+#pragma unroll
+        for (int u = 0; u < (NI + 255) / 256; ++u) {
+            const int e = threadIdx.x + 256 * u, pix = e / QI, q = e % QI;
+            const int gy = ty0 + pix / kH - 1, gx = tx0 + pix % kH - 1;
+            vi[u] = s8_t{0, 0, 0, 0, 0, 0, 0, 0};
+            if (e < NI && gy >= 0 && gy < S && gx >= 0 && gx < S)
+                vi[u] = reinterpret_cast<const s8_t*>(in + (((size_t)b * S + gy) * S + gx) * CI)[q];
+        }
+#pragma unroll
+        for (int u = 0; u < NO / 256; ++u) {
+            const int e = threadIdx.x + 256 * u, pix = e / QO, q = e % QO;
+            const int gy = ty0 + pix / kT, gx = tx0 + pix % kT;
+            vo[u] = s8_t{0, 0, 0, 0, 0, 0, 0, 0};
+            if (gy < S && gx < S) vo[u] = reinterpret_cast<const s8_t*>(dz + (((size_t)b * S + gy) * S + gx) * CO)[q];
+        }
+#pragma unroll
+        for (int u = 0; u < (NI + 255) / 256; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            if (e < NI) *reinterpret_cast<s8_t*>(sin + e / QI * PI + e % QI * 8) = vi[u];
+        }
+#pragma unroll
+        for (int u = 0; u < NO / 256; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            *reinterpret_cast<s8_t*>(sdz + e / QO * PO + e % QO * 8) = vo[u];
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int pi = lane & 15, kq = (lane >> 4) * 4;
+    // wave w: 16 input channels cit, taps t0 .. t0 + ntap - 1, all output
+    // channels; the waves with fewer taps take the bias of 16 output channels
+    constexpr int NCO = CO / 16, NCI = CI / 16, MT = NCI == 2 ? 5 : 3;
+    const int cit = NCI == 2 ? wave & 1 : 0;
+    const int t0 = NCI == 2 ? (wave >> 1) * 5 : (wave ? 2 * wave + 1 : 0);
+    const int ntap = NCI == 2 ? 5 - (wave >> 1) : (wave ? 2 : 3);
+    const int bt = NCI == 2 ? wave - 2 : wave - 1;  // its bias tile
+    const bool bias = bt >= 0 && bt < NCO;
+    f4_t acc[MT][NCO], accb = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < MT; ++q)
+#pragma unroll
+        for (int c = 0; c < NCO; ++c) acc[q][c] = f4_t{0.f, 0.f, 0.f, 0.f};
+    constexpr short kOne = 0x3f80;
+    const s8_t ones = {kOne, kOne, kOne, kOne, kOne, kOne, kOne, kOne};
+    // K = the tile's pixels, 32 (two rows) per step: pixel 32 st + 8 (l / 16) + e;
+    // this lane addresses pixels + pi / 4 (e < 4) and + 4 + pi / 4
+    const int p8 = (lane >> 4) * 8 + (pi >> 2), ch = (pi & 3) * 4;
+    const short* dzp = sdz + p8 * PO + ch;
+    const short* inp = sin + (p8 / kT * kH + p8 % kT) * PI + cit * 16 + ch;
+    auto join = [](s4_t lo, s4_t hi) { return s8_t{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]}; };
+#pragma unroll 2
+    for (int st = 0; st < kT * kT / 32; ++st) {
+        s8_t a[NCO];
+#pragma unroll
+        for (int c = 0; c < NCO; ++c)
+            a[c] = join(read_tr(dzp + 32 * st * PO + c * 16), read_tr(dzp + (32 * st + 4) * PO + c * 16));
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+            if (q >= ntap) break;
+            const int t = t0 + q, dy = t / 3, dx = t - 3 * dy;
+            const short* ip = inp + ((2 * st + dy) * kH + dx) * PI;
+            const s8_t x = join(read_tr(ip), read_tr(ip + 4 * PI));
+#pragma unroll
+            for (int c = 0; c < NCO; ++c) acc[q][c] = mfma_k32(a[c], x, acc[q][c]);
+        }
+        if (bias) accb = mfma_k32(NCO == 1 || bt == 0 ? a[0] : a[NCO - 1], ones, accb);
+    }
+    float* pw = part + wg * kWgStride;
+#pragma unroll
+    for (int q = 0; q < MT; ++q) {
+        if (q >= ntap) break;
+#pragma unroll
+        for (int c = 0; c < NCO; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                pw[((t0 + q) * CO + c * 16 + kq + v) * CI + cit * 16 + pi] = acc[q][c][v];
+    }
+    if (bias && pi == 0)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pw[9 * CO * CI + bt * 16 + kq + v] = accb[v];
+}
+
 // Weight and bias gradients from the per-tile partials, in two fixed-order
 // stages that read the partials coalesced (index j runs over one tile's
 // partial layout [t][co][ci] then the biases):
-//   tmp[sp][j] = sum over the tiles of split sp of part[tile][j],
+//   tmp[layer][sp][j] = sum over the tiles of split sp of part[layer][tile][j],
 //   then the kDwSplit sums in order, scattered into the packed gradient.
+// Every layer in one launch (grid.z; l0: the first one, its partials at part).
 constexpr int kDwSplit = 16;
-__global__ void k_dw_partial(int nwg, int J, const float* __restrict__ part, double* __restrict__ tmp) {
+struct DwLayers {
+    int J[Cnn::kLayers];
+    int co[Cnn::kLayers], ci[Cnn::kLayers], COp[Cnn::kLayers], CIp[Cnn::kLayers], woff[Cnn::kLayers],
+        boff[Cnn::kLayers];
+};
+__global__ void k_dw_partial(int nwg, int l0, DwLayers L, const float* __restrict__ part, double* __restrict__ tmp) {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int sp = blockIdx.y;
-    if (j >= J) return;
+    const int sp = blockIdx.y, l = l0 + blockIdx.z;
+    if (j >= L.J[l]) return;
     const int g0 = (int)((long long)sp * nwg / kDwSplit), g1 = (int)((long long)(sp + 1) * nwg / kDwSplit);
+    const float* p = part + (size_t)blockIdx.z * nwg * kWgStride + j;
     double s = 0.0;
-    for (int g = g0; g < g1; ++g) s += part[(size_t)g * kWgStride + j];
-    tmp[(size_t)sp * J + j] = s;
+#pragma unroll 8
+    for (int g = g0; g < g1; ++g) s += p[(size_t)g * kWgStride];
+    tmp[((size_t)l * kDwSplit + sp) * kWgStride + j] = s;
 }
 
-__global__ void k_dw_reduce(int J, int co_r, int ci_r, int COp, int CIp, const double* __restrict__ tmp,
-                            float* __restrict__ gW, float* __restrict__ gb) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= J) return;
+__global__ void k_dw_reduce(DwLayers L, const double* __restrict__ tmp, float* __restrict__ grad) {
+    const int j = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.y;
+    if (j >= L.J[l]) return;
     double s = 0.0;
-    for (int sp = 0; sp < kDwSplit; ++sp) s += tmp[(size_t)sp * J + j];
-    const int nw = 9 * COp * CIp;
+#pragma unroll
+    for (int sp = 0; sp < kDwSplit; ++sp) s += tmp[((size_t)l * kDwSplit + sp) * kWgStride + j];
+    const int COp = L.COp[l], CIp = L.CIp[l], nw = 9 * COp * CIp;
     if (j < nw) {
         const int t = j / (COp * CIp), r = j - t * COp * CIp, co = r / CIp, ci = r - co * CIp;
-        if (co < co_r && ci < ci_r) gW[(co * ci_r + ci) * 9 + t] = (float)s;
-    } else if (j - nw < co_r) {
-        gb[j - nw] = (float)s;
+        if (co < L.co[l] && ci < L.ci[l]) grad[L.woff[l] + (co * L.ci[l] + ci) * 9 + t] = (float)s;
+    } else if (j - nw < L.co[l]) {
+        grad[L.boff[l] + j - nw] = (float)s;
     }
 }
 
@@ -555,6 +623,11 @@ void Cnn::refresh_weights() {
     weights_fresh_ = true;
 }
 
+// Whether the partials of every layer's gradient are kept until one launch
+// sums them: while they take at most 512 MB (2400 tiles), where a launch a
+// layer would be mostly latency; beyond, layer after layer reuses the space.
+static bool dw_together(int nwg) { return (size_t)nwg * kWgStride * sizeof(float) * Cnn::kLayers <= (512u << 20); }
+
 void Cnn::ensure(int B, int S) {
     if (B <= 0 || S <= 0) fail(HINV_EINVAL, "empty image batch");
     if (S > 8193) fail(HINV_EINVAL, "image side above 8193");
@@ -568,17 +641,15 @@ void Cnn::ensure(int B, int S) {
             h_[l].ensure(np * kCh);
         }
         y_.ensure(np);
-        for (int i = 0; i < 2; ++i) {
-            dz_[i].ensure(np * kCh);
-            gh_[i].ensure(np * kCh);
-        }
+        for (auto& d : dz_) d.ensure(np * kCh);
+        for (auto& d : gh_) d.ensure(np * kCh);
         gy_.ensure(np * kPadIn);
         for (auto& m : mask_) m.ensure((size_t)nwg * 256);
-        part_.ensure((size_t)nwg * kWgStride);
         B_ = B;
         S_ = S;
         nwg_ = nwg;
     }
+    part_.ensure((size_t)nwg * kWgStride * (dw_together(nwg) ? kLayers : 1));
 }
 
 void Cnn::run_forward(int B, int S, float* y) {
@@ -649,37 +720,66 @@ double Cnn::gradient(int B, int S, const float* in, const float* target, int tch
     const dim3 g(tiles, tiles, B);
     const int nwg = tiles * tiles * B;
     float* gr = grad_.get();
-    dwtmp_.ensure((size_t)kDwSplit * (9 * 32 * 32 + 32));
-    auto reduce = [&](int l) {
-        const int J = 9 * L[l].COp * L[l].CIp + L[l].COp;
-        k_dw_partial<<<dim3(ceil_div(J, 256), kDwSplit), 256, 0, s>>>(nwg, J, part_.get(), dwtmp_.get());
-        HINV_LAUNCH_CHECK();
-        k_dw_reduce<<<ceil_div(J, 256), 256, 0, s>>>(J, L[l].co, L[l].ci, L[l].COp, L[l].CIp, dwtmp_.get(),
-                                                      gr + L[l].woff, gr + L[l].boff);
-        HINV_LAUNCH_CHECK();
-    };
+    dwtmp_.ensure((size_t)kLayers * kDwSplit * kWgStride);
     const int top = kLayers - 1;
-    k_conv_dw<32, 16><<<g, 256, 0, s>>>(S, a_[top - 1].get(), gy_.get(), part_.get());
-    HINV_LAUNCH_CHECK();
-    reduce(top);
-    // dL/dh4 and dZ4 = dL/dh4 * [z4 > 0]
-    k_conv<16, 32, EPI_BWD><<<g, 256, 0, s>>>(S, gy_.get(), wb_[top].get(), nullptr, nullptr,
-                                               mask_[top - 1].get(), gh_[0].get(), dz_[0].get());
+    // dL/dh_{top-1} and dZ_{top-1} = dL/dh * [z > 0]; then dL/dh_{l-1} =
+    // conv^T(dZ_l) + dL/dh_l (identity path) and dZ_{l-1}
+    k_conv<16, 32, EPI_BWD><<<g, 256, 0, s>>>(S, gy_.get(), wb_[top].get(), nullptr, nullptr, mask_[top - 1].get(),
+                                               gh_[0].get(), dz_[top - 1].get());
     HINV_LAUNCH_CHECK();
     int cur = 0;
     for (int l = top - 1; l >= 1; --l) {
-        k_conv_dw<32, 32><<<g, 256, 0, s>>>(S, a_[l - 1].get(), dz_[cur].get(), part_.get());
-        HINV_LAUNCH_CHECK();
-        reduce(l);
-        // dL/dh_{l-1} = conv^T(dZ_l) + dL/dh_l (identity path), dZ_{l-1}
-        k_conv<32, 32, EPI_BWD><<<g, 256, 0, s>>>(S, dz_[cur].get(), wb_[l].get(), nullptr, gh_[cur].get(),
-                                                   mask_[l - 1].get(), gh_[1 - cur].get(), dz_[1 - cur].get());
+        k_conv<32, 32, EPI_BWD><<<g, 256, 0, s>>>(S, dz_[l].get(), wb_[l].get(), nullptr, gh_[cur].get(),
+                                                   mask_[l - 1].get(), gh_[1 - cur].get(), dz_[l - 1].get());
         HINV_LAUNCH_CHECK();
         cur = 1 - cur;
     }
-    k_conv_dw<16, 32><<<g, 256, 0, s>>>(S, in0_.get(), dz_[cur].get(), part_.get());
+    DwLayers D{};
+    int Jmax = 0;
+    for (int l = 0; l < kLayers; ++l) {
+        D.J[l] = 9 * L[l].COp * L[l].CIp + L[l].COp;
+        D.co[l] = L[l].co;
+        D.ci[l] = L[l].ci;
+        D.COp[l] = L[l].COp;
+        D.CIp[l] = L[l].CIp;
+        D.woff[l] = L[l].woff;
+        D.boff[l] = L[l].boff;
+        Jmax = std::max(Jmax, D.J[l]);
+    }
+    // weight gradients of layers l0 .. l0 + n - 1, n > 1 for the middle ones only
+    auto dw = [&](int l0, int n, float* part) {
+        DwArgs a{};
+        for (int i = 0; i < n; ++i) {
+            a.in[i] = l0 + i ? a_[l0 + i - 1].get() : in0_.get();
+            a.dz[i] = l0 + i == top ? gy_.get() : dz_[l0 + i].get();
+        }
+        const dim3 gd(tiles, tiles, B * n);
+        if (l0 == top)
+            k_conv_dw<32, 16><<<gd, 256, 0, s>>>(S, B, a, part);
+        else if (l0 > 0)
+            k_conv_dw<32, 32><<<gd, 256, 0, s>>>(S, B, a, part);
+        else
+            k_conv_dw<16, 32><<<gd, 256, 0, s>>>(S, B, a, part);
+        HINV_LAUNCH_CHECK();
+    };
+    auto partials = [&](int l0, int n) {
+        k_dw_partial<<<dim3(ceil_div(Jmax, 256), kDwSplit, n), 256, 0, s>>>(nwg, l0, D, part_.get(), dwtmp_.get());
+        HINV_LAUNCH_CHECK();
+    };
+    if (dw_together(nwg)) {
+        const size_t ps = (size_t)nwg * kWgStride;
+        dw(0, 1, part_.get());
+        dw(1, top - 1, part_.get() + ps);
+        dw(top, 1, part_.get() + top * ps);
+        partials(0, kLayers);
+    } else {
+        for (int l = 0; l < kLayers; ++l) {
+            dw(l, 1, part_.get());
+            partials(l, 1);
+        }
+    }
+    k_dw_reduce<<<dim3(ceil_div(Jmax, 256), kLayers), 256, 0, s>>>(D, dwtmp_.get(), gr);
     HINV_LAUNCH_CHECK();
-    reduce(0);
     std::vector<double> r(B);
     HINV_HIP(hipMemcpyAsync(r.data(), ratio_.get(), sizeof(double) * B, hipMemcpyDeviceToHost, s));
     if (grad_host)
