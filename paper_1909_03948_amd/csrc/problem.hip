@@ -279,142 +279,117 @@ __global__ void k_prior_apply(OpKA<double> op, const double* __restrict__ x, int
 
 // Chebyshev iteration for M x = b with the Jacobi-scaled spectrum in [1/2, 2]
 // (x = 0, r = b, d = D^-1 b / theta; then per step r <- r - M d, x <- x + d,
-// d <- c1 d + c2 D^-1 r), kMassSteps steps per launch on LDS tiles: a
-// workgroup owns T x T nodes (T = 32, or 16 when the 32-tiles would leave
-// most of the GPU idle) and holds r and d on a halo of kMassSteps rings, so
-// step s updates the tile shrunk by s + 1 rings from values it holds.  The
-// next launch reads the other copy of r and d (the halos of a tile are owned
-// by its neighbours).
-constexpr int kMassSteps = 8;
+// d <- c1 d + c2 D^-1 r), kMassSteps steps per launch.  A wave holds r, d and
+// x of 64 columns and R rows in registers, one column a lane: east and west
+// neighbours come through lane shifts, north and south ones are the next
+// registers, and only the first and last row of a wave pass through LDS (one
+// barrier a step).  The 8 waves of a workgroup stack to 8 R rows; a halo of
+// kMassSteps nodes around the owned ones absorbs the wrong values that move
+// in from the cut by one node a step.
+// Bound by FP64 arithmetic in batches and by the chain of steps for few
+// columns.  With r and d in LDS tiles (12 LDS accesses and two barriers a node
+// and step) R mhat = K M^-1 K mhat took 2309 us at 512^2 x 64 and 228 / 70 us for
+// one column of 1024^2 / 256^2, here 910 and 87 / 31.
+constexpr int kMassSteps = 12, kMassWaves = 8;
+constexpr int kMassOwnX = 64 - 2 * kMassSteps;
+// R: 4 while the launch is one round of short chains, 8 (less halo a node)
+// from 160 workgroups on: R mhat of 256^2 x 1 takes 31.3 / 41.8 us with R = 4 / 8
+// (49 workgroups of the larger kind), 512^2 x 1 (169) 58.7 / 48.0, 512^2 x 64
+// 1895 / 910 (16 or 20: 968 / 985, more registers than two workgroups a compute
+// unit have).
+constexpr int kMassRowsFew = 4, kMassRowsMany = 8;
+constexpr int mass_own_y(int R) { return kMassWaves * R - 2 * kMassSteps; }
 struct MassSteps {
     double c1[kMassSteps], c2[kMassSteps];
 };
 
-template <int T>
-__global__ __launch_bounds__(256) void k_cheb_mass(OpKA<double> op, const double* __restrict__ b, int ldb,
-                                                   double* __restrict__ x, const double* __restrict__ r_in,
-                                                   const double* __restrict__ d_in, double* __restrict__ r_out,
-                                                   double* __restrict__ d_out, int ld, MassSteps cs, int first,
-                                                   double inv_theta) {
-    constexpr int H = kMassSteps, W = T + 2 * H, NN = W * W, E = (NN + 255) / 256;
-    constexpr int OWN = (T * T + 255) / 256;
-    __shared__ double sr[NN], sd[NN];
+template <int R>
+__global__ __launch_bounds__(64 * kMassWaves, 4) void k_cheb_mass(OpKA<double> op, const double* __restrict__ b, int ldb,
+                                                               double* __restrict__ x, double* __restrict__ r_io,
+                                                               double* __restrict__ d_io, int ld, MassSteps cs,
+                                                               int first, int last, double inv_theta) {
+    __shared__ KARow<double> rows[10];  // by node class; 9: a node off the mesh
+    __shared__ double edge[2][kMassWaves][2][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int N = op.N, N1 = N + 1;
-    const int ox = blockIdx.x * T - H, oy = blockIdx.y * T - H;  // node of local (0, 0)
+    const int i = blockIdx.x * kMassOwnX - kMassSteps + lane;
+    const int jt = blockIdx.y * mass_own_y(R) - kMassSteps, j0 = jt + wave * R;
     const size_t co = (size_t)blockIdx.z * ld;
-    // loads first (r and d, or b on the first launch; x of the owned nodes)
-    double vr[E], vd[E], vx[OWN];
+    if (threadIdx.x < 10) rows[threadIdx.x] = threadIdx.x < 9 ? op.rows[threadIdx.x] : KARow<double>{};
+    const bool in_x = i >= 0 && i <= N;
+    const int ic = min(max(i, 0), N);
+    const int cx = in_x ? (i == 0 ? 1 : (i == N ? 2 : 0)) : 9;
+    const bool own_x = in_x && lane >= kMassSteps && lane < 64 - kMassSteps;
+    // this lane's owned rows: [q0, q1)
+    const int q0 = max(jt + kMassSteps - j0, 0), q1 = min(min(jt + kMassWaves * R - kMassSteps, N1) - j0, R);
+    double r[R], d[R], xs[R];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int t = threadIdx.x + 256 * e;
-        const int i = ox + t % W, j = oy + t / W;
-        const bool in = t < NN && i >= 0 && i <= N && j >= 0 && j <= N;
-        const int k = j * N1 + i;
-        vr[e] = vd[e] = 0.0;
-        if (in) {
-            if (first) {
-                const double bv = b[(size_t)blockIdx.z * ldb + k];
-                vr[e] = bv;
-                vd[e] = op.inv_diag(i, j, k) * bv * inv_theta;
-            } else {
-                vr[e] = r_in[co + k];
-                vd[e] = d_in[co + k];
-            }
-        }
-    }
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-        const int t = threadIdx.x + 256 * o;
-        const int i = ox + H + t % T, j = oy + H + t / T;
-        vx[o] = (!first && t < T * T && i <= N && j <= N) ? x[co + j * N1 + i] : 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int t = threadIdx.x + 256 * e;
-        if (t < NN) {
-            sr[t] = vr[e];
-            sd[t] = vd[e];
+    for (int q = 0; q < R; ++q) {
+        const int k = min(max(j0 + q, 0), N) * N1 + ic;
+        if (first) {
+            r[q] = b[(size_t)blockIdx.z * ldb + k];
+            d[q] = 0.0;
+            xs[q] = 0.0;
+        } else {
+            r[q] = r_io[co + k];
+            d[q] = d_io[co + k];
+            xs[q] = q >= q0 && q < q1 ? x[co + k] : 0.0;
         }
     }
     __syncthreads();
-    // Tiles strictly inside the mesh (every node 1 <= i, j <= N - 1) have the
-    // interior row everywhere: its seven couplings stay in scalar registers.
-    const bool inner = ox >= 1 && oy >= 1 && ox + W <= N && oy + W <= N;
-    if (inner) {
-        const KARow<double>& q0 = op.rows[0];
-        const double mc = q0.c, me = q0.e, mw = q0.w, mn = q0.n, ms = q0.s, mne = q0.ne, msw = q0.sw;
-        const double mdv = q0.dinv;
-        for (int st = 0; st < H; ++st) {
-            const int lo = st + 1, hi = W - lo;
+    const KARow<double> m = rows[cx];
+    auto row_class = [&](int j) { return cx == 9 || j < 0 || j > N ? 9 : cx + (j == 0 ? 3 : (j == N ? 6 : 0)); };
+    // a wave without rows on or beyond the mesh's edges has its coefficients in registers
+    const bool plain = j0 > 0 && j0 + R <= N;
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int t = threadIdx.x + 256 * e;
-                const int li = t % W, lj = t / W;
-                if (t >= NN || li < lo || li >= hi || lj < lo || lj >= hi) continue;
-                const double Md = mc * sd[t] + me * sd[t + 1] + mw * sd[t - 1] + mn * sd[t + W] + ms * sd[t - W] +
-                                  mne * sd[t + W + 1] + msw * sd[t - W - 1];
-                sr[t] = sr[t] - Md;
-            }
-#pragma unroll
-            for (int o = 0; o < OWN; ++o) {
-                const int t = threadIdx.x + 256 * o;
-                if (t < T * T) vx[o] += sd[(H + t / T) * W + H + t % T];
-            }
-            __syncthreads();
-            const double c1 = cs.c1[st], c2 = cs.c2[st];
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int t = threadIdx.x + 256 * e;
-                const int li = t % W, lj = t / W;
-                if (t >= NN || li < lo || li >= hi || lj < lo || lj >= hi) continue;
-                sd[t] = c1 * sd[t] + c2 * mdv * sr[t];
-            }
-            __syncthreads();
-        }
+    for (int q = 0; q < R; ++q) {
+        const int j = j0 + q;
+        if (!in_x || j < 0 || j > N) r[q] = d[q] = 0.0;
+        if (first) d[q] = rows[row_class(j)].dinv * r[q] * inv_theta;
     }
-    for (int st = 0; !inner && st < H; ++st) {
-        const int lo = st + 1, hi = W - lo;  // region [lo, hi)^2
-        // r <- r - M d on the region (each r read and written by one thread);
-        // x <- x + d on the owned nodes, before d changes.  The loops walk the
-        // whole tile (compile-time width) and skip what lies outside.
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int t = threadIdx.x + 256 * e;
-            const int li = t % W, lj = t / W, i = ox + li, j = oy + lj;
-            if (t >= NN || li < lo || li >= hi || lj < lo || lj >= hi) continue;
-            if (i < 0 || i > N || j < 0 || j > N) continue;
-            const double Md = op.apply(i, j, j * N1 + i, [&](int ii, int jj, int) {
-                return sd[(jj - oy) * W + (ii - ox)];
-            });
-            sr[t] = sr[t] - Md;
-        }
-#pragma unroll
-        for (int o = 0; o < OWN; ++o) {
-            const int t = threadIdx.x + 256 * o;
-            if (t < T * T) vx[o] += sd[(H + t / T) * W + H + t % T];
-        }
+    for (int st = 0; st < kMassSteps; ++st) {
+        double(*e)[2][64] = edge[st & 1];
+        e[wave][0][lane] = d[0];
+        e[wave][1][lane] = d[R - 1];
         __syncthreads();
+        const double up = wave + 1 < kMassWaves ? e[wave + 1][0][lane] : 0.0;
+        double below = wave > 0 ? e[wave - 1][1][lane] : 0.0;
         const double c1 = cs.c1[st], c2 = cs.c2[st];
+        double below_w = lane_west(below), at_e = lane_east(d[0]);
+        auto sweep = [&](auto plain_rows) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int t = threadIdx.x + 256 * e;
-            const int li = t % W, lj = t / W, i = ox + li, j = oy + lj;
-            if (t >= NN || li < lo || li >= hi || lj < lo || lj >= hi) continue;
-            if (i < 0 || i > N || j < 0 || j > N) continue;
-            sd[t] = c1 * sd[t] + c2 * op.inv_diag(i, j, j * N1 + i) * sr[t];
-        }
-        __syncthreads();
+            for (int q = 0; q < R; ++q) {
+                const double at = d[q], above = q + 1 < R ? d[q + 1] : up;
+                const double at_w = lane_west(at), above_e = lane_east(above);
+                KARow<double> c;
+                if constexpr (decltype(plain_rows)::value)
+                    c = m;
+                else
+                    c = rows[row_class(j0 + q)];
+                const double Md = c.c * at + c.e * at_e + c.w * at_w + c.n * above + c.s * below + c.ne * above_e +
+                                  c.sw * below_w;
+                r[q] -= Md;
+                xs[q] += at;
+                d[q] = c1 * at + c2 * c.dinv * r[q];
+                below = at;
+                below_w = at_w;
+                at_e = above_e;
+            }
+        };
+        if (plain)
+            sweep(std::true_type{});
+        else
+            sweep(std::false_type{});
     }
+    if (!own_x) return;
 #pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-        const int t = threadIdx.x + 256 * o;
-        const int i = ox + H + t % T, j = oy + H + t / T;
-        if (t < T * T && i <= N && j <= N) {
-            const int l = (H + t / T) * W + H + t % T;
-            const size_t k = co + j * N1 + i;
-            x[k] = vx[o];
-            r_out[k] = sr[l];
-            d_out[k] = sd[l];
+    for (int q = 0; q < R; ++q) {
+        if (q < q0 || q >= q1) continue;
+        const size_t k = co + (size_t)(j0 + q) * N1 + i;
+        x[k] = xs[q];
+        if (!last) {
+            r_io[k] = r[q];
+            d_io[k] = d[q];
         }
     }
 }
@@ -910,14 +885,17 @@ void Problem::mass_solve(int nc, const double* b, int ldb, double* x, int ldx, h
     const double lo = 0.5, hi = 2.0;
     const double theta = 0.5 * (hi + lo), dl = 0.5 * (hi - lo), sigma1 = theta / dl;
     const size_t blk = (size_t)n * nc;
-    double* r[2] = {ws ? ws : scratch(5, nc), ws ? ws + 3 * blk : scratch(8, nc)};
-    double* d[2] = {ws ? ws + blk : scratch(6, nc), ws ? ws + 2 * blk : scratch(7, nc)};
+    double* r = ws ? ws : scratch(5, nc);
+    double* d = ws ? ws + blk : scratch(6, nc);
     if (ldx != n) fail(HINV_EINVAL, "mass_solve needs a packed output");
     if (nc > 65535) fail(HINV_EINVAL, "mass_solve: at most 65535 columns per call");
-    const bool small = (long long)ceil_div(N + 1, 32) * ceil_div(N + 1, 32) * nc < 512;
-    const int tiles = ceil_div(N + 1, small ? 16 : 32);
+    const int tx = ceil_div(N + 1, kMassOwnX);
+    auto tiles = [&](int R) { return ceil_div(N + 1, mass_own_y(R)); };
+    const bool many = (long long)tx * tiles(kMassRowsMany) * nc >= 160;
     double rho = 1.0 / sigma1;
-    for (int launch = 0; launch < kMassCheb / kMassSteps; ++launch) {
+    constexpr int launches = kMassCheb / kMassSteps;
+    static_assert(launches <= 2, "a launch in the middle would read its neighbours' new r and d");
+    for (int launch = 0; launch < launches; ++launch) {
         MassSteps cs;
         for (int st = 0; st < kMassSteps; ++st) {
             const double rho_n = 1.0 / (2.0 * sigma1 - rho);
@@ -925,13 +903,14 @@ void Problem::mass_solve(int nc, const double* b, int ldb, double* x, int ldx, h
             cs.c2[st] = 2.0 * rho_n / dl;
             rho = rho_n;
         }
-        const int in = launch & 1;
-        if (small)
-            k_cheb_mass<16><<<dim3(tiles, tiles, nc), 256, 0, s>>>(M, b, ldb, x, r[in], d[in], r[1 - in],
-                                                                   d[1 - in], n, cs, launch == 0, 1.0 / theta);
+        auto run = [&](auto kern, int R) {
+            kern<<<dim3(tx, tiles(R), nc), 64 * kMassWaves, 0, s>>>(M, b, ldb, x, r, d, n, cs, launch == 0,
+                                                                    launch == launches - 1, 1.0 / theta);
+        };
+        if (many)
+            run(k_cheb_mass<kMassRowsMany>, kMassRowsMany);
         else
-            k_cheb_mass<32><<<dim3(tiles, tiles, nc), 256, 0, s>>>(M, b, ldb, x, r[in], d[in], r[1 - in],
-                                                                   d[1 - in], n, cs, launch == 0, 1.0 / theta);
+            run(k_cheb_mass<kMassRowsFew>, kMassRowsFew);
         HINV_LAUNCH_CHECK();
     }
 }

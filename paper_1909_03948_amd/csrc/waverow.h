@@ -41,14 +41,6 @@ struct March {
     double inv_strips;
 };
 
-// Value of the lane's east / west neighbour (0 beyond the wave).
-__device__ inline float lane_east(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
-}
-__device__ inline float lane_west(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
-}
-
 // A vector read through a buffer descriptor: row offset in a scalar register,
 // lane offset in one 32-bit vector register shared by every row in flight
 // (64-bit vector addresses took half of the registers), and reads past the
@@ -72,19 +64,6 @@ struct BufRef {
 template <typename V>
 __device__ inline void row_put(V* row, unsigned ic, V v) {
     *reinterpret_cast<V*>(reinterpret_cast<char*>(row) + (unsigned)(ic * (unsigned)sizeof(V))) = v;
-}
-
-__device__ inline double lane_east(double v) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x130, 0xf, 0xf, true);
-    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), 0x130, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-__device__ inline double lane_west(double v) {
-    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, 0x138, 0xf, 0xf, true);
-    const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), 0x138, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
 // One row of the operator at the lane's node.
