@@ -143,51 +143,74 @@ __global__ void k_coarse_matrix(Op op, double* __restrict__ M) {
     M[id] = v;
 }
 
-// Gauss-Jordan inversion of an SPD matrix (no pivoting), one workgroup of
-// 1024 threads, n <= kGJMaxN, in place in M.  Pivot step p:  a = M[p][p];
+// Gauss-Jordan inversion of an SPD matrix (no pivoting), one workgroup, n <=
+// kGJMaxN, in place in M.  Pivot step p:  a = M[p][p];
 // M[i][j] -= M[i][p] M[p][j] / a (i, j != p);  M[p][j] /= a;
-// M[i][p] = -M[i][p] / a;  M[p][p] = 1 / a.  The matrix is held twice in LDS:
-// step p reads one copy and writes the other, so a step needs one barrier
-// and no staging of the pivot row and column.  Thread t owns the entries
-// t, t + 1024, ... of the row-major matrix (indices divided once, up front).
-constexpr int kGJMaxN = 81;
-constexpr int kGJOwn = (kGJMaxN * kGJMaxN + 1023) / 1024;
-__global__ __launch_bounds__(1024) void k_gauss_jordan(int n, double* __restrict__ M) {
-    extern __shared__ double sm[];
-    const int nn = n * n;
-    int oi[kGJOwn], oj[kGJOwn];
+// M[i][p] = -M[i][p] / a;  M[p][p] = 1 / a.  Thread (ti, tj) of a kGJSide
+// square holds the entries (ti + kGJSide a, tj + kGJSide b), a, b < 3, in
+// registers; a step reads the pivot row and column from LDS, and the owners
+// of the next ones write them to the other buffer: one barrier a step.  Bound
+// by that chain (a division, an update, a barrier).  With the matrix in LDS
+// (28 reads and writes a thread and step) 110 us at n = 81, here 44.
+constexpr int kGJSide = 27, kGJMaxN = 3 * kGJSide;
+__global__ __launch_bounds__(768) void k_gauss_jordan(int n, double* __restrict__ M) {
+    __shared__ double prow[2][kGJMaxN], pcol[2][kGJMaxN];
+    const int ti = threadIdx.x / kGJSide, tj = threadIdx.x - ti * kGJSide;
+    double A[3][3];
 #pragma unroll
-    for (int e = 0; e < kGJOwn; ++e) {
-        const int id = threadIdx.x + 1024 * e;
-        oi[e] = id < nn ? id / n : 0;
-        oj[e] = id < nn ? id - oi[e] * n : 0;
-        if (id < nn) sm[id] = M[id];
-    }
-    __syncthreads();
-    for (int p = 0; p < n; ++p) {
-        const double* A = sm + (p & 1) * nn;
-        double* B = sm + (1 - (p & 1)) * nn;
-        const double ia = 1.0 / A[p * n + p];
+    for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int e = 0; e < kGJOwn; ++e) {
-            const int id = threadIdx.x + 1024 * e;
-            if (id >= nn) break;
-            const int i = oi[e], j = oj[e];
-            double v;
-            if (i == p && j == p)
-                v = ia;
-            else if (i == p)
-                v = A[id] * ia;
-            else if (j == p)
-                v = -A[id] * ia;
-            else
-                v = A[id] - A[i * n + p] * A[p * n + j] * ia;
-            B[id] = v;
+        for (int b = 0; b < 3; ++b) {
+            const int i = ti + kGJSide * a, j = tj + kGJSide * b;
+            A[a][b] = i < n && j < n && ti < kGJSide ? M[i * n + j] : 0.0;
         }
-        __syncthreads();
+    // row and column pr + kGJSide a to buffer buf (a: a constant)
+    auto publish = [&](int pr, int a, int buf) {
+        if (ti == pr)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) prow[buf][tj + kGJSide * b] = A[a][b];
+        if (tj == pr && ti < kGJSide)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) pcol[buf][ti + kGJSide * b] = A[b][a];
+    };
+    publish(0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int ap = 0; ap < 3; ++ap) {
+        for (int pr = 0; pr < kGJSide; ++pr) {
+            const int p = pr + kGJSide * ap;
+            if (p >= n) break;
+            const double *R = prow[p & 1], *C = pcol[p & 1];
+            const double ia = 1.0 / R[p];
+            double rv[3], cv[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                rv[a] = R[tj + kGJSide * a];
+                cv[a] = C[min(ti, kGJSide - 1) + kGJSide * a];
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    double v = A[a][b] - cv[a] * rv[b] * ia;
+                    if (a == ap) v = ti == pr ? rv[b] * ia : v;
+                    if (b == ap) v = tj == pr ? (a == ap && ti == pr ? ia : -cv[a] * ia) : v;
+                    A[a][b] = v;
+                }
+            if (pr + 1 < kGJSide)
+                publish(pr + 1, ap, 1 - (p & 1));
+            else if (ap + 1 < 3)
+                publish(0, ap + 1, 1 - (p & 1));
+            __syncthreads();
+        }
     }
-    const double* A = sm + (n & 1) * nn;
-    for (int id = threadIdx.x; id < nn; id += 1024) M[id] = A[id];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const int i = ti + kGJSide * a, j = tj + kGJSide * b;
+            if (i < n && j < n && ti < kGJSide) M[i * n + j] = A[a][b];
+        }
 }
 
 __global__ void k_cast_d2f(const double* a, float* b, int n) {
@@ -493,8 +516,7 @@ void Hierarchy::build_coarse(int inst) {
             make_prior_op<double>(L.N, inst_pp_[inst]), c64);
     HINV_LAUNCH_CHECK();
     if (nc > kGJMaxN) fail(HINV_EINVAL, "coarse level too large for the dense inverse");
-    const size_t shm = sizeof(double) * 2 * (size_t)nc * nc;
-    k_gauss_jordan<<<1, 1024, shm, s>>>(nc, c64);
+    k_gauss_jordan<<<1, 768, 0, s>>>(nc, c64);
     HINV_LAUNCH_CHECK();
     k_cast_d2f<<<ceil_div(tot, kBlock), kBlock, 0, s>>>(c64, cinv32_.get() + (size_t)inst * tot, tot);
     HINV_LAUNCH_CHECK();
