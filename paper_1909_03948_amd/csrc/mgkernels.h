@@ -701,31 +701,32 @@ struct BottomArgs {
 // long instruction sequence on the vector ALU).
 __device__ inline int small_div(int q, float inv_d) { return (int)(((float)q + 0.5f) * inv_d); }
 
-// x_top = V-cycle(b_top) for every column (blockIdx.x = column).  When rv is
-// given (the bottom is the whole hierarchy), sum_k rv_k x_k is written as the
-// single partial of r^T z.  Each level lies in LDS with a ring of zeros (padded
+// The cycle of one column.  Each level lies in LDS with a ring of zeros (padded
 // width N_l + 3), so the stencil applies without boundary branches; Dirichlet
 // rows are masked by their zero inverse diagonal.  Node slots of a thread:
 // nodes t and t + 1024 of level 0, node t of levels 1 and 2.
-template <typename TV, int KIND>
-__global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restrict__ bg, TV* __restrict__ xg,
-                                                 int ld, int* __restrict__ act, ChebCoef cc,
-                                                 const TV* __restrict__ rv, PcgRed red,
-                                                 ColState* __restrict__ st, int check) {
-    constexpr bool PRIOR = KIND == kOpPrior;
-    constexpr int NT = 1024, LV = kBottomLevels, NS = LV + 1;
-    constexpr int PN = (kBottomN + 3) * (kBottomN + 3) + (kBottomN / 2 + 3) * (kBottomN / 2 + 3) + 11 * 11;
+template <int KIND>
+struct BottomCycle {
+    static constexpr bool PRIOR = KIND == kOpPrior;
+    static constexpr int NT = 1024, LV = kBottomLevels, NS = LV + 1, S = 12, kCU = 8;
+    static constexpr int PN = (kBottomN + 3) * (kBottomN + 3) + (kBottomN / 2 + 3) * (kBottomN / 2 + 3) + 11 * 11;
     static_assert(kBottomN == 32 && LV == 3 && (kBottomN + 1) * (kBottomN + 1) <= 2 * NT, "node slots");
-    const int col = blockIdx.x;
-    if (!check && !column_on(act, col)) return;
-    // the convergence test's partials load together with the level data
-    // below; the test itself follows the loads
-    const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
-    __shared__ float sx[PN], sw[PN], sbc[81], tmp[NT];
-    const int inst = a.cpi ? uniform(col / a.cpi) : 0;
-    const int nlev = a.nlev, L = nlev - 1;  // L: the coarsest level, solved with its dense inverse
+    struct Row {
+        float c, e, w, n, s, ne, sw, dv;
+    };
+    int L;  // the coarsest level, solved with its dense inverse
     int Nl[LV], Pl[LV], po[LV];
-    {
+    int sp[NS], si[NS], sj[NS];  // padded position (-1 past the level), (i, j)
+    Row rw[NS];
+    float bl[NS];  // right-hand sides
+    int cr, cpart, nc;
+    float cv[kCU];  // the thread's part of the dense inverse
+    static __device__ int level(int s) { return s < 2 ? 0 : s - 1; }
+
+    template <class F>
+    __device__ __forceinline__ void load(const BottomArgs& a, int inst, F rhs) {
+        const int nlev = a.nlev;
+        L = nlev - 1;
         int p = 0;
 #pragma unroll
         for (int l = 0; l < LV; ++l) {
@@ -734,57 +735,192 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
             po[l] = p;
             p += Pl[l] * Pl[l];
         }
-    }
-    // ---- this thread's nodes: padded position (-1 past the level), (i, j),
-    // operator row, right-hand side; every global load issued here
-    struct Row {
-        float c, e, w, n, s, ne, sw, dv;
-    };
-    auto level = [](int s) { return s < 2 ? 0 : s - 1; };
-    int sp[NS], si[NS], sj[NS];
-    Row rw[NS];
-    float bl[NS];
+        // ---- this thread's nodes: padded position (-1 past the level), (i, j),
+        // operator row, right-hand side rhs(q); every global load issued here
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int l = level(s), q = threadIdx.x + (s == 1 ? NT : 0), N = Nl[l], N1 = N + 1;
-        const bool in = l < nlev && q < N1 * N1;
-        const int jq = small_div(q, 1.0f / (float)N1);
-        const int i = in ? q - jq * N1 : 0, j = in ? jq : 0;
-        si[s] = i;
-        sj[s] = j;
-        sp[s] = in ? po[l] + (j + 1) * Pl[l] + i + 1 : -1;
-        bl[s] = 0.0f;
-        rw[s] = Row{};
-        if (!in) continue;
-        if constexpr (PRIOR) {
-            const int c = ka_class(i, j, N);
-            const KARow<float> r = a.cpi ? a.karows[l][9 * inst + c] : a.ka[l][c];
-            rw[s] = Row{r.c, r.e, r.w, r.n, r.s, r.ne, r.sw, r.dinv};
-        } else {
-            const long long at = a.cpi ? inst * a.cs[l] : 0;
-            const float* pE = a.wE[l] + at;
-            const float* pN = a.wN[l] + at;
-            const float vE = pE[q], vW = pE[i > 0 ? q - 1 : q], vN = pN[q], vS = pN[j > 0 ? q - N1 : q];
-            Row& r = rw[s];
-            r.e = -vE;
-            r.w = i > 0 ? -vW : 0.0f;
-            r.n = -vN;
-            r.s = j > 0 ? -vS : 0.0f;
-            r.c = -(r.e + r.w + r.n + r.s);
-            r.dv = (a.dinv[l] + at)[q];
+        for (int s = 0; s < NS; ++s) {
+            const int l = level(s), q = threadIdx.x + (s == 1 ? NT : 0), N = Nl[l], N1 = N + 1;
+            const bool in = l < nlev && q < N1 * N1;
+            const int jq = small_div(q, 1.0f / (float)N1);
+            const int i = in ? q - jq * N1 : 0, j = in ? jq : 0;
+            si[s] = i;
+            sj[s] = j;
+            sp[s] = in ? po[l] + (j + 1) * Pl[l] + i + 1 : -1;
+            bl[s] = 0.0f;
+            rw[s] = Row{};
+            if (!in) continue;
+            if constexpr (PRIOR) {
+                const int c = ka_class(i, j, N);
+                const KARow<float> r = a.cpi ? a.karows[l][9 * inst + c] : a.ka[l][c];
+                rw[s] = Row{r.c, r.e, r.w, r.n, r.s, r.ne, r.sw, r.dinv};
+            } else {
+                const long long at = a.cpi ? inst * a.cs[l] : 0;
+                const float* pE = a.wE[l] + at;
+                const float* pN = a.wN[l] + at;
+                const float vE = pE[q], vW = pE[i > 0 ? q - 1 : q], vN = pN[q], vS = pN[j > 0 ? q - N1 : q];
+                Row& r = rw[s];
+                r.e = -vE;
+                r.w = i > 0 ? -vW : 0.0f;
+                r.n = -vN;
+                r.s = j > 0 ? -vS : 0.0f;
+                r.c = -(r.e + r.w + r.n + r.s);
+                r.dv = (a.dinv[l] + at)[q];
+            }
+            if (l == 0) bl[s] = rhs(q);
         }
-        if (l == 0) bl[s] = (float)bg[(size_t)col * ld + q];
-    }
-    // the thread's part of the dense coarse inverse
-    constexpr int S = 12, kCU = 8;
-    const float* ci = a.cinv + (a.cpi ? inst * a.cinv_stride : 0);
-    const int cr = threadIdx.x / S, cpart = threadIdx.x % S;
-    float cv[kCU];
+        // the thread's part of the dense coarse inverse
+        const float* ci = a.cinv + (a.cpi ? inst * a.cinv_stride : 0);
+        cr = threadIdx.x / S;
+        cpart = threadIdx.x % S;
+        nc = a.nc;
 #pragma unroll
-    for (int u = 0; u < kCU; ++u) {
-        const int c = cpart + u * S;
-        cv[u] = (cr < a.nc && c < a.nc) ? ci[cr * a.nc + c] : 0.0f;
+        for (int u = 0; u < kCU; ++u) {
+            const int c = cpart + u * S;
+            cv[u] = (cr < nc && c < nc) ? ci[cr * nc + c] : 0.0f;
+        }
     }
+
+    // From bl of level 0 to x in sx[sp[0]], sx[sp[1]] (written and to be read
+    // by their own threads); sx and sw hold zeros off the nodes, and a barrier
+    // has to lie between earlier reads of them and the call.
+    __device__ __forceinline__ void run(const ChebCoef& cc, float* sx, float* sw, float* sbc, float* tmp) {
+        const float inv_theta = (float)cc.inv_theta, theta = (float)cc.theta, cA = (float)cc.cA, cB = (float)cc.cB,
+                    c1 = (float)cc.c1;
+        // d0 of the first smoothing step (or the right-hand side of the dense solve)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+            if (sp[s] >= 0) {
+                sw[sp[s]] = rw[s].dv * bl[s] * inv_theta;
+                if (L == 0 && s == 0) sbc[threadIdx.x] = bl[s];
+            }
+        lds_barrier();
+        // (A x)_p at padded position p of level l
+        auto apply = [&](const Row& r, int P, int p, const float* x) -> float {
+            if constexpr (PRIOR)
+                return r.c * x[p] + r.e * x[p + 1] + r.w * x[p - 1] + r.n * x[p + P] + r.s * x[p - P] +
+                       r.ne * x[p + P + 1] + r.sw * x[p - P - 1];
+            else  // the diagonal's product is the rounded one of the sum
+                return __builtin_fmaf(r.e, x[p + 1], r.c * x[p]) + r.w * x[p - 1] + r.n * x[p + P] + r.s * x[p - P];
+        };
+        // ---- down
+#pragma unroll
+        for (int l = 0; l < LV - 1; ++l) {
+            if (l >= L) break;
+            const int P = Pl[l];
+            const int s0 = l == 0 ? 0 : l + 1, s1 = l + 2;
+            // x2 = cA d0 + cB D^-1 (b - A d0), d0 in sw
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                const int p = sp[s];
+                if (p < 0) continue;
+                const float ad = apply(rw[s], P, p, sw);
+                sx[p] = cA * sw[p] + cB * rw[s].dv * (bl[s] - ad);
+            }
+            lds_barrier();
+            // residual b - A x2 on the free nodes, into sw
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                const int p = sp[s];
+                if (p < 0) continue;
+                const float v = bl[s] - apply(rw[s], P, p, sx);
+                sw[p] = rw[s].dv != 0.0f ? v : 0.0f;
+            }
+            lds_barrier();
+            // restriction P^T to level l + 1, and its first smoothing correction d0
+            {
+                const int sc = l + 2, pc = sp[sc];
+                if (pc >= 0) {
+                    const int f = po[l] + (2 * sj[sc] + 1) * P + 2 * si[sc] + 1;
+                    const float dvc = rw[sc].dv;
+                    float v = 0.0f;
+                    if (dvc != 0.0f)
+                        v = sw[f] + 0.5f * (sw[f - 1] + sw[f + 1] + sw[f - P] + sw[f + P] + sw[f + P + 1] + sw[f - P - 1]);
+                    bl[sc] = v;
+                    sw[pc] = dvc * v * inv_theta;
+                    if (l + 1 == L) sbc[threadIdx.x] = v;
+                }
+            }
+            lds_barrier();
+        }
+        // ---- coarsest: dense inverse, S threads per row (entries prefetched in cv)
+        if (cr < nc) {
+            float s = 0.0f;
+#pragma unroll
+            for (int u = 0; u < kCU; ++u) {
+                const int c = cpart + u * S;
+                if (c < nc) s += cv[u] * sbc[c];
+            }
+            tmp[threadIdx.x] = s;
+        }
+        lds_barrier();
+        {
+            const int s0 = sp[0], s2 = sp[2], s3 = sp[3], p = L == 0 ? s0 : (L == 1 ? s2 : s3);
+            if ((int)threadIdx.x < nc) {
+                float s = 0.0f;
+                for (int part = 0; part < S; ++part) s += tmp[threadIdx.x * S + part];
+                sx[p] = s;
+            }
+        }
+        lds_barrier();
+        // ---- up
+#pragma unroll
+        for (int l = LV - 2; l >= 0; --l) {
+            if (l >= L) continue;
+            const int P = Pl[l], Pc = Pl[l + 1];
+            const int s0 = l == 0 ? 0 : l + 1, s1 = l + 2;
+            // x += P x_coarse on the free nodes
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                const int p = sp[s];
+                if (p < 0 || rw[s].dv == 0.0f) continue;
+                const int i = si[s], j = sj[s], I = i >> 1, J = j >> 1;
+                const int ca0 = po[l + 1] + (J + 1) * Pc + I + 1;
+                const int ca1 = po[l + 1] + (J + 1 + (j & 1)) * Pc + I + 1 + (i & 1);
+                sx[p] += ((i | j) & 1) ? 0.5f * (sx[ca0] + sx[ca1]) : sx[ca0];
+            }
+            lds_barrier();
+            // d0 = D^-1 (b - A x) / theta
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                const int p = sp[s];
+                if (p < 0) continue;
+                const float ax = apply(rw[s], P, p, sx);
+                sw[p] = rw[s].dv * (bl[s] - ax) * inv_theta;
+            }
+            lds_barrier();
+            // x += (1 + c1) d0 + cB D^-1 r1 with r1 = theta D d0 - A d0
+#pragma unroll
+            for (int s = s0; s < s1; ++s) {
+                const int p = sp[s];
+                if (p < 0) continue;
+                const float ad = apply(rw[s], P, p, sw);
+                const float dk = sw[p];
+                const float r1 = theta * dk * rw[s].c - ad;
+                sx[p] += (1.0f + c1) * dk + cB * rw[s].dv * r1;
+            }
+            if (l > 0) lds_barrier();  // level 0 is read back by its own threads
+        }
+    }
+};
+
+// x_top = V-cycle(b_top) for every column (blockIdx.x = column).  When rv is
+// given (the bottom is the whole hierarchy), sum_k rv_k x_k is written as the
+// single partial of r^T z.
+template <typename TV, int KIND>
+__global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restrict__ bg, TV* __restrict__ xg,
+                                                 int ld, int* __restrict__ act, ChebCoef cc,
+                                                 const TV* __restrict__ rv, PcgRed red,
+                                                 ColState* __restrict__ st, int check) {
+    using BC = BottomCycle<KIND>;
+    constexpr int NT = BC::NT, PN = BC::PN;
+    const int col = blockIdx.x;
+    if (!check && !column_on(act, col)) return;
+    // the convergence test's partials load together with the level data
+    // below; the test itself follows the loads
+    const double rr_share = check ? partial_share(red.rr, col, red.stride, red.nrr) : 0.0;
+    __shared__ float sx[PN], sw[PN], sbc[81], tmp[NT];
+    BC c;
+    c.load(a, a.cpi ? uniform(col / a.cpi) : 0, [&](int q) { return (float)bg[(size_t)col * ld + q]; });
     // ---- LDS: zeros everywhere (the rings stay zero)
     for (int q = threadIdx.x; q < PN; q += NT) sx[q] = sw[q] = 0.0f;
     if (check) {
@@ -792,128 +928,13 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
     } else {
         lds_barrier();
     }
-    const float inv_theta = (float)cc.inv_theta, theta = (float)cc.theta, cA = (float)cc.cA, cB = (float)cc.cB,
-                c1 = (float)cc.c1;
-    // d0 of the first smoothing step (or the right-hand side of the dense solve)
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-        if (sp[s] >= 0) {
-            sw[sp[s]] = rw[s].dv * bl[s] * inv_theta;
-            if (L == 0 && s == 0) sbc[threadIdx.x] = bl[s];
-        }
-    lds_barrier();
-    // (A x)_p at padded position p of level l
-    auto apply = [&](const Row& r, int P, int p, const float* x) -> float {
-        if constexpr (PRIOR)
-            return r.c * x[p] + r.e * x[p + 1] + r.w * x[p - 1] + r.n * x[p + P] + r.s * x[p - P] +
-                   r.ne * x[p + P + 1] + r.sw * x[p - P - 1];
-        else  // the diagonal's product is the rounded one of the sum
-            return __builtin_fmaf(r.e, x[p + 1], r.c * x[p]) + r.w * x[p - 1] + r.n * x[p + P] + r.s * x[p - P];
-    };
-    // ---- down
-#pragma unroll
-    for (int l = 0; l < LV - 1; ++l) {
-        if (l >= L) break;
-        const int P = Pl[l];
-        const int s0 = l == 0 ? 0 : l + 1, s1 = l + 2;
-        // x2 = cA d0 + cB D^-1 (b - A d0), d0 in sw
-#pragma unroll
-        for (int s = s0; s < s1; ++s) {
-            const int p = sp[s];
-            if (p < 0) continue;
-            const float ad = apply(rw[s], P, p, sw);
-            sx[p] = cA * sw[p] + cB * rw[s].dv * (bl[s] - ad);
-        }
-        lds_barrier();
-        // residual b - A x2 on the free nodes, into sw
-#pragma unroll
-        for (int s = s0; s < s1; ++s) {
-            const int p = sp[s];
-            if (p < 0) continue;
-            const float v = bl[s] - apply(rw[s], P, p, sx);
-            sw[p] = rw[s].dv != 0.0f ? v : 0.0f;
-        }
-        lds_barrier();
-        // restriction P^T to level l + 1, and its first smoothing correction d0
-        {
-            const int sc = l + 2, pc = sp[sc];
-            if (pc >= 0) {
-                const int f = po[l] + (2 * sj[sc] + 1) * P + 2 * si[sc] + 1;
-                const float dvc = rw[sc].dv;
-                float v = 0.0f;
-                if (dvc != 0.0f)
-                    v = sw[f] + 0.5f * (sw[f - 1] + sw[f + 1] + sw[f - P] + sw[f + P] + sw[f + P + 1] + sw[f - P - 1]);
-                bl[sc] = v;
-                sw[pc] = dvc * v * inv_theta;
-                if (l + 1 == L) sbc[threadIdx.x] = v;
-            }
-        }
-        lds_barrier();
-    }
-    // ---- coarsest: dense inverse, S threads per row (entries prefetched in cv)
-    if (cr < a.nc) {
-        float s = 0.0f;
-#pragma unroll
-        for (int u = 0; u < kCU; ++u) {
-            const int c = cpart + u * S;
-            if (c < a.nc) s += cv[u] * sbc[c];
-        }
-        tmp[threadIdx.x] = s;
-    }
-    lds_barrier();
-    {
-        const int sl = L == 0 ? 0 : L + 1, p = L == 0 ? sp[0] : (L == 1 ? sp[2] : sp[3]);
-        if ((int)threadIdx.x < a.nc) {
-            float s = 0.0f;
-            for (int part = 0; part < S; ++part) s += tmp[threadIdx.x * S + part];
-            sx[p] = s;
-        }
-    }
-    lds_barrier();
-    // ---- up
-#pragma unroll
-    for (int l = LV - 2; l >= 0; --l) {
-        if (l >= L) continue;
-        const int P = Pl[l], Pc = Pl[l + 1];
-        const int s0 = l == 0 ? 0 : l + 1, s1 = l + 2;
-        // x += P x_coarse on the free nodes
-#pragma unroll
-        for (int s = s0; s < s1; ++s) {
-            const int p = sp[s];
-            if (p < 0 || rw[s].dv == 0.0f) continue;
-            const int i = si[s], j = sj[s], I = i >> 1, J = j >> 1;
-            const int ca0 = po[l + 1] + (J + 1) * Pc + I + 1;
-            const int ca1 = po[l + 1] + (J + 1 + (j & 1)) * Pc + I + 1 + (i & 1);
-            sx[p] += ((i | j) & 1) ? 0.5f * (sx[ca0] + sx[ca1]) : sx[ca0];
-        }
-        lds_barrier();
-        // d0 = D^-1 (b - A x) / theta
-#pragma unroll
-        for (int s = s0; s < s1; ++s) {
-            const int p = sp[s];
-            if (p < 0) continue;
-            const float ax = apply(rw[s], P, p, sx);
-            sw[p] = rw[s].dv * (bl[s] - ax) * inv_theta;
-        }
-        lds_barrier();
-        // x += (1 + c1) d0 + cB D^-1 r1 with r1 = theta D d0 - A d0
-#pragma unroll
-        for (int s = s0; s < s1; ++s) {
-            const int p = sp[s];
-            if (p < 0) continue;
-            const float ad = apply(rw[s], P, p, sw);
-            const float dk = sw[p];
-            const float r1 = theta * dk * rw[s].c - ad;
-            sx[p] += (1.0f + c1) * dk + cB * rw[s].dv * r1;
-        }
-        if (l > 0) lds_barrier();  // level 0 is read back by its own threads
-    }
+    c.run(cc, sx, sw, sbc, tmp);
     double dot = 0.0;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         const int q = threadIdx.x + NT * s;
-        if (sp[s] >= 0) {
-            const TV v = (TV)sx[sp[s]];
+        if (c.sp[s] >= 0) {
+            const TV v = (TV)sx[c.sp[s]];
             xg[(size_t)col * ld + q] = v;
             if (rv) dot += (double)v * (double)rv[(size_t)col * ld + q];
         }
@@ -925,7 +946,7 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
 }
 
 // ------------------------------------------------------------------ PCG ---
-// The linear kernels (few columns, and hierarchies of bottom levels only):
+// The linear kernels (few columns):
 // workgroup blockIdx.x covers nodes [chunk x, chunk (x + 1)) of column
 // blockIdx.y with vec_threads(per) threads, at most kVecNodes nodes a thread.
 
@@ -1083,49 +1104,141 @@ __global__ __launch_bounds__(NT, 4) void k_pcg_apply_few(Op op_, const T* __rest
     if (threadIdx.x == 0) red.pq[(size_t)col * red.stride + bx] = slot_sum(slots, bd >> 6);
 }
 
-// alpha = (r^T z) / (p^T q), r <- r - alpha q into r_new; partials of r^T r.
-// For hierarchies whose levels all run in the bottom kernel; larger ones do
-// this in k_down.  Workgroup 0 records rz (the next beta's denominator) and
-// alpha, with which the next apply kernel (or the refinement step) advances
-// x; a column with p^T q <= 0 (breakdown) stops.
+// A node's stencil values from a padded LDS vector (row width P).
 template <typename T>
-__global__ __launch_bounds__(1024) void k_pcg_update(const T* __restrict__ r, T* __restrict__ r_new,
-                                                     const T* __restrict__ q, int ld, int n, int* __restrict__ act,
-                                                     ColState* __restrict__ st, PcgRed red) {
-    const int col = blockIdx.y;
-    // workgroup 0 clears act[col] on breakdown while the others read it: one
-    // decision per workgroup (see k_down)
-    if (!__syncthreads_or(act[col])) return;
-    double spq = partial_first(red.pq, col, red.stride, red.npq);
-    const double rz = st[col].rz_new;
-    const int k0 = blockIdx.x * red.chunk, k1 = min(n, k0 + red.chunk);
-    T rk[kVecNodes], qk[kVecNodes];
-#pragma unroll
-    for (int e = 0; e < kVecNodes; ++e) {
-        const int k = k0 + e * blockDim.x + threadIdx.x;
-        const size_t o = (size_t)col * ld + k;
-        rk[e] = qk[e] = 0;
-        if (k < k1) {
-            rk[e] = r[o];
-            qk[e] = q[o];
-        }
+__device__ inline typename OpA<T>::Nb lds_nb(const typename OpA<T>::Nb*, const T* v, int P) {
+    return {v[0], v[1], v[-1], v[P], v[-P]};
+}
+template <typename T>
+__device__ inline KANb<T> lds_nb(const KANb<T>*, const T* v, int P) {
+    return {v[0], v[1], v[-1], v[P], v[-P], v[P + 1], v[-P - 1]};
+}
+
+// Hierarchies whose levels all run in the bottom kernel (N <= kBottomN): the
+// whole PCG of a column in one launch, one workgroup.  r, x and p stay in the
+// registers of the nodes' threads, z and p lie in padded LDS for the operator,
+// and an iteration is the V-cycle's ~18 phases and three sums: ~6.8 us at
+// N = 32 in FP64 where three launches (cycle, apply, update) took ~16.  Ends as
+// the other path does: x without the last step, its alpha and p for the
+// refinement step.
+template <typename T, int KIND, class Op>
+__global__ __launch_bounds__(1024) void k_pcg_small(BottomArgs a, Op op_, const T* __restrict__ r, T* __restrict__ x,
+                                                    T* __restrict__ p0, T* __restrict__ p1, int ld,
+                                                    int* __restrict__ act, ColState* __restrict__ st, ChebCoef cc,
+                                                    int max_iter) {
+    using BC = BottomCycle<KIND>;
+    constexpr int NT = BC::NT, PN = BC::PN, W = kBottomN + 3;
+    const int col = blockIdx.x;
+    if (!column_on(act, col)) return;
+    __shared__ float sx[PN], sw[PN], sbc[81], tmp[NT];
+    __shared__ T sz[W * W], sp[W * W];
+    __shared__ __attribute__((aligned(16))) double slots[2][16];
+    const auto& op = op_.at(col);
+    using Form = ApplyForm<std::decay_t<decltype(op)>>;
+    using OpT = typename Form::type;
+    __shared__ KARow<T> krows[Form::kTable ? 9 : 1];
+    OpT sop;
+    if constexpr (Form::kTable) {
+        sop = OpT{op.N, krows};
+        if (threadIdx.x < 9) krows[threadIdx.x] = ka_row(op, threadIdx.x);
+    } else {
+        sop = op;
     }
-    spq = partial_rest(spq, red.pq, col, red.stride, red.npq);
-    const double pq = share_total(spq);
-    const double alpha = pcg_alpha(rz, pq, st + col, act + col, blockIdx.x == 0);
-    double rr = 0.0;
-    const T a = (T)alpha;
+    BC c;
+    c.load(a, a.cpi ? uniform(col / a.cpi) : 0, [](int) { return 0.0f; });
+    const int P = c.Pl[0];
+    const size_t co = (size_t)col * ld;
+    typename OpT::Row row[2];
+    T rk[2], xk[2] = {0, 0}, pk[2] = {0, 0};
+    bool fr[2];
 #pragma unroll
-    for (int e = 0; e < kVecNodes; ++e) {
-        const int k = k0 + e * blockDim.x + threadIdx.x;
-        if (k < k1) {
-            const T rv = rk[e] - a * qk[e];
-            r_new[(size_t)col * ld + k] = rv;
-            rr += (double)rv * (double)rv;
-        }
+    for (int s = 0; s < 2; ++s) {
+        const int q = threadIdx.x + NT * s;
+        rk[s] = 0;
+        fr[s] = false;
+        if (c.sp[s] < 0) continue;
+        rk[s] = r[co + q];
+        row[s] = sop.row(c.si[s], c.sj[s], q);
+        fr[s] = sop.is_free(c.si[s], c.sj[s]);
     }
-    const double s = group_sum(rr);
-    if (threadIdx.x == 0) red.rr[(size_t)col * red.stride + blockIdx.x] = s;
+    for (int q = threadIdx.x; q < PN; q += NT) sx[q] = sw[q] = 0.0f;
+    for (int q = threadIdx.x; q < W * W; q += NT) sz[q] = sp[q] = (T)0;
+    const double stop = st[col].tol2 * st[col].bb;
+    int par = 0;
+    auto total = [&](double v) {  // in every thread; one barrier
+        v = wave_sum(v);
+        par ^= 1;
+        if ((threadIdx.x & 63) == 0) slots[par][threadIdx.x >> 6] = v;
+        lds_barrier();
+        return slot_sum(slots[par], NT / 64);
+    };
+    double rz_old = 1.0, rz = 0.0, pq = 0.0, alpha = 0.0;
+    bool off = false;
+    int it = 0;
+    while (it < max_iter) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) c.bl[s] = (float)rk[s];
+        // LDS addresses and scaled coefficients are formed anew each iteration:
+        // kept across it they would take the registers of the vectors
+#pragma unroll
+        for (int s = 0; s < BC::NS; ++s)
+            asm volatile("" : "+v"(c.sp[s]), "+v"(c.si[s]), "+v"(c.sj[s]), "+v"(c.rw[s].c), "+v"(c.rw[s].dv));
+        lds_barrier();  // the last reads of sx and sw are done
+        c.run(cc, sx, sw, sbc, tmp);
+        double d = 0.0;
+        T zk[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            zk[s] = c.sp[s] >= 0 ? (T)sx[c.sp[s]] : (T)0;
+            if (c.sp[s] >= 0) sz[c.sp[s]] = zk[s];
+            d += (double)zk[s] * (double)rk[s];
+        }
+        rz = total(d);
+        const T beta = it ? (T)(rz / rz_old) : (T)0, a_last = (T)alpha;
+        T qk[2];
+        d = 0.0;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            qk[s] = 0;
+            if (c.sp[s] < 0) continue;
+            using Nb = typename OpT::Nb;
+            const T az = fr[s] ? sop.combine(c.si[s], c.sj[s], row[s], lds_nb((const Nb*)nullptr, sz + c.sp[s], P)) : (T)0;
+            const T ap = fr[s] ? sop.combine(c.si[s], c.sj[s], row[s], lds_nb((const Nb*)nullptr, sp + c.sp[s], P)) : (T)0;
+            xk[s] += a_last * pk[s];
+            pk[s] = zk[s] + beta * pk[s];
+            qk[s] = az + beta * ap;
+            d += (double)pk[s] * (double)qk[s];
+        }
+        pq = total(d);  // and every read of sp is done
+        ++it;
+        alpha = pq > 0.0 ? rz / pq : 0.0;
+        rz_old = rz;
+        d = 0.0;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (c.sp[s] >= 0) sp[c.sp[s]] = pk[s];
+            rk[s] -= (T)alpha * qk[s];
+            d += (double)rk[s] * (double)rk[s];
+        }
+        off = !(pq > 0.0);
+        if (off) break;  // uniform
+        off = total(d) <= stop;
+        if (off) break;
+    }
+    T* pl = it & 1 ? p1 : p0;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        if (c.sp[s] < 0) continue;
+        x[co + threadIdx.x + NT * s] = xk[s];
+        pl[co + threadIdx.x + NT * s] = pk[s];
+    }
+    if (threadIdx.x == 0) {
+        st[col].rz = rz;
+        st[col].pq = pq;
+        st[col].alpha = alpha;
+        st[col].its = it;
+        if (off) act[col] = 0;
+    }
 }
 
 }  // namespace hinv

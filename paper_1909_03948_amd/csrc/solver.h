@@ -123,6 +123,7 @@ class Hierarchy {
     template <typename T, typename TI>
     void vcycle_impl(int nc, int rcur, bool upd);
     struct PcgRed pcg_red(int nc) const;
+    struct BottomArgs bottom_args(int Lb);
     template <typename T>
     PcgWork<T>& work();
     void ensure_cols(int nc);

@@ -844,6 +844,7 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
             return;
         }
     shape_ = default_shape(nc);
+    if (N_ <= kBottomN) return;  // one workgroup a column throughout: nothing to choose
     // HINV_SHAPE forces a shape (tests of every launch path)
     if (const char* f = std::getenv("HINV_SHAPE")) {
         // HINV_SHAPE=<s|l><per>[c<cb>][k<chunk>]
@@ -1001,6 +1002,41 @@ static void launch_chain(int NL, int nt, dim3 g, hipStream_t s, const ChainArgs<
     }
 }
 
+// The bottom computes in FP32 (its coefficients, coarse inverse and prior rows
+// are the FP32 copies) on the cycle's vectors, from level Lb down.
+BottomArgs Hierarchy::bottom_args(int Lb) {
+    const int nlev = (int)lev_.size();
+    BottomArgs a{};
+    a.nlev = nlev - Lb;
+    if (a.nlev > kBottomLevels) fail(HINV_EINVAL, "internal: too many bottom levels");
+    for (int l = 0; l < a.nlev; ++l) {
+        const Level& L = *lev_[Lb + l];
+        a.N[l] = L.N;
+        if (kind_ == kOpState) {
+            a.wE[l] = L.wE32.get();
+            a.wN[l] = L.wN32.get();
+            a.dinv[l] = L.dinv32.get();
+        }
+    }
+    a.cinv = cinv32_.get();
+    a.nc = nc_coarse_;
+    if (kind_ == kOpPrior && ninst_ == 1)
+        for (int l = 0; l < a.nlev; ++l) {
+            const OpKA<float> o = make_opKA<float>(a.N[l], pp_);
+            for (int c = 0; c < 9; ++c) a.ka[l][c] = o.rows[c];
+        }
+    if (ninst_ > 1) {
+        a.cpi = cpi_;
+        a.cinv_stride = (long long)nc_coarse_ * nc_coarse_;
+        for (int l = 0; l < a.nlev; ++l) {
+            a.cs[l] = lev_[Lb + l]->n;
+            const size_t off = (size_t)(Lb + l) * ninst_ * 9;
+            a.karows[l] = karow32_.get() ? karow32_.get() + off : nullptr;
+        }
+    }
+    return a;
+}
+
 template <typename T, typename TI>
 void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
     hipStream_t s = launch_stream_;
@@ -1098,36 +1134,7 @@ void Hierarchy::vcycle_impl(int nc, int rcur, bool upd) {
         HINV_LAUNCH_CHECK();
     }
     {
-        // the bottom computes in FP32 (its coefficients, coarse inverse and
-        // prior rows are the FP32 copies) on the cycle's vectors
-        BottomArgs a{};
-        a.nlev = nlev - Lb;
-        if (a.nlev > kBottomLevels) fail(HINV_EINVAL, "internal: too many bottom levels");
-        for (int l = 0; l < a.nlev; ++l) {
-            const Level& L = *lev_[Lb + l];
-            a.N[l] = L.N;
-            if (kind_ == kOpState) {
-                a.wE[l] = L.wE32.get();
-                a.wN[l] = L.wN32.get();
-                a.dinv[l] = L.dinv32.get();
-            }
-        }
-        a.cinv = cinv32_.get();
-        a.nc = nc_coarse_;
-        if (kind_ == kOpPrior && ninst_ == 1)
-            for (int l = 0; l < a.nlev; ++l) {
-                const OpKA<float> o = make_opKA<float>(a.N[l], pp_);
-                for (int c = 0; c < 9; ++c) a.ka[l][c] = o.rows[c];
-            }
-        if (ninst_ > 1) {
-            a.cpi = cpi_;
-            a.cinv_stride = (long long)nc_coarse_ * nc_coarse_;
-            for (int l = 0; l < a.nlev; ++l) {
-                a.cs[l] = lev_[Lb + l]->n;
-                const size_t off = (size_t)(Lb + l) * ninst_ * 9;
-                a.karows[l] = karow32_.get() ? karow32_.get() + off : nullptr;
-            }
-        }
+        const BottomArgs a = bottom_args(Lb);
         const int chk = Lb <= 1 && upd ? 1 : 0;
         // per column: read b (and r for r^T z), write x; once per launch: the
         // state coefficients of every bottom level and the dense coarse inverse
@@ -1244,7 +1251,7 @@ void Hierarchy::pcg_iteration(int nc, int cur, int first) {
     const int n = L.n, ld = n;
     int* act = act_.get();
     const PcgRed red = pcg_red(nc);
-    const bool linear = nc < kFewCols || L.N <= kBottomN;
+    const bool linear = nc < kFewCols;
     const int nvec = ceil_div(n, red.chunk);
     T* P[2] = {w.p.get(), w.p2.get()};
     {
@@ -1287,14 +1294,6 @@ void Hierarchy::pcg_iteration(int nc, int cur, int first) {
             else
                 launch(k_pcg_apply<T, Op, false, kBatchChunk, 1>, 1);
         });
-        HINV_LAUNCH_CHECK();
-    }
-    if (L.N <= kBottomN) {
-        T* R[2] = {w.r.get(), w.r2.get()};
-        const T* rc = R[cur];
-        const T* qc = w.q.get();
-        timed_launch(ctx_, kclass_for(kKPcgUpdate, nc), sizeof(T) * (double)nc * 3.0 * n, k_pcg_update<T>,
-                     dim3(nvec, nc), dim3(vec_threads(red.per)), s, rc, R[1 - cur], qc, ld, n, act, st_.get(), red);
         HINV_LAUNCH_CHECK();
     }
     vcycle<T>(nc, cur, true);
@@ -1396,6 +1395,30 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
     hipStream_t s = ctx_->stream;
     launch_stream_ = s;
     int* act = act_.get();
+    if (N_ <= kBottomN && max_iter > 0) {
+        // iterations come in pairs after the first, as in the loop below
+        const int cap = 1 + 2 * (max_iter / 2);
+        PcgWork<T>& w = work<T>();
+        const BottomArgs ba = bottom_args(0);
+        with_op<T>(0, [&](auto op) {
+            using Op = decltype(op);
+            constexpr int kind = std::is_same_v<Op, OpA<T>> ? (int)kOpState : (int)kOpPrior;
+            k_pcg_small<T, kind, Op><<<nc, 1024, 0, s>>>(ba, op, w.r.get(), w.x.get(), w.p.get(), w.p2.get(), n_, act,
+                                                         st_.get(), cheb_coef(), cap);
+        });
+        HINV_LAUNCH_CHECK();
+        if (trace_on()) trace_cols(s, "pcg", cap, st_.get(), act, nc);
+        if (tail) (*tail)();
+        read_state(s, nc, tail ? 2 : 1);
+        HINV_HIP(hipStreamSynchronize(s));
+        int live = 0, taken = 0;
+        for (int c = 0; c < nc; ++c) {
+            live += host_act()[c];
+            taken = std::max(taken, (int)host_st()[c].its);
+        }
+        *iters += taken;
+        return tail && !live;
+    }
     tune_shape<T>(nc, true);
     const bool graphs = !std::getenv("HINV_NO_GRAPHS");
     // The prologue (V-cycle of the initial residual, first iteration) is a
@@ -1465,7 +1488,7 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
                 it += 2 * reps;
                 // two iterations per replay: two launches of each finest-level class
                 for (int k : {kclass_for(kKDown, nc), kclass_for(kKUp, nc), (int)kKBottom,
-                                  kclass_for(kKPcgApply, nc), kclass_for(kKPcgUpdate, nc)})
+                                  kclass_for(kKPcgApply, nc)})
                     ctx_->timer.count_only(k, 2 * reps);
             } else {
                 // odd tail: one eager iteration keeps the ping-pong parity at P[1]
