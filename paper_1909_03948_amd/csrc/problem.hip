@@ -117,21 +117,21 @@ __device__ inline double sens_coef(int N, const double* cT, const double* mh, in
 
 // y[:,c] = scale * (K[s(mhat[:,c])] w)_k on free rows, 0 on Dirichlet rows.
 // w is one full state-space vector (its Dirichlet values take part).
-__global__ void k_sens(int N, const double* __restrict__ cT, const double* __restrict__ mhat,
+template <int C>
+__global__ void k_sens(int N, int nc, const double* __restrict__ cT, const double* __restrict__ mhat,
                        int ldm, const double* __restrict__ w, double scale, double* __restrict__ y,
                        int ldy) {
     const int N1 = N + 1;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= N1 * N1) return;
-    const int j = k / N1, i = k - j * N1;
-    double v = 0.0;
-    if (j > 0 && j < N) {
+    const int j = k / N1, i = k - j * N1, col0 = blockIdx.y * C;
+    const bool fr = j > 0 && j < N;
+    if (fr) {
         // Straight-line form: the six triangles around C = (i, j), as in the
         // Hessian output kernel; a triangle outside the mesh (i = 0 or N)
         // reads C in place of its missing nodes and has weight 0, so every
         // load is issued before the first product.  Each edge takes the mean
         // of the coefficients of its two triangles, in the order E, W, N, S.
-        const double* mh = colp(mhat, ldm);
         const bool e = i < N, wv = i > 0;
         const int kE = e ? k + 1 : k, kW = wv ? k - 1 : k, kN = k + N1, kS = k - N1;
         const int kNE = e ? k + N1 + 1 : k, kSW = wv ? k - N1 - 1 : k;
@@ -140,27 +140,37 @@ __global__ void k_sens(int N, const double* __restrict__ cT, const double* __res
         const double t1 = fe * cT[e ? 2 * c0 : 0], t2 = fe * cT[e ? 2 * c0 + 1 : 0];
         const double t3 = fw * cT[wv ? 2 * (c0 - 1) : 0], t4 = fe * cT[e ? 2 * (c0 - N) + 1 : 0];
         const double t5 = fw * cT[wv ? 2 * (c0 - N - 1) : 0], t6 = fw * cT[wv ? 2 * (c0 - N - 1) + 1 : 0];
-        const double mC = mh[k], mE = mh[kE], mN = mh[kN], mNE = mh[kNE], mW = mh[kW], mS = mh[kS],
-                     mSW = mh[kSW];
         const double wk = w[k], wE = w[kE], wW = w[kW], wN = w[kN], wS = w[kS];
-        const double s1 = t1 * (1.0 / 3.0) * (mC + mE + mNE);   // (C, E, NE)
-        const double s2 = t2 * (1.0 / 3.0) * (mC + mN + mNE);   // (C, N, NE)
-        const double s3 = t3 * (1.0 / 3.0) * (mW + mC + mN);    // (W, C, N)
-        const double s4 = t4 * (1.0 / 3.0) * (mS + mC + mE);    // (S, C, E)
-        const double s5 = t5 * (1.0 / 3.0) * (mSW + mS + mC);   // (SW, S, C)
-        const double s6 = t6 * (1.0 / 3.0) * (mSW + mW + mC);   // (SW, W, C)
-        if (e) v += 0.5 * (s1 + s4) * (wk - wE);
-        if (wv) v += 0.5 * (s3 + s6) * (wk - wW);
-        v += 0.5 * (s2 + s3) * (wk - wN);
-        v += 0.5 * (s4 + s5) * (wk - wS);
-        v *= scale;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int col = min(col0 + c, nc - 1);  // past the end: the last column again
+            const double* mh = mhat + (size_t)col * ldm;
+            const double mC = mh[k], mE = mh[kE], mN = mh[kN], mNE = mh[kNE], mW = mh[kW], mS = mh[kS],
+                         mSW = mh[kSW];
+            double v = 0.0;
+            const double s1 = t1 * (1.0 / 3.0) * (mC + mE + mNE);   // (C, E, NE)
+            const double s2 = t2 * (1.0 / 3.0) * (mC + mN + mNE);   // (C, N, NE)
+            const double s3 = t3 * (1.0 / 3.0) * (mW + mC + mN);    // (W, C, N)
+            const double s4 = t4 * (1.0 / 3.0) * (mS + mC + mE);    // (S, C, E)
+            const double s5 = t5 * (1.0 / 3.0) * (mSW + mS + mC);   // (SW, S, C)
+            const double s6 = t6 * (1.0 / 3.0) * (mSW + mW + mC);   // (SW, W, C)
+            if (e) v += 0.5 * (s1 + s4) * (wk - wE);
+            if (wv) v += 0.5 * (s3 + s6) * (wk - wW);
+            v += 0.5 * (s2 + s3) * (wk - wN);
+            v += 0.5 * (s4 + s5) * (wk - wS);
+            v *= scale;
+            y[(size_t)col * ldy + k] = v;
+        }
+        return;
     }
-    colp(y, ldy)[k] = v;
+#pragma unroll
+    for (int c = 0; c < C; ++c) y[(size_t)min(col0 + c, nc - 1) * ldy + k] = 0.0;
 }
 
 // Hessian output without the prior term (see file header).  gn drops the
 // terms that carry the adjoint p.
-__global__ void k_hess_out(int N, const double* __restrict__ cT, const double* __restrict__ u,
+template <int C>
+__global__ void k_hess_out(int N, int nc, const double* __restrict__ cT, const double* __restrict__ u,
                            const double* __restrict__ p, const double* __restrict__ uh, int ldu,
                            const double* __restrict__ ph, int ldp, const double* __restrict__ mh,
                            int ldm, double* __restrict__ out, int ldo, int gn,
@@ -186,43 +196,45 @@ __global__ void k_hess_out(int N, const double* __restrict__ cT, const double* _
     const double t3 = w3 * cT[w && nn ? 2 * (c0 - 1) : 0], t4 = w4 * cT[e && sd ? 2 * (c0 - N) + 1 : 0];
     const double t5 = w5 * cT[w && sd ? 2 * (c0 - N - 1) : 0], t6 = w5 * cT[w && sd ? 2 * (c0 - N - 1) + 1 : 0];
     const int nd[7] = {k, kE, kN, kNE, kW, kS, kSW};  // C E N NE W S SW
-    double vu[7], vph[7], vp[7], vuh[7], vmh[7];
-    const double* uhc = colp(uh, ldu);
-    const double* phc = colp(ph, ldp);
-    const double* mhc = colp(mh, ldm);
+    double vu[7], vp[7];
 #pragma unroll
     for (int q = 0; q < 7; ++q) {
         vu[q] = u[nd[q]];
-        vph[q] = phc[nd[q]];
-        vp[q] = vuh[q] = vmh[q] = 0.0;
+        vp[q] = gn ? 0.0 : p[nd[q]];
     }
-    if (!gn) {
+#pragma unroll
+    for (int cc = 0; cc < C; ++cc) {
+        const int col = min((int)blockIdx.y * C + cc, nc - 1);  // past the end: the last column again
+        const double* uhc = uh + (size_t)col * ldu;
+        const double* phc = ph + (size_t)col * ldp;
+        const double* mhc = mh + (size_t)col * ldm;
+        double vph[7], vuh[7], vmh[7];
 #pragma unroll
         for (int q = 0; q < 7; ++q) {
-            vp[q] = p[nd[q]];
-            vuh[q] = uhc[nd[q]];
-            vmh[q] = mhc[nd[q]];
+            vph[q] = phc[nd[q]];
+            vuh[q] = gn ? 0.0 : uhc[nd[q]];
+            vmh[q] = gn ? 0.0 : mhc[nd[q]];
         }
+        const double addv = add ? add[(size_t)col * ldadd + k] : 0.0;
+        auto tri = [&](int a, int r, int b) {
+            double v = tri_form(vu[a], vu[r], vu[b], vph[a], vph[r], vph[b]);
+            if (!gn) {
+                v += tri_form(vuh[a], vuh[r], vuh[b], vp[a], vp[r], vp[b]);
+                v += (1.0 / 3.0) * (vmh[a] + vmh[r] + vmh[b]) * tri_form(vu[a], vu[r], vu[b], vp[a], vp[r], vp[b]);
+            }
+            return v;
+        };
+        constexpr int O = 0, E = 1, NN = 2, NE = 3, W = 4, S = 5, SW = 6;
+        double acc = 0.0;
+        acc += t1 * (1.0 / 3.0) * tri(O, E, NE);
+        acc += t2 * (1.0 / 3.0) * tri(O, NN, NE);
+        acc += t3 * (1.0 / 3.0) * tri(W, O, NN);
+        acc += t4 * (1.0 / 3.0) * tri(S, O, E);
+        acc += t5 * (1.0 / 3.0) * tri(SW, S, O);
+        acc += t6 * (1.0 / 3.0) * tri(SW, W, O);
+        if (add) acc = addv + acc;  // the prior term, as the accumulating apply adds it
+        out[(size_t)col * ldo + k] = acc;
     }
-    const double addv = add ? colp(add, ldadd)[k] : 0.0;
-    auto tri = [&](int a, int r, int b) {
-        double v = tri_form(vu[a], vu[r], vu[b], vph[a], vph[r], vph[b]);
-        if (!gn) {
-            v += tri_form(vuh[a], vuh[r], vuh[b], vp[a], vp[r], vp[b]);
-            v += (1.0 / 3.0) * (vmh[a] + vmh[r] + vmh[b]) * tri_form(vu[a], vu[r], vu[b], vp[a], vp[r], vp[b]);
-        }
-        return v;
-    };
-    constexpr int C = 0, E = 1, NN = 2, NE = 3, W = 4, S = 5, SW = 6;
-    double acc = 0.0;
-    acc += t1 * (1.0 / 3.0) * tri(C, E, NE);
-    acc += t2 * (1.0 / 3.0) * tri(C, NN, NE);
-    acc += t3 * (1.0 / 3.0) * tri(W, C, NN);
-    acc += t4 * (1.0 / 3.0) * tri(S, C, E);
-    acc += t5 * (1.0 / 3.0) * tri(SW, S, C);
-    acc += t6 * (1.0 / 3.0) * tri(SW, W, C);
-    if (add) acc = addv + acc;  // the prior term, as the accumulating apply adds it
-    colp(out, ldo)[k] = acc;
 }
 
 // g_v = sum_{T ni v} (c_T/3) |T| grad u . grad p  (data part of the gradient).
@@ -472,6 +484,25 @@ __global__ void k_white_noise(int L, uint64_t seed, uint64_t stream, long long f
     double* e = eta + (size_t)blockIdx.y * ld + 4 * b;
     box_muller(c[0], c[1], e[0], e[1]);
     box_muller(c[2], c[3], e[2], e[3]);
+}
+
+__global__ void k_zero_cols(int n, double* __restrict__ x, int ld) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) colp(x, ld)[k] = 0.0;
+}
+
+// Columns that share a thread's reading of the coefficient and of the fields at
+// the linearization point in k_sens and k_hess_out, from kShareMin columns on
+// (bound by bandwidth there; below, more threads hide the latency better).
+// 1024^2 x 61: k_sens 703 us a column a thread, 479 with four; k_hess_out
+// (Gauss-Newton) 754 and 521.
+constexpr int kShareCols = 4, kShareMin = 8;
+void launch_sens(hipStream_t s, int N, int n, int nc, const double* cT, const double* mhat, int ldm, const double* w,
+                 double* y, int ldy) {
+    if (nc >= kShareMin)
+        k_sens<kShareCols><<<grid2(n, ceil_div(nc, kShareCols)), kBlock, 0, s>>>(N, nc, cT, mhat, ldm, w, -1.0, y, ldy);
+    else
+        k_sens<1><<<grid2(n, nc), kBlock, 0, s>>>(N, nc, cT, mhat, ldm, w, -1.0, y, ldy);
 }
 
 OpKA<double> prior_op(int N, const PriorParams& pp) { return make_prior_op<double>(N, pp); }
@@ -760,8 +791,7 @@ void Problem::inc_forward_rhs(int nc, const double* mhat, int ldm, double* rhs, 
         S2->sens(nc, mhat, ldm, u_lin.get(), -1.0, rhs, ldr);
         return;
     }
-    k_sens<<<grid2(n, nc), kBlock, 0, ctx->stream>>>(N, HA->coefficient(), mhat, ldm, u_lin.get(),
-                                                     -1.0, rhs, ldr);
+    launch_sens(ctx->stream, N, n, nc, HA->coefficient(), mhat, ldm, u_lin.get(), rhs, ldr);
     HINV_LAUNCH_CHECK();
 }
 
@@ -781,9 +811,10 @@ void Problem::inc_adjoint_rhs(int nc, bool gn, const double* mhat, int ldm, cons
         }
         return;
     }
-    // the scale 0 zeroes the column under Gauss-Newton
-    k_sens<<<grid2(n, nc), kBlock, 0, s>>>(N, HA->coefficient(), mhat, ldm, p_lin.get(),
-                                           gn ? 0.0 : -1.0, rhs, ldr);
+    if (gn)
+        k_zero_cols<<<grid2(n, nc), kBlock, 0, s>>>(n, rhs, ldr);
+    else
+        launch_sens(s, N, n, nc, HA->coefficient(), mhat, ldm, p_lin.get(), rhs, ldr);
     HINV_LAUNCH_CHECK();
     if (q > 0) {
         double* Bu = obs_scratch(nc);
@@ -806,9 +837,15 @@ void Problem::hess_output(int mode, int nc, const double* mhat, int ldm, const d
         if (with_prior && !rm) prior_apply(nc, mhat, ldm, out, ldo, true);
         return;
     }
-    k_hess_out<<<grid2(n, nc), kBlock, 0, ctx->stream>>>(N, HA->coefficient(), u_lin.get(),
-                                                         p_lin.get(), uh, ldu, ph, ldp, mhat, ldm,
-                                                         out, ldo, gn ? 1 : 0, with_prior ? rm : nullptr, n);
+    auto run = [&](auto kern, int C) {
+        kern<<<grid2(n, ceil_div(nc, C)), kBlock, 0, ctx->stream>>>(
+            N, nc, HA->coefficient(), u_lin.get(), p_lin.get(), uh, ldu, ph, ldp, mhat, ldm, out, ldo, gn ? 1 : 0,
+            with_prior ? rm : nullptr, n);
+    };
+    if (nc >= kShareMin)
+        run(k_hess_out<kShareCols>, kShareCols);
+    else
+        run(k_hess_out<1>, 1);
     HINV_LAUNCH_CHECK();
     if (with_prior && !rm) prior_apply(nc, mhat, ldm, out, ldo, true);
 }

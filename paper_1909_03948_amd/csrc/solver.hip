@@ -246,50 +246,82 @@ __device__ inline bool ir_step_on(int c, const int* oact, const int* inner, cons
     return oact[c] && !(inner && inner[c]) && !(tdone && tdone[c]);
 }
 
-// r64 = b - A x64 on the gated columns, partial |r64|^2.
-template <class Op>
-__global__ void k_ir_residual(Op op_, const double* __restrict__ b, int ldb,
-                              const double* __restrict__ x64, double* __restrict__ r64, int ld,
-                              const int* __restrict__ act, const int* __restrict__ inner,
-                              const int* __restrict__ tdone, double* __restrict__ partial) {
-    if (!ir_step_on(blockIdx.y, act, inner, tdone)) return;
-    const auto& op = op_.at(blockIdx.y);
+// r64 = b - A x64 on the gated columns, partial |r64|^2.  A workgroup takes 256
+// nodes of C columns of one instance (cpi columns each): the state operator's
+// row is read once for them.  Bound by bandwidth in batches: 1024^2 x 61
+// 418 us a column at a time (16 of 40 bytes a node are the operator), 337 with
+// C = 4.  The prior operator reads no arrays: C = 1 (512^2 x 64 123 against 128 us).
+constexpr int kResidualCols = 4;
+template <int C, class Op>
+__global__ __launch_bounds__(kBlock) void k_ir_residual(Op op_, const double* __restrict__ b, int ldb,
+                                                        const double* __restrict__ x64, double* __restrict__ r64,
+                                                        int ld, const int* __restrict__ act,
+                                                        const int* __restrict__ inner, const int* __restrict__ tdone,
+                                                        double* __restrict__ partial, int cpi) {
+    __shared__ double part[C][kBlock / 64];
+    const int groups = (cpi + C - 1) / C, inst = C == 1 ? 0 : blockIdx.y / groups;
+    const int c0 = C == 1 ? blockIdx.y : inst * cpi + (blockIdx.y - inst * groups) * C;
+    const int c1 = C == 1 ? c0 + 1 : min(c0 + C, (inst + 1) * cpi);
+    bool on[C], any = false;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        on[c] = c0 + c < c1 && ir_step_on(c0 + c, act, inner, tdone);
+        any = any || on[c];
+    }
+    if (!any) return;
+    const auto& op = op_.at(c0);
+    using OpT = std::decay_t<decltype(op)>;
     const int N1 = op.N + 1, n = N1 * N1;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    double v2 = 0.0;
-    if constexpr (ApplyForm<std::decay_t<decltype(op)>>::kTable) {
+    const bool in = k < n;
+    const int j = in ? k / N1 : 0, i = k - j * N1;
+    double v2[C]{};
+    if constexpr (ApplyForm<OpT>::kTable) {
         // prior operators: node by node (the LDS row table costs a barrier
         // that one node per thread does not repay; measured)
-        if (k < n) {
-            const int i = k % N1, j = k / N1;
+        static_assert(C == 1, "prior operators take one column");
+        if (in) {
+            const double* xc = x64 + (size_t)c0 * ld;
             double v = 0.0;
-            if (op.is_free(i, j)) {
-                const double* xc = col(x64, ld);
-                v = col(b, ldb)[k] - op.apply(i, j, k, [&](int, int, int kk) { return xc[kk]; });
-            }
-            col(r64, ld)[k] = v;
-            v2 = v * v;
+            if (op.is_free(i, j))
+                v = b[(size_t)c0 * ldb + k] - op.apply(i, j, k, [&](int, int, int kk) { return xc[kk]; });
+            r64[(size_t)c0 * ld + k] = v;
+            v2[0] = v * v;
         }
-    } else {
+    } else if (in) {
         // state operator: straight-line form (the PCG apply kernel's), the
         // node's row, stencil values and b loaded before the first product
-        const bool in = k < n;
-        const int j = in ? k / N1 : 0, i = k - j * N1;
-        typename std::decay_t<decltype(op)>::Row rw{};
-        typename std::decay_t<decltype(op)>::Nb nb{};
-        double bk = 0.0;
-        if (in) {
-            rw = op.row(i, j, k);
-            nb = op.gather(i, j, k, col(x64, ld));
-            bk = col(b, ldb)[k];
-            double v = 0.0;
-            if (op.is_free(i, j)) v = bk - op.combine(i, j, rw, nb);
-            col(r64, ld)[k] = v;
-            v2 = v * v;
-        }
+        const typename OpT::Row rw = op.row(i, j, k);
+        typename OpT::Nb nb[C];
+        double bk[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (on[c]) {
+                nb[c] = op.gather(i, j, k, x64 + (size_t)(c0 + c) * ld);
+                bk[c] = b[(size_t)(c0 + c) * ldb + k];
+            }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (on[c]) {
+                double v = 0.0;
+                if (op.is_free(i, j)) v = bk[c] - op.combine(i, j, rw, nb[c]);
+                r64[(size_t)(c0 + c) * ld + k] = v;
+                v2[c] = v * v;
+            }
     }
-    const double s = block_sum(v2);
-    if (threadIdx.x == 0) partial[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const double s = wave_sum(v2[c]);
+        if ((threadIdx.x & 63) == 0) part[c][threadIdx.x >> 6] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < C && c0 + (int)threadIdx.x < c1) {
+        const int c = c0 + threadIdx.x;
+        double s = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) s += part[threadIdx.x][w];
+        // a gated column's partials stay as they are
+        if (ir_step_on(c, act, inner, tdone)) partial[(size_t)c * gridDim.x + blockIdx.x] = s;
+    }
 }
 
 // Column sums of the partials of one reduction, one workgroup per column.
@@ -1699,8 +1731,18 @@ void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int 
                                              colnorm_.get(), inner, tdone_.get(), st_.get());
             HINV_LAUNCH_CHECK();
             with_op<double>(0, [&](auto op) {
-                k_ir_residual<<<g, kBlock, 0, s>>>(op, b, ldb, xw, r64_.get(), ld, oact_.get(), inner, tdone_.get(),
-                                                   partial_.get());
+                auto run = [&](auto kern, int cols) {
+                    kern<<<dim3(g.x, cols), kBlock, 0, s>>>(op, b, ldb, xw, r64_.get(), ld, oact_.get(), inner,
+                                                            tdone_.get(), partial_.get(), ninst_ == 1 ? nc : cpi_);
+                };
+                using Op = decltype(op);
+                if constexpr (!ApplyForm<Op>::kTable)
+                    if (nc >= kFewCols) {
+                        run(k_ir_residual<kResidualCols, Op>,
+                            ninst_ * ceil_div(ninst_ == 1 ? nc : cpi_, kResidualCols));
+                        return;
+                    }
+                run(k_ir_residual<1, Op>, nc);
             });
             HINV_LAUNCH_CHECK();
             k_ir_finalize<<<nc, kBlock, 0, s>>>(0, partial_.get(), nblk, st_.get(), oact_.get(), colnorm_.get(),
