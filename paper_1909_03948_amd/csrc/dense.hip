@@ -673,7 +673,7 @@ __device__ __forceinline__ void rr_pair(int step, int k, int m, int& p, int& q) 
 // with h = aqq - app and g = 2 apq, t = sign(h) g / (|h| + sqrt(h^2 + g^2)).
 // h and g are scaled by the larger one's exponent, so the squares neither
 // overflow nor vanish.  No branch and no IEEE division or root sequence: the
-// rotations are the serial chain of a step (k_jacobi_pairs 16.7 -> 12.1 us).
+// rotations are the serial chain of a step (in a launch of its own 16.7 -> 12.1 us a step).
 __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double apq, double& c, double& sv) {
     double h = aqq - app, g = 2.0 * apq;
     const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(h), fabs(g)));
@@ -785,9 +785,10 @@ __device__ __forceinline__ void jacobi_apply(int s, int np, double* T, int ldt, 
 }
 
 // Largest s of the one-workgroup sweeps (two copies of the matrix in LDS; one
-// step costs ~2 us there, ~14 us a block step of 16 indices beyond): measured
-// at s = 66 / 72 / 80 / 96 1253 / 1587 / 1805 / 3067 us against 1420 blocked.
-constexpr int kJacLdsMax = 72;
+// step costs ~2 us there, ~16 us a block step of 16 indices beyond): measured
+// at s = 48 / 64 / 70 / 80 / 96 590 / 1113 / 1483 / 1805 / 3067 us against 762 /
+// 833 / 1167 / 1179 / 1179 blocked.
+constexpr int kJacLdsMax = 56;
 
 // Parallel cyclic Jacobi (round-robin pairing), one workgroup, on T and S
 // (ld ldt, lds): per step, the np disjoint rotations, then jacobi_apply.
@@ -824,15 +825,15 @@ __device__ __forceinline__ void jacobi_sweeps(int s, double* T, int ldt, double*
 // Blocked Jacobi for matrices beyond the LDS of one compute unit, over all
 // compute units.  The matrix is padded with zero rows and columns to sp (a
 // multiple of 32) and cut into blocks of kJacB indices; step t of a sweep
-// pairs the blocks by rr_pair.  For each block pair k_jacobi_pairs runs the
+// pairs the blocks by rr_pair.  For each block pair k_jacobi_step runs the
 // rotations of every index pair between the two blocks once (in the first step of a sweep also those within the blocks), so
 // a sweep meets each index pair once, as a cyclic sweep does, and leaves the
-// product of its rotations in Q (32 x 32).  k_jacobi_tiles applies them:
-// T <- Q^T T Q, one 32 x 32 tile a workgroup on the matrix cores, and S <- S Q.
+// product of its rotations in Q (32 x 32), which is applied on the matrix cores:
+// T <- Q^T T Q and S <- S Q, one 32 x 32 tile a workgroup.
 // Padding stays exactly zero (a zero off-diagonal has the identity rotation).
 // One workgroup rotating T in global memory moved 2 s^2 doubles through one
 // compute unit s - 1 times a sweep.  Whole eigenproblem, s = 99 / 300 / 512:
-// 4.4 / 96 / 486 ms there, 2.0 / 5.4 / 9.9 ms here (as many sweeps).
+// 4.4 / 96 / 486 ms there, 1.8 / 4.8 / 9.3 ms here (as many sweeps).
 constexpr int kJacB = 16, kJacT = 2 * kJacB;
 constexpr int kJacLd = 48;  // LDS column stride: two columns' 16-row runs cover all banks
 
@@ -855,108 +856,166 @@ __global__ __launch_bounds__(256) void k_jacobi_init(int s, int sp, const double
     S[o] = r == c ? 1.0 : 0.0;
 }
 
-// Latency-bound: a step is one chain of LDS reads, two rotations (every
-// thread computes those of its row and column pair itself, which saves a
-// barrier) and LDS writes into the other buffer.
-__global__ __launch_bounds__(256) void k_jacobi_pairs(int sp, int step, const double* __restrict__ T,
-                                                      double* __restrict__ Q, const int* __restrict__ done) {
-    if (done[blockIdx.y]) return;
-    __shared__ double tt[2][kJacT * kJacLd];
-    __shared__ double qq[kJacT * kJacLd];
-    T += (size_t)blockIdx.y * sp * sp;
-    Q += ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * kJacT * kJacT;
-    int I, J;
-    rr_pair(step, blockIdx.x, sp / kJacB, I, J);
-    auto at = [&](int r) { return (r < kJacB ? I : J - 1) * kJacB + r; };  // global index of local index r
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int id = threadIdx.x + 256 * u, r = id & 31, c = id >> 5;
-        tt[0][r + c * kJacLd] = T[at(r) + (size_t)at(c) * sp];
-        qq[r + c * kJacLd] = r == c ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    const int k = threadIdx.x & 15, l = threadIdx.x >> 4;
-    const bool all = step == 0;
-    const int nst = all ? kJacT - 1 : kJacB;
-    for (int t = 0; t < nst; ++t) {
-        int pk = k, qk = kJacB + ((k + t) & 15), pl = l, ql = kJacB + ((l + t) & 15);
-        if (all) {
-            rr_pair(t, k, kJacT, pk, qk);
-            rr_pair(t, l, kJacT, pl, ql);
-        }
-        const double* a = tt[t & 1];
-        double* b = tt[1 - (t & 1)];
-        const double va = a[pk + pl * kJacLd], vb = a[pk + ql * kJacLd], vc = a[qk + pl * kJacLd],
-                     vd = a[qk + ql * kJacLd];
-        const double q0p = qq[k + pl * kJacLd], q0q = qq[k + ql * kJacLd];
-        const double q1p = qq[k + 16 + pl * kJacLd], q1q = qq[k + 16 + ql * kJacLd];
-        double ck, sk, cl, sl;
-        jacobi_rotation(a[pk + pk * kJacLd], a[qk + qk * kJacLd], a[pk + qk * kJacLd], ck, sk);
-        jacobi_rotation(a[pl + pl * kJacLd], a[ql + ql * kJacLd], a[pl + ql * kJacLd], cl, sl);
-        const double r0x = ck * va - sk * vc, r0y = ck * vb - sk * vd;
-        const double r1x = sk * va + ck * vc, r1y = sk * vb + ck * vd;
-        b[pk + pl * kJacLd] = cl * r0x - sl * r0y;
-        b[pk + ql * kJacLd] = sl * r0x + cl * r0y;
-        b[qk + pl * kJacLd] = cl * r1x - sl * r1y;
-        b[qk + ql * kJacLd] = sl * r1x + cl * r1y;
-        // columns pl, ql of Q are this thread row's alone during the step
-        qq[k + pl * kJacLd] = cl * q0p - sl * q0q;
-        qq[k + ql * kJacLd] = sl * q0p + cl * q0q;
-        qq[k + 16 + pl * kJacLd] = cl * q1p - sl * q1q;
-        qq[k + 16 + ql * kJacLd] = sl * q1p + cl * q1q;
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int id = threadIdx.x + 256 * u;
-        Q[id] = qq[(id & 31) + (id >> 5) * kJacLd];
-    }
+// Pair index of block A in step `step` of rr_pair's order of m blocks.
+__device__ __forceinline__ int rr_index(int step, int A, int m) {
+    if (A == step || A == m - 1) return 0;
+    const int e = A > step ? A - step : A - step + m - 1;
+    return e <= (m - 2) / 2 ? e : m - 1 - e;
 }
 
-// grid (column pair, row pair of T then 32-row slab of S, matrix).  A
-// workgroup reads and writes its own tile only; wave w owns the 16 x 16
-// quadrant (w & 1, w >> 1).  norms (last step of a sweep): the tile's squared
-// off-diagonal and total sums to part.
-__global__ __launch_bounds__(256) void k_jacobi_tiles(int sp, int step, double* __restrict__ T,
-                                                      double* __restrict__ S, const double* __restrict__ Q,
-                                                      double* __restrict__ part, int norms,
-                                                      const int* __restrict__ done) {
-    if (done[blockIdx.z]) return;
-    constexpr int kLd = kJacT + 2;
-    __shared__ double ps[kJacT * kLd];
-    const int np = gridDim.x, l = blockIdx.x;
-    const bool is_t = (int)blockIdx.y < np;
-    const int k = is_t ? blockIdx.y : blockIdx.y - np;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m0 = (wave & 1) * 16, n0 = (wave >> 1) * 16, mm = lane & 15, kk = lane >> 4;
-    const double* Qb = Q + (size_t)blockIdx.z * np * kJacT * kJacT;
-    double* M = (is_t ? T : S) + (size_t)blockIdx.z * sp * sp;
+// One step in one launch (grid: pairs of the next step, then tiles; matrix).
+// The first np workgroups find the rotations of step `next`: a block pair's
+// 32 x 32 entries after this step, Q_k^T T Q_l of the four blocks (a wave each),
+// then the rotations in LDS, a chain of LDS reads, two rotations (every thread
+// computes those of its row and column pair itself, which saves a barrier) and
+// LDS writes into the other buffer; their product goes to Qn.  The others
+// apply this step's rotations Q: Tn = Q^T T Q, S <- S Q, one 32 x 32 tile a
+// workgroup, one quadrant a wave.  norms (last step of a sweep): the tile's
+// squared off-diagonal and total sums to part.  step < 0: the rotations of
+// step `next` from T itself, nothing applied.
+// Bound by the chain of rotations; with the rotations and the tiles in launches
+// of their own a step took 12.1 + 6.3 us (s = 300), 15.9 in one.
+__global__ __launch_bounds__(256) void k_jacobi_step(int sp, int step, int next, const double* __restrict__ T,
+                                                     double* __restrict__ Tn, double* __restrict__ S,
+                                                     const double* __restrict__ Q, double* __restrict__ Qn,
+                                                     double* __restrict__ part, int norms,
+                                                     const int* __restrict__ done) {
+    if (done[blockIdx.y]) return;
+    constexpr int kQ = kJacT * kJacT, kA = kJacT * kJacLd, kPs = kJacT * (kJacB + 1), kLd = kJacT + 2;
+    __shared__ double sm[3 * kA];
+    static_assert(4 * kPs <= 2 * kA && kJacT * kLd <= 3 * kA, "scratch within the LDS");
+    const int np = sp / kJacT, nblk = sp / kJacB;
+    const size_t mo = (size_t)blockIdx.y * sp * sp, qo = (size_t)blockIdx.y * np * kQ;
+    T += mo;
+    Q += qo;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lm = lane & 15, lk = lane >> 4;
+    if ((int)blockIdx.x < np) {
+        double *t0 = sm, *t1 = sm + kA, *qq = sm + 2 * kA;
+        int I, J;
+        rr_pair(next, blockIdx.x, nblk, I, J);
+        if (step < 0) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int id = threadIdx.x + 256 * u, r = id & 31, c = id >> 5;
+                auto at = [&](int x) { return (x < kJacB ? I : J - 1) * kJacB + x; };
+                t0[r + c * kJacLd] = T[at(r) + (size_t)at(c) * sp];
+            }
+        } else {
+            // wave (a, b): block (a ? J : I, b ? J : I) of Q^T T Q
+            const int a = wave & 1, b = wave >> 1, A = a ? J : I, B = b ? J : I;
+            const int ka = rr_index(step, A, nblk), kb = rr_index(step, B, nblk);
+            int Ia, Ja, Ib, Jb;
+            rr_pair(step, ka, nblk, Ia, Ja);
+            rr_pair(step, kb, nblk, Ib, Jb);
+            const double* qa = Q + (size_t)ka * kQ + (A == Ja ? kJacB : 0) * kJacT;  // its 16 columns
+            const double* qb = Q + (size_t)kb * kQ + (B == Jb ? kJacB : 0) * kJacT;
+            double tv[2][8], bv[8], av[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = 4 * u + lk, col = (k < kJacB ? Ib : Jb - 1) * kJacB + k;
+                tv[0][u] = T[Ia * kJacB + lm + (size_t)col * sp];
+                tv[1][u] = T[Ja * kJacB + lm + (size_t)col * sp];
+                bv[u] = qb[k + lm * kJacT];
+                av[u] = qa[k + lm * kJacT];
+            }
+            double* ps = t1 + wave * kPs;  // this wave's 32 x 16 product T Q_l
+            d4_t acc[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                acc[h] = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    acc[h] = __builtin_amdgcn_mfma_f64_16x16x4f64(tv[h][u], bv[u], acc[h], 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) ps[(h * kJacB + 4 * v + lk) * (kJacB + 1) + lm] = acc[h][v];
+            }
+            __syncthreads();
+            d4_t n = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                n = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], ps[(4 * u + lk) * (kJacB + 1) + lm], n, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t0[a * kJacB + 4 * v + lk + (b * kJacB + lm) * kJacLd] = n[v];
+            __syncthreads();  // ps has been read
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int id = threadIdx.x + 256 * u, r = id & 31, c = id >> 5;
+            qq[r + c * kJacLd] = r == c ? 1.0 : 0.0;
+        }
+        __syncthreads();
+        const int k = threadIdx.x & 15, l = threadIdx.x >> 4;
+        const bool all = next == 0;  // the first step of a sweep: also the pairs within the blocks
+        const int nst = all ? kJacT - 1 : kJacB;
+        for (int t = 0; t < nst; ++t) {
+            int pk = k, qk = kJacB + ((k + t) & 15), pl = l, ql = kJacB + ((l + t) & 15);
+            if (all) {
+                rr_pair(t, k, kJacT, pk, qk);
+                rr_pair(t, l, kJacT, pl, ql);
+            }
+            const double* a = t & 1 ? t1 : t0;
+            double* b = t & 1 ? t0 : t1;
+            const double va = a[pk + pl * kJacLd], vb = a[pk + ql * kJacLd], vc = a[qk + pl * kJacLd],
+                         vd = a[qk + ql * kJacLd];
+            const double q0p = qq[k + pl * kJacLd], q0q = qq[k + ql * kJacLd];
+            const double q1p = qq[k + 16 + pl * kJacLd], q1q = qq[k + 16 + ql * kJacLd];
+            double ck, sk, cl, sl;
+            jacobi_rotation(a[pk + pk * kJacLd], a[qk + qk * kJacLd], a[pk + qk * kJacLd], ck, sk);
+            jacobi_rotation(a[pl + pl * kJacLd], a[ql + ql * kJacLd], a[pl + ql * kJacLd], cl, sl);
+            const double r0x = ck * va - sk * vc, r0y = ck * vb - sk * vd;
+            const double r1x = sk * va + ck * vc, r1y = sk * vb + ck * vd;
+            b[pk + pl * kJacLd] = cl * r0x - sl * r0y;
+            b[pk + ql * kJacLd] = sl * r0x + cl * r0y;
+            b[qk + pl * kJacLd] = cl * r1x - sl * r1y;
+            b[qk + ql * kJacLd] = sl * r1x + cl * r1y;
+            // columns pl, ql of Q are this thread row's alone during the step
+            qq[k + pl * kJacLd] = cl * q0p - sl * q0q;
+            qq[k + ql * kJacLd] = sl * q0p + cl * q0q;
+            qq[k + 16 + pl * kJacLd] = cl * q1p - sl * q1q;
+            qq[k + 16 + ql * kJacLd] = sl * q1p + cl * q1q;
+            __syncthreads();
+        }
+        Qn += qo + (size_t)blockIdx.x * kQ;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int id = threadIdx.x + 256 * u;
+            Qn[id] = qq[(id & 31) + (id >> 5) * kJacLd];
+        }
+        return;
+    }
+    double* ps = sm;
+    const int tile = blockIdx.x - np, ky = tile / np, l = tile - ky * np;
+    const bool is_t = ky < np;
+    const int k = is_t ? ky : ky - np;
+    const int m0 = (wave & 1) * 16, n0 = (wave >> 1) * 16;
+    const double* M = is_t ? T : S + mo;
+    double* Mn = is_t ? Tn + mo : S + mo;
     int Ik = 2 * k, Jk = 2 * k + 1, Il, Jl;
-    rr_pair(step, l, sp / kJacB, Il, Jl);
-    if (is_t) rr_pair(step, k, sp / kJacB, Ik, Jk);
+    rr_pair(step, l, nblk, Il, Jl);
+    if (is_t) rr_pair(step, k, nblk, Ik, Jk);
     auto row = [&](int r) { return (r < kJacB ? Ik : Jk - 1) * kJacB + r; };
     auto col = [&](int c) { return (size_t)((c < kJacB ? Il : Jl - 1) * kJacB + c) * sp; };
     double bq[8], p[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) bq[u] = Qb[(size_t)l * kJacT * kJacT + 4 * u + kk + (n0 + mm) * kJacT];
+    for (int u = 0; u < 8; ++u) bq[u] = Q[(size_t)l * kQ + 4 * u + lk + (n0 + lm) * kJacT];
     if (is_t) {
         double aq[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            aq[u] = Qb[(size_t)k * kJacT * kJacT + 4 * u + kk + (m0 + mm) * kJacT];
-            p[u] = M[row(4 * u + kk) + col(n0 + mm)];
+            aq[u] = Q[(size_t)k * kQ + 4 * u + lk + (m0 + lm) * kJacT];
+            p[u] = M[row(4 * u + lk) + col(n0 + lm)];
         }
         d4_t acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(aq[u], p[u], acc, 0, 0, 0);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) ps[m0 + 4 * v + kk + (n0 + mm) * kLd] = acc[v];
+        for (int v = 0; v < 4; ++v) ps[m0 + 4 * v + lk + (n0 + lm) * kLd] = acc[v];
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < 8; ++u) p[u] = ps[m0 + mm + (4 * u + kk) * kLd];
+        for (int u = 0; u < 8; ++u) p[u] = ps[m0 + lm + (4 * u + lk) * kLd];
     } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) p[u] = M[row(m0 + mm) + col(4 * u + kk)];
+        for (int u = 0; u < 8; ++u) p[u] = M[row(m0 + lm) + col(4 * u + lk)];
         __syncthreads();  // both waves of these rows have read them
     }
     d4_t acc = {0.0, 0.0, 0.0, 0.0};
@@ -965,8 +1024,8 @@ __global__ __launch_bounds__(256) void k_jacobi_tiles(int sp, int step, double* 
     double off = 0.0, tot = 0.0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const int r = m0 + 4 * v + kk, c = n0 + mm;
-        M[row(r) + col(c)] = acc[v];
+        const int r = m0 + 4 * v + lk, c = n0 + lm;
+        Mn[row(r) + col(c)] = acc[v];
         tot += acc[v] * acc[v];
         if (k != l || r != c) off += acc[v] * acc[v];
     }
@@ -980,7 +1039,7 @@ __global__ __launch_bounds__(256) void k_jacobi_tiles(int sp, int step, double* 
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double* o = part + (((size_t)blockIdx.z * np + k) * np + l) * 2;
+        double* o = part + (((size_t)blockIdx.y * np + k) * np + l) * 2;
         o[0] = (ps[0] + ps[1]) + (ps[2] + ps[3]);
         o[1] = (ps[4] + ps[5]) + (ps[6] + ps[7]);
     }
@@ -1287,8 +1346,8 @@ void sym_eig(Ctx* ctx, DenseWork& w, int nb, int s, double* T, int ldt, size_t s
     const size_t s2 = (size_t)s * s;
     const int sp = ceil_div(s, kJacT) * kJacT;
     const size_t sp2 = (size_t)sp * sp, shm = sizeof(double) * 2 * s2;
-    w.part.ensure(nb * (2 * sp2 + s));
-    double* lam_u = w.part.get() + nb * 2 * sp2;
+    w.part.ensure(nb * (3 * sp2 + s));
+    double* lam_u = w.part.get() + nb * 3 * sp2;
     constexpr int kMaxSweeps = 40;
     // lam_u and the columns of V, sorted
     auto sorted = [&](const double* V, int ldv, size_t sv) {
@@ -1307,22 +1366,29 @@ void sym_eig(Ctx* ctx, DenseWork& w, int nb, int s, double* T, int ldt, size_t s
     }
     const int np = sp / kJacT, nsteps = sp / kJacB - 1;
     const size_t q1 = (size_t)np * kJacT * kJacT, p1 = (size_t)np * np * 2;
-    w.rot.ensure(nb * (q1 + p1 + 1));
+    w.rot.ensure(nb * (2 * q1 + p1 + 1));
     w.flag.ensure(nb);
-    double* Q = w.rot.get();
-    double* part = Q + nb * q1;
+    double* const Q[2] = {w.rot.get(), w.rot.get() + nb * q1};
+    double* part = Q[1] + nb * q1;
     double* prev = part + nb * p1;
-    double* Tp = w.part.get();
-    double* Sp = Tp + nb * sp2;
+    // T alternates between two buffers (the next rotations are found while the
+    // tiles are written), S is rotated in place
+    double* const Tb[2] = {w.part.get(), w.part.get() + nb * sp2};
+    double* Tp = Tb[0];
+    double* Sp = Tb[1] + nb * sp2;
     int* done = w.flag.get();
     hipStream_t q = ctx->stream;
     k_jacobi_init<<<dim3(ceil_div(sp * sp, 256), nb), 256, 0, q>>>(s, sp, T, ldt, st, Tp, Sp, done, prev);
     HINV_LAUNCH_CHECK();
     std::vector<int> hd(nb);
+    k_jacobi_step<<<dim3(np, nb), 256, 0, q>>>(sp, -1, 0, Tb[0], nullptr, nullptr, Q[0], Q[0], nullptr, 0, done);
+    HINV_LAUNCH_CHECK();
+    int cur = 0;
     for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
         for (int t = 0; t < nsteps; ++t) {
-            k_jacobi_pairs<<<dim3(np, nb), 256, 0, q>>>(sp, t, Tp, Q, done);
-            k_jacobi_tiles<<<dim3(np, 2 * np, nb), 256, 0, q>>>(sp, t, Tp, Sp, Q, part, t == nsteps - 1, done);
+            k_jacobi_step<<<dim3(np + 2 * np * np, nb), 256, 0, q>>>(sp, t, (t + 1) % nsteps, Tb[cur], Tb[1 - cur], Sp,
+                                                                     Q[cur], Q[1 - cur], part, t == nsteps - 1, done);
+            cur = 1 - cur;
         }
         HINV_LAUNCH_CHECK();
         k_jacobi_check<<<nb, 256, 0, q>>>(np, part, prev, done);

@@ -675,7 +675,9 @@ __global__ __launch_bounds__(NT) void k_up_chain(ChainArgs<T, Op> a, int dirichl
 // One workgroup does ~18 short phases between barriers, so what counts is the
 // instructions and LDS reads of a phase: a thread owns the same nodes of each
 // level throughout and keeps their operator rows, right-hand sides and
-// positions in registers; LDS holds the two vectors that neighbours read.
+// positions in registers; LDS holds the two vectors that neighbours read.  N = 32..8,
+// state operator: 8.3 us with rows, diagonals and positions formed anew in each
+// phase, 5.8 with them in registers (prior 9.4 -> 6.1).
 struct BottomArgs {
     int nlev;                           // levels handled here (the last is the coarsest)
     int N[kBottomLevels];
@@ -990,7 +992,10 @@ constexpr int apply_window() {
 // thread t stands for the virtual threads t and t + NT (bd = 2 NT; or one, bd =
 // NT), and the sums are taken in the order of the bd.  Half of the waves with
 // twice the nodes each: at N = 1024 a column's ~500 workgroups fit the
-// registers of the 256 compute units in one round instead of two.
+// registers of the 256 compute units in one round instead of two.  The
+// node window is what 128 registers hold.  1024^2, one column, state operator
+// (64 bytes a node with the step of x): 16.1 us = 4.2 TB/s (17.1 without x, at
+// 1024 threads).
 template <typename T, class Op, bool FIRST, int NT>
 __global__ __launch_bounds__(NT, 4) void k_pcg_apply_few(Op op_, const T* __restrict__ z, const T* __restrict__ p_old,
                                                       T* __restrict__ p_new, T* __restrict__ q, T* __restrict__ x,

@@ -11,6 +11,14 @@
 // The arithmetic per node and its order are those of the tile kernels of
 // several levels (k_down2, k_up_chain), so one or several levels a launch
 // give the same cycle bit for bit.
+//
+// Batches are bound by HBM bandwidth, few columns by the latency of one pass.
+// Against LDS tiles with a halo and a launch of its own for the PCG step, finest
+// level: 1024^2 x 61 (FP32) down 240 us and step 175 us -> 211 us together,
+// up 221 -> 132, apply 229 -> 214 (it now also moves x: 24 bytes a node at
+// 7.2 TB/s, partly from the last-level cache); one column (FP64) of 1024^2 down
+// 16.2 and step 10.6 -> 11.9 us together, up 12.2 -> 9.8, of 256^2 down 6.4 and
+// step 3.8 -> 6.0, up 4.4 -> 4.2.
 #pragma once
 
 #include "grid.h"
@@ -27,7 +35,10 @@ constexpr int kDownOwn = 29, kUpOwn = 60;
 // Rows a chunk (loaded together) and coarse rows a segment: calls of few
 // columns take at most kLatencyRows coarse rows, i.e. two chunks, both loaded
 // at the start, and aim at kLatencyWaves waves a compute unit; batches small
-// chunks (few registers, many waves) and one of the kBatchRows lengths.
+// chunks (few registers, many waves) and one of the kBatchRows lengths, timed
+// at the first call of a shape (longer segments re-read fewer halo rows, shorter
+// ones give small meshes enough waves).  C = 2 columns a wave share the state
+// operator's coefficients and are picked by the same timing.
 constexpr int kLatencyChunk = 8, kLatencyRows = 5, kLatencyWaves = 6;
 constexpr int kBatchChunk = 4;
 constexpr int kBatchRows[] = {13, 29, 5};

@@ -20,9 +20,9 @@ torch = pytest.importorskip("torch")
 hv = pytest.importorskip("paper_1909_03948_amd.hinv")
 
 
-# 72 | 73: one-workgroup eigensolver | blocked; 96 | 97, 128 | 129: its padding;
-# 5, 31, 32, 33, 160: tiles of 32 and 16
-@pytest.mark.parametrize("s", [5, 31, 32, 33, 72, 73, 96, 97, 129, 160])
+# 56 | 57: one-workgroup eigensolver | blocked; 64 | 65, 96 | 97, 128 | 129: its
+# padding; 5, 31, 32, 33, 160: tiles of 32 and 16
+@pytest.mark.parametrize("s", [5, 31, 32, 33, 56, 57, 64, 65, 72, 73, 96, 97, 129, 160])
 def test_factorizations_at_block_edges(s):
     print(f"[gpu-dense] s={s}", flush=True)
     prob, _, obs = instance(32, 10)
