@@ -1119,41 +1119,79 @@ __device__ inline KANb<T> lds_nb(const KANb<T>*, const T* v, int P) {
     return {v[0], v[1], v[-1], v[P], v[-P], v[P + 1], v[-P - 1]};
 }
 
-// Hierarchies whose levels all run in the bottom kernel (N <= kBottomN): the
-// whole PCG of a column in one launch, one workgroup.  r, x and p stay in the
-// registers of the nodes' threads, z and p lie in padded LDS for the operator,
-// and an iteration is the V-cycle's ~18 phases and three sums: ~6.8 us at
-// N = 32 in FP64 where three launches (cycle, apply, update) took ~16.  Ends as
-// the other path does: x without the last step, its alpha and p for the
-// refinement step.
-template <typename T, int KIND, class Op>
-__global__ __launch_bounds__(1024) void k_pcg_small(BottomArgs a, Op op_, const T* __restrict__ r, T* __restrict__ x,
-                                                    T* __restrict__ p0, T* __restrict__ p1, int ld,
-                                                    int* __restrict__ act, ColState* __restrict__ st, ChebCoef cc,
-                                                    int max_iter) {
+// Hierarchies whose levels all run in the bottom kernel (N <= kBottomN): a
+// whole refinement pass of a column in one launch, one workgroup: the scaled
+// inner right-hand side (first pass: r64 = b on the free rows and |b|), the PCG
+// of precision T, x64 += |r| d, r64 = b - A x64 in FP64 and the column's state.
+// r, x and p stay in the registers of the nodes' threads, z and p lie in padded
+// LDS for the operator, and an iteration is the V-cycle's ~18 phases and three
+// sums: ~6.8 us at N = 32 in FP64 where three launches (cycle, apply, update)
+// took ~16.  The six small launches of a pass around the PCG took ~23 us more.
+struct SmallPass {
+    const double* b;
+    int ldb;
+    double *x64, *r64, *partial, *colnorm;
+    int ld, nblk;  // nblk: partials of |r64|^2 a column has (the first one is the sum)
+    int* oact;
+    double rtol, tol_floor;
+    int first;
+};
+
+// Outer state of a column with |r64|^2 = s: whether it goes on, |r64|, and the
+// inner tolerance (squared) of the next pass.
+__device__ inline bool outer_state(double s, double obb, double rtol, double tol_floor, double& norm, double& tol2) {
+    norm = sqrt(s);
+    if (!(isfinite(s) && isfinite(obb) && s > rtol * rtol * obb && s > 0.0)) return false;
+    double t = 0.5 * rtol * sqrt(obb / s);
+    if (t < tol_floor) t = tol_floor;
+    tol2 = t * t;
+    return true;
+}
+
+template <typename T, int KIND, class Op, class Op64>
+__global__ __launch_bounds__(1024) void k_pcg_small(BottomArgs a, Op op_, Op64 op64_, SmallPass ps,
+                                                    ColState* __restrict__ st, ChebCoef cc, int max_iter) {
     using BC = BottomCycle<KIND>;
     constexpr int NT = BC::NT, PN = BC::PN, W = kBottomN + 3;
     const int col = blockIdx.x;
-    if (!column_on(act, col)) return;
+    if (!ps.first && !column_on(ps.oact, col)) {
+        if (threadIdx.x == 0) st[col].its = 0.0;
+        return;
+    }
     __shared__ float sx[PN], sw[PN], sbc[81], tmp[NT];
     __shared__ T sz[W * W], sp[W * W];
     __shared__ __attribute__((aligned(16))) double slots[2][16];
     const auto& op = op_.at(col);
+    const auto& op64 = op64_.at(col);
     using Form = ApplyForm<std::decay_t<decltype(op)>>;
     using OpT = typename Form::type;
     __shared__ KARow<T> krows[Form::kTable ? 9 : 1];
     OpT sop;
+    using Op64T = typename ApplyForm<std::decay_t<decltype(op64)>>::type;
+    constexpr bool kWide = sizeof(T) == 8;  // the PCG's vectors and rows serve the FP64 residual too
+    __shared__ KARow<double> krows64[Form::kTable && !kWide ? 9 : 1];
+    __shared__ double sx64[kWide ? 1 : W * W];
+    Op64T sop64;
     if constexpr (Form::kTable) {
         sop = OpT{op.N, krows};
         if (threadIdx.x < 9) krows[threadIdx.x] = ka_row(op, threadIdx.x);
+        if constexpr (kWide) {
+            sop64 = sop;
+        } else {
+            sop64 = Op64T{op64.N, krows64};
+            if (threadIdx.x < 9) krows64[threadIdx.x] = ka_row(op64, threadIdx.x);
+        }
     } else {
         sop = op;
+        sop64 = op64;
     }
     BC c;
     c.load(a, a.cpi ? uniform(col / a.cpi) : 0, [](int) { return 0.0f; });
     const int P = c.Pl[0];
-    const size_t co = (size_t)col * ld;
+    const size_t co = (size_t)col * ps.ld;
+    const double* bc = ps.b + (size_t)col * ps.ldb;
     typename OpT::Row row[2];
+    double r6[2] = {0.0, 0.0};
     T rk[2], xk[2] = {0, 0}, pk[2] = {0, 0};
     bool fr[2];
 #pragma unroll
@@ -1162,13 +1200,15 @@ __global__ __launch_bounds__(1024) void k_pcg_small(BottomArgs a, Op op_, const 
         rk[s] = 0;
         fr[s] = false;
         if (c.sp[s] < 0) continue;
-        rk[s] = r[co + q];
         row[s] = sop.row(c.si[s], c.sj[s], q);
         fr[s] = sop.is_free(c.si[s], c.sj[s]);
+        r6[s] = ps.first ? (fr[s] ? bc[q] : 0.0) : ps.r64[co + q];
     }
     for (int q = threadIdx.x; q < PN; q += NT) sx[q] = sw[q] = 0.0f;
-    for (int q = threadIdx.x; q < W * W; q += NT) sz[q] = sp[q] = (T)0;
-    const double stop = st[col].tol2 * st[col].bb;
+    for (int q = threadIdx.x; q < W * W; q += NT) {
+        sz[q] = sp[q] = (T)0;
+        if constexpr (!kWide) sx64[q] = 0.0;
+    }
     int par = 0;
     auto total = [&](double v) {  // in every thread; one barrier
         v = wave_sum(v);
@@ -1177,6 +1217,34 @@ __global__ __launch_bounds__(1024) void k_pcg_small(BottomArgs a, Op op_, const 
         lds_barrier();
         return slot_sum(slots[par], NT / 64);
     };
+    double obb, norm, stop = 0.0;
+    if (ps.first) {
+        const double s2 = total(r6[0] * r6[0] + r6[1] * r6[1]);
+        obb = s2;
+        if (!outer_state(s2, s2, ps.rtol, ps.tol_floor, norm, stop)) {  // b = 0 or not finite: x = 0
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                if (c.sp[s] >= 0) {
+                    ps.x64[co + threadIdx.x + NT * s] = 0.0;
+                    ps.r64[co + threadIdx.x + NT * s] = r6[s];
+                }
+            if (threadIdx.x < ps.nblk) ps.partial[(size_t)col * ps.nblk + threadIdx.x] = threadIdx.x ? 0.0 : s2;
+            if (threadIdx.x == 0) {
+                st[col].obb = st[col].rr = s2;
+                st[col].its = 0.0;
+                ps.oact[col] = 0;
+                ps.colnorm[col] = norm;
+            }
+            return;
+        }
+    } else {
+        obb = st[col].obb;
+        norm = ps.colnorm[col];
+        stop = st[col].tol2;
+    }
+    const double inv_norm = 1.0 / norm;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) rk[s] = (T)(r6[s] * inv_norm);
     double rz_old = 1.0, rz = 0.0, pq = 0.0, alpha = 0.0;
     bool off = false;
     int it = 0;
@@ -1230,19 +1298,44 @@ __global__ __launch_bounds__(1024) void k_pcg_small(BottomArgs a, Op op_, const 
         off = total(d) <= stop;
         if (off) break;
     }
-    T* pl = it & 1 ? p1 : p0;
+    // x64 += |r| d with d the inner solution, the last step included
+    double* const sv = kWide ? (double*)sz : sx64;
+    double x6[2], bk[2];
+    typename Op64T::Row row64[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         if (c.sp[s] < 0) continue;
-        x[co + threadIdx.x + NT * s] = xk[s];
-        pl[co + threadIdx.x + NT * s] = pk[s];
+        const int q = threadIdx.x + NT * s;
+        x6[s] = ps.first ? 0.0 : ps.x64[co + q];
+        bk[s] = bc[q];
+        row64[s] = sop64.row(c.si[s], c.sj[s], q);
+        const T d = xk[s] + (T)alpha * pk[s];
+        x6[s] += norm * (double)d;
+        sv[c.sp[s]] = x6[s];  // earlier reads lie before the last sum's barrier
+        ps.x64[co + q] = x6[s];
     }
+    lds_barrier();
+    double v2 = 0.0;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        if (c.sp[s] < 0) continue;
+        using Nb = typename Op64T::Nb;
+        const double v =
+            fr[s] ? bk[s] - sop64.combine(c.si[s], c.sj[s], row64[s], lds_nb((const Nb*)nullptr, sv + c.sp[s], P)) : 0.0;
+        ps.r64[co + threadIdx.x + NT * s] = v;
+        v2 += v * v;
+    }
+    const double s2 = total(v2);
+    if (threadIdx.x < ps.nblk) ps.partial[(size_t)col * ps.nblk + threadIdx.x] = threadIdx.x ? 0.0 : s2;
     if (threadIdx.x == 0) {
-        st[col].rz = rz;
-        st[col].pq = pq;
-        st[col].alpha = alpha;
+        double tol2 = stop;
+        const bool on = outer_state(s2, obb, ps.rtol, ps.tol_floor, norm, tol2);
+        st[col].obb = obb;
+        st[col].rr = s2;
         st[col].its = it;
-        if (off) act[col] = 0;
+        st[col].tol2 = tol2;
+        ps.oact[col] = on ? 1 : 0;
+        ps.colnorm[col] = norm;
     }
 }
 

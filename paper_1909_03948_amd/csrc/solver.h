@@ -110,6 +110,8 @@ class Hierarchy {
     template <typename T>
     bool pcg(int nc, int max_iter, int* iters, const std::function<void()>* tail = nullptr);
     template <typename T>
+    void small_pass(int nc, int max_iter, int* iters, const struct SmallPass& sp);
+    template <typename T>
     void pcg_iteration(int nc, int cur, int first);
     template <typename T>
     hipGraphExec_t pcg_graph(int nc, int reps);

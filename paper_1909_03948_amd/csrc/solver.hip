@@ -346,15 +346,12 @@ __global__ void k_ir_finalize(int first, const double* __restrict__ partial, int
     c.rr = s;
     // a non-finite residual (NaN or infinity in b, or met in the solve) stops
     // the column; the host reports it as not converged
-    const bool a = isfinite(s) && isfinite(c.obb) && s > rtol * rtol * c.obb && s > 0.0;
+    // (the tolerance is relative to the inner right-hand side, of unit norm)
+    double norm, tol2 = c.tol2;
+    const bool a = outer_state(s, c.obb, rtol, tol_floor, norm, tol2);
     oact[blockIdx.x] = a ? 1 : 0;
-    colnorm[blockIdx.x] = sqrt(s);
-    if (a) {
-        // inner target: the remaining factor to rtol |b|, with margin, floored
-        double t = 0.5 * rtol * sqrt(c.obb / s);
-        if (t < tol_floor) t = tol_floor;
-        c.tol2 = t * t;  // relative to the inner right-hand side (unit norm)
-    }
+    colnorm[blockIdx.x] = norm;
+    c.tol2 = tol2;
 }
 
 // Inner right-hand side r / |r| in precision T; zero initial guess.  The first
@@ -1427,30 +1424,6 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
     hipStream_t s = ctx_->stream;
     launch_stream_ = s;
     int* act = act_.get();
-    if (N_ <= kBottomN && max_iter > 0) {
-        // iterations come in pairs after the first, as in the loop below
-        const int cap = 1 + 2 * (max_iter / 2);
-        PcgWork<T>& w = work<T>();
-        const BottomArgs ba = bottom_args(0);
-        with_op<T>(0, [&](auto op) {
-            using Op = decltype(op);
-            constexpr int kind = std::is_same_v<Op, OpA<T>> ? (int)kOpState : (int)kOpPrior;
-            k_pcg_small<T, kind, Op><<<nc, 1024, 0, s>>>(ba, op, w.r.get(), w.x.get(), w.p.get(), w.p2.get(), n_, act,
-                                                         st_.get(), cheb_coef(), cap);
-        });
-        HINV_LAUNCH_CHECK();
-        if (trace_on()) trace_cols(s, "pcg", cap, st_.get(), act, nc);
-        if (tail) (*tail)();
-        read_state(s, nc, tail ? 2 : 1);
-        HINV_HIP(hipStreamSynchronize(s));
-        int live = 0, taken = 0;
-        for (int c = 0; c < nc; ++c) {
-            live += host_act()[c];
-            taken = std::max(taken, (int)host_st()[c].its);
-        }
-        *iters += taken;
-        return tail && !live;
-    }
     tune_shape<T>(nc, true);
     const bool graphs = !std::getenv("HINV_NO_GRAPHS");
     // The prologue (V-cycle of the initial residual, first iteration) is a
@@ -1599,6 +1572,32 @@ void Hierarchy::precondition(int nc, const double* r, int ldr, double* z, int ld
     HINV_LAUNCH_CHECK();
 }
 
+// One refinement pass of every column on a mesh N <= kBottomN; reads back the
+// column states and outer flags.  Iterations come in pairs after the first, as
+// in pcg().
+template <typename T>
+void Hierarchy::small_pass(int nc, int max_iter, int* iters, const SmallPass& sp) {
+    hipStream_t s = ctx_->stream;
+    const BottomArgs ba = bottom_args(0);
+    const int cap = 1 + 2 * (max_iter / 2);
+    with_op<T>(0, [&](auto op) {
+        with_op<double>(0, [&](auto op64) {
+            using Op = decltype(op);
+            using Op64 = decltype(op64);
+            constexpr bool state = std::is_same_v<Op, OpA<T>>, ref = std::is_same_v<Op, OpKARef<T>>;
+            if constexpr (state == std::is_same_v<Op64, OpA<double>> && ref == std::is_same_v<Op64, OpKARef<double>>)
+                k_pcg_small<T, state ? (int)kOpState : (int)kOpPrior, Op, Op64>
+                    <<<nc, 1024, 0, s>>>(ba, op, op64, sp, st_.get(), cheb_coef(), cap);
+        });
+    });
+    HINV_LAUNCH_CHECK();
+    read_state(s, nc, 2);
+    HINV_HIP(hipStreamSynchronize(s));
+    int taken = 0;
+    for (int c = 0; c < nc; ++c) taken = std::max(taken, (int)host_st()[c].its);
+    *iters += taken;
+}
+
 void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int precision,
                       double rtol, int max_iter, SolveStats* stats, double accept) {
     if (!ready_) fail(HINV_ESTATE, "solve before the operator coefficient was set");
@@ -1622,7 +1621,10 @@ void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int 
     auto launch_init = [&](auto op) {
         k_ir_init<<<g, kBlock, 0, s>>>(op, b, ldb, xw, r64_.get(), ld, partial_.get());
     };
-    with_op<double>(0, launch_init);
+    // meshes of bottom levels only: a pass is one launch, which also starts the
+    // column's state in the first
+    const bool small = N_ <= kBottomN && max_iter > 0;
+    if (!small) with_op<double>(0, launch_init);
     HINV_LAUNCH_CHECK();
     // FP32 refinement: a pass reduces the true residual by no more than about
     // kappa eps_32, whatever the inner tolerance, so the inner PCG stops at half
@@ -1631,8 +1633,9 @@ void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int 
     const auto floor_for = [&](double rho) { return std::min(0.1, std::max(inner_tol32, 0.5 * rho)); };
     double floor32 = floor_for(rho32_), rho_seen = 0.0;
     const double floor64 = 1e-14;
-    k_ir_finalize<<<nc, kBlock, 0, s>>>(1, partial_.get(), nblk, st_.get(), oact_.get(),
-                                        colnorm_.get(), rtol, fp32 ? floor32 : floor64, nullptr, nullptr);
+    if (!small)
+        k_ir_finalize<<<nc, kBlock, 0, s>>>(1, partial_.get(), nblk, st_.get(), oact_.get(),
+                                            colnorm_.get(), rtol, fp32 ? floor32 : floor64, nullptr, nullptr);
     HINV_LAUNCH_CHECK();
     int iters = 0, outer = 0, fallbacks = 0;
     bool have_state = false;  // the host block already holds this pass's outer state
@@ -1749,7 +1752,16 @@ void Hierarchy::solve(int nc, const double* b, int ldb, double* x, int ldx, int 
                                                 rtol, use32 ? floor32 : floor64, inner, tdone_.get());
             HINV_LAUNCH_CHECK();
         };
-        if (use32) {
+        if (small) {
+            const SmallPass sp{b, ldb, xw, r64_.get(), partial_.get(), colnorm_.get(), ld, nblk, oact_.get(), rtol,
+                               use32 ? floor32 : floor64, outer == 0 ? 1 : 0};
+            if (use32)
+                small_pass<float>(nc, max_iter - iters, &iters, sp);
+            else
+                small_pass<double>(nc, max_iter - iters, &iters, sp);
+            have_state = true;
+            last64 = !use32;
+        } else if (use32) {
             start_pass<float>(nc);
             pcg<float>(nc, max_iter - iters, &iters);
             step(w32_, nullptr);
