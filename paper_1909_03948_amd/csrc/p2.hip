@@ -7,6 +7,7 @@
 
 #include "grid.h"
 #include "p2.h"
+#include "problem.h"
 
 namespace hinv {
 
@@ -743,6 +744,14 @@ void P2Space::run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hi
         HINV_LAUNCH_CHECK();
         finish(2);
     };
+    // the first kernel zeroes x and reads b around the nodes of a tile, so
+    // columns of b and x that may overlap are solved from a copy of b
+    const auto at = [](const void* p) { return reinterpret_cast<uintptr_t>(p); };
+    if (at(x + (size_t)ldx * nc) > at(b) && at(b + (size_t)ldb * nc) > at(x)) {
+        dev_copy(ctx_, ns, nc, b, ldb, R[1], ns);
+        b = R[1];
+        ldb = ns;
+    }
     k_p2_down<true><<<g, 256, 0, s>>>(N, cT_, dinv_.get(), b, ldb, R[0], nullptr, nullptr, x, ldx, z_.get(), rc,
                                          n1, rdown, ch, st_.get(), 0, act);
     HINV_LAUNCH_CHECK();
