@@ -25,10 +25,12 @@ struct P2Elem {
 };
 
 // State of a right-hand side of the solver: |b|^2, |r|^2, r^T z (by the parity
-// of the iteration), iterations taken, and whether it is still iterating.
+// of the iteration), iterations taken, whether it is still iterating, and
+// whether it was when the last k_p2_down ran: k_p2_up clears the flags of a
+// column that ends, so its workgroups go by this one, which no k_p2_up writes.
 struct P2Col {
     double bb, rr, rz[2];
-    int its, live;
+    int its, live, on;
 };
 
 constexpr int kP2Tile = 8;  // P1 vertices a side of a workgroup's tile

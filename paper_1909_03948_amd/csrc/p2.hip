@@ -230,12 +230,14 @@ __global__ __launch_bounds__(256) void k_p2_down(int N, const double* __restrict
                                                  int ldr, double* __restrict__ r_out, const double* __restrict__ p,
                                                  const double* __restrict__ q, double* __restrict__ x, int ldx,
                                                  double* __restrict__ z, double* __restrict__ rc, int ldc,
-                                                 P2Red red, P2Cheb ch, const P2Col* __restrict__ st, int cur,
+                                                 P2Red red, P2Cheb ch, P2Col* __restrict__ st, int cur,
                                                  const int* __restrict__ act) {
     using T = P2Tile;
     constexpr int V = T::V;
     const int col = blockIdx.z;
-    if (!FIRST && !act[col]) return;
+    const bool on = FIRST || act[col];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) st[col].on = on;
+    if (!on) return;
     const T t(N);
     const int side = 2 * N + 1, ns = side * side;
     __shared__ double cs[2 * T::C * T::C], sr[T::D * T::D], sd[T::D * T::D], sa[T::D * T::D], sz[T::D * T::D];
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(256) void k_p2_up(int N, const double* __restrict__
     using T = P2Tile;
     constexpr int V = T::V;
     const int col = blockIdx.z;
-    if (!act[col]) return;
+    if (!st[col].on) return;  // not act: this launch clears it
     const T t(N);
     const int side = 2 * N + 1, ns = side * side, N1 = N + 1;
     __shared__ double cs[2 * T::C * T::C], sr[T::D * T::D], sd[T::D * T::D], sa[T::D * T::D], sz[T::D * T::D];
@@ -464,7 +466,7 @@ __global__ __launch_bounds__(256) void k_p2_finish(const double* __restrict__ pa
 
 __global__ void k_p2_start(int nc, P2Col* __restrict__ st) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < nc) st[c] = P2Col{0.0, 0.0, {0.0, 0.0}, 0, 1};
+    if (c < nc) st[c] = P2Col{0.0, 0.0, {0.0, 0.0}, 0, 1, 1};
 }
 
 __global__ void k_p2_zero(int ns, double* __restrict__ x, int ld) {
