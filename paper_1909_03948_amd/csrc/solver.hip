@@ -804,6 +804,7 @@ int Hierarchy::min_per() const {
 // precision, and the version of the kernels' launch-shape rules.
 namespace {
 constexpr int kTuneVersion = 4;
+constexpr int kMaxRows = 4096;  // longest segment a record or HINV_SHAPE may name
 std::mutex g_tune_mu;
 bool g_tune_loaded = false;
 struct TuneRec {
@@ -836,7 +837,7 @@ void tune_load_locked() {
                         "\"rows\": %d, \"per\": %d, \"cb\": %d, \"chunk\": %d}",
                         &ver, arch, &r.kind, &r.N, &r.ninst, &r.nc, &r.fp32, &r.small, &r.len, &r.per,
                         &r.cb, &r.chunk) == 12 &&
-            ver == kTuneVersion && r.len >= 1 && r.len <= 4096 && r.per >= 1 && r.per <= 16 && r.cb >= 1 && r.cb <= 64 && r.chunk >= 0 &&
+            ver == kTuneVersion && r.len >= 1 && r.len <= kMaxRows && r.per >= 1 && r.per <= 16 && r.cb >= 1 && r.cb <= 64 && r.chunk >= 0 &&
             r.chunk % 64 == 0 && r.chunk <= kVecNodes * vec_threads(r.per)) {
             r.arch = arch;
             g_tune.push_back(r);
@@ -876,7 +877,8 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
     if (N_ <= kBottomN) return;  // one workgroup a column throughout: nothing to choose
     // HINV_SHAPE forces a shape (tests of every launch path)
     if (const char* f = std::getenv("HINV_SHAPE")) {
-        // HINV_SHAPE=<s|l><per>[c<cb>][k<chunk>]
+        // HINV_SHAPE=<s|l><per>[c<cb>][k<chunk>][r<rows>]: per and chunk shape
+        // the PCG kernels of few columns, cb and rows the wave-row kernels of batches
         if ((f[0] == 's' || f[0] == 'l') && std::atoi(f + 1) >= 1) {
             shape_.small = f[0] == 's';
             shape_.per = std::min(16, std::atoi(f + 1));
@@ -884,6 +886,8 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
             shape_.cb = c ? std::max(1, std::min(64, std::atoi(c + 1))) : 1;
             const char* k = std::strchr(f, 'k');
             shape_.chunk = k ? std::atoi(k + 1) : 0;
+            const char* r = std::strchr(f, 'r');
+            if (r) shape_.len = std::max(1, std::min(kMaxRows, std::atoi(r + 1)));
             if (shape_.chunk && (shape_.chunk % 64 || shape_.chunk > kVecNodes * vec_threads(shape_.per) ||
                                  ceil_div(n_, shape_.chunk) > red_stride_))
                 fail(HINV_EINVAL, "HINV_SHAPE: chunk must be a multiple of 64 that the per's threads cover");
