@@ -154,6 +154,7 @@ class Hierarchy {
     int cus_ = 0;  // compute units of the device
     LaunchShape default_shape(int nc) const;
     int min_per() const;
+    bool few_waves(int nc) const;
     template <typename T>
     void tune_shape(int nc, bool in_pass);
     // the inner right-hand side, zero iterate and column states of a refinement pass

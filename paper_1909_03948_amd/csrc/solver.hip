@@ -767,7 +767,7 @@ Hierarchy::LaunchShape Hierarchy::default_shape(int nc) const {
     sh.per = nc < kFewCols ? 1 : std::min(16, std::max(1, ceil_div(nb, 64)));
     sh.per = std::max(sh.per, min_per());
     sh.cb = 1;
-    sh.len = kBatchRows[0];
+    sh.len = few_waves(nc) ? 2 : kBatchRows[0];
     if (nc < kFewCols && min_per() > 1) {
         // too many node blocks for one a workgroup: the column split into one or
         // two workgroups of 1024 threads per compute unit (a partial last round
@@ -781,6 +781,13 @@ Hierarchy::LaunchShape Hierarchy::default_shape(int nc) const {
         }
     }
     return sh;
+}
+
+// Whether the finest launch of nc columns in segments of kShortRows is at most
+// kShortWaves waves a compute unit.
+bool Hierarchy::few_waves(int nc) const {
+    const int nodes = N_ / 2 + 1;
+    return (long long)ceil_div(nodes, kDownOwn) * ceil_div(nodes, kShortRows) * nc <= (long long)kShortWaves * cus_;
 }
 
 // Every workgroup of the kernels after a reduction sums all of its partials,
@@ -803,7 +810,7 @@ int Hierarchy::min_per() const {
 // unit count, operator kind, mesh size, stacked instances, columns, solve
 // precision, and the version of the kernels' launch-shape rules.
 namespace {
-constexpr int kTuneVersion = 4;
+constexpr int kTuneVersion = 5;
 constexpr int kMaxRows = 4096;  // longest segment a record or HINV_SHAPE may name
 std::mutex g_tune_mu;
 bool g_tune_loaded = false;
@@ -943,10 +950,13 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
     // reading of the operator (a wave of the wave-row kernels, a workgroup of
     // the multi-level ones).
     if (nc >= kFewCols) {
+        const bool few = few_waves(nc);
         for (int small : {0, 1})
             for (int len : kBatchRows)
                 for (int cb : {1, 2}) {
-                    if (small && (len != kBatchRows[0] || cb > 1)) continue;
+                    if (few ? len > kShortRows || cb > 1
+                            : len < kShortRows || (small && (len != kBatchRows[0] || cb > 1)))
+                        continue;
                     shape_.small = small != 0;
                     shape_.len = len;
                     shape_.cb = cb;

@@ -39,9 +39,15 @@ constexpr int kDownOwn = 29, kUpOwn = 60;
 // at the first call of a shape (longer segments re-read fewer halo rows, shorter
 // ones give small meshes enough waves).  C = 2 columns a wave share the state
 // operator's coefficients and are picked by the same timing.
+// Batches of at most kShortWaves waves a compute unit at 5 rows are bound by the
+// march's length: they are timed at 5, 2 and 1 rows, one column a wave.
+// Gauss-Newton action at 5 / 2 / 1 rows: 64^2 x 8 (0.4 waves) 768 / 676 / 641 us,
+// 128^2 x 24 (3.7) 1147 / 1065 / 1141, 256^2 x 12 (6.1) 1630 / 1538 / 1632;
+// past the line 128^2 x 70 (10.7) 1555 / 1697 / 1927, 64^2 x 220 (12) 1348 /
+// 1508 / 1733.
 constexpr int kLatencyChunk = 8, kLatencyRows = 5, kLatencyWaves = 6;
 constexpr int kBatchChunk = 4;
-constexpr int kBatchRows[] = {13, 29, 5};
+constexpr int kBatchRows[] = {13, 29, 5, 2, 1}, kShortRows = 5, kShortWaves = 8;
 
 // Rows of a row pipeline: a segment of len coarse rows of the down step takes
 // 2 len + 5 rows, one of len fine rows of the up step len + 4.
