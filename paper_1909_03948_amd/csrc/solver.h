@@ -173,7 +173,7 @@ class Hierarchy {
     int ninst_ = 1;
     int cpi_ = 1;  // columns per instance of the current call
     LaunchShape shape_{true, 1, 1, 1};  // launch shape of the current call
-    std::vector<std::pair<long long, LaunchShape>> tuned_;  // (nc * 2 + fp32, shape)
+    std::vector<std::pair<long long, LaunchShape>> tuned_;  // (4 nc + 2 pass + fp32, shape)
     std::vector<std::pair<long long, int>> last_iters_;    // (nc * 2 + fp32, PCG iterations)
     std::vector<PriorParams> inst_pp_;
     std::vector<char> inst_ready_;

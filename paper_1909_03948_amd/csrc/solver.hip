@@ -808,15 +808,16 @@ int Hierarchy::min_per() const {
 // line of a key wins), so that later processes on the same kind of device
 // reuse them instead of timing again.  Key: device architecture and compute
 // unit count, operator kind, mesh size, stacked instances, columns, solve
-// precision, and the version of the kernels' launch-shape rules.
+// precision, what was timed (a refinement pass or the V-cycle alone), and the
+// version of the kernels' launch-shape rules.
 namespace {
-constexpr int kTuneVersion = 5;
+constexpr int kTuneVersion = 6;
 constexpr int kMaxRows = 4096;  // longest segment a record or HINV_SHAPE may name
 std::mutex g_tune_mu;
 bool g_tune_loaded = false;
 struct TuneRec {
     std::string arch;
-    int kind, N, ninst, nc, fp32, small, len, per, cb, chunk;
+    int kind, N, ninst, nc, fp32, pass, small, len, per, cb, chunk;
 };
 std::vector<TuneRec> g_tune;
 long g_tune_timed = 0, g_tune_cached = 0;
@@ -840,10 +841,10 @@ void tune_load_locked() {
         int ver = 0;
         if (std::sscanf(line,
                         "{\"version\": %d, \"device\": \"%127[^\"]\", \"kind\": %d, \"N\": %d, "
-                        "\"instances\": %d, \"columns\": %d, \"fp32\": %d, \"small\": %d, "
+                        "\"instances\": %d, \"columns\": %d, \"fp32\": %d, \"pass\": %d, \"small\": %d, "
                         "\"rows\": %d, \"per\": %d, \"cb\": %d, \"chunk\": %d}",
-                        &ver, arch, &r.kind, &r.N, &r.ninst, &r.nc, &r.fp32, &r.small, &r.len, &r.per,
-                        &r.cb, &r.chunk) == 12 &&
+                        &ver, arch, &r.kind, &r.N, &r.ninst, &r.nc, &r.fp32, &r.pass, &r.small, &r.len, &r.per,
+                        &r.cb, &r.chunk) == 13 &&
             ver == kTuneVersion && r.len >= 1 && r.len <= kMaxRows && r.per >= 1 && r.per <= 16 && r.cb >= 1 && r.cb <= 64 && r.chunk >= 0 &&
             r.chunk % 64 == 0 && r.chunk <= kVecNodes * vec_threads(r.per)) {
             r.arch = arch;
@@ -874,7 +875,7 @@ void Hierarchy::start_pass(int nc) {
 
 template <typename T>
 void Hierarchy::tune_shape(int nc, bool in_pass) {
-    const long long key = 2LL * nc + (sizeof(T) == 4);
+    const long long key = 4LL * nc + 2 * in_pass + (sizeof(T) == 4);
     for (const auto& kv : tuned_)
         if (kv.first == key) {
             shape_ = kv.second;
@@ -910,7 +911,7 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
         tune_load_locked();
         for (auto it = g_tune.rbegin(); it != g_tune.rend(); ++it)
             if (it->arch == arch && it->kind == (int)kind_ && it->N == N_ && it->ninst == ninst_ && it->nc == nc &&
-                it->fp32 == fp32 && it->per >= min_per()) {
+                it->fp32 == fp32 && it->pass == (int)in_pass && it->per >= min_per()) {
                 shape_.small = it->small != 0;
                 shape_.len = it->len;
                 shape_.per = it->per;
@@ -986,18 +987,18 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         ++g_tune_timed;
-        TuneRec r{arch, (int)kind_, N_, ninst_, nc, fp32, best.small ? 1 : 0, best.len, best.per, best.cb,
-                  best.chunk};
+        TuneRec r{arch, (int)kind_, N_, ninst_, nc, fp32, in_pass ? 1 : 0, best.small ? 1 : 0, best.len, best.per,
+                  best.cb, best.chunk};
         g_tune.push_back(r);
         const char* path = std::getenv("HINV_TUNE_CACHE");
         if (path && *path)
             if (std::FILE* f = std::fopen(path, "a")) {
                 std::fprintf(f,
                              "{\"version\": %d, \"device\": \"%s\", \"kind\": %d, \"N\": %d, \"instances\": %d, "
-                             "\"columns\": %d, \"fp32\": %d, \"small\": %d, \"rows\": %d, \"per\": %d, "
-                             "\"cb\": %d, \"chunk\": %d}\n",
-                             kTuneVersion, r.arch.c_str(), r.kind, r.N, r.ninst, r.nc, r.fp32, r.small, r.len,
-                             r.per, r.cb, r.chunk);
+                             "\"columns\": %d, \"fp32\": %d, \"pass\": %d, \"small\": %d, \"rows\": %d, "
+                             "\"per\": %d, \"cb\": %d, \"chunk\": %d}\n",
+                             kTuneVersion, r.arch.c_str(), r.kind, r.N, r.ninst, r.nc, r.fp32, r.pass, r.small,
+                             r.len, r.per, r.cb, r.chunk);
                 std::fclose(f);
             }
     }
