@@ -91,7 +91,10 @@ class P2Space {
     DBuf<double> r_, r2_, z_, z2_, p_, p2_, q_v_, part_;
     DBuf<P2Col> st_;
     P2Col* hst_ = nullptr;
-    int last_its_ = 8;  // iterations of the last solve
+    // iterations of the last solve that met its tolerance, by column count and
+    // decade of the tolerance
+    std::vector<std::pair<long long, int>> last_its_;
+    int& last_its(int nc, double rtol);
     void ensure(int nc);
     void run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hierarchy& coarse, double rtol,
                    int max_iter);

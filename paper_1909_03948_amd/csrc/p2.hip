@@ -701,12 +701,23 @@ P2Space::~P2Space() {
     if (hst_) (void)hipHostFree(hst_);
 }
 
+constexpr int kFirstRun = 16;  // a solve to 1e-10 takes 8 or 9 iterations from 4^2 to 256^2
+
+int& P2Space::last_its(int nc, double rtol) {
+    const long long key = 64LL * nc + std::min(63, std::max(0, (int)std::lround(-std::log10(rtol))));
+    for (auto& kv : last_its_)
+        if (kv.first == key) return kv.second;
+    last_its_.push_back({key, 8});
+    return last_its_.back().second;
+}
+
 // PCG with the two-level cycle: degree-2 Chebyshev-Jacobi on [lmax / 4, lmax]
 // from zero, P^T of the residual through one V-cycle of the P1 hierarchy, P
 // back, and the same smoother again from the corrected iterate.  An iteration
 // is k_p2_dir, k_p2_down, the V-cycle and k_p2_up, which tests the column; the
-// host enqueues as many iterations as the last solve took before it first
-// looks (launches for finished columns return at once).
+// host enqueues as many iterations as the last such solve took, at most
+// kFirstRun, before it first looks (launches for finished columns return at
+// once, but are launches all the same).
 void P2Space::run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hierarchy& coarse, double rtol,
                           int max_iter) {
     hipStream_t s = ctx_->stream;
@@ -772,7 +783,7 @@ void P2Space::run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hi
             cycle(it + 1);
         }
     };
-    run(std::min(max_iter, last_its_));
+    run(std::min({max_iter, kFirstRun, last_its(nc, rtol)}));
     for (;;) {
         HINV_HIP(hipMemcpyAsync(hst_, st_.get(), sizeof(P2Col) * nc, hipMemcpyDeviceToHost, s));
         HINV_HIP(hipStreamSynchronize(s));
@@ -802,7 +813,7 @@ void P2Space::solve(int nc, const double* b, int ldb, double* x, int ldx, Hierar
         if (!std::isfinite(rel)) finite = false;
         else worst = std::max(worst, rel);
     }
-    last_its_ = std::max(1, its);
+    if (live == 0 && finite) last_its(nc, rtol) = std::max(1, its);
     if (!finite) worst = std::numeric_limits<double>::quiet_NaN();
     if (st) {
         st->solves += nc;
