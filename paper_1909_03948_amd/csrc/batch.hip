@@ -56,6 +56,7 @@ void Batch::sync(Group& g) {
 
 void Batch::ensure(Group& g, int nrhs) {
     if (nrhs <= g.cap) return;
+    g.cap = 0;  // until every buffer is there
     const size_t len = (size_t)g.n * g.mem.size() * nrhs;
     g.a.ensure(len);
     g.b.ensure(len);

@@ -635,6 +635,7 @@ void Cnn::ensure(int B, int S) {
     const int tiles = ceil_div(S, kT);
     const int nwg = tiles * tiles * B;
     if (np > (size_t)B_ * S_ * S_ || nwg > nwg_) {
+        B_ = S_ = nwg_ = 0;  // until every buffer is there
         in0_.ensure(np * kPadIn);
         for (int l = 0; l < kLayers - 1; ++l) {
             a_[l].ensure(np * kCh);

@@ -686,6 +686,7 @@ void P2Space::forward_rhs(double* rhs) {
 
 void P2Space::ensure(int nc) {
     if (nc <= cap_) return;
+    cap_ = 0;  // until every buffer is there
     const size_t len = (size_t)ns * nc;
     for (auto* b : {&r_, &r2_, &z_, &z2_, &p_, &p2_, &q_v_}) b->ensure(len);
     const int nt = ceil_div(N + 1, kP2Tile);

@@ -650,6 +650,7 @@ void Problem::set_data(const double* d_host, double sig) {
 double* Problem::scratch(int which, int nc) {
     if (which < 0 || which >= kScratch) fail(HINV_EINVAL, "internal: scratch index out of range");
     if (nc > cap_) {
+        cap_ = 0;  // until every buffer is there
         for (auto& w : w_) w.release();
         for (auto& w : w_) w.ensure((size_t)std::max(n, ns) * nc);
         cap_ = nc;
@@ -659,6 +660,7 @@ double* Problem::scratch(int which, int nc) {
 
 double* Problem::obs_scratch(int nc) {
     if (nc > qcap_) {
+        qcap_ = 0;
         wq_.ensure((size_t)std::max(q, 1) * nc);
         qcap_ = nc;
     }
@@ -901,10 +903,21 @@ void Problem::hessian(int mode, int nc, const double* mhat, int ldm, double* out
         prior_apply(nc, mhat, ldm, rm, n, false, side);
         HINV_HIP(hipEventRecord(ev_join_, side));
     }
-    // the P2 state solves in FP64 PCG: no chained tightening
-    inc_forward(nc, mhat, ldm, uh, ns, st, S2 ? rtol : chained_first_rtol(precision, nc, rtol));
-    inc_adjoint(nc, gn, mhat, ldm, uh, ns, ph, ns, st);
-    if (with_prior) HINV_HIP(hipStreamWaitEvent(ctx->stream, ev_join_, 0));
+    // joined also when a solve throws: the context's stream hands out again
+    // what the side stream still works on
+    struct Join {
+        hipStream_t s;
+        hipEvent_t ev;
+        ~Join() {
+            if (ev) (void)hipStreamWaitEvent(s, ev, 0);
+        }
+    };
+    {
+        const Join join{ctx->stream, with_prior ? ev_join_ : nullptr};
+        // the P2 state solves in FP64 PCG: no chained tightening
+        inc_forward(nc, mhat, ldm, uh, ns, st, S2 ? rtol : chained_first_rtol(precision, nc, rtol));
+        inc_adjoint(nc, gn, mhat, ldm, uh, ns, ph, ns, st);
+    }
     hess_output(mode, nc, mhat, ldm, uh, ns, ph, ns, out, ldo, rm);
 }
 

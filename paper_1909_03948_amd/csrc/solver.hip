@@ -625,6 +625,7 @@ PcgWork<float>& Hierarchy::work<float>() {
 void Hierarchy::ensure_cols(int nc) {
     if (nc <= cap_) return;
     drop_graphs();
+    cap_ = 0;  // until every buffer is there
     const size_t n = n_;
     x64_.ensure(n * nc);
     r64_.ensure(n * nc);
@@ -653,6 +654,7 @@ void Hierarchy::read_state(hipStream_t s, int nc, int nflags) {
 template <typename T>
 static void ensure_work(PcgWork<T>& w, const std::vector<std::unique_ptr<Level>>& lev, int nc) {
     if (nc <= w.cap) return;
+    w.cap = 0;  // until every buffer is there
     const size_t n = lev[0]->n;
     w.x.ensure(n * nc);
     w.r.ensure(n * nc);
