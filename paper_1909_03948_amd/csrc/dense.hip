@@ -784,11 +784,18 @@ __device__ __forceinline__ void jacobi_apply(int s, int np, double* T, int ldt, 
     }
 }
 
-// Largest s of the one-workgroup sweeps (two copies of the matrix in LDS; one
-// step costs ~2 us there, ~16 us a block step of 16 indices beyond): measured
-// at s = 48 / 64 / 70 / 80 / 96 590 / 1113 / 1483 / 1805 / 3067 us against 762 /
-// 833 / 1167 / 1179 / 1179 blocked.
-constexpr int kJacLdsMax = 56;
+// The one-workgroup sweeps (two copies of the matrix in LDS) take nb matrices of
+// a launch at the price of one, ~2 us a step; a block step of 16 indices
+// beyond takes ~16 us and np + 2 np^2 workgroups a matrix.  So the former serve
+// s <= 56 and, where the blocks come in threes (64 < s <= 96), large batches:
+// one matrix, LDS / blocked, s = 48 / 64 / 70 / 80 / 96 590 / 1088 / 1486 / 1809 / 3080
+// against 762 / 838 / 1180 / 1287 / 1182 us; 32 matrices, s = 65 / 72 / 80 1350 /
+// 1603 / 1989 against 1632 / 1647 / 1760; 52 (more than 1024 workgroups a step),
+// s = 65 / 72 / 76 1332 / 1607 / 1820 against 2144 / 2187 / 2204.
+constexpr int kJacLdsMax = 80;
+inline bool jacobi_one_group(int nb, int s) {
+    return s <= 56 || (s > 64 && s <= kJacLdsMax && nb >= (s <= 72 ? 32 : 49));
+}
 
 // Parallel cyclic Jacobi (round-robin pairing), one workgroup, on T and S
 // (ld ldt, lds): per step, the np disjoint rotations, then jacobi_apply.
@@ -1355,7 +1362,7 @@ void sym_eig(Ctx* ctx, DenseWork& w, int nb, int s, double* T, int ldt, size_t s
                                                                                 lam, sl);
         HINV_LAUNCH_CHECK();
     };
-    if (s <= kJacLdsMax && lds_fits(ctx, shm)) {
+    if (jacobi_one_group(nb, s) && lds_fits(ctx, shm)) {
         double* Stmp = w.part.get();
         k_jacobi_lds<<<nb, 1024, shm, ctx->stream>>>(s, T, ldt, st, Stmp, s, s2, kMaxSweeps);
         HINV_LAUNCH_CHECK();
