@@ -198,8 +198,9 @@ const char* hinv_status_string(int status);
 /* ---- kernel timing (roofline reports) ------------------------------------- */
 #define HINV_KCLASS_MG_DOWN     0  /* r -= alpha q, finest-level pre-smooth + residual + restriction */
 #define HINV_KCLASS_MG_UP       1  /* finest-level prolongation + post-smooth (+ r^T z) */
-#define HINV_KCLASS_MG_BOTTOM   2  /* all levels N <= 32, one workgroup per column (on meshes
-                                     N <= 32 a whole pass is one untimed launch) */
+#define HINV_KCLASS_MG_BOTTOM   2  /* all levels N <= 32, one workgroup per column; on meshes
+                                     N <= 32 that is a whole refinement pass, with no
+                                     launches of the classes 0, 1 and 3 */
 #define HINV_KCLASS_PCG_APPLY   3  /* p = z + beta p, q = A p, x += alpha p of the step before */
 #define HINV_KCLASS_PCG_UPDATE  4  /* no launches of its own: the step is part of 0 and 3 */
 #define HINV_KCLASS_GRAM        5  /* tall-skinny block product X^T Y on the matrix cores */

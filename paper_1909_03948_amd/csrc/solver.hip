@@ -1597,14 +1597,26 @@ void Hierarchy::small_pass(int nc, int max_iter, int* iters, const SmallPass& sp
     hipStream_t s = ctx_->stream;
     const BottomArgs ba = bottom_args(0);
     const int cap = 1 + 2 * (max_iter / 2);
+    // bytes: per running column b and x (later passes also x and r in), r and x
+    // out; once per launch and instance the state coefficients, and the coarse inverse
+    int cols = nc;
+    if (!sp.first) {
+        cols = 0;
+        for (int c = 0; c < nc; ++c) cols += host_oact()[c];
+    }
+    double ncoef = 0.0;
+    for (const auto& L : lev_) ncoef += L->n;
+    const double bytes = sizeof(double) * (sp.first ? 3.0 : 5.0) * n_ * cols +
+                         ninst_ * (kind_ == kOpState ? 3.0 * (sizeof(float) * ncoef + sizeof(double) * n_) : 0.0) +
+                         ninst_ * sizeof(float) * (double)nc_coarse_ * nc_coarse_;
     with_op<T>(0, [&](auto op) {
         with_op<double>(0, [&](auto op64) {
             using Op = decltype(op);
             using Op64 = decltype(op64);
             constexpr bool state = std::is_same_v<Op, OpA<T>>, ref = std::is_same_v<Op, OpKARef<T>>;
             if constexpr (state == std::is_same_v<Op64, OpA<double>> && ref == std::is_same_v<Op64, OpKARef<double>>)
-                k_pcg_small<T, state ? (int)kOpState : (int)kOpPrior, Op, Op64>
-                    <<<nc, 1024, 0, s>>>(ba, op, op64, sp, st_.get(), cheb_coef(), cap);
+                timed_launch(ctx_, kKBottom, bytes, k_pcg_small<T, state ? (int)kOpState : (int)kOpPrior, Op, Op64>,
+                             dim3(nc), dim3(1024), s, ba, op, op64, sp, st_.get(), cheb_coef(), cap);
         });
     });
     HINV_LAUNCH_CHECK();
