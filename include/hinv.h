@@ -218,8 +218,10 @@ int hinv_ctx_kernel_timer(hinv_ctx* ctx, int kclass, int enable, int period);
 /* Synchronizes the stream and returns, for the timed launches of a class:
  * their number, their summed duration (ms) and their summed algorithmic work
  * (bytes moved for the stencil and vector kernels -- each array counted once
- * per launch -- or flops for HINV_KCLASS_GRAM); `launches_total` is the number
- * of launches of the class while enabled. */
+ * per launch, for the columns that the launch ran for; a launch that found every
+ * column finished is not among the timed ones -- or flops for
+ * HINV_KCLASS_GRAM); `launches_total` is the number of launches of the class
+ * while enabled. */
 int hinv_ctx_kernel_timer_read(hinv_ctx* ctx, int kclass, int* timed, long* launches_total,
                                double* total_ms, double* total_work);
 

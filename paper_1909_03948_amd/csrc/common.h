@@ -119,6 +119,20 @@ struct KernelTimer {
         k.work[slot] = work;
         return slot;
     }
+    // Sampled launches of a stretch: columns that end early skip their kernels,
+    // which the host learns afterwards.  cut leaves a share f of the work of the
+    // launches recorded between two marks (none: the launches are not counted).
+    struct Mark {
+        int used[kClasses];
+    };
+    Mark mark() const {
+        Mark m;
+        for (int c = 0; c < kClasses; ++c) m.used[c] = cls[c].used;
+        return m;
+    }
+    void cut(const Mark& from, const Mark& to, int c, double f) {
+        for (int i = from.used[c]; i < to.used[c]; ++i) cls[c].work[i] = f > 0.0 ? f * cls[c].work[i] : -1.0;
+    }
     // Launches that ran inside a graph replay: counted, not timed.
     void count_only(int c, long n) {
         if (c >= 0 && cls[c].on) cls[c].launches += n;

@@ -750,9 +750,13 @@ void P2Space::run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hi
     double *R[2] = {r_.get(), r2_.get()}, *P[2] = {p_.get(), p2_.get()};
     k_p2_start<<<ceil_div(nc, 64), 64, 0, s>>>(nc, st_.get());
     HINV_LAUNCH_CHECK();
+    const bool timing = ctx_->timer.any_on();
+    std::vector<KernelTimer::Mark> marks;  // around the V-cycle of each iteration
     auto cycle = [&](int it) {
         finish(1);
+        if (timing) marks.push_back(ctx_->timer.mark());
         coarse.cycle(nc);
+        if (timing) marks.push_back(ctx_->timer.mark());
         k_p2_up<<<g, 256, 0, s>>>(N, cT_, dinv_.get(), R[it & 1], z_.get(), e, n1, z2_.get(), rup, ch, st_.get(),
                                      rtol * rtol, it == 0, act);
         HINV_LAUNCH_CHECK();
@@ -792,6 +796,13 @@ void P2Space::run_solve(int nc, const double* b, int ldb, double* x, int ldx, Hi
         for (int c = 0; c < nc; ++c) live += hst_[c].live;
         if (!live || it >= max_iter) break;
         run(std::min(max_iter, it + 2));
+    }
+    // the V-cycle of iteration i ran for the columns that took i steps
+    for (size_t i = 0; 2 * i < marks.size(); ++i) {
+        int ran = 0;
+        for (int c = 0; c < nc; ++c) ran += hst_[c].its >= (int)i;
+        for (int k : {kclass_for(kKDown, nc), kclass_for(kKUp, nc), (int)kKBottom})
+            ctx_->timer.cut(marks[2 * i], marks[2 * i + 1], k, (double)ran / nc);
     }
 }
 

@@ -1481,6 +1481,8 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
         }
     }
     bool first_check = true, tail_state = false;
+    KernelTimer::Mark mark[3];
+    int sampled_at = 0;  // first of the two sampled iterations of this run
     const ColState* hst = host_st();  // pinned, so the read-backs need no staging copy
     const int* hact = host_act();
     bool pre_ran = pre > 0;
@@ -1493,10 +1495,14 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
             while (reps > 0 && it + 2 * reps > max_iter) --reps;
             if (sampled && it + 2 <= max_iter) {
                 ctx_->timer.force = true;
+                mark[0] = ctx_->timer.mark();
                 pcg_iteration<T>(nc, 1, 0);
+                mark[1] = ctx_->timer.mark();
                 pcg_iteration<T>(nc, 0, 0);
+                mark[2] = ctx_->timer.mark();
                 ctx_->timer.force = false;
                 sampled = false;
+                sampled_at = it + 1;
                 it += 2;
                 if (reps > 1 && graphs) {
                     HINV_HIP(hipGraphLaunch(pcg_graph<T>(nc, reps - 1), s));
@@ -1526,6 +1532,23 @@ bool Hierarchy::pcg(int nc, int max_iter, int* iters, const std::function<void()
         first_check = false;
         int live = 0;
         for (int c = 0; c < nc; ++c) live += hact[c];
+        // the work of the sampled iterations: a column that takes its steps in
+        // iteration j ends before the way up if that was its last
+        if (sampled_at) {
+            for (int i = 0; i < 2; ++i) {
+                int stepped = 0, up = 0;
+                for (int c = 0; c < nc; ++c) {
+                    const int last = (int)hst[c].its;
+                    stepped += last >= sampled_at + i;
+                    up += last > sampled_at + i || (last == sampled_at + i && hact[c]);
+                }
+                for (int k : {kKDown, kKPcgApply})
+                    ctx_->timer.cut(mark[i], mark[i + 1], kclass_for(k, nc), (double)stepped / nc);
+                for (int k : {kclass_for(kKUp, nc), (int)kKBottom})
+                    ctx_->timer.cut(mark[i], mark[i + 1], k, (double)up / nc);
+            }
+            sampled_at = 0;
+        }
         if (!live) {
             tail_state = tail != nullptr;
             break;

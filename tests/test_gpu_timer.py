@@ -1,5 +1,7 @@
 """GPU: what the kernel timer reports.  Meshes N <= 32: the launch of a whole
-refinement pass counts and is timed as the bottom levels.
+refinement pass counts and is timed as the bottom levels.  The recorded work is
+that of the columns a launch ran for: columns without work, or that ended
+before, add nothing.
 """
 import numpy as np
 import pytest
@@ -42,3 +44,74 @@ def test_small_meshes_are_timed(N, precision):
     ctx.kernel_timer("mg_bottom", False, 1)
     print(f"[gpu-timer] {r}", flush=True)
     assert r["launches"] == r["timed"] == passes and r["ms"] > 0 and r["work"] > 0
+
+
+CLASSES = ["mg_down_b", "mg_up_b", "pcg_apply_b", "mg_bottom"]
+
+
+def timed_solve(ctx, gp, b):
+    for c in CLASSES:
+        ctx.kernel_timer(c, True, 1)
+    info = gp.state_solve(b, torch.zeros_like(b))
+    out = {c: ctx.kernel_timer_read(c) for c in CLASSES}
+    for c in CLASSES:
+        ctx.kernel_timer(c, False, 1)
+    assert info["rc"] == hv.HINV_OK
+    return info, out
+
+
+@pytest.mark.parametrize("N", [64, 128])
+def test_work_of_running_columns(N):
+    print(f"[gpu-timer] N={N}", flush=True)
+    ctx = hv.Context(0)
+    gp = problem(ctx, N, hv.PREC_AUTO)
+    b = dev(synth.test_vectors((N + 1) ** 2, 16, seed=8))
+    half = b.clone()
+    half[::2] = 0.0
+    timed_solve(ctx, gp, b)  # tuned, and an estimate of the iterations made
+    info, full = timed_solve(ctx, gp, b)
+    _, part = timed_solve(ctx, gp, half)
+    for c in CLASSES:
+        f, p = full[c], part[c]
+        assert f["timed"] > 0 and p["timed"] > 0, c
+        ratio = p["work"] / p["timed"] / (f["work"] / f["timed"])
+        print(f"[gpu-timer] {c}: {f['timed']} / {p['timed']} timed, work ratio {ratio:.6f}", flush=True)
+        assert abs(ratio - 0.5) < 1e-9, c
+
+
+def test_launches_after_every_column_has_ended():
+    """A smooth right-hand side that ends after fewer iterations than the two
+    timed ones leaves no launch with work but without columns."""
+    ctx = hv.Context(0)
+    gp = problem(ctx, 64, hv.PREC_AUTO)
+    gp.set_solver(hv.PREC_AUTO, 0.5)
+    b = dev(synth.test_vectors(65 * 65, 9, seed=9))
+    timed_solve(ctx, gp, b)
+    info, r = timed_solve(ctx, gp, b)
+    print(f"[gpu-timer] {info['iterations']} iterations, {r}", flush=True)
+    assert info["iterations"] <= 2 * info["refinements"]
+    assert r["mg_up_b"]["timed"] == 0 and r["mg_up_b"]["launches"] > 0
+
+
+def test_quadratic_state_cycles():
+    print("[gpu-timer] quadratic", flush=True)
+    prob, _, obs = instance(16, 10, state_degree=2)
+    N = 64
+    ctx = hv.Context(0)
+    gp = hv.Problem(ctx, N, prob.gamma, prob.delta, obs_xy=obs, d_obs=prob.d, sigma=prob.sigma, beta=prob.beta,
+                    precision=hv.PREC_FP64, rtol=1e-10, state_degree=2)
+    ns = (2 * N + 1) ** 2
+    zero = dev(np.zeros(ns))
+    gp.linearize(dev(0.4 * synth.smooth_field(N)), zero, zero)
+    b = dev(synth.test_vectors(ns, 9, seed=10))
+    names = ["mg_down_b", "mg_up_b"]
+    for c in names:
+        ctx.kernel_timer(c, True, 1)
+    for _ in range(2):  # the first call enqueues by a guess, the second by its count
+        info = gp.state_solve(b, torch.zeros_like(b))
+    r = {c: ctx.kernel_timer_read(c) for c in names}
+    for c in names:
+        ctx.kernel_timer(c, False, 1)
+    print(f"[gpu-timer] {info['iterations']} iterations, {r}", flush=True)
+    for c in names:
+        assert r[c]["timed"] == 2 * (info["iterations"] + 1) <= r[c]["launches"]
