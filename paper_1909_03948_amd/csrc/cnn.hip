@@ -650,7 +650,6 @@ void Cnn::ensure(int B, int S) {
         S_ = S;
         nwg_ = nwg;
     }
-    part_.ensure((size_t)nwg * kWgStride * (dw_together(nwg) ? kLayers : 1));
 }
 
 void Cnn::run_forward(int B, int S, float* y) {
@@ -721,6 +720,7 @@ double Cnn::gradient(int B, int S, const float* in, const float* target, int tch
     const dim3 g(tiles, tiles, B);
     const int nwg = tiles * tiles * B;
     float* gr = grad_.get();
+    part_.ensure((size_t)nwg * kWgStride * (dw_together(nwg) ? kLayers : 1));
     dwtmp_.ensure((size_t)kLayers * kDwSplit * kWgStride);
     const int top = kLayers - 1;
     // dL/dh_{top-1} and dZ_{top-1} = dL/dh * [z > 0]; then dL/dh_{l-1} =
