@@ -60,7 +60,7 @@ FP64_MFMA_PEAK_TFLOPS = 78.6   # dense FP64 matrix cores
 BF16_MFMA_PEAK_TFLOPS = 2500.0
 # timer classes: single-column launches, the same kernels batched (_b), the
 # one-workgroup bottom levels (latency-bound) and the block product (MFMA)
-HBM_CLASSES = ["mg_down", "mg_up", "pcg_apply", "pcg_update", "mg_down_b", "mg_up_b", "pcg_apply_b", "pcg_update_b"]
+HBM_CLASSES = ["mg_down", "mg_up", "pcg_apply", "mg_down_b", "mg_up_b", "pcg_apply_b"]
 TIMED_CLASSES = HBM_CLASSES + ["mg_bottom", "gram"]
 PMC_FILE = os.path.join(ROOT, "profiles", "pmc_traffic.json")
 

@@ -7,9 +7,9 @@
 // workgroup owns a 16 x 16 pixel tile of one image and all output channels;
 // its input tile with a one-pixel halo and the layer's 3x3 x C_out x C_in
 // weights sit in LDS.  Each of the 4 waves computes 4 rows of 16 pixels; per
-// tap (dy, dx) and K-step of input channels, operand A is 16 pixels x K
-// channels read from the halo tile at the shifted position and operand B the
-// tap's K x 16 weight block.  Operand layouts (wave64; checked on the device
+// tap (dy, dx) and K-step of input channels, operand A is the tap's weights, 16
+// output channels x K, and operand B 16 pixels' K channels read from the halo
+// tile at the shifted position.  Operand layouts (wave64; checked on the device
 // against a host product): with K = 32, A: lane l holds A[l % 16][8 (l / 16) + e],
 // B: lane l holds B[8 (l / 16) + e][l % 16] (e < 8); with K = 16 the same
 // with 4 (l / 16) + e (e < 4); D: lane l item v holds D[4 (l / 16) + v][l % 16].

@@ -1,12 +1,14 @@
 // Fused multigrid V-cycle and PCG kernels (included by solver.hip only).
 //
-// V-cycle, per level above the bottom (N_l > kBottomN), two LDS-tiled kernels:
+// V-cycle, per level above the bottom (N_l > kBottomN), two kernels on wave rows
+// (waverow.h):
 //   k_down: x2 = S(b) (two Chebyshev steps from zero), r = b - A x2, b_coarse = P^T r
 //   k_up:   x = x2 + P x_coarse, then two Chebyshev steps on A x = b
-// and one kernel for all levels with N_l <= kBottomN (one workgroup per column,
-// every vector in LDS in FP32, the coarsest level solved with its dense inverse).
-// PCG reductions finish in the producing kernel: the last workgroup of a column
-// to arrive sums the per-workgroup partials in a fixed order.
+// or, with few columns, several coarse levels a launch on LDS tiles (k_down2,
+// k_up_chain), and one kernel for all levels with N_l <= kBottomN (one workgroup
+// per column, in FP32, the coarsest level solved with its dense inverse).
+// PCG reductions: every workgroup writes its partial sum, and each workgroup of
+// the next launch that needs the total sums the column's partials in a fixed order.
 #pragma once
 
 #include "grid.h"
@@ -43,25 +45,11 @@ struct ChebCoef {
 // In-kernel reductions: every workgroup writes one partial sum per column to
 // part[col * stride + blk]; a later kernel (after the kernel boundary, so no
 // fences are needed) sums them in a fixed order.
-// First phase: this thread's strided share of the partials (loads only, so
-// that a kernel can issue them together with its other loads).
-// In two steps, so that a kernel can issue other loads in between:
-// partial_first loads this thread's first partial (usually its only one),
-// partial_rest adds the further ones.
-__device__ inline double partial_first(const double* part, int col, int stride, int nblk) {
-    const int t = threadIdx.x;
-    return t < nblk ? part[(size_t)col * stride + t] : 0.0;
-}
-__device__ inline double partial_rest(double s, const double* part, int col, int stride, int nblk) {
-    const double* p = part + (size_t)col * stride;
-    for (int b = threadIdx.x + blockDim.x; b < nblk; b += blockDim.x) s += p[b];
-    return s;
-}
-// The whole share of nblk >= 1 partials with the first kShareLoads per thread
-// loaded without branches (clamped index, dropped afterwards), so that they
-// are in flight together with the caller's other loads (a loop waits for
-// each load it accumulates); more partials than kShareLoads per thread
-// follow in a loop.  Summed in index order, as partial_rest does.
+// First phase: this thread's strided share of nblk >= 1 partials, the first
+// kShareLoads per thread loaded without branches (clamped index, dropped
+// afterwards), so that they are in flight together with the caller's other
+// loads (a loop waits for each load it accumulates); more partials than
+// kShareLoads per thread follow in a loop.  Summed in index order.
 constexpr int kShareLoads = 4;
 __device__ inline double partial_share(const double* part, int col, int stride, int nblk) {
     const double* p = part + (size_t)col * stride;
@@ -122,7 +110,7 @@ constexpr int kVtMax = 4;  // virtual threads a thread of a 256-thread workgroup
 struct VtShare {
     double v[kVtMax];
 };
-__device__ inline VtShare vt_first(const double* part, int col, int stride, int nblk, int bd) {
+__device__ inline VtShare vt_first(const double* part, int col, int stride, int nblk) {
     const double* p = part + (size_t)col * stride;
     VtShare s;
 #pragma unroll
@@ -962,8 +950,8 @@ __global__ __launch_bounds__(1024) void k_bottom(BottomArgs a, const TV* __restr
 // else node by node with apply_window() nodes in flight (FP64 rows would spill).
 // Node k = j (N + 1) + i is split by a double reciprocal: (k + 1/2) / (N + 1)
 // lies at least 1 / (2 (N + 1)) from an integer and the product errs by far
-// less, so the truncation is exact.  Workgroup 0 records r^T z for the update
-// kernel, which then reads one value instead of the partials.
+// less, so the truncation is exact.  Workgroup 0 records r^T z for the finest
+// k_down, which forms alpha from it and reads one value instead of the partials.
 // The operator form the apply kernel combines with: the state operator as it
 // is, the prior operators through their rows staged in LDS.
 template <class OpT>

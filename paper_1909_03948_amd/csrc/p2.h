@@ -35,7 +35,7 @@ struct P2Col {
 
 constexpr int kP2Tile = 8;  // P1 vertices a side of a workgroup's tile
 // Every workgroup sums a column's partials itself while they are few (a launch
-// of its own costs ~4 us); N >= 184 has more than this many.
+// of its own costs ~4 us); from N = 176 on there are more than this many.
 constexpr int kP2MaxParts = 512;
 
 class P2Space {

@@ -301,14 +301,14 @@ __global__ void k_prior_apply(OpKA<double> op, const double* __restrict__ x, int
 // Bound by FP64 arithmetic in batches and by the chain of steps for few
 // columns.  With r and d in LDS tiles (12 LDS accesses and two barriers a node
 // and step) R mhat = K M^-1 K mhat took 2309 us at 512^2 x 64 and 228 / 70 us for
-// one column of 1024^2 / 256^2, here 910 and 87 / 31.
+// one column of 1024^2 / 256^2, here 946 and 92 / 30.
 constexpr int kMassSteps = 12, kMassWaves = 8;
 constexpr int kMassOwnX = 64 - 2 * kMassSteps;
 // R: 4 while the launch is one round of short chains, 8 (less halo a node)
-// from 160 workgroups on: R mhat of 256^2 x 1 takes 31.3 / 41.8 us with R = 4 / 8
-// (49 workgroups of the larger kind), 512^2 x 1 (169) 58.7 / 48.0, 512^2 x 64
-// 1895 / 910 (16 or 20: 968 / 985, more registers than two workgroups a compute
-// unit have).
+// from 160 workgroups on: R mhat of 256^2 x 1 takes 31 / 40 us with R = 4 / 8
+// (49 workgroups of the larger kind), 512^2 x 1 (169) 60 / 49, 512^2 x 64
+// 1882 / 903 (16 and 20 rows spill under the 128 registers of two workgroups a
+// compute unit: 4583 / 6860).
 constexpr int kMassRowsFew = 4, kMassRowsMany = 8;
 constexpr int mass_own_y(int R) { return kMassWaves * R - 2 * kMassSteps; }
 struct MassSteps {

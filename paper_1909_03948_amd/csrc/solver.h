@@ -134,11 +134,13 @@ class Hierarchy {
     // of each (column count, precision); HINV_AUTOTUNE=0 uses the fixed rule
     // instead.
     struct LaunchShape {
-        bool small;  // latency bound: short segments, several coarse levels a launch
-        int len;     // otherwise: coarse rows per segment of the wave-row kernels
-        int per;     // node blocks per workgroup of the PCG vector kernels
-        int cb;      // columns that share one reading of the operator in the V-cycle kernels
-        // nodes per workgroup of the PCG vector kernels; 0: 256 per.  A
+        bool small;  // several coarse levels a launch
+        int len;     // batches: coarse rows per segment of the wave-row kernels
+        int per;     // few columns: node blocks per workgroup of the linear PCG kernels
+        // columns that share one reading of the operator: a wave's (wave-row
+        // kernels of batches, 1 or 2) or a workgroup's (several levels a launch)
+        int cb;
+        // few columns: nodes per workgroup of the linear PCG kernels; 0: 256 per.  A
         // balanced chunk spreads a column over a whole number of workgroups
         // per compute unit instead of whole 256-node blocks.
         int chunk = 0;

@@ -759,15 +759,12 @@ PcgRed Hierarchy::pcg_red(int nc) const {
 }
 
 // Fixed rule: short segments and several coarse levels a launch below kFewCols
-// columns (latency bound); batched calls give each workgroup of the PCG vector
-// kernels several node blocks, since every workgroup sums all partials of its
-// column.
+// columns (latency bound), and there the node blocks a workgroup of the linear PCG
+// kernels takes.
 Hierarchy::LaunchShape Hierarchy::default_shape(int nc) const {
-    const int nb = ceil_div(n_, kBlock);
     LaunchShape sh;
     sh.small = nc < kFewCols;
-    sh.per = nc < kFewCols ? 1 : std::min(16, std::max(1, ceil_div(nb, 64)));
-    sh.per = std::max(sh.per, min_per());
+    sh.per = min_per();
     sh.cb = 1;
     sh.len = few_waves(nc) ? 2 : kBatchRows[0];
     if (nc < kFewCols && min_per() > 1) {
@@ -793,10 +790,8 @@ bool Hierarchy::few_waves(int nc) const {
 }
 
 // Every workgroup of the kernels after a reduction sums all of its partials,
-// so their count enters squared: the PCG vector kernels keep it at or below
-// kMaxVecPartials by giving each workgroup 1, 4, 8 or 16 node blocks (the
-// tuner, which times the apply kernel alone, would otherwise pick more
-// workgroups than pay inside the iteration).
+// so their count enters squared: the linear PCG kernels (few columns) keep it at
+// or below kMaxVecPartials by giving each workgroup 1, 4, 8 or 16 node blocks.
 int Hierarchy::min_per() const {
     const int nb = ceil_div(n_, kBlock);
     for (int per : {1, 4, 8, 16})

@@ -656,7 +656,7 @@ __global__ __launch_bounds__(64 * kMarchWaves) void k_down(Op op_, const TB* __r
         if (check) share[c] = partial_share(red.rr, col0 + c, red.stride, red.nrr);
         if constexpr (UPD) {
             live[c] = act[col0 + c];
-            vt[c] = vt_first(red.pq, col0 + c, red.stride, red.npq, bd);
+            vt[c] = vt_first(red.pq, col0 + c, red.stride, red.npq);
             rz[c] = st[col0 + c].rz_new;
         }
     }
