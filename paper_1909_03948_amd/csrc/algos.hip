@@ -261,10 +261,8 @@ __global__ void k_scale_cols(int s, int r, const double* __restrict__ U, const d
 // qr(Y) of a block of numerical rank r < s (one instance): Y^T Y = U diag(g) U^T
 // (descending), the r directions with g_i > tau g_1 kept, Z = Y U_r diag(g_r)^-1/2,
 // then two Cholesky QR passes on the n x r block (its condition number is at
-// most tau^-1/2).  tau = (10 rtol)^2: the solves that produced Y leave
-// components of relative size rtol outside its exact range.  Returns r, 0 on
-// failure.  Y <- Z (n x r, ld n).
-int orthonormalize_rank(Ctx* c, DenseWork& w, int n, int s, double rtol, double* Y, double* tmp, double* G,
+// most tau^-1/2).  Returns r, 0 on failure.  Y <- Z (n x r, ld n).
+int orthonormalize_rank(Ctx* c, DenseWork& w, int n, int s, double tau, double* Y, double* tmp, double* G,
                         double* Ri, double* U, double* g) {
     const size_t ss = (size_t)s * s;
     gram(c, w, n, s, s, Y, n, Y, n, G, s);
@@ -273,7 +271,6 @@ int orthonormalize_rank(Ctx* c, DenseWork& w, int n, int s, double rtol, double*
     HINV_HIP(hipMemcpyAsync(hg.data(), g, sizeof(double) * s, hipMemcpyDeviceToHost, c->stream));
     HINV_HIP(hipStreamSynchronize(c->stream));
     if (!(hg[0] > 0.0)) return 0;
-    const double tau = std::max(1e-24, 100.0 * rtol * rtol);
     int r = 0;
     while (r < s && hg[r] > tau * hg[0]) ++r;
     k_scale_cols<<<ceil_div(s * r, kBlock), kBlock, 0, c->stream>>>(s, r, U, g, Ri);
@@ -295,32 +292,46 @@ int orthonormalize_rank(Ctx* c, DenseWork& w, int n, int s, double rtol, double*
 
 // PreCholQR (Algorithm 4) on each Y_j (n x s): Z = qr(Y), Zbar = B Z,
 // R_Z = chol(Z^T Zbar), Q = Z R_Z^-1 written to Q_j.  Y_j is overwritten by
-// Z_j; Zb is scratch.
+// Z_j; Zb holds Zbar, or, with a rank asked for, scratch.
 int precholqr(Problem* const* P, int ni, DenseWork& dw, int s, double* Y, double* Zb, double* Q, double* G,
               double* Ri, bool b_identity, int* rank, double* U, double* g) {
     Ctx* c = P[0]->ctx;
     const int n = P[0]->n;
     const bool revealing = rank && ni == 1 && U && g;
     if (rank) *rank = s;
-    // a copy of Y for the rank-revealing retry (Zb is not needed before Z exists)
+    // a copy of Y for the rank-revealing retry; Zbar goes to Q meanwhile
     if (revealing) dev_copy(c, n, s, Y, n, Zb, n);
-    if (!orthonormalize(c, dw, ni, n, s, Y, Q, G, Ri)) {  // Y <- Z
+    double* const Bz = revealing ? Q : Zb;
+    auto factor = [&] {  // R_Z of the basis Z in Y
+        const size_t ts = (size_t)n * s, ss = (size_t)s * s;
+        for (int j = 0; j < ni; ++j) {
+            if (b_identity)
+                dev_copy(c, n, s, Y + j * ts, n, Bz + j * ts, n);     // Zbar = Z
+            else
+                P[j]->prior_apply(s, Y + j * ts, n, Bz + j * ts, n);  // Zbar = B Z
+            gram(c, dw, n, s, s, Y + j * ts, n, Bz + j * ts, n, G + j * ss, s);  // Z^T Zbar
+        }
+        return cholesky_upper(c, dw, ni, s, G, s, ss);
+    };
+    // a basis that breaks down in either factorization has lost its rank
+    if (!orthonormalize(c, dw, ni, n, s, Y, Q, G, Ri) || !factor()) {  // Y <- Z
         if (!revealing) return HINV_EBREAK;
-        dev_copy(c, n, s, Zb, n, Y, n);
-        const int r = orthonormalize_rank(c, dw, n, s, P[0]->rtol, Y, Q, G, Ri, U, g);
-        if (r == 0) return HINV_EBREAK;
-        *rank = r;
-        s = r;
+        // the solves that produced Y leave components of relative size rtol
+        // outside its exact range; rounding of the Gram matrix (1e-16 of its
+        // largest eigenvalue) may pass for a direction above that, and the basis
+        // breaks down again: then with a higher threshold
+        const int cols = s;
+        double tau = std::max(1e-24, 100.0 * P[0]->rtol * P[0]->rtol);
+        s = 0;
+        for (int attempt = 0; attempt < 4 && s == 0; ++attempt, tau *= 100.0) {
+            dev_copy(c, n, cols, Zb, n, Y, n);
+            s = orthonormalize_rank(c, dw, n, cols, tau, Y, Q, G, Ri, U, g);
+            if (s > 0 && !factor()) s = 0;
+        }
+        if (s == 0) return HINV_EBREAK;
+        *rank = s;
     }
     const size_t ts = (size_t)n * s, ss = (size_t)s * s;
-    for (int j = 0; j < ni; ++j) {
-        if (b_identity)
-            dev_copy(c, n, s, Y + j * ts, n, Zb + j * ts, n);                      // Zbar = Z
-        else
-            P[j]->prior_apply(s, Y + j * ts, n, Zb + j * ts, n);                   // Zbar = B Z
-        gram(c, dw, n, s, s, Y + j * ts, n, Zb + j * ts, n, G + j * ss, s);      // Z^T Zbar
-    }
-    if (!cholesky_upper(c, dw, ni, s, G, s, ss)) return HINV_EBREAK;            // R_Z
     tri_inverse_upper(c, dw, ni, s, G, s, ss, Ri, s, ss);
     for (int j = 0; j < ni; ++j)
         gemm_tall(c, n, s, s, 1.0, Y + j * ts, n, Ri + j * ss, s, 0.0, Q + j * ts, n);  // Q = Z R_Z^-1
