@@ -76,3 +76,22 @@ def test_stacked_segments_and_columns_a_wave(shape, monkeypatch):
         e = col_rel(o.cpu().numpy(), r[6])
         print(f"[gpu-seg] {e:.1e}", flush=True)
         assert e <= 1e-8
+
+
+@pytest.mark.parametrize("shape", ["s1", "s2", "s3", "s4", "s16", "s1k320", "s2k960", "s3k704", "s4k4032", "l3"])
+@pytest.mark.parametrize("nc", [1, 7])
+def test_partitions_of_few_columns(nc, shape, monkeypatch):
+    """The linear apply kernel of few columns: one or two virtual threads a
+    thread, whole blocks and chunks that end inside one."""
+    print(f"[gpu-seg] few nc={nc} {shape}", flush=True)
+    N = 256
+    monkeypatch.setenv("HINV_SHAPE", shape)
+    gp = problem(hv.Context(0), N, 41)
+    X, H, R = (a[:nc] for a in reference(N, 41)[5:])
+    Y, Z = dev(np.zeros_like(X)), dev(np.zeros_like(X))
+    for info in (gp.hessian_apply(hv.HESS_GN_MISFIT, dev(X), Y), gp.prior_solve(dev(X), Z)):
+        assert info["rc"] == 0 and info["max_relres"] <= 1e-10, info
+    torch.cuda.synchronize()
+    e = col_rel(Y.cpu().numpy(), H), col_rel(Z.cpu().numpy(), R)
+    print(f"[gpu-seg] {e[0]:.1e} {e[1]:.1e}", flush=True)
+    assert max(e) <= 1e-8
