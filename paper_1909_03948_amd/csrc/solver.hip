@@ -908,7 +908,8 @@ void Hierarchy::tune_shape(int nc, bool in_pass) {
         tune_load_locked();
         for (auto it = g_tune.rbegin(); it != g_tune.rend(); ++it)
             if (it->arch == arch && it->kind == (int)kind_ && it->N == N_ && it->ninst == ninst_ && it->nc == nc &&
-                it->fp32 == fp32 && it->pass == (int)in_pass && it->per >= min_per()) {
+                it->fp32 == fp32 && it->pass == (int)in_pass && it->per >= min_per() &&
+                (it->chunk == 0 || ceil_div(n_, it->chunk) <= red_stride_)) {
                 shape_.small = it->small != 0;
                 shape_.len = it->len;
                 shape_.per = it->per;
